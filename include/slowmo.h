@@ -17,7 +17,7 @@
  *  - Tensor lists are worker-major: entry [i * n_tensors + j] belongs to
  *    worker i, tensor j.  Tensor j has numel[j] contiguous elements on every
  *    worker.  Pointers need element alignment only (4 bytes fp32, 2 bytes
- *    bf16); 16-byte alignment selects the vectorized path.
+ *    bf16); every alignment takes the same vector instructions.
  *  - Ownership: parameters, gradients and the state workspace belong to the
  *    caller.  The library keeps the parameter pointers and the workspace for
  *    the context's lifetime and never frees them; they must not overlap.
@@ -49,9 +49,9 @@
  *    last launch was accepted.  A call that fails therefore leaves the
  *    context's state unchanged, with one exception: some calls issue several
  *    kernels or copies (slowmo_mix_step and slowmo_local_mix_step launch one
- *    kernel per connected group of workers; slowmo_local_outer_step and
- *    slowmo_local_mix_step launch two kernels when a pointer is not 16-byte
- *    aligned; slowmo_outer_step and slowmo_local_outer_step launch one kernel
+ *    kernel per connected group of workers; slowmo_local_mix_step launches
+ *    the local step and the mixing step one after the other when a replica
+ *    pointer is not 16-byte aligned; slowmo_outer_step and slowmo_local_outer_step launch one kernel
  *    for the whole 65 536-element pieces of the tensors and one for the rest
  *    when the tensor list has at least 160 such pieces -- the former from 16
  *    workers on, the latter from 8 on under SLOWMO_BUF_RESET;
@@ -188,9 +188,7 @@ slowmo_status slowmo_outer_step(slowmo_ctx *ctx, float lr, void *stream);
  * the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_outer_step(ctx, outer_lr, stream);
- * but when cfg.no_average is 0 and every replica and gradient pointer is
- * 16-byte aligned (8 bytes for bf16 gradients) both run in ONE kernel that
- * keeps the stepped replicas in registers for the average: the replicas are
+ * but when cfg.no_average is 0 both run in ONE kernel that keeps the stepped replicas in registers for the average: the replicas are
  * read and written once instead of twice (8 m bytes less traffic per element),
  * and the per-worker buffers of this step are not written under the RESET and
  * AVERAGE policies.  Otherwise the two kernels are launched back to back.
@@ -228,8 +226,7 @@ slowmo_status slowmo_mix_step(slowmo_ctx *ctx, const int32_t *in_peer, void *str
  * outer iteration): the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_mix_step(ctx, in_peer, stream);
- * but when every replica and gradient pointer is 16-byte aligned (8 bytes for
- * bf16 gradients) both run in ONE kernel that keeps the stepped replicas in
+ * but when every replica pointer is 16-byte aligned both run in ONE kernel that keeps the stepped replicas in
  * registers for the mix: the replicas are read and written once instead of
  * twice (8 bytes less traffic per worker and element).  Otherwise the two
  * kernels are launched back to back.

@@ -458,6 +458,15 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->tune.nontemporal = env_flag("SLOWMO_NT", 1) ? 1 : 0;
   ctx->tune.fuse_last = env_flag("SLOWMO_FUSE_LAST", 1) ? 1 : 0;
   ctx->tune.fuse_mix = env_flag("SLOWMO_FUSE_MIX", 1) ? 1 : 0;
+  // 160 KiB / 8 KiB: at most 20 single-wave workgroups per CU.  With all 32 the
+  // requests of too many tiles meet in the memory and each of its pages is opened
+  // more often; with 20 the local step still has twice the requests in flight that
+  // it needs.  ResNet-18-shaped round, m = 8: 3.565 ms without the cap, 3.45 with 22,
+  // 3.440 with 20, 3.446 with 17 wavefronts; tensors packed back to back 2.82 ->
+  // 2.65 ms; Adam with bf16 gradients 0.669 -> 0.643 ms; outer step without the
+  // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
+  // 30 % slower with the cap.
+  ctx->tune.local_lds = std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", 8192), 0), 64 * 1024);
   ctx->tune.outer_lds = std::min(std::max(env_flag("SLOWMO_OUTER_LDS", 0), 0), 64 * 1024);
   // big tiles: -1 = by the worker count (see kBigFusedFromWorkers), 0 = never, 1 = always
   const int32_t big = env_flag("SLOWMO_BIG_TILES", -1);
@@ -641,10 +650,9 @@ extern "C++" {
 namespace {
 
 // Checks the arguments of a local step, uploads the gradient-pointer table if
-// it changed and fills the kernel arguments.  *all_aligned tells whether every
-// gradient pointer allows 16-byte vector loads.
+// it changed and fills the kernel arguments.
 slowmo_status prepare_local(slowmo_ctx *ctx, const void *const *grads, float lr,
-                            hipStream_t stream, LocalArgs *out, bool *all_aligned) {
+                            hipStream_t stream, LocalArgs *out) {
   if (ctx->broken) return fail(ctx, SLOWMO_ERR_STATE, kBrokenMsg);
   if (!grads) return fail(ctx, SLOWMO_ERR_ARG, "grads is NULL");
   if (!finite_pos(lr)) return fail(ctx, SLOWMO_ERR_ARG, "lr must be finite and > 0");
@@ -653,15 +661,12 @@ slowmo_status prepare_local(slowmo_ctx *ctx, const void *const *grads, float lr,
   const slowmo_config &c = ctx->cfg;
   const size_t n_ptr = static_cast<size_t>(c.m) * ctx->n_tensors;
   const size_t gsize = c.grad_dtype == SLOWMO_BF16 ? 2 : 4;
-  uintptr_t low_bits = 0;
   for (size_t i = 0; i < n_ptr; ++i) {
     if (ctx->numel[i % ctx->n_tensors] == 0) continue;
     if (!grads[i]) return fail(ctx, SLOWMO_ERR_ARG, "a gradient pointer is NULL");
     if (reinterpret_cast<uintptr_t>(grads[i]) % gsize)
       return fail(ctx, SLOWMO_ERR_ALIGN, "a gradient pointer is not aligned to its element size");
-    low_bits |= reinterpret_cast<uintptr_t>(grads[i]);
   }
-  *all_aligned = (low_bits & (4 * gsize - 1)) == 0;
 
   // gradient-pointer table: reuse a device copy if one of the recent calls had these pointers
   int slot = ctx->gtab.find(grads, n_ptr * sizeof(void *));
@@ -728,8 +733,7 @@ slowmo_status slowmo_local_step(slowmo_ctx *ctx, const void *const *grads, float
   if (!ctx) return fail(nullptr, SLOWMO_ERR_ARG, "ctx is NULL");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   LocalArgs a{};
-  bool aligned = false;
-  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a, &aligned);
+  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a);
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
   // Under the reset policy the buffers written by the last step of an outer
@@ -832,12 +836,11 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
                 "must have been taken");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   LocalArgs a{};
-  bool aligned = false;
-  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a, &aligned);
+  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a);
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
   const bool bf16 = c.grad_dtype == SLOWMO_BF16;
-  if (c.no_average || !aligned || !ctx->params_aligned || !ctx->tune.fuse_last) {
+  if (c.no_average || !ctx->tune.fuse_last) {
     // same two kernels as the separate calls
     hipError_t e = guarded(ctx, [&] {
       return launch_local_step(a, c.base, bf16, ctx->buffers_zero, c.policy == SLOWMO_BUF_RESET,
@@ -1052,12 +1055,12 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
     return fail(ctx, SLOWMO_ERR_ARG, "in_peer entries must lie in 0..m-1");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   LocalArgs a{};
-  bool aligned = false;
-  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a, &aligned);
+  slowmo_status st = prepare_local(ctx, grads, lr, stream, &a);
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
   const bool bf16 = c.grad_dtype == SLOWMO_BF16;
-  const bool two_kernels = !aligned || !ctx->params_aligned || !ctx->tune.fuse_mix || ctx->n_otiles == 0;
+  // replicas that are not 16-byte aligned: documented (and tested) to be two kernels
+  const bool two_kernels = !ctx->params_aligned || !ctx->tune.fuse_mix || ctx->n_otiles == 0;
   // both tables are on their way to the device before the first kernel is launched
   StagedMix sm;
   st = stage_mix(ctx, in_peer, /*with_idle=*/!two_kernels, stream, &sm);

@@ -81,6 +81,8 @@ struct LaunchTuning {
   int32_t fuse_last;    // 1: slowmo_local_outer_step runs one fused kernel when it can
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
+  int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
+                        // outer step without the average: caps the wavefronts per CU
   int32_t outer_lds;    // bytes of (unused) dynamic LDS per outer-step workgroup: caps the
                         // number of resident wavefronts per CU (160 KiB / outer_lds); 0 = no cap
 };
@@ -92,15 +94,14 @@ hipError_t launch_local_step(const LocalArgs &a, int base, bool bf16, bool first
                              const LaunchTuning &tune, hipStream_t stream);
 hipError_t launch_outer_step(const OuterArgs &a, const LaunchTuning &tune, hipStream_t stream);
 // The last local step of an outer iteration and the outer step in one pass
-// (one workgroup = 256 elements of one tensor, all workers).  Requires every
-// replica and gradient pointer to be 16-byte aligned (8 for bf16).  policy:
+// (one workgroup = 256 elements of one tensor, all workers).  policy:
 // 0 reset (buffers not stored), 1 maintain (stored), 2 average (their mean
 // over the workers is stored).
 hipError_t launch_local_outer_step(const LocalArgs &l, const OuterArgs &o, int32_t n_tensors,
                                    int base, bool bf16, bool first, int policy,
                                    const LaunchTuning &tune, hipStream_t stream);
 // The same two operations on BIG tiles (a.tiles / o.tiles list whole kBigTile
-// pieces, every one full and 16-byte aligned in every stream).  Results are
+// pieces, every one full, of tensors all of whose replicas are 16-byte aligned).  Results are
 // bit-identical to the ordinary tiles'.  launch_outer_big handles no buffer
 // average (a.avg_h must be NULL); launch_local_outer_big handles policies 0 and 1.
 hipError_t launch_outer_big(const OuterArgs &a, const LaunchTuning &tune, hipStream_t stream);
@@ -114,8 +115,7 @@ hipError_t launch_init_broadcast(const OuterArgs &a, int32_t x0_copies, const La
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &tune,
                               hipStream_t stream);
 // The local step and the mixing step that follows it in one kernel; x.seq must
-// list EVERY worker (plan_mix with idle workers).  Needs 16-byte aligned
-// replicas and gradient pointers that allow vector loads.
+// list EVERY worker (plan_mix with idle workers).
 hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                  int32_t n_tensors, int base, bool bf16, bool first,
                                  const LaunchTuning &tune, hipStream_t stream);

@@ -78,8 +78,14 @@ typedef uint32_t U2 __attribute__((ext_vector_type(2)));
 // accesses for them.  They are global memory: say so, to get global_load /
 // global_store.
 #define SLOWMO_GLOBAL __attribute__((address_space(1)))
-typedef SLOWMO_GLOBAL V4 GV4;
-typedef SLOWMO_GLOBAL U2 GU2;
+// Vectors with the alignment of their elements: one global_load_dwordx4 /
+// global_store_dwordx4 takes any 4-byte aligned address (any 2-byte aligned one
+// for the 8 bytes of four bf16), so tensors packed back to back run on the same
+// instructions as aligned ones.
+typedef float V4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t U2u __attribute__((ext_vector_type(2), aligned(2)));
+typedef SLOWMO_GLOBAL V4u GV4;
+typedef SLOWMO_GLOBAL U2u GU2;
 
 template <typename T>
 __device__ __forceinline__ SLOWMO_GLOBAL T *as_global(const void *p) {
@@ -88,59 +94,133 @@ __device__ __forceinline__ SLOWMO_GLOBAL T *as_global(const void *p) {
 
 template <bool NT>
 __device__ __forceinline__ V4 ld4(const float *p) {
-  const GV4 *q = as_global<V4>(p);
+  const GV4 *q = as_global<V4u>(p);
   if constexpr (NT) return __builtin_nontemporal_load(q);
   return *q;
 }
 template <bool NT>
 __device__ __forceinline__ void st4(float *p, V4 v) {
-  GV4 *q = as_global<V4>(p);
+  GV4 *q = as_global<V4u>(p);
   if constexpr (NT) {
     __builtin_nontemporal_store(v, q);
   } else {
     *q = v;
   }
 }
-__device__ __forceinline__ float ld1(const float *p) { return *as_global<float>(p); }
-__device__ __forceinline__ void st1(float *p, float v) { *as_global<float>(p) = v; }
 
-// Gradient access: fp32 as is, bf16 widened exactly (the 16 bits become the
-// high half of an fp32 word).
-template <bool BF16>
-__device__ __forceinline__ float ldg1(const void *g, int j) {
-  if constexpr (BF16) {
-    uint32_t w = as_global<uint16_t>(g)[j];
-    return __uint_as_float(w << 16);
+// Stores one vector per lane to p + e0 (p uniform over the wave, e0 the lane's
+// element).  Where the wave's vectors cover whole 128-byte lines the store is "nt
+// sc1": streaming, and written through the XCD's L2 at once instead of when the
+// line is evicted, which the local step's mix of reads and writes likes better
+// (ResNet-18-shaped round, m = 8: 3.472 -> 3.452 ms).  Lines that two waves share
+// must stay in the L2 until both halves are there (tensors packed back to back:
+// 2.61 ms "nt", 3.00 ms "nt sc1").  Only the buffer form lets a builtin ask for it.
+constexpr int kWriteThrough = 18;   // bits of the buffer store's cache policy: nt = 2, sc1 = 16
+template <bool NT>
+__device__ __forceinline__ void st4_at(float *p, int e0, V4 v) {
+  if (NT && (reinterpret_cast<uintptr_t>(p) & 127) == 0) {
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
   } else {
-    return as_global<float>(g)[j];
+    st4<NT>(p + e0, v);
   }
 }
-template <bool BF16, bool NT>
-__device__ __forceinline__ V4 ldg4(const void *g, int vec) {
-  if constexpr (BF16) {
-    const GU2 *p = as_global<U2>(g) + vec;
-    U2 w = NT ? __builtin_nontemporal_load(p) : *p;
+// The same for a place in a state arena, every slice of which starts at a
+// multiple of 256 bytes.
+template <bool NT>
+__device__ __forceinline__ void st4_arena(float *p, int e0, V4 v) {
+  if constexpr (NT) {
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
+  } else {
+    st4<false>(p + e0, v);
+  }
+}
+
+// Lane offset of the tail path.  Opaque, so that the compiler does not share one
+// 64-bit address per lane and stream between it and the full vectors' path,
+// which addresses with a scalar base and a 32-bit lane offset.
+__device__ __forceinline__ int tail_offset(int e0) {
+  asm volatile("" : "+v"(e0));
+  return e0;
+}
+
+// The last lane of a tensor may own fewer than four elements (cnt = 1, 2 or 3).
+// It loads element min(j, cnt - 1) in place of element j, so that its loads are
+// as independent of each other as the other lanes' are, goes through the same
+// arithmetic, and stores the elements it owns.
+template <bool TAIL, bool NT>
+__device__ __forceinline__ V4 ldv(const float *p, int cnt) {
+  if constexpr (TAIL) {
+    const SLOWMO_GLOBAL float *q = as_global<float>(p);
     V4 r;
-    r.x = __uint_as_float(w.x << 16);
-    r.y = __uint_as_float(w.x & 0xffff0000u);
-    r.z = __uint_as_float(w.y << 16);
-    r.w = __uint_as_float(w.y & 0xffff0000u);
+    r.x = q[0];
+    r.y = q[cnt > 1 ? 1 : 0];
+    r.z = q[cnt > 2 ? 2 : 0];
+    r.w = r.x;
     return r;
   } else {
-    return ld4<NT>(reinterpret_cast<const float *>(g) + 4 * vec);
+    return ld4<NT>(p);
   }
+}
+template <bool TAIL, bool NT>
+__device__ __forceinline__ void stv(float *p, V4 v, int cnt) {
+  if constexpr (TAIL) {
+    SLOWMO_GLOBAL float *q = as_global<float>(p);
+    q[0] = v.x;
+    if (cnt > 1) q[1] = v.y;
+    if (cnt > 2) q[2] = v.z;
+  } else {
+    st4<NT>(p, v);
+  }
+}
+
+// Gradients: fp32 as is, bf16 widened exactly (the 16 bits become the high half
+// of an fp32 word).  Elements [e0, e0 + cnt) of g.
+template <bool BF16, bool TAIL, bool NT>
+__device__ __forceinline__ V4 ldgv(const void *g, int e0, int cnt) {
+  if constexpr (BF16) {
+    V4 r;
+    if constexpr (TAIL) {
+      const SLOWMO_GLOBAL uint16_t *q = as_global<uint16_t>(g) + e0;
+      r.x = __uint_as_float(static_cast<uint32_t>(q[0]) << 16);
+      r.y = __uint_as_float(static_cast<uint32_t>(q[cnt > 1 ? 1 : 0]) << 16);
+      r.z = __uint_as_float(static_cast<uint32_t>(q[cnt > 2 ? 2 : 0]) << 16);
+      r.w = r.x;
+    } else {
+      const GU2 *q = reinterpret_cast<const GU2 *>(as_global<uint16_t>(g) + e0);
+      const U2 w = NT ? __builtin_nontemporal_load(q) : *q;
+      r.x = __uint_as_float(w.x << 16);
+      r.y = __uint_as_float(w.x & 0xffff0000u);
+      r.z = __uint_as_float(w.y << 16);
+      r.w = __uint_as_float(w.y & 0xffff0000u);
+    }
+    return r;
+  } else {
+    return ldv<TAIL, NT>(static_cast<const float *>(g) + e0, cnt);
+  }
+}
+template <bool BF16>
+__device__ __forceinline__ const void *grad_at(const void *g, int64_t j) {
+  return static_cast<const char *>(g) + j * (BF16 ? 2 : 4);
 }
 
 // Tile of workgroup b.  Workgroup b runs on XCD b mod 8; with the remap, XCD c
 // walks the contiguous tile range [c * chunk, (c + 1) * chunk), so each XCD's
 // L2 and TLB see one compact window of every stream instead of a 1-in-8 comb.
 __device__ __forceinline__ int tile_of(int b, int chunk, int run) {
-  // run == 0: workgroup b takes tile b.  Otherwise the workgroups of one XCD
-  // (b % 8) take runs of `run` consecutive tiles, the 8 XCDs side by side;
-  // run == chunk gives every XCD one contiguous eighth of the tiles.
+  // run == 0: workgroup b takes tile b.  run == chunk: every XCD has one
+  // contiguous eighth of the tiles (the default; no division, which would be a
+  // chain of some 40 instructions in front of a wave's first load).  Otherwise
+  // the workgroups of one XCD (b % 8) take runs of `run` consecutive tiles, the
+  // 8 XCDs side by side.
   if (run == 0) return b;
-  const int q = b / kXcd, x = b % kXcd;
-  return (q / run) * (kXcd * run) + x * run + q % run;
+  const unsigned q = static_cast<unsigned>(b) / kXcd, x = static_cast<unsigned>(b) % kXcd;
+  if (run == chunk) return static_cast<int>(x * static_cast<unsigned>(chunk) + q);
+  const unsigned r = static_cast<unsigned>(run);
+  return static_cast<int>((q / r) * (kXcd * r) + x * r + q % r);
 }
 
 // ---- per-element arithmetic -------------------------------------------------
@@ -181,6 +261,25 @@ __device__ __forceinline__ void adam_elem(float &x, float &h, float &v, float g,
   x = x - p.lr * dir;
 }
 
+// One base-optimizer step of four elements.
+template <int BASE, bool FIRST>
+__device__ __forceinline__ void step4(V4 &xv, V4 &hv, V4 &vv, V4 gv, const SgdP &sp,
+                                      const AdamP &ap) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    float xe = xv[c], he = FIRST ? 0.f : hv[c];
+    if constexpr (BASE == 0) {
+      sgd_elem<FIRST>(xe, he, gv[c], sp);
+    } else {
+      float ve = FIRST ? 0.f : vv[c];
+      adam_elem<FIRST>(xe, he, ve, gv[c], ap);
+      vv[c] = ve;
+    }
+    xv[c] = xe;
+    hv[c] = he;
+  }
+}
+
 struct OuterP {
   float lr, alpha_lr, beta, m_f, alpha;
 };
@@ -200,6 +299,27 @@ __device__ __forceinline__ float outer_elem(float s, float x0, float &u, const O
   return x0 - p.alpha_lr * un;
 }
 
+// The same for four elements; u is updated in place.
+__device__ __forceinline__ V4 outer4(V4 s, V4 x0, V4 &u, const OuterP &p) {
+  V4 xn;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    float ue = u[c];
+    xn[c] = outer_elem(s[c], x0[c], ue, p);
+    u[c] = ue;
+  }
+  return xn;
+}
+
+// Makes the (uniform) table words behind a tile arrive together: without it the
+// compiler moves the loads of those that are not needed for the bounds check
+// behind its branch, one more trip to the scalar cache in front of a wave's
+// first vector load.
+template <typename T>
+__device__ __forceinline__ void have_now(const T &a) {
+  asm volatile("" ::"s"(a));
+}
+
 // ---- local step ---------------------------------------------------------------
 // One workgroup = one tile = up to 4 * blockDim elements of one (worker,
 // tensor).  Lane t owns elements [4t, 4t + 4) of the tile.
@@ -216,68 +336,51 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];         // uniform: scalar loads
   const SlotInfo s = slots[t.owner];
+  const void *const g0 = gtab[t.owner];
+  have_now(s.x), have_now(s.so), have_now(s.lr_scale), have_now(g0);
   // per-tensor hyper-parameters (uniform over the workgroup)
   sp.lr = sp.lr * s.lr_scale;
   sp.wd = s.wd;
   ap.lr = ap.lr * s.lr_scale;
   ap.wd = s.wd;
-  constexpr int gsize = BF16 ? 2 : 4;
   const int64_t go = static_cast<int64_t>(t.k) * kLocalTile;  // offset of the tile in its tensor
-  const void *g = static_cast<const char *>(gtab[t.owner]) + go * gsize;
+  const void *g = grad_at<BF16>(g0, go);
   float *x = s.x + go;
   float *h = hbase + s.so + go;
   float *v = BASE == 1 ? vbase + s.so + go : nullptr;
   const int64_t left = s.numel - go;
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
-  // h and v are 16-byte aligned by construction of the arena
-  uintptr_t bits = reinterpret_cast<uintptr_t>(x) |
-                   (BF16 ? reinterpret_cast<uintptr_t>(g) << 1 : reinterpret_cast<uintptr_t>(g));
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if ((bits & 15) == 0 && e0 + 4 <= n) {
-    const int idx = threadIdx.x;
-    V4 xv = ld4<NT>(x + e0), hv, vv;
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  V4 xv, hv, vv, gv;
+  if (cnt >= 4) {
+    xv = ld4<NT>(x + e0);
     // With only two loads per wave (buffers read as zero) the step measures 2.5 %
     // faster when the second load is issued after the first has returned
     // (2.125 -> 2.072 ms, m = 32, 25.6 M elements, four alternating runs); with
     // three or four loads the same wait changes nothing or costs 1-2 %.
     if constexpr (FIRST) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xv)::"memory");
+    gv = ldgv<BF16, false, NT>(g, e0, 4);
     if constexpr (!FIRST) hv = ld4<NT>(h + e0);
     if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
-    V4 gv = ldg4<BF16, NT>(g, idx);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float xe = xv[c], he = FIRST ? 0.f : hv[c];
-      if constexpr (BASE == 0) {
-        sgd_elem<FIRST>(xe, he, gv[c], sp);
-      } else {
-        float ve = FIRST ? 0.f : vv[c];
-        adam_elem<FIRST>(xe, he, ve, gv[c], ap);
-        vv[c] = ve;
-      }
-      xv[c] = xe;
-      hv[c] = he;
-    }
-    st4<NT>(x + e0, xv);
-    if constexpr (!LAST) st4<NT>(h + e0, hv);
-    if constexpr (!LAST && BASE == 1) st4<NT>(v + e0, vv);
   } else {
-    // element-wise: the ragged tail of a tensor, or pointers that are not
-    // 16-byte aligned
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) {
-      float xe = ld1(x + j), he = FIRST ? 0.f : ld1(h + j);
-      float ge = ldg1<BF16>(g, j);
-      if constexpr (BASE == 0) {
-        sgd_elem<FIRST>(xe, he, ge, sp);
-      } else {
-        float ve = FIRST ? 0.f : ld1(v + j);
-        adam_elem<FIRST>(xe, he, ve, ge, ap);
-        if constexpr (!LAST) st1(v + j, ve);
-      }
-      st1(x + j, xe);
-      if constexpr (!LAST) st1(h + j, he);
-    }
+    const int et = tail_offset(e0);
+    xv = ldv<true, NT>(x + et, cnt);
+    if constexpr (!FIRST) hv = ldv<true, NT>(h + et, cnt);
+    if constexpr (!FIRST && BASE == 1) vv = ldv<true, NT>(v + et, cnt);
+    gv = ldgv<BF16, true, NT>(g, et, cnt);
+  }
+  step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+  if (cnt >= 4) {
+    st4_at<NT>(x, e0, xv);
+    if constexpr (!LAST) st4_arena<NT>(h, e0, hv);
+    if constexpr (!LAST && BASE == 1) st4_arena<NT>(v, e0, vv);
+  } else {
+    const int et = tail_offset(e0);
+    stv<true, NT>(x + et, xv, cnt);
+    if constexpr (!LAST) stv<true, NT>(h + et, hv, cnt);
+    if constexpr (!LAST && BASE == 1) stv<true, NT>(v + et, vv, cnt);
   }
 }
 
@@ -299,28 +402,41 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
 #define SLOWMO_PRAGMA_UNROLL_OUTER _Pragma(SLOWMO_STR(unroll SLOWMO_OUTER_UNROLL))
 
 // Buffer strategy "average" for this lane's elements of one arena (h or v):
-// every worker's value becomes the ordered mean over the workers.  The arena
-// is 16-byte aligned by construction, so only a ragged tail is element-wise.
-template <bool NTL, bool NTS>
+// every worker's value becomes the ordered mean over the workers.
+template <bool TAIL, bool NTL, bool NTS>
 __device__ __forceinline__ void average_arena(float *__restrict__ b0, int64_t stride, int m,
-                                              float m_f, int e0, int n) {
-  if (e0 + 4 <= n) {
-    V4 acc = ld4<NTL>(b0 + e0);
-    SLOWMO_PRAGMA_UNROLL_OUTER
-    for (int i = 1; i < m; ++i) acc = acc + ld4<NTL>(b0 + i * stride + e0);
-    V4 mean;
+                                              float m_f, int e0, int cnt) {
+  V4 acc = ldv<TAIL, NTL>(b0 + e0, cnt);
+  SLOWMO_PRAGMA_UNROLL_OUTER
+  for (int i = 1; i < m; ++i) acc = acc + ldv<TAIL, NTL>(b0 + i * stride + e0, cnt);
+  V4 mean;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) mean[c] = acc[c] / m_f;
-    SLOWMO_PRAGMA_UNROLL_OUTER
-    for (int i = 0; i < m; ++i) st4<NTS>(b0 + i * stride + e0, mean);
-  } else {
-    for (int j = e0; j < n; ++j) {
-      float s = ld1(b0 + j);
-      for (int i = 1; i < m; ++i) s = s + ld1(b0 + i * stride + j);
-      float mean = s / m_f;
-      for (int i = 0; i < m; ++i) st1(b0 + i * stride + j, mean);
-    }
-  }
+  for (int c = 0; c < 4; ++c) mean[c] = acc[c] / m_f;
+  SLOWMO_PRAGMA_UNROLL_OUTER
+  for (int i = 0; i < m; ++i) stv<TAIL, NTS>(b0 + i * stride + e0, mean, cnt);
+}
+
+// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor; xp:
+// its m replicas; x0, u, h0, v0: the tile's place in the arenas.
+template <bool NT, int AVG, bool TAIL>
+__device__ __forceinline__ void outer_lane(float *const *__restrict__ xp, int64_t eo, float *x0,
+                                           float *u, float *h0, float *v0, int64_t d_pad, int m,
+                                           const OuterP &p, int e0, int cnt) {
+  constexpr bool NTL = NT && SLOWMO_OUTER_NTL, NTS = NT && SLOWMO_OUTER_NTS;
+  // line 6: ordered sum over the replicas, i = 0, 1, ..., m-1
+  V4 acc = ldv<TAIL, NTL>(xp[0] + eo + e0, cnt);
+  SLOWMO_PRAGMA_UNROLL_OUTER
+  for (int i = 1; i < m; ++i) acc = acc + ldv<TAIL, NTL>(xp[i] + eo + e0, cnt);
+  const V4 x0v = ldv<TAIL, NTL>(x0 + e0, cnt);
+  V4 uv = ldv<TAIL, NTL>(u + e0, cnt);
+  const V4 xn = outer4(acc, x0v, uv, p);
+  stv<TAIL, NTS>(u + e0, uv, cnt);
+  stv<TAIL, NTS>(x0 + e0, xn, cnt);
+  SLOWMO_PRAGMA_UNROLL_OUTER
+  for (int i = 0; i < m; ++i) stv<TAIL, NTS>(xp[i] + eo + e0, xn, cnt);
+  // line 2 of the next outer iteration, strategy "average"
+  if constexpr (AVG >= 1) average_arena<TAIL, NTL, NTS>(h0, d_pad, m, p.m_f, e0, cnt);
+  if constexpr (AVG >= 2) average_arena<TAIL, NTL, NTS>(v0, d_pad, m, p.m_f, e0, cnt);
 }
 
 // AVG: 0 = lines 6-8 only; 1 = also average h over the workers; 2 = h and v.
@@ -335,49 +451,20 @@ __global__ __launch_bounds__(kOuterBlock) void k_outer_step(
   const TileRef t = tiles[tile];         // uniform: scalar loads
   const TensorInfo ti = tensors[t.owner];
   const OuterP p = for_tensor(p0, ti.lr_scale);
+  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;  // m replica pointers
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const bool aligned = ti.unaligned == 0;
-  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;  // m replica pointers
-  float *x0 = x0base + ti.fo + eo;
-  float *u = ubase + ti.fo + eo;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  constexpr bool NTL = NT && SLOWMO_OUTER_NTL, NTS = NT && SLOWMO_OUTER_NTS;
-  if (aligned && e0 + 4 <= n) {
-    // line 6: ordered sum over the replicas, i = 0, 1, ..., m-1
-    V4 acc = ld4<NTL>(xp[0] + eo + e0);
-    SLOWMO_PRAGMA_UNROLL_OUTER
-    for (int i = 1; i < m; ++i) acc = acc + ld4<NTL>(xp[i] + eo + e0);
-    V4 x0v = ld4<NTL>(x0 + e0);
-    V4 uv = ld4<NTL>(u + e0);
-    V4 xn;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float ue = uv[c];
-      xn[c] = outer_elem(acc[c], x0v[c], ue, p);
-      uv[c] = ue;
-    }
-    st4<NTS>(u + e0, uv);
-    st4<NTS>(x0 + e0, xn);
-    SLOWMO_PRAGMA_UNROLL_OUTER
-    for (int i = 0; i < m; ++i) st4<NTS>(xp[i] + eo + e0, xn);
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  float *x0 = x0base + ti.fo + eo, *u = ubase + ti.fo + eo;
+  float *h0 = AVG >= 1 ? hbase + ti.fo + eo : nullptr, *v0 = AVG >= 2 ? vbase + ti.fo + eo : nullptr;
+  if (cnt >= 4) {
+    outer_lane<NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, e0, 4);
   } else {
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) {
-      float s = ld1(xp[0] + eo + j);
-      for (int i = 1; i < m; ++i) s = s + ld1(xp[i] + eo + j);
-      float ue = ld1(u + j);
-      float xn = outer_elem(s, ld1(x0 + j), ue, p);
-      st1(u + j, ue);
-      st1(x0 + j, xn);
-      for (int i = 0; i < m; ++i) st1(xp[i] + eo + j, xn);
-    }
+    outer_lane<NT, AVG, true>(xp, eo, x0, u, h0, v0, d_pad, m, p, tail_offset(e0), cnt);
   }
-  // line 2 of the next outer iteration, strategy "average"
-  if constexpr (AVG >= 1) average_arena<NTL, NTS>(hbase + ti.fo + eo, d_pad, m, p.m_f, e0, n);
-  if constexpr (AVG >= 2) average_arena<NTL, NTS>(vbase + ti.fo + eo, d_pad, m, p.m_f, e0, n);
 }
 
 // ---- common starting point (Algorithm 1, "Input") ------------------------------
@@ -392,25 +479,24 @@ __global__ __launch_bounds__(kOuterBlock) void k_init_broadcast(
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const TensorInfo ti = tensors[t.owner];
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
-  float *x0 = x0base + ti.fo + eo;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if (ti.unaligned == 0 && e0 + 4 <= n) {
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+  float *x0 = x0base + ti.fo + eo;
+  if (cnt >= 4) {
     const V4 v = ld4<NT>(xp[0] + eo + e0);
     for (int c = 0; c < x0_copies; ++c) st4<NT>(x0 + c * d_pad + e0, v);
 #pragma unroll 8
     for (int i = 1; i < m; ++i) st4<NT>(xp[i] + eo + e0, v);
   } else {
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) {
-      const float v = ld1(xp[0] + eo + j);
-      for (int c = 0; c < x0_copies; ++c) st1(x0 + c * d_pad + j, v);
-      for (int i = 1; i < m; ++i) st1(xp[i] + eo + j, v);
-    }
+    const int et = tail_offset(e0);
+    const V4 v = ldv<true, NT>(xp[0] + eo + et, cnt);
+    for (int c = 0; c < x0_copies; ++c) stv<true, NT>(x0 + c * d_pad + et, v, cnt);
+    for (int i = 1; i < m; ++i) stv<true, NT>(xp[i] + eo + et, v, cnt);
   }
 }
 
@@ -436,26 +522,28 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0 && e0 + 4 <= n) {
-    V4 xv = ld4<NT>(x + e0), x0v = ld4<NT>(x0 + e0), uv = ld4<NT>(u + e0);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float ue = uv[c];
-      xv[c] = outer_elem(xv[c], x0v[c], ue, p);
-      uv[c] = ue;
-    }
-    st4<NT>(u + e0, uv);
-    st4<NT>(x0 + e0, xv);
-    st4<NT>(x + e0, xv);
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  V4 xv, x0v, uv;
+  if (cnt >= 4) {
+    xv = ld4<NT>(x + e0);
+    x0v = ld4<NT>(x0 + e0);
+    uv = ld4<NT>(u + e0);
   } else {
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) {
-      float ue = ld1(u + j);
-      float xn = outer_elem(ld1(x + j), ld1(x0 + j), ue, p);
-      st1(u + j, ue);
-      st1(x0 + j, xn);
-      st1(x + j, xn);
-    }
+    const int et = tail_offset(e0);
+    xv = ldv<true, NT>(x + et, cnt);
+    x0v = ldv<true, NT>(x0 + et, cnt);
+    uv = ldv<true, NT>(u + et, cnt);
+  }
+  const V4 xn = outer4(xv, x0v, uv, p);
+  if (cnt >= 4) {
+    st4_arena<NT>(u, e0, uv);
+    st4_arena<NT>(x0, e0, xn);
+    st4_at<NT>(x, e0, xn);
+  } else {
+    const int et = tail_offset(e0);
+    stv<true, NT>(u + et, uv, cnt);
+    stv<true, NT>(x0 + et, xn, cnt);
+    stv<true, NT>(x + et, xn, cnt);
   }
 }
 
@@ -467,6 +555,66 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
 // replicas are read once and written once (the unfused pair writes and
 // re-reads them), and under "reset" / "average" the per-worker buffers of this
 // step are never written.
+#ifndef SLOWMO_FUSED_NTL
+#define SLOWMO_FUSED_NTL 1
+#endif
+#ifndef SLOWMO_FUSED_UNROLL
+#define SLOWMO_FUSED_UNROLL 8
+#endif
+// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor; xp:
+// its replicas, gp: its gradients (worker i: gp[i * n_tensors]); x0, u, h0, v0:
+// the tile's place in the arenas (worker i's buffers: + i * d_pad).
+template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool TAIL>
+__device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
+                                                 const void *const *__restrict__ gp, int64_t eo,
+                                                 float *x0, float *u, float *h0, float *v0,
+                                                 int64_t d_pad, int n_tensors, int m,
+                                                 const SgdP &sp, const AdamP &ap, const OuterP &p,
+                                                 int e0, int cnt) {
+  constexpr bool NTL = NT && SLOWMO_FUSED_NTL;
+  V4 acc, acch, accv;
+  _Pragma(SLOWMO_STR(unroll SLOWMO_FUSED_UNROLL))
+  for (int i = 0; i < m; ++i) {
+    float *hi = h0 + i * d_pad + e0;
+    float *vi = BASE == 1 ? v0 + i * d_pad + e0 : nullptr;
+    V4 xv = ldv<TAIL, NTL>(xp[i] + eo + e0, cnt), hv, vv;
+    if constexpr (!FIRST) hv = ldv<TAIL, NTL>(hi, cnt);
+    if constexpr (!FIRST && BASE == 1) vv = ldv<TAIL, NTL>(vi, cnt);
+    const V4 gv =
+        ldgv<BF16, TAIL, NTL>(grad_at<BF16>(gp[static_cast<int64_t>(i) * n_tensors], eo), e0, cnt);
+    step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+    if constexpr (POLICY == 1) {
+      stv<TAIL, NT>(hi, hv, cnt);
+      if constexpr (BASE == 1) stv<TAIL, NT>(vi, vv, cnt);
+    }
+    if constexpr (POLICY == 2) {
+      acch = (i == 0) ? hv : acch + hv;
+      if constexpr (BASE == 1) accv = (i == 0) ? vv : accv + vv;
+    }
+    acc = (i == 0) ? xv : acc + xv;
+  }
+  const V4 x0v = ldv<TAIL, NT>(x0 + e0, cnt);
+  V4 uv = ldv<TAIL, NT>(u + e0, cnt);
+  const V4 xn = outer4(acc, x0v, uv, p);
+  stv<TAIL, NT>(u + e0, uv, cnt);
+  stv<TAIL, NT>(x0 + e0, xn, cnt);
+#pragma unroll 8
+  for (int i = 0; i < m; ++i) stv<TAIL, NT>(xp[i] + eo + e0, xn, cnt);
+  if constexpr (POLICY == 2) {
+    V4 mh, mv;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      mh[c] = acch[c] / p.m_f;
+      if constexpr (BASE == 1) mv[c] = accv[c] / p.m_f;
+    }
+#pragma unroll 8
+    for (int i = 0; i < m; ++i) {
+      stv<TAIL, NT>(h0 + i * d_pad + e0, mh, cnt);
+      if constexpr (BASE == 1) stv<TAIL, NT>(v0 + i * d_pad + e0, mv, cnt);
+    }
+  }
+}
+
 template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT>
 __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
@@ -483,119 +631,24 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
   sp.wd = ti.wd;
   ap.lr = ap.lr * ti.lr_scale;
   ap.wd = ti.wd;
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
-  const void *const *__restrict__ gp = gtab + t.owner;       // worker i: gp[i * n_tensors]
-  float *x0 = x0base + ti.fo + eo;
-  float *u = ubase + ti.fo + eo;
-  float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
-  float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
-  constexpr int gsize = BF16 ? 2 : 4;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if (e0 + 4 <= n) {
-    V4 acc, acch, accv;
-#ifndef SLOWMO_FUSED_NTL
-#define SLOWMO_FUSED_NTL 1
-#endif
-#ifndef SLOWMO_FUSED_UNROLL
-#define SLOWMO_FUSED_UNROLL 8
-#endif
-    _Pragma(SLOWMO_STR(unroll SLOWMO_FUSED_UNROLL))
-    for (int i = 0; i < m; ++i) {
-      float *xi = xp[i] + eo + e0;
-      float *hi = h0 + i * d_pad + e0;
-      float *vi = BASE == 1 ? v0 + i * d_pad + e0 : nullptr;
-      const void *gi = static_cast<const char *>(gp[static_cast<int64_t>(i) * n_tensors]) + eo * gsize;
-      V4 xv = ld4<NT && SLOWMO_FUSED_NTL>(xi), hv, vv;
-      if constexpr (!FIRST) hv = ld4<NT && SLOWMO_FUSED_NTL>(hi);
-      if constexpr (!FIRST && BASE == 1) vv = ld4<NT && SLOWMO_FUSED_NTL>(vi);
-      V4 gv = ldg4<BF16, NT && SLOWMO_FUSED_NTL>(gi, threadIdx.x);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        float xe = xv[c], he = FIRST ? 0.f : hv[c];
-        if constexpr (BASE == 0) {
-          sgd_elem<FIRST>(xe, he, gv[c], sp);
-        } else {
-          float ve = FIRST ? 0.f : vv[c];
-          adam_elem<FIRST>(xe, he, ve, gv[c], ap);
-          vv[c] = ve;
-        }
-        xv[c] = xe;
-        hv[c] = he;
-      }
-      if constexpr (POLICY == 1) {
-        st4<NT>(hi, hv);
-        if constexpr (BASE == 1) st4<NT>(vi, vv);
-      }
-      if constexpr (POLICY == 2) {
-        acch = (i == 0) ? hv : acch + hv;
-        if constexpr (BASE == 1) accv = (i == 0) ? vv : accv + vv;
-      }
-      acc = (i == 0) ? xv : acc + xv;
-    }
-    V4 x0v = ld4<NT>(x0 + e0), uv = ld4<NT>(u + e0), xn;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float ue = uv[c];
-      xn[c] = outer_elem(acc[c], x0v[c], ue, p);
-      uv[c] = ue;
-    }
-    st4<NT>(u + e0, uv);
-    st4<NT>(x0 + e0, xn);
-#pragma unroll 8
-    for (int i = 0; i < m; ++i) st4<NT>(xp[i] + eo + e0, xn);
-    if constexpr (POLICY == 2) {
-      V4 mh, mv;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        mh[c] = acch[c] / p.m_f;
-        if constexpr (BASE == 1) mv[c] = accv[c] / p.m_f;
-      }
-#pragma unroll 8
-      for (int i = 0; i < m; ++i) {
-        st4<NT>(h0 + i * d_pad + e0, mh);
-        if constexpr (BASE == 1) st4<NT>(v0 + i * d_pad + e0, mv);
-      }
-    }
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+  const void *const *__restrict__ gp = gtab + t.owner;
+  float *x0 = x0base + ti.fo + eo;
+  float *u = ubase + ti.fo + eo;
+  float *h0 = hbase + ti.fo + eo;
+  float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
+  if (cnt >= 4) {
+    local_outer_lane<BASE, BF16, FIRST, POLICY, NT, false>(xp, gp, eo, x0, u, h0, v0, d_pad,
+                                                           n_tensors, m, sp, ap, p, e0, 4);
   } else {
-    for (int j = e0; j < n; ++j) {        // ragged tail of the tensor
-      float s = 0.f, sh = 0.f, sv = 0.f;
-      for (int i = 0; i < m; ++i) {
-        float *xi = xp[i] + eo + j;
-        float *hi = h0 + i * d_pad + j;
-        float *vi = BASE == 1 ? v0 + i * d_pad + j : nullptr;
-        const void *gi = static_cast<const char *>(gp[static_cast<int64_t>(i) * n_tensors]) + eo * gsize;
-        float xe = ld1(xi), he = FIRST ? 0.f : ld1(hi), ve = 0.f;
-        float ge = ldg1<BF16>(gi, j);
-        if constexpr (BASE == 0) {
-          sgd_elem<FIRST>(xe, he, ge, sp);
-        } else {
-          ve = FIRST ? 0.f : ld1(vi);
-          adam_elem<FIRST>(xe, he, ve, ge, ap);
-        }
-        if constexpr (POLICY == 1) {
-          st1(hi, he);
-          if constexpr (BASE == 1) st1(vi, ve);
-        }
-        sh = (i == 0) ? he : sh + he;
-        sv = (i == 0) ? ve : sv + ve;
-        s = (i == 0) ? xe : s + xe;
-      }
-      float ue = ld1(u + j);
-      float xn = outer_elem(s, ld1(x0 + j), ue, p);
-      st1(u + j, ue);
-      st1(x0 + j, xn);
-      for (int i = 0; i < m; ++i) st1(xp[i] + eo + j, xn);
-      if constexpr (POLICY == 2) {
-        for (int i = 0; i < m; ++i) {
-          st1(h0 + i * d_pad + j, sh / p.m_f);
-          if constexpr (BASE == 1) st1(v0 + i * d_pad + j, sv / p.m_f);
-        }
-      }
-    }
+    local_outer_lane<BASE, BF16, FIRST, POLICY, NT, true>(
+        xp, gp, eo, x0, u, h0, v0, d_pad, n_tensors, m, sp, ap, p, tail_offset(e0), cnt);
   }
 }
 
@@ -643,13 +696,8 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
 #pragma unroll
   for (int v = 0; v < kBigVpt; ++v) {
     const V4 x0v = ld4<true>(x0 + v * kBigStride + lane);
-    V4 uv = ld4<true>(u + v * kBigStride + lane), xn;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float ue = uv[c];
-      xn[c] = outer_elem(acc[v][c], x0v[c], ue, p);
-      uv[c] = ue;
-    }
+    V4 uv = ld4<true>(u + v * kBigStride + lane);
+    const V4 xn = outer4(acc[v], x0v, uv, p);
     st4<true>(u + v * kBigStride + lane, uv);
     st4<true>(x0 + v * kBigStride + lane, xn);
     acc[v] = xn;
@@ -706,23 +754,11 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
         xv[v] = ld4<true>(xi + off + lane);
         if constexpr (!FIRST) hv[v] = ld4<true>(hi + off + lane);
         if constexpr (!FIRST && BASE == 1) vv[v] = ld4<true>(vi + off + lane);
-        gv[v] = ldg4<BF16, true>(gi + static_cast<int64_t>(off) * gsize, threadIdx.x);
+        gv[v] = ldgv<BF16, false, true>(gi + static_cast<int64_t>(off) * gsize, lane, 4);
       }
 #pragma unroll
       for (int v = 0; v < SUB; ++v) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          float xe = xv[v][c], he = FIRST ? 0.f : hv[v][c];
-          if constexpr (BASE == 0) {
-            sgd_elem<FIRST>(xe, he, gv[v][c], sp);
-          } else {
-            float ve = FIRST ? 0.f : vv[v][c];
-            adam_elem<FIRST>(xe, he, ve, gv[v][c], ap);
-            vv[v][c] = ve;
-          }
-          xv[v][c] = xe;
-          hv[v][c] = he;
-        }
+        step4<BASE, FIRST>(xv[v], hv[v], vv[v], gv[v], sp, ap);
         if constexpr (POLICY == 1) {
           const int off = (s0 + v) * kBigStride;
           st4<true>(hi + off + lane, hv[v]);
@@ -735,13 +771,8 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
 #pragma unroll
   for (int v = 0; v < kBigVpt; ++v) {
     const V4 x0v = ld4<true>(x0 + v * kBigStride + lane);
-    V4 uv = ld4<true>(u + v * kBigStride + lane), xn;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float ue = uv[c];
-      xn[c] = outer_elem(acc[v][c], x0v[c], ue, p);
-      uv[c] = ue;
-    }
+    V4 uv = ld4<true>(u + v * kBigStride + lane);
+    const V4 xn = outer4(acc[v], x0v, uv, p);
     st4<true>(u + v * kBigStride + lane, uv);
     st4<true>(x0 + v * kBigStride + lane, xn);
     acc[v] = xn;
@@ -775,14 +806,13 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
 #endif
 constexpr int kMixBatch = SLOWMO_MIX_BATCH;
 
-// The saved registers of the mixing kernels: kMixSaved values of type T, read
-// and written with a register number 1..kMixSaved that is uniform over the
+// The saved registers of the mixing kernels: kMixSaved vectors, read and
+// written with a register number 1..kMixSaved that is uniform over the
 // workgroup (named members, so that they live in registers).
-template <typename T>
 struct SavedRegs {
-  T r1, r2, r3, r4;
-  __device__ __forceinline__ void clear(const T &z) { r1 = r2 = r3 = r4 = z; }
-  __device__ __forceinline__ void put(int k, const T &v) {
+  V4 r1, r2, r3, r4;
+  __device__ __forceinline__ void clear(const V4 &z) { r1 = r2 = r3 = r4 = z; }
+  __device__ __forceinline__ void put(int k, const V4 &v) {
     if (k == 1) {
       r1 = v;
     } else if (k == 2) {
@@ -793,7 +823,7 @@ struct SavedRegs {
       r4 = v;
     }
   }
-  __device__ __forceinline__ T get(int k, T v) const {   // v: the result for k == 0
+  __device__ __forceinline__ V4 get(int k, V4 v) const {   // v: the result for k == 0
     if (k == 1) {
       v = r1;
     } else if (k == 2) {
@@ -815,6 +845,50 @@ __device__ __forceinline__ bool mix_src_in_register(int32_t flags) {
   return (flags & (kMixSrcFromS | kMixSrcFromFirst)) || mix_src_saved(flags);
 }
 
+// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor whose
+// replicas are xp.
+template <bool NT, bool TAIL>
+__device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
+                                         const MixEntry *__restrict__ seq, int len, int64_t eo,
+                                         int e0, int cnt) {
+  V4 S = {0.f, 0.f, 0.f, 0.f}, first = S;
+  SavedRegs H;
+  H.clear(S);
+  for (int base = 0; base < len; base += kMixBatch) {
+    V4 own[kMixBatch], sv[kMixBatch];
+    float *ptr[kMixBatch];
+#pragma unroll
+    for (int q = 0; q < kMixBatch; ++q) {
+      if (base + q < len) {
+        const MixEntry en = seq[base + q];
+        ptr[q] = xp[en.node] + eo + e0;
+        if (!mix_own_in_register(en.flags)) own[q] = ldv<TAIL, NT && SLOWMO_MIX_OWN_NT>(ptr[q], cnt);
+        if (!(en.flags & kMixNoSrc) && !mix_src_in_register(en.flags))
+          sv[q] = ldv<TAIL, NT && SLOWMO_MIX_SRC_NT>(xp[en.src] + eo + e0, cnt);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kMixBatch; ++q) {
+      if (base + q < len) {
+        const MixEntry en = seq[base + q];
+        const V4 o = (en.flags & kMixOwnFromS) ? S : H.get(mix_own_saved(en.flags), own[q]);
+        if (en.flags & kMixSaveFirst) first = o;
+        if (en.flags & kMixNoSrc) {
+          stv<TAIL, NT>(ptr[q], en.a * o, cnt);
+        } else {
+          H.put(mix_save(en.flags), S);
+          if (en.flags & kMixSrcFromFirst) {
+            S = first;
+          } else if (!(en.flags & kMixSrcFromS)) {
+            S = H.get(mix_src_saved(en.flags), sv[q]);
+          }
+          stv<TAIL, NT>(ptr[q], en.a * o + en.b * S, cnt);
+        }
+      }
+    }
+  }
+}
+
 template <bool NT>
 __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
@@ -824,77 +898,17 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const TensorInfo ti = tensors[t.owner];
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if (ti.unaligned == 0 && e0 + 4 <= n) {
-    V4 S = {0.f, 0.f, 0.f, 0.f}, first = S;
-    SavedRegs<V4> H;
-    H.clear(S);
-    for (int base = 0; base < len; base += kMixBatch) {
-      V4 own[kMixBatch], sv[kMixBatch];
-      float *ptr[kMixBatch];
-#pragma unroll
-      for (int q = 0; q < kMixBatch; ++q) {
-        if (base + q < len) {
-          const MixEntry en = seq[base + q];
-          ptr[q] = xp[en.node] + eo + e0;
-          if (!mix_own_in_register(en.flags)) own[q] = ld4<NT && SLOWMO_MIX_OWN_NT>(ptr[q]);
-          if (!(en.flags & kMixNoSrc) && !mix_src_in_register(en.flags))
-            sv[q] = ld4<NT && SLOWMO_MIX_SRC_NT>(xp[en.src] + eo + e0);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < kMixBatch; ++q) {
-        if (base + q < len) {
-          const MixEntry en = seq[base + q];
-          const V4 o = (en.flags & kMixOwnFromS) ? S : H.get(mix_own_saved(en.flags), own[q]);
-          if (en.flags & kMixSaveFirst) first = o;
-          if (en.flags & kMixNoSrc) {
-            st4<NT>(ptr[q], en.a * o);
-          } else {
-            H.put(mix_save(en.flags), S);
-            if (en.flags & kMixSrcFromFirst) {
-              S = first;
-            } else if (!(en.flags & kMixSrcFromS)) {
-              S = H.get(mix_src_saved(en.flags), sv[q]);
-            }
-            st4<NT>(ptr[q], en.a * o + en.b * S);
-          }
-        }
-      }
-    }
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+  if (cnt >= 4) {
+    mix_lane<NT, false>(xp, seq, len, eo, e0, 4);
   } else {
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) {
-      float S = 0.f, first = 0.f;
-      SavedRegs<float> H;
-      H.clear(0.f);
-      for (int i = 0; i < len; ++i) {
-        const MixEntry en = seq[i];
-        float *ptr = xp[en.node] + eo + j;
-        const float o = (en.flags & kMixOwnFromS)       ? S
-                        : mix_own_saved(en.flags) != 0 ? H.get(mix_own_saved(en.flags), 0.f)
-                                                       : ld1(ptr);
-        if (en.flags & kMixSaveFirst) first = o;
-        if (en.flags & kMixNoSrc) {
-          st1(ptr, en.a * o);
-        } else {
-          H.put(mix_save(en.flags), S);
-          if (en.flags & kMixSrcFromFirst) {
-            S = first;
-          } else if (mix_src_saved(en.flags)) {
-            S = H.get(mix_src_saved(en.flags), 0.f);
-          } else if (!(en.flags & kMixSrcFromS)) {
-            S = ld1(xp[en.src] + eo + j);
-          }
-          st1(ptr, en.a * o + en.b * S);
-        }
-      }
-    }
+    mix_lane<NT, true>(xp, seq, len, eo, tail_offset(e0), cnt);
   }
 }
 
@@ -909,42 +923,67 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
 // whose stepped value is needed as a source before its own turn, and is not
 // the next in the order, is stepped again from memory at its own turn: its x,
 // h and v in memory stay untouched until then.
-template <int BASE, bool BF16, bool FIRST, bool NT>
-__device__ __forceinline__ void step_vec4(const float *xi, const float *hi, const float *vi,
-                                          const void *gi, int lane, const SgdP &sp,
-                                          const AdamP &ap, V4 &xv, V4 &hv, V4 &vv) {
-  xv = ld4<NT>(xi);
-  if constexpr (!FIRST) hv = ld4<NT>(hi);
-  if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(vi);
-  const V4 gv = ldg4<BF16, NT>(gi, lane);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    float xe = xv[c], he = FIRST ? 0.f : hv[c];
-    if constexpr (BASE == 0) {
-      sgd_elem<FIRST>(xe, he, gv[c], sp);
-    } else {
-      float ve = FIRST ? 0.f : vv[c];
-      adam_elem<FIRST>(xe, he, ve, gv[c], ap);
-      vv[c] = ve;
-    }
-    xv[c] = xe;
-    hv[c] = he;
-  }
+template <int BASE, bool BF16, bool FIRST, bool NT, bool TAIL>
+__device__ __forceinline__ void step_from_memory(const float *xi, const float *hi, const float *vi,
+                                                 const void *gi, int e0, int cnt, const SgdP &sp,
+                                                 const AdamP &ap, V4 &xv, V4 &hv, V4 &vv) {
+  xv = ldv<TAIL, NT>(xi + e0, cnt);
+  if constexpr (!FIRST) hv = ldv<TAIL, NT>(hi + e0, cnt);
+  if constexpr (!FIRST && BASE == 1) vv = ldv<TAIL, NT>(vi + e0, cnt);
+  const V4 gv = ldgv<BF16, TAIL, NT>(gi, e0, cnt);
+  step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
 }
 
-template <int BASE, bool BF16, bool FIRST>
-__device__ __forceinline__ void step_1(const float *xi, const float *hi, const float *vi,
-                                       const void *gi, int j, const SgdP &sp, const AdamP &ap,
-                                       float &xe, float &he, float &ve) {
-  xe = ld1(xi);
-  he = FIRST ? 0.f : ld1(hi);
-  ve = 0.f;
-  const float ge = ldg1<BF16>(gi, j);
-  if constexpr (BASE == 0) {
-    sgd_elem<FIRST>(xe, he, ge, sp);
-  } else {
-    ve = FIRST ? 0.f : ld1(vi);
-    adam_elem<FIRST>(xe, he, ve, ge, ap);
+// One lane's elements [e0, e0 + cnt) of a tile; pointers as in local_outer_lane.
+template <int BASE, bool BF16, bool FIRST, bool NT, bool TAIL>
+__device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
+                                               const void *const *__restrict__ gp, int64_t eo,
+                                               float *h0, float *v0, int64_t d_pad, int n_tensors,
+                                               const MixEntry *__restrict__ seq, int len,
+                                               const SgdP &sp, const AdamP &ap, int e0, int cnt) {
+  V4 Sx = {0.f, 0.f, 0.f, 0.f}, Sh = Sx, Sv = Sx, first = Sx;
+  SavedRegs Hx, Hh, Hv;           // saved stepped workers: new x, h and v
+  Hx.clear(Sx);
+  Hh.clear(Sx);
+  Hv.clear(Sx);
+#pragma unroll 1
+  for (int i = 0; i < len; ++i) {
+    const MixEntry en = seq[i];
+    float *xi = xp[en.node] + eo;
+    float *hi = h0 + en.node * d_pad;
+    float *vi = BASE == 1 ? v0 + en.node * d_pad : nullptr;
+    V4 xo, ho, vo;
+    if (mix_own_in_register(en.flags)) {       // in a saved register, else held in S
+      xo = Hx.get(mix_own_saved(en.flags), Sx);
+      ho = Hh.get(mix_own_saved(en.flags), Sh);
+      vo = Hv.get(mix_own_saved(en.flags), Sv);
+    } else {
+      const void *gi = grad_at<BF16>(gp[static_cast<int64_t>(en.node) * n_tensors], eo);
+      step_from_memory<BASE, BF16, FIRST, NT, TAIL>(xi, hi, vi, gi, e0, cnt, sp, ap, xo, ho, vo);
+    }
+    stv<TAIL, NT>(hi + e0, ho, cnt);
+    if constexpr (BASE == 1) stv<TAIL, NT>(vi + e0, vo, cnt);
+    if (en.flags & kMixSaveFirst) first = xo;
+    if (en.flags & kMixNoSrc) {
+      stv<TAIL, NT>(xi + e0, en.a * xo, cnt);
+    } else {
+      Hx.put(mix_save(en.flags), Sx);
+      Hh.put(mix_save(en.flags), Sh);
+      Hv.put(mix_save(en.flags), Sv);
+      if (en.flags & kMixSrcFromFirst) {
+        Sx = first;
+      } else if (mix_src_saved(en.flags)) {
+        Sx = Hx.get(mix_src_saved(en.flags), Sx);
+        Sh = Hh.get(mix_src_saved(en.flags), Sh);
+        Sv = Hv.get(mix_src_saved(en.flags), Sv);
+      } else if (!(en.flags & kMixSrcFromS)) {
+        const void *gs = grad_at<BF16>(gp[static_cast<int64_t>(en.src) * n_tensors], eo);
+        step_from_memory<BASE, BF16, FIRST, NT, TAIL>(
+            xp[en.src] + eo, h0 + en.src * d_pad, BASE == 1 ? v0 + en.src * d_pad : nullptr, gs,
+            e0, cnt, sp, ap, Sx, Sh, Sv);
+      }
+      stv<TAIL, NT>(xi + e0, en.a * xo + en.b * Sx, cnt);
+    }
   }
 }
 
@@ -962,111 +1001,22 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   sp.wd = ti.wd;
   ap.lr = ap.lr * ti.lr_scale;
   ap.wd = ti.wd;
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
+  const int e0 = 4 * static_cast<int>(threadIdx.x);
+  if (e0 >= n) return;
+  const int cnt = n - e0;             // 4 or more: a whole vector
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   const void *const *__restrict__ gp = gtab + t.owner;       // worker i: gp[i * n_tensors]
   float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
-  constexpr int gsize = BF16 ? 2 : 4;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  if (e0 + 4 <= n) {
-    V4 Sx = {0.f, 0.f, 0.f, 0.f}, Sh = Sx, Sv = Sx, first = Sx;
-    SavedRegs<V4> Hx, Hh, Hv;       // saved stepped workers: new x, h and v
-    Hx.clear(Sx);
-    Hh.clear(Sx);
-    Hv.clear(Sx);
-#pragma unroll 1
-    for (int i = 0; i < len; ++i) {
-      const MixEntry en = seq[i];
-      float *xi = xp[en.node] + eo + e0;
-      float *hi = h0 + en.node * d_pad + e0;
-      float *vi = BASE == 1 ? v0 + en.node * d_pad + e0 : nullptr;
-      V4 xo, ho, vo;
-      if (mix_own_in_register(en.flags)) {       // in a saved register, else held in S
-        xo = Hx.get(mix_own_saved(en.flags), Sx);
-        ho = Hh.get(mix_own_saved(en.flags), Sh);
-        vo = Hv.get(mix_own_saved(en.flags), Sv);
-      } else {
-        const void *gi =
-            static_cast<const char *>(gp[static_cast<int64_t>(en.node) * n_tensors]) + eo * gsize;
-        step_vec4<BASE, BF16, FIRST, NT>(xi, hi, vi, gi, threadIdx.x, sp, ap, xo, ho, vo);
-      }
-      st4<NT>(hi, ho);
-      if constexpr (BASE == 1) st4<NT>(vi, vo);
-      if (en.flags & kMixSaveFirst) first = xo;
-      if (en.flags & kMixNoSrc) {
-        st4<NT>(xi, en.a * xo);
-      } else {
-        Hx.put(mix_save(en.flags), Sx);
-        Hh.put(mix_save(en.flags), Sh);
-        Hv.put(mix_save(en.flags), Sv);
-        if (en.flags & kMixSrcFromFirst) {
-          Sx = first;
-        } else if (mix_src_saved(en.flags)) {
-          Sx = Hx.get(mix_src_saved(en.flags), Sx);
-          Sh = Hh.get(mix_src_saved(en.flags), Sh);
-          Sv = Hv.get(mix_src_saved(en.flags), Sv);
-        } else if (!(en.flags & kMixSrcFromS)) {
-          const void *gs =
-              static_cast<const char *>(gp[static_cast<int64_t>(en.src) * n_tensors]) + eo * gsize;
-          step_vec4<BASE, BF16, FIRST, NT>(xp[en.src] + eo + e0, h0 + en.src * d_pad + e0,
-                                           BASE == 1 ? v0 + en.src * d_pad + e0 : nullptr, gs,
-                                           threadIdx.x, sp, ap, Sx, Sh, Sv);
-        }
-        st4<NT>(xi, en.a * xo + en.b * Sx);
-      }
-    }
+  if (cnt >= 4) {
+    local_mix_lane<BASE, BF16, FIRST, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len,
+                                                 sp, ap, e0, 4);
   } else {
-    for (int j = e0; j < n; ++j) {        // ragged tail of the tensor
-      float Sx = 0.f, Sh = 0.f, Sv = 0.f, first = 0.f;
-      SavedRegs<float> Hx, Hh, Hv;
-      Hx.clear(0.f);
-      Hh.clear(0.f);
-      Hv.clear(0.f);
-      for (int i = 0; i < len; ++i) {
-        const MixEntry en = seq[i];
-        float *xi = xp[en.node] + eo + j;
-        float *hi = h0 + en.node * d_pad + j;
-        float *vi = BASE == 1 ? v0 + en.node * d_pad + j : nullptr;
-        float xo, ho, vo;
-        if (mix_own_in_register(en.flags)) {
-          xo = Hx.get(mix_own_saved(en.flags), Sx);
-          ho = Hh.get(mix_own_saved(en.flags), Sh);
-          vo = Hv.get(mix_own_saved(en.flags), Sv);
-        } else {
-          const void *gi =
-              static_cast<const char *>(gp[static_cast<int64_t>(en.node) * n_tensors]) + eo * gsize;
-          step_1<BASE, BF16, FIRST>(xi, hi, vi, gi, j, sp, ap, xo, ho, vo);
-        }
-        st1(hi, ho);
-        if constexpr (BASE == 1) st1(vi, vo);
-        if (en.flags & kMixSaveFirst) first = xo;
-        if (en.flags & kMixNoSrc) {
-          st1(xi, en.a * xo);
-        } else {
-          Hx.put(mix_save(en.flags), Sx);
-          Hh.put(mix_save(en.flags), Sh);
-          Hv.put(mix_save(en.flags), Sv);
-          if (en.flags & kMixSrcFromFirst) {
-            Sx = first;
-          } else if (mix_src_saved(en.flags)) {
-            Sx = Hx.get(mix_src_saved(en.flags), Sx);
-            Sh = Hh.get(mix_src_saved(en.flags), Sh);
-            Sv = Hv.get(mix_src_saved(en.flags), Sv);
-          } else if (!(en.flags & kMixSrcFromS)) {
-            const void *gs =
-                static_cast<const char *>(gp[static_cast<int64_t>(en.src) * n_tensors]) + eo * gsize;
-            step_1<BASE, BF16, FIRST>(xp[en.src] + eo + j, h0 + en.src * d_pad + j,
-                                      BASE == 1 ? v0 + en.src * d_pad + j : nullptr, gs, j, sp, ap,
-                                      Sx, Sh, Sv);
-          }
-          st1(xi, en.a * xo + en.b * Sx);
-        }
-      }
-    }
+    local_mix_lane<BASE, BF16, FIRST, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len, sp,
+                                                ap, tail_offset(e0), cnt);
   }
 }
 
@@ -1088,14 +1038,18 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
   const int e0 = 4 * static_cast<int>(threadIdx.x);
   if (e0 >= n) return;
-  if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(z)) & 15) == 0 && e0 + 4 <= n) {
+  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (cnt >= 4) {
     V4 xv = ld4<NT>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
-    st4<NT>(z + e0, xv);
+    st4_at<NT>(z, e0, xv);
   } else {
-    const int e1 = e0 + 4 < n ? e0 + 4 : n;
-    for (int j = e0; j < e1; ++j) st1(z + j, ld1(x + j) / wi);
+    const int et = tail_offset(e0);
+    V4 xv = ldv<true, NT>(x + et, cnt);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
+    stv<true, NT>(z + et, xv, cnt);
   }
 }
 
@@ -1128,11 +1082,11 @@ hipError_t launch_local_t(const LocalArgs &a, const LaunchTuning &t, hipStream_t
   const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
   if (t.nontemporal) {
     hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, true>), dim3(g.blocks),
-                       dim3(kLocalBlock), 0, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
+                       dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
                        g.chunk, g.run, sp, ap);
   } else {
     hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, false>), dim3(g.blocks),
-                       dim3(kLocalBlock), 0, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
+                       dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
                        g.chunk, g.run, sp, ap);
   }
   return hipGetLastError();
@@ -1376,10 +1330,10 @@ hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &
   const Grid g = make_grid(a.ntiles, t);
   const OuterP p{a.lr, 0.f, a.beta, 1.0f, a.alpha};
   if (t.nontemporal) {
-    hipLaunchKernelGGL((k_outer_noavg<true>), dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles,
+    hipLaunchKernelGGL((k_outer_noavg<true>), dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles,
                        a.slots, a.x0, a.u, a.ntiles, g.chunk, g.run, p);
   } else {
-    hipLaunchKernelGGL((k_outer_noavg<false>), dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles,
+    hipLaunchKernelGGL((k_outer_noavg<false>), dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles,
                        a.slots, a.x0, a.u, a.ntiles, g.chunk, g.run, p);
   }
   return hipGetLastError();
