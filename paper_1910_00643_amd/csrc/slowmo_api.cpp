@@ -37,11 +37,11 @@ size_t ztab_bytes(int32_t m, int32_t n_tensors) {
 
 // Byte offsets of the sections of the caller's workspace.
 struct Sections {
-  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots, tensors, ltiles, otiles, btiles, rtiles, total;
+  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots, tensors, ltiles, otiles, btiles, rtiles, ptiles, prtiles, pace, total;
 };
 
 Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &L, size_t n_ltiles,
-                       size_t n_otiles, size_t n_btiles) {
+                       size_t n_otiles, size_t n_btiles, size_t n_ptiles) {
   Sections s{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -67,6 +67,9 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &
   // big tiles and the ordinary tiles they leave over (at most all of them)
   s.btiles = take(n_btiles * sizeof(TileRef));
   s.rtiles = take(n_btiles ? n_otiles * sizeof(TileRef) : 0);
+  s.ptiles = take(n_ptiles * sizeof(TileRef));
+  s.prtiles = take(n_ptiles ? n_otiles * sizeof(TileRef) : 0);
+  s.pace = take(kPaceWords * sizeof(uint32_t));
   s.total = off;
   return s;
 }
@@ -240,6 +243,11 @@ struct slowmo_ctx {
   // over.  Otherwise n_btiles = 0 and the rest list is the whole ordinary list.
   TileRef *d_btiles = nullptr, *d_rtiles = nullptr;
   int32_t n_btiles = 0, n_rtiles = 0;
+  // Paced walks (gossip step fused with the local step): tiles, and the ordinary
+  // tiles they leave over; paced.ntiles = 0 when the list is too short.
+  PacedArgs paced{};
+  TileRef *d_prtiles = nullptr;
+  int32_t n_prtiles = 0;
   bool big_outer = false;  // the plain outer step uses them too (it gains only with many workers)
   bool big_forced = false; // SLOWMO_BIG_TILES=1: wherever the kernels allow
 
@@ -354,7 +362,8 @@ size_t slowmo_state_bytes(const slowmo_config *cfg, int32_t n_tensors, const int
   return make_sections(*cfg, n_tensors, L,
                        static_cast<size_t>(count_local_tiles(cfg->m, n_tensors, numel)),
                        static_cast<size_t>(count_outer_tiles(n_tensors, numel)),
-                       static_cast<size_t>(count_big_tiles(n_tensors, numel)))
+                       static_cast<size_t>(count_big_tiles(n_tensors, numel)),
+                       static_cast<size_t>(count_pieces(n_tensors, numel, kPacedTile)))
       .total;
 }
 
@@ -474,13 +483,16 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
       ((big < 0 ? m >= kBigFusedFromWorkers : big != 0) && ctx->tune.nontemporal) ? 1 : 0;
   ctx->big_outer = ctx->tune.big_tiles && (big > 0 || m >= kBigOuterFromWorkers);
   ctx->big_forced = big > 0;
+  // paced walks: 0 = never, 1 = by the rule, 2 = wherever the kernels allow
+  ctx->tune.paced = env_flag("SLOWMO_PACED", 1);
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
   const int64_t n_otiles = count_outer_tiles(n_tensors, numel);
   const Sections sec = make_sections(*cfg, n_tensors, ctx->layout, static_cast<size_t>(n_ltiles),
                                      static_cast<size_t>(n_otiles),
-                                     static_cast<size_t>(count_big_tiles(n_tensors, numel)));
+                                     static_cast<size_t>(count_big_tiles(n_tensors, numel)),
+                                     static_cast<size_t>(count_pieces(n_tensors, numel, kPacedTile)));
   if (state_bytes < sec.total) {
     delete ctx;
     return fail(nullptr, SLOWMO_ERR_NOMEM, "state workspace is smaller than slowmo_state_bytes()");
@@ -528,6 +540,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->n_otiles = static_cast<int32_t>(n_otiles);
   ctx->d_btiles = reinterpret_cast<TileRef *>(base + sec.btiles);
   ctx->d_rtiles = reinterpret_cast<TileRef *>(base + sec.rtiles);
+  ctx->d_prtiles = reinterpret_cast<TileRef *>(base + sec.prtiles);
+  ctx->paced.counters = reinterpret_cast<uint32_t *>(base + sec.pace);
 
 #define CREATE_HIP(call, what)              \
   do {                                      \
@@ -608,6 +622,47 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     ctx->n_btiles = static_cast<int32_t>(bt.size());
     ctx->n_rtiles = static_cast<int32_t>(rt.size());
   }
+  // paced tiles: full rows of one tile per CU, plus a last one that is at least
+  // three quarters full (a row takes the same time however full it is: 384 tiles in
+  // two rows were 0-5 % slower, 320 in one row and single waves 2-11 % faster than
+  // all in single waves); what is left over goes to the ordinary tiles.  Below
+  // kPacedMinTiles the second launch costs what the first one gains.
+  std::vector<TileRef> pt, prt;
+  {
+    int cus = 0;
+    CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
+               "number of CUs");
+    ctx->paced.members = cus / 8;
+    const int64_t row = 8 * static_cast<int64_t>(ctx->paced.members);
+    int64_t n = ctx->tune.nontemporal && row > 0 && cus % 8 == 0
+                    ? count_pieces(n_tensors, numel, kPacedTile) : 0;
+    if (ctx->tune.paced < 2) {
+      if (n < kPacedMinTiles) n = 0;
+      if (n % row < row / 4 * 3) n = n / row * row;
+    }
+    if (ctx->tune.paced == 0) n = 0;
+    constexpr int64_t per = kPacedTile / kOuterTile;
+    for (int32_t j = 0; n > 0 && j < n_tensors; ++j) {
+      const int64_t whole = std::min(numel[j] / kPacedTile, n - static_cast<int64_t>(pt.size()));
+      for (int64_t k = 0; k < whole; ++k) pt.push_back({j, static_cast<int32_t>(k)});
+      for (int64_t k = whole * per; k * kOuterTile < numel[j]; ++k)
+        prt.push_back({j, static_cast<int32_t>(k)});
+    }
+  }
+  if (!pt.empty()) {
+    CREATE_HIP(hipMemcpyAsync(base + sec.ptiles, pt.data(), pt.size() * sizeof(TileRef),
+                              hipMemcpyHostToDevice, stream),
+               "upload of the paced tiles");
+    if (!prt.empty())
+      CREATE_HIP(hipMemcpyAsync(ctx->d_prtiles, prt.data(), prt.size() * sizeof(TileRef),
+                                hipMemcpyHostToDevice, stream),
+                 "upload of the tiles the paced ones leave over");
+    ctx->paced.tiles = reinterpret_cast<const TileRef *>(base + sec.ptiles);
+    ctx->paced.ntiles = static_cast<int32_t>(pt.size());
+    ctx->n_prtiles = static_cast<int32_t>(prt.size());
+  }
+  CREATE_HIP(hipMemsetAsync(ctx->paced.counters, 0, kPaceWords * sizeof(uint32_t), stream),
+             "clearing the pace counters");
   CREATE_HIP(hipMemcpyAsync(ctx->d_tensors, tinfo.data(), tinfo.size() * sizeof(TensorInfo),
                             hipMemcpyHostToDevice, stream),
              "upload of the tensor table");
@@ -964,19 +1019,41 @@ std::vector<std::pair<int32_t, int32_t>> mix_launch_ranges(const std::vector<Mix
 struct StagedMix {
   std::vector<std::pair<int32_t, int32_t>> ranges;  // one kernel launch each
   const MixEntry *d_seq = nullptr;
+  int32_t len = 0;                                  // entries of all ranges together
+  bool paced = false;                               // planned for the paced kernel
 };
 
+// Whether the fused gossip step takes the paced tiles.  They keep the chip on one
+// worker at a time, which pays when a launch over one connected group would walk
+// many of them.  Measured with one tensor of 330 to 1555 paced tiles (SGD with fp32
+// and Adam with bf16 gradients, time against single waves): groups of 8 or more
+// workers 0.83-0.98; groups of 4 0.92-1.01 with 16 or 32 workers, 0.93-1.06 with 8;
+// groups of 2 0.93-1.06.  With 4 workers 0.95-1.12.
+bool paced_mix(const slowmo_ctx *ctx, const std::vector<MixEntry> &seq) {
+  if (ctx->paced.ntiles <= 0) return false;
+  if (ctx->tune.paced >= 2) return true;
+  const int32_t m = ctx->cfg.m;
+  size_t groups = 0;
+  for (const MixEntry &e : seq) groups += (e.flags & kMixGroupStart) != 0;
+  return m >= 8 && seq.size() >= groups * (m >= 16 ? 4 : 8);
+}
+
 slowmo_status stage_mix(slowmo_ctx *ctx, const int32_t *in_peer, bool with_idle, hipStream_t stream,
-                        StagedMix *out) {
+                        StagedMix *out, bool may_pace = false) {
   std::vector<MixEntry> seq;
   std::vector<float> share;
   plan_mix(ctx->cfg.m, in_peer, seq, share, with_idle);
+  if (may_pace && paced_mix(ctx, seq)) {
+    out->paced = true;
+    plan_mix(ctx->cfg.m, in_peer, seq, share, with_idle, kPacedSaved);
+  }
   if (seq.empty() || ctx->n_otiles == 0) return SLOWMO_OK;  // nothing to launch
   hipError_t e = hipSuccess;
   const int slot = ctx->mixtab.upload(seq.data(), seq.size() * sizeof(MixEntry), stream, &e);
   if (slot < 0) return fail_hip(ctx, e, "upload of the mixing entries");
   out->d_seq = static_cast<const MixEntry *>(ctx->mixtab.d[slot]);
   out->ranges = mix_launch_ranges(seq);
+  out->len = static_cast<int32_t>(seq.size());
   return SLOWMO_OK;
 }
 
@@ -1063,7 +1140,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
   const bool two_kernels = !ctx->params_aligned || !ctx->tune.fuse_mix || ctx->n_otiles == 0;
   // both tables are on their way to the device before the first kernel is launched
   StagedMix sm;
-  st = stage_mix(ctx, in_peer, /*with_idle=*/!two_kernels, stream, &sm);
+  st = stage_mix(ctx, in_peer, /*with_idle=*/!two_kernels, stream, &sm, /*may_pace=*/!two_kernels);
   if (st != SLOWMO_OK) return st;
   if (two_kernels) {
     // same kernels as the separate calls
@@ -1077,6 +1154,20 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
   } else {
     MixArgs x = mix_args(ctx);
     int launched = 0;
+    if (sm.paced) {
+      x.seq = sm.d_seq;
+      x.len = sm.len;
+      const hipError_t e = guarded(ctx, [&] {
+        return launch_local_mix_paced(a, x, ctx->layout.d_pad, ctx->n_tensors, c.base, bf16,
+                                      ctx->buffers_zero, ctx->paced, stream);
+      });
+      if (e != hipSuccess) return fail_hip(ctx, e, "paced local+mixing kernel launch");
+      ++launched;
+      x.tiles = ctx->d_prtiles;
+      x.ntiles = ctx->n_prtiles;
+      // few tiles are left over: one launch takes them through all groups
+      sm.ranges.assign(ctx->n_prtiles > 0 ? 1 : 0, {0, sm.len});
+    }
     for (const auto &r : sm.ranges) {
       x.seq = sm.d_seq + r.first;
       x.len = r.second - r.first;
@@ -1112,7 +1203,7 @@ int32_t slowmo_plan_mix(int32_t m, const int32_t *in_peer, slowmo_mix_entry *out
   std::vector<float> share;
   plan_mix(m, in_peer, seq, share);
   for (size_t i = 0; i < seq.size(); ++i)
-    out[i] = {seq[i].node, seq[i].src, seq[i].a, seq[i].b, seq[i].flags, 0};
+    out[i] = {seq[i].node, seq[i].src, seq[i].a, seq[i].b, seq[i].flags & ~kMixSrcDone, 0};
   return static_cast<int32_t>(seq.size());
 }
 

@@ -63,6 +63,14 @@ struct MixArgs {
   int32_t len;
 };
 
+// Tiles of a paced walk (see kPacedTile), and what its workgroups pace each other with.
+struct PacedArgs {
+  const TileRef *tiles;        // device: whole kPacedTile pieces (owner = tensor)
+  int32_t ntiles;
+  int32_t members;             // workgroups per XCD: its number of CUs
+  uint32_t *counters;          // device: kPaceWords words, zero between launches
+};
+
 // De-biased parameters of push-sum: z^{(i)} = x^{(i)} / w_i, over the local tiles.
 struct DebiasArgs {
   const TileRef *tiles;        // device (owner = slot)
@@ -80,6 +88,7 @@ struct LaunchTuning {
   int32_t nontemporal;  // 1: streaming (non-temporal) loads and stores
   int32_t fuse_last;    // 1: slowmo_local_outer_step runs one fused kernel when it can
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
+  int32_t paced;        // 1: kernels that store inside a walk over all workers take paced tiles
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
                         // outer step without the average: caps the wavefronts per CU
@@ -119,6 +128,11 @@ hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &tune,
 hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                  int32_t n_tensors, int base, bool bf16, bool first,
                                  const LaunchTuning &tune, hipStream_t stream);
+// The same on paced tiles (whole kPacedTile pieces of any tensors); x.seq must come
+// from plan_mix with saved_limit = kPacedSaved.
+hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
+                                  int32_t n_tensors, int base, bool bf16, bool first,
+                                  const PacedArgs &p, hipStream_t stream);
 hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &tune, hipStream_t stream);
 
 // Static device memory for the entry point that allocates nothing: room for

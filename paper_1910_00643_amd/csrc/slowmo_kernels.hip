@@ -1020,6 +1020,216 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   }
 }
 
+// ---- paced walks over all workers ------------------------------------------------
+// The kernels that take a tile through all workers are bound by the memory's
+// pages: their waves are spread over 2m+4 to 5m streams, each in another place,
+// and the same bytes that run at 0.79 of peak when the chip is busy in a few
+// compact windows run at 0.64.  A paced walk keeps those windows compact.  One
+// 512-thread workgroup per CU stays for the whole launch and takes 16 384 elements
+// (64 KiB of a stream, 8 vectors per lane) at a time; the workgroups of one XCD
+// take neighbouring tiles, and at every worker they wait for each other, so that
+// an XCD reads and writes 2 MiB of one worker's streams, then 2 MiB of the next
+// worker's.  Inside a workgroup each stream is loaded in one burst, and nothing is
+// stored before all its waves have their operands.  Measured on the access
+// pattern of the gossip step (m = 32, 25 M elements, streams at random offsets): single
+// waves 0.64, bursts alone 0.68, with the barrier inside the workgroup 0.72, paced
+// 0.775 of 8 TB/s; 1024 threads or other vector counts are 0.03-0.06 lower.
+//
+// The pace is a matter of speed only: no result depends on it, and no wait is
+// without end.  A workgroup that has waited kPaceSpins polls (about 0.3 ms: some of
+// the others are not running, another kernel has their CUs) waits no more in this
+// launch.
+
+// Counters in the workspace, zero between launches: per XCD one for arrivals and,
+// 256 bytes on, one for the step everybody may begin; after the XCDs' one that
+// counts the workgroups that are done.
+struct Pacer {
+  uint32_t *arrive, *go;
+  uint32_t members, step;
+  bool on;
+  __device__ __forceinline__ Pacer(uint32_t *base, int xcd, int members_)
+      : arrive(base + xcd * kPaceStride), go(arrive + kPaceStride / 2),
+        members(static_cast<uint32_t>(members_)), step(0), on(true) {}
+  // Called by all threads of the workgroup.
+  __device__ __forceinline__ void next() {
+    ++step;
+    __builtin_amdgcn_s_barrier();
+    if (threadIdx.x == 0) {
+      const uint32_t before =
+          __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (before == step * members - 1) {
+        __hip_atomic_store(go, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else if (on) {
+        int spins = 0;
+        while (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < step) {
+          if (++spins == kPaceSpins) {
+            on = false;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(8);
+        }
+      }
+    }
+    __builtin_amdgcn_s_barrier();
+  }
+  // The last workgroup of the launch clears the counters for the next one: by
+  // then every other one has finished its last access to them.
+  __device__ __forceinline__ static void leave(uint32_t *base, uint32_t workgroups) {
+    if (threadIdx.x != 0) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint32_t *done = base + kXcd * kPaceStride;
+    const uint32_t before =
+        __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before != workgroups - 1) return;
+    for (int c = 0; c < 2 * kXcd; ++c)
+      __hip_atomic_store(base + c * (kPaceStride / 2), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+
+constexpr int kPV = kPacedVpt;
+constexpr int kPacedStride = 4 * kPacedBlock;  // floats between a lane's consecutive vectors
+struct PV {                                    // a lane's elements of one stream
+  V4 v[kPV];
+};
+// keeps the bursts apart and in order
+__device__ __forceinline__ void burst_end() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void loads_done() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+}
+__device__ __forceinline__ void paced_load(PV &r, const float *p, int lane) {
+#pragma unroll
+  for (int k = 0; k < kPV; ++k) r.v[k] = ld4<true>(p + k * kPacedStride + lane);
+  burst_end();
+}
+template <bool BF16>
+__device__ __forceinline__ void paced_load_grad(PV &r, const void *g, int lane) {
+#pragma unroll
+  for (int k = 0; k < kPV; ++k) r.v[k] = ldgv<BF16, false, true>(grad_at<BF16>(g, k * kPacedStride), lane, 4);
+  burst_end();
+}
+__device__ __forceinline__ void paced_store(float *p, int lane, const PV &r) {
+#pragma unroll
+  for (int k = 0; k < kPV; ++k) st4<true>(p + k * kPacedStride + lane, r.v[k]);
+  burst_end();
+}
+// One worker's base-optimizer step: x, h and v come back stepped, all waves of the
+// workgroup have their operands.
+template <int BASE, bool BF16, bool FIRST>
+__device__ __forceinline__ void paced_step(PV &x, PV &h, PV &v, const float *xi, const float *hi,
+                                           const float *vi, const void *gi, int lane,
+                                           const SgdP &sp, const AdamP &ap) {
+  PV g;
+  paced_load(x, xi, lane);
+  if constexpr (!FIRST) paced_load(h, hi, lane);
+  if constexpr (!FIRST && BASE == 1) paced_load(v, vi, lane);
+  paced_load_grad<BF16>(g, gi, lane);
+  loads_done();
+#pragma unroll
+  for (int k = 0; k < kPV; ++k) step4<BASE, FIRST>(x.v[k], h.v[k], v.v[k], g.v[k], sp, ap);
+}
+
+// k_local_mix_step on paced tiles.  A worker's buffers are stored as soon as its
+// step is taken for good: at its own turn, or where it is stepped as a source and
+// kept in a register until then (kMixSrcDone), so only x is carried from entry to
+// entry: the held source in registers, the value that opened the cycle and the
+// first saved value in LDS (64 KiB each), the second saved value in registers.
+template <int BASE, bool BF16, bool FIRST>
+__global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
+    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
+    float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
+    float *__restrict__ hbase, float *__restrict__ vbase, const MixEntry *__restrict__ seq, int len,
+    int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int m, uint32_t *pace,
+    SgdP sp0, AdamP ap0) {
+  static_assert(kPacedSaved == 2, "one saved value in LDS, one in registers");
+  __shared__ V4 kept[2][kPV][kPacedBlock];     // [0]: opened the cycle, [1]: saved value 1
+  const int xcd = static_cast<int>(blockIdx.x) % kXcd, rank = static_cast<int>(blockIdx.x) / kXcd;
+  const int lane = 4 * static_cast<int>(threadIdx.x);
+  const int mine = ntiles - xcd * chunk < chunk ? ntiles - xcd * chunk : chunk;  // this XCD's tiles
+  Pacer pacer(pace, xcd, members);
+  for (int at = 0; at + rank < mine; at += members) {
+    const bool paced = at + members <= mine;   // the last, partly filled row of tiles runs free
+    const TileRef t = tiles[xcd * chunk + at + rank];
+    const TensorInfo ti = tensors[t.owner];
+    SgdP sp = sp0;
+    AdamP ap = ap0;
+    sp.lr = sp.lr * ti.lr_scale;
+    sp.wd = ti.wd;
+    ap.lr = ap.lr * ti.lr_scale;
+    ap.wd = ti.wd;
+    const int64_t eo = static_cast<int64_t>(t.k) * kPacedTile;
+    float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+    const void *const *__restrict__ gp = gtab + t.owner;     // worker i: gp[i * n_tensors]
+    float *h0 = hbase + ti.fo + eo;                            // worker i: h0 + i * d_pad
+    float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
+    PV S, saved2, x, h, v;
+#pragma unroll 1
+    for (int i = 0; i < len; ++i) {
+      const MixEntry en = seq[i];
+      if (paced) pacer.next();
+      float *xi = xp[en.node] + eo;
+      PV mixed;                                // a * own, then + b * source
+      if (mix_own_in_register(en.flags)) {
+        const int k = mix_own_saved(en.flags);
+        if (k == 1) {
+#pragma unroll
+          for (int q = 0; q < kPV; ++q) x.v[q] = kept[1][q][threadIdx.x];
+        } else if (k == 2) {
+          x = saved2;
+        } else {
+          x = S;
+        }
+      } else {
+        float *hi = h0 + en.node * d_pad, *vi = BASE == 1 ? v0 + en.node * d_pad : nullptr;
+        paced_step<BASE, BF16, FIRST>(
+            x, h, v, xi, hi, vi, grad_at<BF16>(gp[static_cast<int64_t>(en.node) * n_tensors], eo),
+            lane, sp, ap);
+        paced_store(hi, lane, h);
+        if constexpr (BASE == 1) paced_store(vi, lane, v);
+      }
+      if (en.flags & kMixSaveFirst) {
+#pragma unroll
+        for (int q = 0; q < kPV; ++q) kept[0][q][threadIdx.x] = x.v[q];
+      }
+#pragma unroll
+      for (int q = 0; q < kPV; ++q) mixed.v[q] = en.a * x.v[q];
+      if (!(en.flags & kMixNoSrc)) {
+        const int put = mix_save(en.flags);
+        if (put == 1) {
+#pragma unroll
+          for (int q = 0; q < kPV; ++q) kept[1][q][threadIdx.x] = S.v[q];
+        } else if (put == 2) {
+          saved2 = S;
+        }
+        const int get = mix_src_saved(en.flags);
+        if (en.flags & kMixSrcFromFirst) {
+#pragma unroll
+          for (int q = 0; q < kPV; ++q) S.v[q] = kept[0][q][threadIdx.x];
+        } else if (get == 1) {
+#pragma unroll
+          for (int q = 0; q < kPV; ++q) S.v[q] = kept[1][q][threadIdx.x];
+        } else if (get == 2) {
+          S = saved2;
+        } else if (!(en.flags & kMixSrcFromS)) {
+          float *hs = h0 + en.src * d_pad, *vs = BASE == 1 ? v0 + en.src * d_pad : nullptr;
+          paced_step<BASE, BF16, FIRST>(
+              S, h, v, xp[en.src] + eo, hs, vs,
+              grad_at<BF16>(gp[static_cast<int64_t>(en.src) * n_tensors], eo), lane, sp, ap);
+          if (en.flags & kMixSrcDone) {
+            paced_store(hs, lane, h);
+            if constexpr (BASE == 1) paced_store(vs, lane, v);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < kPV; ++q) mixed.v[q] = mixed.v[q] + en.b * S.v[q];
+      }
+      paced_store(xi, lane, mixed);
+    }
+  }
+  Pacer::leave(pace, gridDim.x);
+}
+
 // z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.
 template <bool NT>
 __global__ __launch_bounds__(kLocalBlock) void k_debias(
@@ -1310,6 +1520,41 @@ hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d
   }
   return bf16 ? launch_local_mix_f<1, true>(l, x, d_pad, n_tensors, first, t, s)
               : launch_local_mix_f<1, false>(l, x, d_pad, n_tensors, first, t, s);
+}
+
+namespace {
+
+template <int BASE, bool BF16, bool FIRST>
+hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pad, int n_tensors,
+                              const PacedArgs &p, hipStream_t s) {
+  const SgdP sp{l.lr, l.mu, l.wd};
+  const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
+  hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
+                     dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
+                     x.len, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members, x.m,
+                     p.counters, sp, ap);
+  return hipGetLastError();
+}
+
+template <int BASE, bool BF16>
+hipError_t launch_mix_paced_f(const LocalArgs &l, const MixArgs &x, int64_t d_pad, int n_tensors,
+                              bool first, const PacedArgs &p, hipStream_t s) {
+  return first ? launch_mix_paced_t<BASE, BF16, true>(l, x, d_pad, n_tensors, p, s)
+               : launch_mix_paced_t<BASE, BF16, false>(l, x, d_pad, n_tensors, p, s);
+}
+
+}  // namespace
+
+hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
+                                  int32_t n_tensors, int base, bool bf16, bool first,
+                                  const PacedArgs &p, hipStream_t s) {
+  if (p.ntiles <= 0 || x.len <= 0) return hipSuccess;
+  if (base == 0) {
+    return bf16 ? launch_mix_paced_f<0, true>(l, x, d_pad, n_tensors, first, p, s)
+                : launch_mix_paced_f<0, false>(l, x, d_pad, n_tensors, first, p, s);
+  }
+  return bf16 ? launch_mix_paced_f<1, true>(l, x, d_pad, n_tensors, first, p, s)
+              : launch_mix_paced_f<1, false>(l, x, d_pad, n_tensors, first, p, s);
 }
 
 hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t s) {

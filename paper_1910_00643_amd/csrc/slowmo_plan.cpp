@@ -31,10 +31,14 @@ int64_t count_outer_tiles(int32_t n_tensors, const int64_t *numel) {
   return t;
 }
 
-int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel) {
+int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece) {
   int64_t t = 0;
-  for (int32_t j = 0; j < n_tensors; ++j) t += numel[j] / kBigTile;
+  for (int32_t j = 0; j < n_tensors; ++j) t += numel[j] / piece;
   return t;
+}
+
+int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel) {
+  return count_pieces(n_tensors, numel, kBigTile);
 }
 
 static void cut(int32_t worker, int32_t n_tensors, const int64_t *numel, int64_t tile,
@@ -77,7 +81,7 @@ void plan_outer(int32_t n_tensors, const int64_t *numel, std::vector<PlanRun> &r
 // other share that register.  A cycle comes after the trees of its members,
 // each member before its source.
 void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
-              std::vector<float> &share, bool with_idle) {
+              std::vector<float> &share, bool with_idle, int32_t saved_limit) {
   std::vector<int32_t> outdeg(m, 0);
   for (int32_t i = 0; i < m; ++i)
     if (in_peer[i] != i) ++outdeg[in_peer[i]];
@@ -180,6 +184,7 @@ void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
       if (w >= 0 && saved[k] == w) return k;
     return -1;
   };
+  std::vector<int32_t> stepped_at(m, -1);  // entry that read the worker as a source last
   for (size_t idx = 0; idx < seq.size(); ++idx) {
     MixEntry &e = seq[idx];
     if (e.flags & kMixGroupStart) {
@@ -193,6 +198,8 @@ void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
       e.flags |= (own_saved + 1) << kMixOwnSavedShift;
     }
     if (own_saved >= 0) saved[own_saved] = -1;  // the worker's own turn is its last use
+    if ((e.node == held || own_saved >= 0) && stepped_at[e.node] >= 0)
+      seq[stepped_at[e.node]].flags |= kMixSrcDone;
     if (e.flags & kMixNoSrc) continue;
     const bool from_first = (e.flags & kMixSrcFromFirst) != 0;
     if (!from_first && e.src == held) {
@@ -201,7 +208,7 @@ void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
     }
     // the source register gets a new value: keep the old one if it is needed again
     if (held >= 0 && last_use[held] > static_cast<int32_t>(idx) && saved_in(held) < 0) {
-      for (int k = 0; k < kMixSaved; ++k) {
+      for (int k = 0; k < saved_limit; ++k) {
         if (saved[k] < 0) {
           saved[k] = held;
           e.flags |= (k + 1) << kMixSaveShift;
@@ -211,6 +218,7 @@ void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
     }
     const int src_saved = from_first ? -1 : saved_in(e.src);
     if (src_saved >= 0) e.flags |= (src_saved + 1) << kMixSrcSavedShift;
+    if (src_saved < 0 && !from_first) stepped_at[e.src] = static_cast<int32_t>(idx);
     held = e.src;
   }
 }

@@ -55,6 +55,18 @@ constexpr int32_t kBigOuterFromWorkers = 16;
 constexpr int32_t kBigMinTiles = 160;
 static_assert(kBigTile % kOuterTile == 0, "a big tile is a whole number of ordinary tiles");
 
+// Paced tiles of the kernels that walk all workers and store inside the walk: one
+// 512-thread workgroup per CU, 8 vectors per lane, 64 KiB of a stream per tile.
+constexpr int32_t kPacedBlock = 512;
+constexpr int32_t kPacedVpt = 8;
+constexpr int32_t kPacedTile = 4 * kPacedBlock * kPacedVpt;
+constexpr int32_t kPacedMinTiles = 300;
+constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMixSaved in single waves)
+constexpr int32_t kPaceStride = 128;    // words between the counters of two XCDs
+constexpr int32_t kPaceWords = 8 * kPaceStride + kPaceStride;
+constexpr int32_t kPaceSpins = 300;
+static_assert(kPacedTile % kOuterTile == 0, "a paced tile is a whole number of ordinary tiles");
+
 // One tile of either kernel: the k-th piece of a tensor.  For the local step
 // `owner` is the slot (worker * n_tensors + tensor); for the outer step it is
 // the tensor.  8 bytes, read with one scalar load.
@@ -122,6 +134,9 @@ enum MixFlag : int32_t {
 //          source value again).
 constexpr int32_t kMixSaveShift = 6, kMixOwnSavedShift = 9, kMixSrcSavedShift = 12;
 constexpr int32_t kMixFieldMask = 7;
+// The source is stepped here for the last time: its own turn takes x from a
+// register, so its buffers may be stored now.
+constexpr int32_t kMixSrcDone = 1 << 15;
 constexpr int32_t mix_save(int32_t flags) { return (flags >> kMixSaveShift) & kMixFieldMask; }
 constexpr int32_t mix_own_saved(int32_t flags) { return (flags >> kMixOwnSavedShift) & kMixFieldMask; }
 constexpr int32_t mix_src_saved(int32_t flags) { return (flags >> kMixSrcSavedShift) & kMixFieldMask; }
@@ -138,8 +153,9 @@ static_assert(sizeof(MixEntry) == 24, "MixEntry layout");
 // The update order of one mixing step for the in-neighbour map in_peer (m
 // entries in 0..m-1); share[j] = 1 / (1 + outdeg(j)).  Workers that neither
 // send nor receive get no entry unless with_idle is set (then: a = 1, kMixNoSrc).
+// saved_limit: how many of the kMixSaved saved registers may be used.
 void plan_mix(int32_t m, const int32_t *in_peer, std::vector<MixEntry> &seq,
-              std::vector<float> &share, bool with_idle = false);
+              std::vector<float> &share, bool with_idle = false, int32_t saved_limit = kMixSaved);
 
 Layout make_layout(int32_t n_tensors, const int64_t *numel);
 
@@ -148,6 +164,7 @@ int64_t count_local_tiles(int32_t m, int32_t n_tensors, const int64_t *numel);
 int64_t count_outer_tiles(int32_t n_tensors, const int64_t *numel);
 // Whole kBigTile pieces over all tensors (an upper bound on the big tiles in use).
 int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel);
+int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
 
 // Tiles in launch order: worker-major, tensors in list order, offsets ascending.
 void plan_local(int32_t m, int32_t n_tensors, const int64_t *numel, std::vector<PlanRun> &runs);
