@@ -476,7 +476,11 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
   // 30 % slower with the cap.
   ctx->tune.local_lds = std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", 8192), 0), 64 * 1024);
-  ctx->tune.outer_lds = std::min(std::max(env_flag("SLOWMO_OUTER_LDS", 0), 0), 64 * 1024);
+  // at most 16 single-wave workgroups per CU in the outer step and the fused last
+  // step, for the same reason: Lookahead with Adam (m = 1) 643 -> 637 us, odd-width
+  // layers packed back to back 2.66 -> 2.64 ms, Transformer-big-shaped round 86.1 ->
+  // 85.9 ms; with 8 the first two are back where they were.
+  ctx->tune.outer_lds = std::min(std::max(env_flag("SLOWMO_OUTER_LDS", 10240), 0), 64 * 1024);
   // big tiles: -1 = by the worker count (see kBigFusedFromWorkers), 0 = never, 1 = always
   const int32_t big = env_flag("SLOWMO_BIG_TILES", -1);
   ctx->tune.big_tiles =

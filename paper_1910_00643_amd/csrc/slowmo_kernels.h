@@ -92,8 +92,8 @@ struct LaunchTuning {
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
                         // outer step without the average: caps the wavefronts per CU
-  int32_t outer_lds;    // bytes of (unused) dynamic LDS per outer-step workgroup: caps the
-                        // number of resident wavefronts per CU (160 KiB / outer_lds); 0 = no cap
+  int32_t outer_lds;    // the same for the outer step and the fused last step (160 KiB / outer_lds
+                        // wavefronts per CU; 0 = no cap)
 };
 
 // base: 0 SGD-Nesterov, 1 Adam.  bf16: gradient dtype.  first: the stored
