@@ -191,7 +191,7 @@ def slowmo_create(cfg: slowmo_config, numel: Sequence[int], params: Sequence[int
                              len(numel) if numel is not None else 0,
                              _i64_array(numel) if numel is not None else None,
                              _ptr_array(params), C.c_void_p(state) if state else None,
-                             state_bytes, C.c_void_p(stream) if stream else None)
+                             state_bytes, stream or None)
     _check(st, None)
     return ctx
 
@@ -199,24 +199,24 @@ def slowmo_create(cfg: slowmo_config, numel: Sequence[int], params: Sequence[int
 def slowmo_local_step(ctx, grads, lr: float, stream: int = 0) -> None:
     """grads: m * n_tensors device addresses, or a prepared ctypes array."""
     arr = grads if (grads is None or isinstance(grads, C.Array)) else _ptr_array(grads)
-    _check(lib().slowmo_local_step(ctx, arr, lr, C.c_void_p(stream) if stream else None), ctx)
+    _check(lib().slowmo_local_step(ctx, arr, lr, stream or None), ctx)
 
 
 def slowmo_local_outer_step(ctx, grads, lr: float, outer_lr: float, stream: int = 0) -> None:
     """The last local step of an outer iteration and the outer step in one call."""
     arr = grads if (grads is None or isinstance(grads, C.Array)) else _ptr_array(grads)
     _check(lib().slowmo_local_outer_step(ctx, arr, lr, outer_lr,
-                                         C.c_void_p(stream) if stream else None), ctx)
+                                         stream or None), ctx)
 
 
 def slowmo_outer_step(ctx, lr: float, stream: int = 0) -> None:
-    _check(lib().slowmo_outer_step(ctx, lr, C.c_void_p(stream) if stream else None), ctx)
+    _check(lib().slowmo_outer_step(ctx, lr, stream or None), ctx)
 
 
 def slowmo_mix_step(ctx, in_peer: Sequence[int], stream: int = 0) -> None:
     """in_peer: m worker indices; worker i receives from in_peer[i]."""
     arr = (C.c_int32 * len(in_peer))(*[int(v) for v in in_peer]) if in_peer is not None else None
-    _check(lib().slowmo_mix_step(ctx, arr, C.c_void_p(stream) if stream else None), ctx)
+    _check(lib().slowmo_mix_step(ctx, arr, stream or None), ctx)
 
 
 def slowmo_local_mix_step(ctx, grads, lr: float, in_peer: Sequence[int], stream: int = 0) -> None:
@@ -224,7 +224,7 @@ def slowmo_local_mix_step(ctx, grads, lr: float, in_peer: Sequence[int], stream:
     arr = grads if (grads is None or isinstance(grads, C.Array)) else _ptr_array(grads)
     peers = (C.c_int32 * len(in_peer))(*[int(v) for v in in_peer]) if in_peer is not None else None
     _check(lib().slowmo_local_mix_step(ctx, arr, lr, peers,
-                                       C.c_void_p(stream) if stream else None), ctx)
+                                       stream or None), ctx)
 
 
 def slowmo_check_device_range(ptr: int, nbytes: int) -> None:
@@ -255,14 +255,14 @@ def slowmo_get_pushsum_weights(ctx, m: int):
 def slowmo_debias(ctx, z, stream: int = 0) -> None:
     """z: m * n_tensors device addresses that receive x^{(i)} / w_i."""
     arr = z if (z is None or isinstance(z, C.Array)) else _ptr_array(z)
-    _check(lib().slowmo_debias(ctx, arr, C.c_void_p(stream) if stream else None), ctx)
+    _check(lib().slowmo_debias(ctx, arr, stream or None), ctx)
 
 
 def slowmo_debias_static(ctx, z, stream: int = 0) -> None:
     """slowmo_debias with its table in the library's static device array
     (no allocation; m * n_tensors <= SLOWMO_STATIC_MAX_POINTERS)."""
     arr = z if (z is None or isinstance(z, C.Array)) else _ptr_array(z)
-    _check(lib().slowmo_debias_static(ctx, arr, C.c_void_p(stream) if stream else None), ctx)
+    _check(lib().slowmo_debias_static(ctx, arr, stream or None), ctx)
 
 
 def slowmo_lr_step_decay(base_lr: float, start_lr: float, warmup_steps: int, milestones,
@@ -299,7 +299,7 @@ def _f32_array(values):
 def slowmo_set_tensor_hparams(ctx, weight_decay=None, lr_scale=None, stream: int = 0) -> None:
     """Per-tensor weight decay / learning-rate scale (sequences of n_tensors or None)."""
     _check(lib().slowmo_set_tensor_hparams(ctx, _f32_array(weight_decay), _f32_array(lr_scale),
-                                           C.c_void_p(stream) if stream else None), ctx)
+                                           stream or None), ctx)
 
 
 def slowmo_export_bytes(ctx) -> int:
@@ -309,12 +309,12 @@ def slowmo_export_bytes(ctx) -> int:
 def slowmo_export_state(ctx, dst: int, nbytes: int, stream: int = 0) -> None:
     """dst: device address of a buffer of at least slowmo_export_bytes(ctx)."""
     _check(lib().slowmo_export_state(ctx, C.c_void_p(dst) if dst else None, nbytes,
-                                     C.c_void_p(stream) if stream else None), ctx)
+                                     stream or None), ctx)
 
 
 def slowmo_import_state(ctx, src: int, nbytes: int, stream: int = 0) -> None:
     _check(lib().slowmo_import_state(ctx, C.c_void_p(src) if src else None, nbytes,
-                                     C.c_void_p(stream) if stream else None), ctx)
+                                     stream or None), ctx)
 
 
 def slowmo_destroy(ctx) -> None:

@@ -720,16 +720,16 @@ slowmo_status prepare_local(slowmo_ctx *ctx, const void *const *grads, float lr,
   const slowmo_config &c = ctx->cfg;
   const size_t n_ptr = static_cast<size_t>(c.m) * ctx->n_tensors;
   const size_t gsize = c.grad_dtype == SLOWMO_BF16 ? 2 : 4;
-  for (size_t i = 0; i < n_ptr; ++i) {
-    if (ctx->numel[i % ctx->n_tensors] == 0) continue;
-    if (!grads[i]) return fail(ctx, SLOWMO_ERR_ARG, "a gradient pointer is NULL");
-    if (reinterpret_cast<uintptr_t>(grads[i]) % gsize)
-      return fail(ctx, SLOWMO_ERR_ALIGN, "a gradient pointer is not aligned to its element size");
-  }
-
-  // gradient-pointer table: reuse a device copy if one of the recent calls had these pointers
+  // gradient-pointer table: reuse a device copy if one of the recent calls had these
+  // very pointers (compared one by one; they passed the checks then)
   int slot = ctx->gtab.find(grads, n_ptr * sizeof(void *));
   if (slot < 0) {
+    for (size_t i = 0, j = 0; i < n_ptr; ++i, j = j + 1 == ctx->numel.size() ? 0 : j + 1) {
+      if (ctx->numel[j] == 0) continue;
+      if (!grads[i]) return fail(ctx, SLOWMO_ERR_ARG, "a gradient pointer is NULL");
+      if (reinterpret_cast<uintptr_t>(grads[i]) % gsize)
+        return fail(ctx, SLOWMO_ERR_ALIGN, "a gradient pointer is not aligned to its element size");
+    }
     hipError_t e = hipSuccess;
     if (ctx->check_pointers >= 2) {
       for (size_t i = 0; i < n_ptr; ++i) {

@@ -30,6 +30,18 @@ def make_config(m: int, tau: int, alpha: float, beta: float, base: str = "sgd_ne
                            beta1=beta1, beta2=beta2, eps=eps, no_average=int(no_average))
 
 
+def _raw_stream(device: torch.device) -> int:
+    """The current stream's handle.  torch.cuda.current_stream() builds a Stream object
+    around it, which takes longer than the rest of a step call's Python."""
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _raw_stream(device: torch.device) -> int:  # noqa: F811
+        i = device.index
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if i is None else i)
+
+
 class SlowMo:
     """params[i][j]: worker i's replica of tensor j (fp32, contiguous, on one
     GPU).  Worker 0's values become the common starting point."""
@@ -80,22 +92,22 @@ class SlowMo:
     def local_step(self, grads, lr: float) -> None:
         """grads: m lists of tensors, or an array from grad_pointer_array()."""
         arr = grads if isinstance(grads, C.Array) else self.grad_pointer_array(grads)
-        B.slowmo_local_step(self.ctx, arr, lr, torch.cuda.current_stream(self.device).cuda_stream)
+        B.slowmo_local_step(self.ctx, arr, lr, _raw_stream(self.device))
 
     def local_outer_step(self, grads, lr: float, outer_lr: Optional[float] = None) -> None:
         """Last local step of the outer iteration + outer step (fused when possible)."""
         arr = grads if isinstance(grads, C.Array) else self.grad_pointer_array(grads)
         B.slowmo_local_outer_step(self.ctx, arr, lr, lr if outer_lr is None else outer_lr,
-                                  torch.cuda.current_stream(self.device).cuda_stream)
+                                  _raw_stream(self.device))
 
     def local_mix_step(self, grads, lr: float, in_peer: Sequence[int]) -> None:
         """A local step and the gossip step after it (fused when possible)."""
         arr = grads if isinstance(grads, C.Array) else self.grad_pointer_array(grads)
         B.slowmo_local_mix_step(self.ctx, arr, lr, in_peer,
-                                torch.cuda.current_stream(self.device).cuda_stream)
+                                _raw_stream(self.device))
 
     def mix_step(self, in_peer: Sequence[int]) -> None:
-        B.slowmo_mix_step(self.ctx, in_peer, torch.cuda.current_stream(self.device).cuda_stream)
+        B.slowmo_mix_step(self.ctx, in_peer, _raw_stream(self.device))
 
     def pushsum_weights(self):
         return B.slowmo_get_pushsum_weights(self.ctx, self.m)
@@ -104,27 +116,27 @@ class SlowMo:
         """z[i][j] <- x^{(i)}_j / w_i (fp32 CUDA tensors shaped like the replicas, or an
         array from param_pointer_array())."""
         arr = z if isinstance(z, C.Array) else self.param_pointer_array(z)
-        B.slowmo_debias(self.ctx, arr, torch.cuda.current_stream(self.device).cuda_stream)
+        B.slowmo_debias(self.ctx, arr, _raw_stream(self.device))
 
     def outer_step(self, lr: float) -> None:
-        B.slowmo_outer_step(self.ctx, lr, torch.cuda.current_stream(self.device).cuda_stream)
+        B.slowmo_outer_step(self.ctx, lr, _raw_stream(self.device))
 
     def set_tensor_hparams(self, weight_decay=None, lr_scale=None) -> None:
         B.slowmo_set_tensor_hparams(self.ctx, weight_decay, lr_scale,
-                                    torch.cuda.current_stream(self.device).cuda_stream)
+                                    _raw_stream(self.device))
 
     def export_state(self) -> torch.Tensor:
         """The optimizer state (x0, u, h, v, counters) as one uint8 CUDA tensor."""
         n = B.slowmo_export_bytes(self.ctx)
         blob = torch.empty(n, dtype=torch.uint8, device=self.device)
         B.slowmo_export_state(self.ctx, blob.data_ptr(), n,
-                              torch.cuda.current_stream(self.device).cuda_stream)
+                              _raw_stream(self.device))
         return blob
 
     def import_state(self, blob: torch.Tensor) -> None:
         assert blob.dtype == torch.uint8 and blob.is_contiguous() and blob.device == self.device
         B.slowmo_import_state(self.ctx, blob.data_ptr(), blob.numel(),
-                              torch.cuda.current_stream(self.device).cuda_stream)
+                              _raw_stream(self.device))
 
     def counters(self):
         return B.slowmo_get_counters(self.ctx)
