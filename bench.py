@@ -345,8 +345,8 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
     }
     names = {"local": "k_local_step (steady state)", "local_first": "k_local_step (buffers read as zero)",
              "local_last": "k_local_step (buffers not stored)",
-             "local_mix": "k_local_mix_step (steady state; all launches of one step)",
-             "local_mix_first": "k_local_mix_step (buffers read as zero)",
+             "local_mix": "k_local_mix_step / k_local_mix_paced (steady state; all launches of one step)",
+             "local_mix_first": "k_local_mix_step / k_local_mix_paced (buffers read as zero)",
              "mix": "k_mix_step (all launches of one step)",
              "outer": "k_outer_noavg" if not w.exact_average else
                       "k_outer_big + k_outer_step (whole 65 536-element pieces + rest)"

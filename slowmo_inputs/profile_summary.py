@@ -63,6 +63,14 @@ def _durations(path):
     return out
 
 
+def _merge_gossip(values):
+    """The fused gossip step runs as paced tiles plus the ordinary kernel for the rest of the
+    list (and for maps of small groups): both under the paced kernel's name."""
+    for k in [k for k in values if k.startswith("k_local_mix_paced")]:
+        values[k] += values.pop("k_local_mix_step" + k[len("k_local_mix_paced"):-1] + ", true>", [])
+    return values
+
+
 def _targs(kernel):
     inner = kernel.partition("<")[2].rstrip(">")
     return [a.strip() for a in inner.split(",")] if inner else []
@@ -75,12 +83,14 @@ def family(kernel):
     a = _targs(kernel)
     fam = {"k_local_step": "local", "k_local_outer_step": "local_outer", "k_outer_step": "outer",
            "k_local_outer_big": "local_outer", "k_outer_big": "outer",
-           "k_mix_step": "mix", "k_local_mix_step": "local_mix", "k_outer_noavg": "outer_noavg",
+           "k_mix_step": "mix", "k_local_mix_step": "local_mix", "k_local_mix_paced": "local_mix",
+           "k_outer_noavg": "outer_noavg",
            "k_debias": "debias", "k_calib_copy": "copy"}.get(name)
     steady = True
     if name == "k_local_step":
         steady = a[2] == "false" and a[3] == "false"
-    elif name in ("k_local_mix_step", "k_local_outer_step", "k_local_outer_big"):
+    elif name in ("k_local_mix_step", "k_local_mix_paced", "k_local_outer_step",
+                  "k_local_outer_big"):
         steady = a[2] == "false"
     return fam, steady
 
@@ -106,7 +116,7 @@ def algorithmic_bytes(kernel, w, rounds, dispatches):
     if name == "k_local_step":
         r, wr = local(a[2] == "true", a[3] == "true")
         return r * md * calls, wr * md * calls, calls
-    if name == "k_local_mix_step":
+    if name in ("k_local_mix_step", "k_local_mix_paced"):
         first = a[2] == "true"
         r, wr = local(first, False)
         calls = (rounds if reset else 1) if first else rounds * w.tau - (rounds if reset else 1)
@@ -157,10 +167,10 @@ def summarize(directory, bench_args, out_md, title, extra_note=""):
     if a.mix:
         w = dataclasses.replace(w, mix=a.mix)
     rounds = a.warmup + 2 * a.steps          # warm-up, timed pass, per-kernel pass
-    dur = _durations(_newest(f"{directory}/kt/*/*_kernel_trace.csv"))
+    dur = _merge_gossip(_durations(_newest(f"{directory}/kt/*/*_kernel_trace.csv")))
     try:
-        fetch = _counter(_newest(f"{directory}/fetch/*/*_counter_collection.csv"))
-        write = _counter(_newest(f"{directory}/write/*/*_counter_collection.csv"))
+        fetch = _merge_gossip(_counter(_newest(f"{directory}/fetch/*/*_counter_collection.csv")))
+        write = _merge_gossip(_counter(_newest(f"{directory}/write/*/*_counter_collection.csv")))
     except FileNotFoundError:       # a kernel-trace-only profile: traffic not measured
         fetch = write = None
     line = [ln for ln in open(f"{directory}/kt.log") if ln.startswith("{")][-1]
@@ -190,7 +200,8 @@ def summarize(directory, bench_args, out_md, title, extra_note=""):
             f"WRITE_SIZE {sum(write[cal]) / len(write[cal]):.2f} (factor {ws:.5f}).\n") if counters
            else "Kernel trace only: the HBM counters were not collected for this command.\n",
            "A library call may launch its kernel several times (the gossip kernels run once per "
-           "connected group of workers): durations, traffic and algorithmic bytes below are "
+           "connected group of workers, or as paced tiles and a rest, listed here under "
+           "`k_local_mix_paced`): durations, traffic and algorithmic bytes below are "
            "summed over all dispatches of a kernel and divided by the number of library calls.\n",
            "| kernel | dispatches | calls | ms per call (kernel trace) | min / max ms per dispatch | "
            "algorithmic bytes per call | GB/s | of 8 TB/s | fetched (scaled) / algorithmic read | "
