@@ -1288,15 +1288,22 @@ Grid make_grid(int ntiles, const LaunchTuning &t) {
 template <int BASE, bool BF16, bool FIRST, bool LAST>
 hipError_t launch_local_t(const LocalArgs &a, const LaunchTuning &t, hipStream_t s) {
   const Grid g = make_grid(a.ntiles, t);
+  // The first step's waves wait between their two loads and have one in flight at a
+  // time: under the cap that is too little.  SGD with fp32 / bf16 gradients, 25.5 M
+  // elements, m = 32: 2.10 / 1.95 ms with it, 1.91-2.01 / 1.79 ms without (without
+  // the wait 2.03-2.08 / 1.78 ms, cap or not).  Adam stores three streams in that
+  // step and likes the middle, 26 wavefronts: 2.36-2.45 ms with the cap, 2.36
+  // without, 2.23-2.25 so.
+  const unsigned lds = !FIRST ? t.local_lds : BASE == 1 ? t.local_lds * 3 / 4 : 0;
   const SgdP sp{a.lr, a.mu, a.wd};
   const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
   if (t.nontemporal) {
     hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, true>), dim3(g.blocks),
-                       dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
+                       dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
                        g.chunk, g.run, sp, ap);
   } else {
     hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, false>), dim3(g.blocks),
-                       dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
+                       dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
                        g.chunk, g.run, sp, ap);
   }
   return hipGetLastError();
