@@ -37,7 +37,7 @@ size_t ztab_bytes(int32_t m, int32_t n_tensors) {
 
 // Byte offsets of the sections of the caller's workspace.
 struct Sections {
-  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots, tensors, ltiles, otiles, btiles, rtiles, ptiles, prtiles, pace, total;
+  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots, tensors, ltiles, otiles, btiles, rtiles, ptiles, pace, cleared, total;
 };
 
 Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &L, size_t n_ltiles,
@@ -56,6 +56,8 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &
   s.u = take(arena * outer_copies);
   s.h = take(arena * c.m);
   s.v = take(c.base == SLOWMO_ADAM ? arena * c.m : 0);
+  s.pace = take(kPaceWords * sizeof(uint32_t));
+  s.cleared = off - s.x0;   // x0, u, h, v and the pace counters start as zeros
   s.xtab_t = take(n_ptr * sizeof(void *));
   for (int i = 0; i < kGradSlots; ++i) s.gtab[i] = take(n_ptr * sizeof(void *));
   for (int i = 0; i < kSlots; ++i) s.mixtab[i] = take(mixtab_bytes(c.m));
@@ -67,9 +69,8 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &
   // big tiles and the ordinary tiles they leave over (at most all of them)
   s.btiles = take(n_btiles * sizeof(TileRef));
   s.rtiles = take(n_btiles ? n_otiles * sizeof(TileRef) : 0);
-  s.ptiles = take(n_ptiles * sizeof(TileRef));
-  s.prtiles = take(n_ptiles ? n_otiles * sizeof(TileRef) : 0);
-  s.pace = take(kPaceWords * sizeof(uint32_t));
+  // paced tiles, then the ordinary tiles they leave over
+  s.ptiles = take(n_ptiles ? (n_ptiles + n_otiles) * sizeof(TileRef) : 0);
   s.total = off;
   return s;
 }
@@ -544,7 +545,6 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->n_otiles = static_cast<int32_t>(n_otiles);
   ctx->d_btiles = reinterpret_cast<TileRef *>(base + sec.btiles);
   ctx->d_rtiles = reinterpret_cast<TileRef *>(base + sec.rtiles);
-  ctx->d_prtiles = reinterpret_cast<TileRef *>(base + sec.prtiles);
   ctx->paced.counters = reinterpret_cast<uint32_t *>(base + sec.pace);
 
 #define CREATE_HIP(call, what)              \
@@ -633,18 +633,21 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // kPacedMinTiles the second launch costs what the first one gains.
   std::vector<TileRef> pt, prt;
   {
-    int cus = 0;
-    CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
-               "number of CUs");
-    ctx->paced.members = cus / 8;
-    const int64_t row = 8 * static_cast<int64_t>(ctx->paced.members);
-    int64_t n = ctx->tune.nontemporal && row > 0 && cus % 8 == 0
+    int64_t n = ctx->tune.nontemporal && ctx->tune.paced != 0
                     ? count_pieces(n_tensors, numel, kPacedTile) : 0;
-    if (ctx->tune.paced < 2) {
-      if (n < kPacedMinTiles) n = 0;
-      if (n % row < row / 4 * 3) n = n / row * row;
+    if (ctx->tune.paced < 2 && (n < kPacedMinTiles || m < kPacedFromWorkers)) n = 0;
+    if (n > 0) {
+      int cus = 0;
+      CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
+                 "number of CUs");
+      ctx->paced.members = cus / 8;
+      const int64_t row = 8 * static_cast<int64_t>(ctx->paced.members);
+      if (row == 0 || cus % 8 != 0) {
+        n = 0;
+      } else if (ctx->tune.paced < 2 && n % row < row / 4 * 3) {
+        n = n / row * row;
+      }
     }
-    if (ctx->tune.paced == 0) n = 0;
     constexpr int64_t per = kPacedTile / kOuterTile;
     for (int32_t j = 0; n > 0 && j < n_tensors; ++j) {
       const int64_t whole = std::min(numel[j] / kPacedTile, n - static_cast<int64_t>(pt.size()));
@@ -654,19 +657,15 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     }
   }
   if (!pt.empty()) {
-    CREATE_HIP(hipMemcpyAsync(base + sec.ptiles, pt.data(), pt.size() * sizeof(TileRef),
-                              hipMemcpyHostToDevice, stream),
-               "upload of the paced tiles");
-    if (!prt.empty())
-      CREATE_HIP(hipMemcpyAsync(ctx->d_prtiles, prt.data(), prt.size() * sizeof(TileRef),
-                                hipMemcpyHostToDevice, stream),
-                 "upload of the tiles the paced ones leave over");
     ctx->paced.tiles = reinterpret_cast<const TileRef *>(base + sec.ptiles);
     ctx->paced.ntiles = static_cast<int32_t>(pt.size());
+    ctx->d_prtiles = reinterpret_cast<TileRef *>(base + sec.ptiles) + pt.size();
     ctx->n_prtiles = static_cast<int32_t>(prt.size());
+    pt.insert(pt.end(), prt.begin(), prt.end());
+    CREATE_HIP(hipMemcpyAsync(base + sec.ptiles, pt.data(), pt.size() * sizeof(TileRef),
+                              hipMemcpyHostToDevice, stream),
+               "upload of the paced tiles and of those they leave over");
   }
-  CREATE_HIP(hipMemsetAsync(ctx->paced.counters, 0, kPaceWords * sizeof(uint32_t), stream),
-             "clearing the pace counters");
   CREATE_HIP(hipMemcpyAsync(ctx->d_tensors, tinfo.data(), tinfo.size() * sizeof(TensorInfo),
                             hipMemcpyHostToDevice, stream),
              "upload of the tensor table");
@@ -678,12 +677,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
              "upload of the replica pointers");
 
   // u_0 = 0, h = v = 0 (Algorithm 1, "Input"; Table C.1 caption)
-  const size_t arena = static_cast<size_t>(L.d_pad) * sizeof(float);
   const size_t outer_copies = cfg->no_average ? static_cast<size_t>(m) : 1;
-  CREATE_HIP(hipMemsetAsync(ctx->x0, 0, arena * outer_copies, stream), "clearing x0");
-  CREATE_HIP(hipMemsetAsync(ctx->u, 0, arena * outer_copies, stream), "clearing u");
-  CREATE_HIP(hipMemsetAsync(ctx->h, 0, arena * m, stream), "clearing h");
-  if (ctx->v) CREATE_HIP(hipMemsetAsync(ctx->v, 0, arena * m, stream), "clearing v");
+  CREATE_HIP(hipMemsetAsync(ctx->x0, 0, sec.cleared, stream), "clearing x0, u, h and v");
   // common starting point x_{0,0}: worker 0's replica, into x0 and every other replica
   {
     OuterArgs ia{};
@@ -1039,7 +1034,7 @@ bool paced_mix(const slowmo_ctx *ctx, const std::vector<MixEntry> &seq) {
   const int32_t m = ctx->cfg.m;
   size_t groups = 0;
   for (const MixEntry &e : seq) groups += (e.flags & kMixGroupStart) != 0;
-  return m >= 8 && seq.size() >= groups * (m >= 16 ? 4 : 8);
+  return m >= kPacedFromWorkers && seq.size() >= groups * (m >= 16 ? 4 : 8);
 }
 
 slowmo_status stage_mix(slowmo_ctx *ctx, const int32_t *in_peer, bool with_idle, hipStream_t stream,

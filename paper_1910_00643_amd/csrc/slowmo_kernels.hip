@@ -8,6 +8,8 @@
 // k_outer_noavg        lines 7-8 per worker, without line 6 (Section 6)
 // k_mix_step        mixing step of stochastic gradient push (Algorithm C.1)
 // k_local_mix_step     a local step and the mixing step that follows it, fused
+// k_local_mix_paced    the same on 16 384-element pieces of long lists, the chip on one
+//                      worker at a time
 // k_debias             de-biased parameters of stochastic gradient push (Algorithm C.1)
 //
 // All of them are pure streams: every byte is read once and written once, no
@@ -20,6 +22,7 @@
 //     stores do not hold a wave slot, reads and writes of neighbouring
 //     workgroups interleave, and the set of addresses in flight is a compact
 //     window that moves through memory in order;
+//   * 16 to 20 of them per CU, not all 32: fewer places in memory at a time;
 //   * non-temporal loads and stores (nothing is reused);
 //   * workgroup -> tile mapping that gives each XCD one contiguous range of
 //     tiles (workgroups are dealt to the 8 XCDs round-robin);
@@ -658,8 +661,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
 // 16 waves of the workgroup read 256 KiB of replica 0, then of replica 1, ...:
 // measured, a memory region that is visited in pieces of this size serves the
 // many-stream walk about 10 % faster than 1 KiB pieces from unrelated waves
-// (m = 32).  The pieces are full and 16-byte aligned in every stream, so there
-// is no element-wise path.  Same arithmetic, same order of the sum, same
+// (m = 32).  The pieces are full, so there is no tail path.  Same arithmetic, same order of the sum, same
 // results as the ordinary tiles.  Streams are addressed as a uniform base (the
 // piece of vector v) plus the lane's offset, which keeps the addresses in
 // scalar registers: the 128 vector registers a 1024-thread workgroup can have

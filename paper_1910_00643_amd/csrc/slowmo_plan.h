@@ -4,8 +4,9 @@
 // Measured on MI355X: the stream mix of this path (3-4 reads, 2-3 writes per
 // element) runs fastest with many short-lived workgroups that each move one
 // 16-byte vector per lane and retire, dispatched in memory order; looping
-// (persistent) workgroups and larger tiles lose 15-20 % of bandwidth.  A tile
-// is therefore small, and holds exactly one contiguous run of one tensor.
+// (persistent) workgroups and larger tiles lose 15-20 % of bandwidth unless they
+// keep each other's company (big and paced tiles below).  An ordinary tile is
+// therefore small, and holds exactly one contiguous run of one tensor.
 #pragma once
 
 #include <cstdint>
@@ -60,6 +61,7 @@ static_assert(kBigTile % kOuterTile == 0, "a big tile is a whole number of ordin
 constexpr int32_t kPacedBlock = 512;
 constexpr int32_t kPacedVpt = 8;
 constexpr int32_t kPacedTile = 4 * kPacedBlock * kPacedVpt;
+constexpr int32_t kPacedFromWorkers = 8;
 constexpr int32_t kPacedMinTiles = 300;
 constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMixSaved in single waves)
 constexpr int32_t kPaceStride = 128;    // words between the counters of two XCDs
