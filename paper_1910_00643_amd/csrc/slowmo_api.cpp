@@ -37,7 +37,8 @@ size_t ztab_bytes(int32_t m, int32_t n_tensors) {
 
 // Byte offsets of the sections of the caller's workspace.
 struct Sections {
-  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots, tensors, ltiles, otiles, btiles, rtiles, ptiles, pace, cleared, total;
+  size_t x0, u, h, v, xtab_t, gtab[kGradSlots], mixtab[kSlots], ztab[kSlots], slots,
+      tensors, ltiles, otiles, pace, cleared, total;
 };
 
 Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &L, size_t n_ltiles,
@@ -65,14 +66,32 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const Layout &
   s.slots = take(n_ptr * sizeof(SlotInfo));
   s.tensors = take(static_cast<size_t>(n_tensors) * sizeof(TensorInfo));
   s.ltiles = take(n_ltiles * sizeof(TileRef));
-  s.otiles = take(n_otiles * sizeof(TileRef));
-  // big tiles and the ordinary tiles they leave over (at most all of them)
-  s.btiles = take(n_btiles * sizeof(TileRef));
-  s.rtiles = take(n_btiles ? n_otiles * sizeof(TileRef) : 0);
-  // paced tiles, then the ordinary tiles they leave over
-  s.ptiles = take(n_ptiles ? (n_ptiles + n_otiles) * sizeof(TileRef) : 0);
+  // ordinary tiles, then, one list after the other, big tiles, the ordinary tiles
+  // they leave over (at most all of them), and the same for paced tiles
+  s.otiles = take((n_otiles + (n_btiles ? n_btiles + n_otiles : 0) +
+                   (n_ptiles ? n_ptiles + n_otiles : 0)) * sizeof(TileRef));
   s.total = off;
   return s;
+}
+
+int32_t env_flag(const char *name, int32_t dflt) {
+  const char *s = std::getenv(name);
+  if (!s || !*s) return dflt;
+  return static_cast<int32_t>(std::strtol(s, nullptr, 10));
+}
+
+// SLOWMO_PACED, read at slowmo_state_bytes and slowmo_create.  Paced walks: 0 = never,
+// 1 = by the rule, 2 = wherever the kernels allow.
+int32_t paced_mode() { return env_flag("SLOWMO_PACED", 1); }
+
+// All sections for a configuration and tensor list that passed check_config.
+Sections make_sections(const slowmo_config &c, int32_t n_tensors, const int64_t *numel,
+                       const Layout &L) {
+  return make_sections(
+      c, n_tensors, L, static_cast<size_t>(count_local_tiles(c.m, n_tensors, numel)),
+      static_cast<size_t>(count_outer_tiles(n_tensors, numel)),
+      static_cast<size_t>(count_big_tiles(n_tensors, numel)),
+      static_cast<size_t>(count_paced_pieces(c.m, n_tensors, numel, paced_mode() >= 2)));
 }
 
 bool finite_pos(float v) { return std::isfinite(v) && v > 0.f; }
@@ -116,12 +135,6 @@ std::string check_config(const slowmo_config *c, int32_t n_tensors, const int64_
   if (count_local_tiles(c->m, n_tensors, numel) > (int64_t(1) << 31) - 16)
     return "too many tiles for one launch (m * total elements too large)";
   return "";
-}
-
-int32_t env_flag(const char *name, int32_t dflt) {
-  const char *s = std::getenv(name);
-  if (!s || !*s) return dflt;
-  return static_cast<int32_t>(std::strtol(s, nullptr, 10));
 }
 
 // A small host->device table that may change from call to call: a ring of
@@ -359,13 +372,7 @@ size_t slowmo_state_bytes(const slowmo_config *cfg, int32_t n_tensors, const int
     g_err = bad;
     return 0;
   }
-  Layout L = make_layout(n_tensors, numel);
-  return make_sections(*cfg, n_tensors, L,
-                       static_cast<size_t>(count_local_tiles(cfg->m, n_tensors, numel)),
-                       static_cast<size_t>(count_outer_tiles(n_tensors, numel)),
-                       static_cast<size_t>(count_big_tiles(n_tensors, numel)),
-                       static_cast<size_t>(count_pieces(n_tensors, numel, kPacedTile)))
-      .total;
+  return make_sections(*cfg, n_tensors, numel, make_layout(n_tensors, numel)).total;
 }
 
 static int64_t plan_query(bool local, int32_t m, int32_t n_tensors, const int64_t *numel,
@@ -488,16 +495,12 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
       ((big < 0 ? m >= kBigFusedFromWorkers : big != 0) && ctx->tune.nontemporal) ? 1 : 0;
   ctx->big_outer = ctx->tune.big_tiles && (big > 0 || m >= kBigOuterFromWorkers);
   ctx->big_forced = big > 0;
-  // paced walks: 0 = never, 1 = by the rule, 2 = wherever the kernels allow
-  ctx->tune.paced = env_flag("SLOWMO_PACED", 1);
+  ctx->tune.paced = paced_mode();
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
   const int64_t n_otiles = count_outer_tiles(n_tensors, numel);
-  const Sections sec = make_sections(*cfg, n_tensors, ctx->layout, static_cast<size_t>(n_ltiles),
-                                     static_cast<size_t>(n_otiles),
-                                     static_cast<size_t>(count_big_tiles(n_tensors, numel)),
-                                     static_cast<size_t>(count_pieces(n_tensors, numel, kPacedTile)));
+  const Sections sec = make_sections(*cfg, n_tensors, numel, ctx->layout);
   if (state_bytes < sec.total) {
     delete ctx;
     return fail(nullptr, SLOWMO_ERR_NOMEM, "state workspace is smaller than slowmo_state_bytes()");
@@ -543,8 +546,6 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->d_otiles = reinterpret_cast<TileRef *>(base + sec.otiles);
   ctx->n_ltiles = static_cast<int32_t>(n_ltiles);
   ctx->n_otiles = static_cast<int32_t>(n_otiles);
-  ctx->d_btiles = reinterpret_cast<TileRef *>(base + sec.btiles);
-  ctx->d_rtiles = reinterpret_cast<TileRef *>(base + sec.rtiles);
   ctx->paced.counters = reinterpret_cast<uint32_t *>(base + sec.pace);
 
 #define CREATE_HIP(call, what)              \
@@ -585,23 +586,25 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     }
   }
   // tiles in launch order: worker-major, tensors in list order, pieces ascending
-  std::vector<TileRef> lt, ot;
+  std::vector<TileRef> lt, lists;  // lists: the ordinary tiles and what is chosen from them
   lt.reserve(static_cast<size_t>(n_ltiles));
-  ot.reserve(static_cast<size_t>(n_otiles));
+  lists.reserve(static_cast<size_t>(n_otiles));
   for (int32_t w = 0; w < m; ++w)
     for (int32_t j = 0; j < n_tensors; ++j)
       for (int64_t k = 0; k * kLocalTile < numel[j]; ++k)
         lt.push_back({w * n_tensors + j, static_cast<int32_t>(k)});
   for (int32_t j = 0; j < n_tensors; ++j)
-    for (int64_t k = 0; k * kOuterTile < numel[j]; ++k) ot.push_back({j, static_cast<int32_t>(k)});
+    for (int64_t k = 0; k * kOuterTile < numel[j]; ++k) lists.push_back({j, static_cast<int32_t>(k)});
   if (!lt.empty())
     CREATE_HIP(hipMemcpyAsync(ctx->d_ltiles, lt.data(), lt.size() * sizeof(TileRef),
                               hipMemcpyHostToDevice, stream),
                "upload of the local-step tiles");
-  if (!ot.empty())
-    CREATE_HIP(hipMemcpyAsync(ctx->d_otiles, ot.data(), ot.size() * sizeof(TileRef),
-                              hipMemcpyHostToDevice, stream),
-               "upload of the outer-step tiles");
+  // appends one more list to the upload; returns its place on the device
+  auto append = [&](const std::vector<TileRef> &v) {
+    TileRef *at = ctx->d_otiles + lists.size();
+    lists.insert(lists.end(), v.begin(), v.end());
+    return at;
+  };
   std::vector<TileRef> bt, rt;
   if (ctx->tune.big_tiles) {
     constexpr int64_t per_big = kBigTile / kOuterTile;
@@ -616,56 +619,29 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     ctx->d_rtiles = ctx->d_otiles;
     ctx->n_rtiles = ctx->n_otiles;
   } else {
-    CREATE_HIP(hipMemcpyAsync(ctx->d_btiles, bt.data(), bt.size() * sizeof(TileRef),
-                              hipMemcpyHostToDevice, stream),
-               "upload of the big tiles");
-    if (!rt.empty())
-      CREATE_HIP(hipMemcpyAsync(ctx->d_rtiles, rt.data(), rt.size() * sizeof(TileRef),
-                                hipMemcpyHostToDevice, stream),
-                 "upload of the tiles the big ones leave over");
+    ctx->d_btiles = append(bt);
+    ctx->d_rtiles = append(rt);
     ctx->n_btiles = static_cast<int32_t>(bt.size());
     ctx->n_rtiles = static_cast<int32_t>(rt.size());
   }
-  // paced tiles: full rows of one tile per CU, plus a last one that is at least
-  // three quarters full (a row takes the same time however full it is: 384 tiles in
-  // two rows were 0-5 % slower, 320 in one row and single waves 2-11 % faster than
-  // all in single waves); what is left over goes to the ordinary tiles.  Below
-  // kPacedMinTiles the second launch costs what the first one gains.
-  std::vector<TileRef> pt, prt;
-  {
-    int64_t n = ctx->tune.nontemporal && ctx->tune.paced != 0
-                    ? count_pieces(n_tensors, numel, kPacedTile) : 0;
-    if (ctx->tune.paced < 2 && (n < kPacedMinTiles || m < kPacedFromWorkers)) n = 0;
-    if (n > 0) {
-      int cus = 0;
-      CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
-                 "number of CUs");
-      ctx->paced.members = cus / 8;
-      const int64_t row = 8 * static_cast<int64_t>(ctx->paced.members);
-      if (row == 0 || cus % 8 != 0) {
-        n = 0;
-      } else if (ctx->tune.paced < 2 && n % row < row / 4 * 3) {
-        n = n / row * row;
-      }
-    }
-    constexpr int64_t per = kPacedTile / kOuterTile;
-    for (int32_t j = 0; n > 0 && j < n_tensors; ++j) {
-      const int64_t whole = std::min(numel[j] / kPacedTile, n - static_cast<int64_t>(pt.size()));
-      for (int64_t k = 0; k < whole; ++k) pt.push_back({j, static_cast<int32_t>(k)});
-      for (int64_t k = whole * per; k * kOuterTile < numel[j]; ++k)
-        prt.push_back({j, static_cast<int32_t>(k)});
-    }
-  }
-  if (!pt.empty()) {
-    ctx->paced.tiles = reinterpret_cast<const TileRef *>(base + sec.ptiles);
+  // paced tiles, for contexts whose fused gossip step is one pass
+  if (ctx->tune.paced != 0 && ctx->tune.nontemporal && ctx->tune.fuse_mix && ctx->params_aligned &&
+      count_paced_pieces(m, n_tensors, numel, ctx->tune.paced >= 2) > 0) {
+    int cus = 0;
+    CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
+               "number of CUs");
+    ctx->paced.members = cus / 8;
+    std::vector<TileRef> pt, prt;
+    plan_paced(m, n_tensors, numel, cus % 8 == 0 ? cus : 0, ctx->tune.paced >= 2, pt, prt);
+    ctx->paced.tiles = append(pt);
     ctx->paced.ntiles = static_cast<int32_t>(pt.size());
-    ctx->d_prtiles = reinterpret_cast<TileRef *>(base + sec.ptiles) + pt.size();
+    ctx->d_prtiles = append(prt);
     ctx->n_prtiles = static_cast<int32_t>(prt.size());
-    pt.insert(pt.end(), prt.begin(), prt.end());
-    CREATE_HIP(hipMemcpyAsync(base + sec.ptiles, pt.data(), pt.size() * sizeof(TileRef),
-                              hipMemcpyHostToDevice, stream),
-               "upload of the paced tiles and of those they leave over");
   }
+  if (!lists.empty())
+    CREATE_HIP(hipMemcpyAsync(ctx->d_otiles, lists.data(), lists.size() * sizeof(TileRef),
+                              hipMemcpyHostToDevice, stream),
+               "upload of the outer-step tiles");
   CREATE_HIP(hipMemcpyAsync(ctx->d_tensors, tinfo.data(), tinfo.size() * sizeof(TensorInfo),
                             hipMemcpyHostToDevice, stream),
              "upload of the tensor table");

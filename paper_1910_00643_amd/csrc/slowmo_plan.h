@@ -167,6 +167,13 @@ int64_t count_outer_tiles(int32_t n_tensors, const int64_t *numel);
 // Whole kBigTile pieces over all tensors (an upper bound on the big tiles in use).
 int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel);
 int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
+// Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
+// worker count is too small (with `forced`, only when no tensor has such a piece).
+int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, bool forced);
+// The pieces a paced walk takes (owner = tensor) on a chip with `row` CUs, and the
+// ordinary tiles they leave over; both empty when it takes none.
+void plan_paced(int32_t m, int32_t n_tensors, const int64_t *numel, int64_t row, bool forced,
+                std::vector<TileRef> &paced, std::vector<TileRef> &rest);
 
 // Tiles in launch order: worker-major, tensors in list order, offsets ascending.
 void plan_local(int32_t m, int32_t n_tensors, const int64_t *numel, std::vector<PlanRun> &runs);

@@ -60,6 +60,19 @@ def test_bad_enums_and_sizes_are_rejected():
     assert P.slowmo_state_bytes(cfg, [16]) > 0
 
 
+@pytest.mark.parametrize("m,pieces,paced", [(7, 400, False), (8, 299, False), (8, 300, True)])
+def test_workspace_holds_paced_tiles_only_where_a_gossip_step_can_take_them(m, pieces, paced):
+    """Tables per 256 elements: m local tiles, an outer tile and, chosen from those, the ones
+    that big tiles leave over; paced walks (8 workers and 300 pieces of 16 384 elements on)
+    need one list more."""
+    d = pieces * 16384
+    arenas = 4 * d * (2 + m)                          # x0, u and m times h (d is a multiple of 64)
+    tables = P.slowmo_state_bytes(_cfg(m=m), [d]) - arenas
+    one_list = 8 * (d // 256)
+    assert ((m + 3) if paced else (m + 2)) * one_list <= tables < \
+        ((m + 3) if paced else (m + 2)) * one_list + one_list // 2
+
+
 def test_create_rejects_bad_pointers_before_using_the_device():
     cfg = _cfg(m=2)
     n = P.slowmo_state_bytes(cfg, [64, 8])
