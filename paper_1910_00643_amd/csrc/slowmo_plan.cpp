@@ -52,15 +52,26 @@ void plan_paced(int32_t m, int32_t n_tensors, const int64_t *numel, int64_t row,
   rest.clear();
   int64_t n = count_paced_pieces(m, n_tensors, numel, forced);
   if (n == 0 || row <= 0) return;
-  // Full rows of one tile per CU, plus a last one that is at least three quarters
-  // full (a row takes the same time however full it is: 384 tiles in two rows were
-  // 0-5 % slower, 320 in one row and single waves 2-11 % faster than all in single
-  // waves); what is left over goes to the ordinary tiles.
-  if (!forced && n % row < row / 4 * 3) n = n / row * row;
-  if (n == 0) return;
   constexpr int64_t per = kPacedTile / kOuterTile;
+  const int64_t tiles = count_outer_tiles(n_tensors, numel);
+  if (!forced) {
+    // Full rows of one tile per CU, plus a last one that is at least 5/8 full: a row
+    // takes the same time however full it is.  Measured on one tensor of one, two and
+    // four full rows and a part of one (8, 16 and 32 workers; SGD with fp32, Adam with
+    // bf16 gradients), time with the part in the paced kernel over time with it in
+    // single waves, by the CUs it occupies: 48 of 256 1.05-1.21, 96 1.02-1.05, 128
+    // 0.99-1.06, 144 0.96-1.00, 160 0.95-1.00, 176 0.94-0.99, 192-240 0.87-0.99.
+    if (n % row < row * 5 / 8) n = n / row * row;
+    // What is left over is a second launch with a tail of its own, which one row does
+    // not always pay for.  Lists of one row, one cycle of 8 to 32 workers, time over
+    // all in single waves: 0.90-0.97 with the rest up to 4/5 of the paced tiles,
+    // 0.91-1.10 beyond (worst where the rest just opens another round of waves).  From
+    // two rows on never more than 1.01.
+    if (n < 2 * row && tiles - n * per > n * per * 4 / 5) return;
+  }
+  if (n == 0) return;
   paced.reserve(static_cast<size_t>(n));
-  rest.reserve(static_cast<size_t>(count_outer_tiles(n_tensors, numel) - n * per));
+  rest.reserve(static_cast<size_t>(tiles - n * per));
   for (int32_t j = 0; j < n_tensors; ++j) {
     const int64_t whole = std::min(numel[j] / kPacedTile, n - static_cast<int64_t>(paced.size()));
     for (int64_t k = 0; k < whole; ++k) paced.push_back({j, static_cast<int32_t>(k)});

@@ -78,7 +78,59 @@ static int replay(int m, const std::vector<int32_t> &peer, int32_t limit) {
   return reads;
 }
 
+// The pieces that plan_paced gives the paced kernel; whole pieces in list order, and
+// together with the rest every ordinary tile once.
+static int64_t paced(int32_t m, const std::vector<int64_t> &numel, int64_t row, bool forced) {
+  const int32_t nt = static_cast<int32_t>(numel.size());
+  constexpr int64_t per = kPacedTile / kOuterTile;
+  std::vector<TileRef> p, r;
+  plan_paced(m, nt, numel.data(), row, forced, p, r);
+  if (p.empty()) {
+    check(r.empty(), "no paced tiles, no rest", m);
+    return 0;
+  }
+  std::vector<int64_t> tile(nt, 0);
+  size_t ip = 0, ir = 0;
+  for (int32_t j = 0; j < nt; ++j) {
+    for (; ip < p.size() && p[ip].owner == j; ++ip, tile[j] += per)
+      check(p[ip].k * per == tile[j] && (p[ip].k + 1) * int64_t{kPacedTile} <= numel[j],
+            "paced tiles are whole pieces in order", m);
+    for (; ir < r.size() && r[ir].owner == j; ++ir, ++tile[j])
+      check(r[ir].k == tile[j], "the rest follows them in order", m);
+    check(tile[j] == (numel[j] + kOuterTile - 1) / kOuterTile, "every tile is in one list", m);
+  }
+  check(ip == p.size() && ir == r.size(), "no tile of another tensor", m);
+  check(static_cast<int64_t>(p.size()) <= count_paced_pieces(m, nt, numel.data(), forced) &&
+            static_cast<int64_t>(r.size()) <= count_outer_tiles(nt, numel.data()),
+        "both lists fit the room that is kept for them", m);
+  return static_cast<int64_t>(p.size());
+}
+
+static void paced_rule() {
+  const int64_t T = kPacedTile, row = 256;
+  check(paced(7, {400 * T}, row, false) == 0 && paced(8, {299 * T}, row, false) == 0 &&
+            paced(8, {400 * T}, 0, false) == 0, "too few workers, pieces, CUs", 0);
+  check(paced(8, {300 * T}, row, false) == 256, "short part of a row: single waves", 0);
+  check(paced(8, {(256 + 159) * T + 5}, row, false) == 256 && paced(8, {(256 + 160) * T}, row, false) == 416 &&
+            paced(8, {(512 + 159) * T}, row, false) == 512 && paced(8, {(512 + 160) * T}, row, false) == 672,
+        "a part of a row from 5/8 on", 0);
+  // whole pieces of several tensors, cut inside one of them
+  check(paced(9, {100 * T + 1, 7, 150 * T, 0, 100 * T + 16383}, row, false) == 256, "cut inside a tensor", 0);
+  // the rest against the pieces of a single row: 44 pieces and the short tensors
+  const int64_t limit = 256 * 64 * 4 / 5 - 44 * 64;
+  for (int64_t more : {0, 1}) {
+    std::vector<int64_t> numel(static_cast<size_t>(limit + more), kOuterTile);
+    numel.push_back(300 * T);
+    check(paced(8, numel, row, false) == (more ? 0 : 256), "one row and a rest of 4/5", 0);
+    numel.back() = 600 * T;
+    check(paced(8, numel, row, false) == 512, "two rows", 0);
+  }
+  check(paced(1, {T - 1, T, 7, T + 5, 2 * T + 4099}, row, true) == 4 && paced(1, {T - 1, 3}, row, true) == 0,
+        "forced: all whole pieces", 0);
+}
+
 int main() {
+  paced_rule();
   std::mt19937 rng(7);
   int reads = 0, workers = 0;
   for (int m = 1; m <= 40; ++m) {
