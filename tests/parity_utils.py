@@ -4,6 +4,9 @@ index subset -- every element evolves independently of the others, so a subset
 is exact), and compare within the stated tolerances."""
 from __future__ import annotations
 
+import contextlib
+import os
+
 import numpy as np
 
 from oracle import slowmo_oracle as O
@@ -159,6 +162,51 @@ def make_gpu(w, prob):
     if w.tensor_wd is not None or w.tensor_lr_scale is not None:
         opt.set_tensor_hparams(w.tensor_wd, w.tensor_lr_scale)
     return opt
+
+
+@contextlib.contextmanager
+def environment(**knobs):
+    """The library's environment variables (read at slowmo_create) set inside the block;
+    a value of None leaves one unset."""
+    old = {k: os.environ.pop(k, None) for k in knobs}
+    os.environ.update({k: v for k, v in knobs.items() if v is not None})
+    try:
+        yield
+    finally:
+        for k, v in old.items():
+            os.environ.pop(k, None)
+            if v is not None:
+                os.environ[k] = v
+
+
+def run_library(w, layouts, step, **knobs):
+    """Two outer iterations in a context created with the given environment variables;
+    step(opt, grads, k) issues the calls of inner step k.  Returns the state as lists
+    of tensors on the device."""
+    from slowmo_inputs.gpu_problem import GpuProblem
+    prob = GpuProblem(w, "cuda:0", param_layout=layouts[0], grad_layout=layouts[1])
+    with environment(**knobs):
+        opt = make_gpu(w, prob)
+    for r in range(2):
+        for k in range(w.tau):
+            prob.fill_grads(0, r * w.tau + k)
+            step(opt, prob.grads[0], k)
+    nt = len(prob.numel)
+    state = {"x": [t for p in prob.params for t in p],
+             "x0": [opt.buffer("x0", j) for j in range(nt)], "u": [opt.buffer("u", j) for j in range(nt)]}
+    if w.policy != "reset":      # under "reset" the buffers mean nothing after an outer step
+        for key in ("h", "v") if w.base == "adam" else ("h",):
+            state[key] = [opt.buffer(key, j, i) for i in range(w.m) for j in range(nt)]
+    opt.close()
+    return state
+
+
+def assert_same_bits(a, b):
+    import torch
+    assert a.keys() == b.keys()
+    for key in a:
+        for i, (s, t) in enumerate(zip(a[key], b[key], strict=True)):
+            assert torch.equal(s, t), (key, i)
 
 
 def _gpu_in_peers(w, step):
