@@ -52,7 +52,8 @@
  *    kernel per connected group of workers; slowmo_local_mix_step launches
  *    the local step and the mixing step one after the other when a replica
  *    pointer is not 16-byte aligned, and from 8 workers on, for long tensor
- *    lists, one kernel for whole 16 384-element pieces and one for the rest;
+ *    lists, one kernel for whole 16 384-element pieces and one, or one per
+ *    connected group, for the rest;
  *    slowmo_outer_step and slowmo_local_outer_step launch one kernel for the
  *    whole 65 536-element pieces of the tensors and one for the rest when the
  *    tensor list has at least 160 such pieces -- the former from 16 workers

@@ -64,7 +64,7 @@ void plan_paced(int32_t m, int32_t n_tensors, const int64_t *numel, int64_t row,
     if (n % row < row * 5 / 8) n = n / row * row;
     // What is left over is a second launch with a tail of its own, which one row does
     // not always pay for.  Lists of one row, one cycle of 8 to 32 workers, time over
-    // all in single waves: 0.90-0.97 with the rest up to 4/5 of the paced tiles,
+    // all in single waves: 0.86-0.99 with the rest up to 4/5 of the paced tiles,
     // 0.91-1.10 beyond (worst where the rest just opens another round of waves).  From
     // two rows on never more than 1.01.
     if (n < 2 * row && tiles - n * per > n * per * 4 / 5) return;

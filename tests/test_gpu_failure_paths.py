@@ -195,6 +195,45 @@ def test_outer_step_on_big_tiles_is_two_launches(fused):
     _assert_same(results[0], results[1])
 
 
+@pytest.mark.parametrize("m,group,launches", [(8, 8, 2), (16, 4, 5)])
+def test_paced_gossip_step_and_the_launches_for_the_rest(m, group, launches):
+    """300 pieces of 16 384 elements and 61 shorter tensors: the paced kernel, then the rest
+    (more than a quarter of the list) once per connected group.  The first launch refused:
+    nothing has changed and the call can be repeated; the last one refused: the call says
+    that memory is partly updated, and the context refuses further steps."""
+    import paper_1910_00643_amd as P
+    B = P.binding
+    shapes = (("a", (300 * 16384 + 3,)),) + tuple((f"s{j}", (16383,)) for j in range(61))
+    w = dataclasses.replace(W.ragged_mini(m=m, policy="maintain"), shapes=shapes, tau=2, rounds=1)
+    idx = np.arange(0, w.d, 97, dtype=np.int64)
+    peers = [i // group * group + (i + 1) % group for i in range(m)]
+    results = []
+    for fail_at in (0, 1, launches):
+        prob = _problem(w, param_layout="arena", grad_layout="padded")
+        opt = _make(w, prob, fail_at)
+        prob.fill_grads(0, 0)
+        call = lambda: opt.local_mix_step(prob.grads[0], w.lr, peers)      # noqa: E731
+        if fail_at == 1:
+            before = _everything(w, prob, opt, idx)
+            with pytest.raises(P.SlowMoError) as e:
+                call()
+            assert e.value.status == B.SLOWMO_ERR_HIP and "partly" not in e.value.message
+            _assert_same(before, _everything(w, prob, opt, idx))
+        if fail_at == launches:
+            with pytest.raises(P.SlowMoError) as e:
+                call()
+            assert e.value.status == B.SLOWMO_ERR_HIP and "partly" in e.value.message
+            assert opt.counters()[:2] == (0, 0) and opt.pushsum_weights() == [1.0] * m
+            with pytest.raises(P.SlowMoError) as e:
+                call()
+            assert e.value.status == B.SLOWMO_ERR_STATE and "destroy" in e.value.message
+        else:
+            call()
+            results.append(_everything(w, prob, opt, idx))
+        opt.close()
+    _assert_same(results[0], results[1])
+
+
 def test_import_checks_the_whole_blob_before_it_touches_the_context():
     """A blob with a good header whose later parts are bad (a non-positive
     push-sum weight; counters that do not fit) is refused with the context's
