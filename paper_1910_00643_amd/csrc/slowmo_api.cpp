@@ -632,6 +632,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
                "number of CUs");
     ctx->paced.members = cus / 8;
+    // test hook: a limit that the workgroups reach, to run on out of step
+    ctx->paced.spins = env_flag("SLOWMO_TEST_PACE_SPINS", kPaceSpins);
     std::vector<TileRef> pt, prt;
     plan_paced(m, n_tensors, numel, cus % 8 == 0 ? cus : 0, ctx->tune.paced >= 2, pt, prt);
     ctx->paced.tiles = append(pt);

@@ -68,6 +68,7 @@ struct PacedArgs {
   const TileRef *tiles;        // device: whole kPacedTile pieces (owner = tensor)
   int32_t ntiles;
   int32_t members;             // workgroups per XCD: its number of CUs
+  int32_t spins;               // polls after which a workgroup stops waiting for the others
   uint32_t *counters;          // device: kPaceWords words, zero between launches
 };
 

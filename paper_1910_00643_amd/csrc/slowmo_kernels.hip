@@ -1038,7 +1038,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
 // 0.775 of 8 TB/s; 1024 threads or other vector counts are 0.03-0.06 lower.
 //
 // The pace is a matter of speed only: no result depends on it, and no wait is
-// without end.  A workgroup that has waited kPaceSpins polls (about 0.3 ms: some of
+// without end.  A workgroup that has waited `spins` polls (kPaceSpins, about 0.3 ms: some of
 // the others are not running, another kernel has their CUs) waits no more in this
 // launch.
 
@@ -1048,10 +1048,11 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
 struct Pacer {
   uint32_t *arrive, *go;
   uint32_t members, step;
+  int spins;
   bool on;
-  __device__ __forceinline__ Pacer(uint32_t *base, int xcd, int members_)
+  __device__ __forceinline__ Pacer(uint32_t *base, int xcd, int members_, int spins_)
       : arrive(base + xcd * kPaceStride), go(arrive + kPaceStride / 2),
-        members(static_cast<uint32_t>(members_)), step(0), on(true) {}
+        members(static_cast<uint32_t>(members_)), step(0), spins(spins_), on(true) {}
   // Called by all threads of the workgroup.
   __device__ __forceinline__ void next() {
     ++step;
@@ -1062,9 +1063,9 @@ struct Pacer {
       if (before == step * members - 1) {
         __hip_atomic_store(go, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else if (on) {
-        int spins = 0;
+        int polls = 0;
         while (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < step) {
-          if (++spins == kPaceSpins) {
+          if (++polls >= spins) {
             on = false;
             break;
           }
@@ -1142,14 +1143,14 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
     float *__restrict__ hbase, float *__restrict__ vbase, const MixEntry *__restrict__ seq, int len,
-    int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int m, uint32_t *pace,
-    SgdP sp0, AdamP ap0) {
+    int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int spins, int m,
+    uint32_t *pace, SgdP sp0, AdamP ap0) {
   static_assert(kPacedSaved == 2, "one saved value in LDS, one in registers");
   __shared__ V4 kept[2][kPV][kPacedBlock];     // [0]: opened the cycle, [1]: saved value 1
   const int xcd = static_cast<int>(blockIdx.x) % kXcd, rank = static_cast<int>(blockIdx.x) / kXcd;
   const int lane = 4 * static_cast<int>(threadIdx.x);
   const int mine = ntiles - xcd * chunk < chunk ? ntiles - xcd * chunk : chunk;  // this XCD's tiles
-  Pacer pacer(pace, xcd, members);
+  Pacer pacer(pace, xcd, members, spins);
   for (int at = 0; at + rank < mine; at += members) {
     const bool paced = at + members <= mine;   // the last, partly filled row of tiles runs free
     const TileRef t = tiles[xcd * chunk + at + rank];
@@ -1540,8 +1541,8 @@ hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
                      dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
-                     x.len, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members, x.m,
-                     p.counters, sp, ap);
+                     x.len, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members,
+                     p.spins, x.m, p.counters, sp, ap);
   return hipGetLastError();
 }
 

@@ -25,6 +25,10 @@ def _free_gpu_memory():
 
 # below a tile, exactly one, one and a few, two and an odd rest, a tile that is not the first
 SMALL = (("a", (TILE - 1,)), ("b", (TILE,)), ("c", (7,)), ("d", (TILE + 5,)), ("e", (2 * TILE + 4099,)))
+# what the library paces by itself: 300 pieces (256 of them paced), the rest with the short
+# tensors more than a quarter of the list; 513 pieces (512 paced), cut inside the last tensor
+ONE_ROW = (("a", (300 * TILE + 3,)),) + tuple((f"s{j}", (TILE - 1,)) for j in range(61))
+TWO_ROWS = (("a", (200 * TILE + 1,)), ("b", (5,)), ("c", (150 * TILE,)), ("d", (163 * TILE + TILE - 1,)))
 # more than one tile per CU: full rows, in which the workgroups pace each other, and a part of one
 ROWS = (("a", (300 * TILE + 3,)), ("b", (301 * TILE,)))
 
@@ -65,3 +69,38 @@ def test_gossip_step(shapes, m, base, grad_dtype, policy):
     step = _gossip(w, maps)
     PU.assert_same_bits(PU.run_library(w, ("separate", "flat"), step, SLOWMO_PACED="2"),
                         PU.run_library(w, ("separate", "flat"), step, SLOWMO_PACED="0"))
+
+
+def _groups(*sizes):
+    """Cycles of the given sizes side by side."""
+    starts = np.cumsum((0,) + sizes[:-1])
+    return [int(a + (i - 1) % n) for a, n in zip(starts, sizes) for i in range(n)]
+
+
+@pytest.mark.parametrize("shapes,m,base,grad_dtype,policy", [
+    (ONE_ROW, 8, "adam", "bf16", "maintain"),
+    (ONE_ROW, 16, "sgd_nesterov", "f32", "reset"),
+    (TWO_ROWS, 9, "adam", "f32", "reset"),
+    (TWO_ROWS, 16, "sgd_nesterov", "bf16", "maintain"),
+])
+def test_gossip_steps_that_the_library_paces_by_itself(shapes, m, base, grad_dtype, policy):
+    """No variable set: whole rows of paced tiles, the pieces beyond them with the rest, and
+    in one context maps that are paced (one cycle, a star, large groups) next to maps that
+    are not (pairs)."""
+    maps = [_groups(m), _groups(*[2] * (m // 2) + [1] * (m % 2)), [0] * m,
+            _groups(*[4] * (m // 4) + [1] * (m % 4)),
+            [int(v) for v in np.random.default_rng(m).integers(0, m, size=m)]]
+    w = _workload(shapes, m, base, grad_dtype, policy, tau=5)
+    step = _gossip(w, maps)
+    PU.assert_same_bits(PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED=None),
+                        PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED="0"))
+
+
+def test_workgroups_that_stop_waiting_for_each_other():
+    """With a limit of one poll almost every workgroup gives up its first wait and runs on
+    out of step, in one launch after the other: the pace is a matter of speed only."""
+    w = _workload(ROWS, 4, "sgd_nesterov", "f32", "maintain", tau=3)
+    step = _gossip(w, [_groups(4), [0, 0, 0, 0], _groups(2, 2)])
+    PU.assert_same_bits(
+        PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED="2", SLOWMO_TEST_PACE_SPINS="1"),
+        PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED="0"))

@@ -42,6 +42,18 @@ def test_fused_last_step_on_unaligned_pointers(base, grad_dtype, policy, layouts
                         PU.run_library(w, layouts, _rounds(w), SLOWMO_FUSE_LAST="0"))
 
 
+@pytest.mark.parametrize("base,grad_dtype,policy", [
+    ("sgd_nesterov", "f32", "reset"), ("sgd_nesterov", "bf16", "reset"), ("adam", "bf16", "maintain"),
+    ("adam", "f32", "reset")])
+def test_fused_last_step_on_big_tiles_with_unaligned_gradients(base, grad_dtype, policy):
+    """Big tiles ask for aligned replicas only: the tensors of 70 001 and 131 077 elements
+    have one and two of them, with gradients at any element."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy=policy, m=3), tau=2)
+    layouts = ("separate", "flat")
+    PU.assert_same_bits(PU.run_library(w, layouts, _rounds(w), SLOWMO_BIG_TILES="1"),
+                        PU.run_library(w, layouts, _rounds(w), SLOWMO_FUSE_LAST="0"))
+
+
 @pytest.mark.parametrize("base,grad_dtype", [("sgd_nesterov", "f32"), ("adam", "bf16")])
 def test_fused_gossip_step_with_unaligned_gradients(base, grad_dtype):
     w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy="maintain", m=5), tau=2)
