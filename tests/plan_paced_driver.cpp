@@ -1,11 +1,12 @@
 // Replays mixing orders planned for the paced gossip kernel (two saved values; a
 // worker's buffers stored where kMixSrcDone says so, or at its own turn) in place,
-// the way the kernel does, against the simultaneous update.
+// the way the kernel does, against the simultaneous update; and checks which pieces of a
+// list plan_paced hands to it.
 #include <cstdio>
 #include <cstdlib>
 #include <random>
 
-#include "../paper_1910_00643_amd/csrc/slowmo_plan.h"
+#include "slowmo_plan.h"
 
 using namespace slowmo;
 
