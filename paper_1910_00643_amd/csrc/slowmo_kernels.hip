@@ -142,56 +142,53 @@ __device__ __forceinline__ void st4_arena(float *p, int e0, V4 v) {
   }
 }
 
-// Lane offset of the tail path.  Opaque, so that the compiler does not share one
-// 64-bit address per lane and stream between it and the full vectors' path,
-// which addresses with a scalar base and a 32-bit lane offset.
-__device__ __forceinline__ int tail_offset(int e0) {
-  asm volatile("" : "+v"(e0));
-  return e0;
+// The lanes of a tile of n elements.  n >= 4: lane t owns the vector at element 4t;
+// the last one of a ragged tile moves back to n - 4, so it takes part in the same
+// instructions as the others, and loads, computes and stores the elements it shares
+// with its neighbour as the neighbour does.  (A path of its own for that lane is a
+// second walk for its wave, and the loads it held cost every wave registers: fused
+// last step 95-131 VGPRs against 59-68 so.  20 tensors of 50 001 elements, m = 32:
+// fused last step 132 -> 115 us with SGD and fp32, 179 -> 155 us with Adam and bf16
+// gradients, gossip step 68 -> 51 us.)  Both lanes read before either writes because they are lanes
+// of one wave: a workgroup must be a single one.  n < 4 (ONE): one element per lane.
+static_assert(kLocalBlock == 64 && kOuterBlock == 64, "a tile belongs to one wave");
+__device__ __forceinline__ int lane_element(int n) {
+  const int e = 4 * static_cast<int>(threadIdx.x);
+  return e < n - 4 ? e : n - 4;
+}
+__device__ __forceinline__ bool lane_idle(int n) {
+  const int t = static_cast<int>(threadIdx.x);
+  return (n >= 4 ? 4 * t : t) >= n;
 }
 
-// The last lane of a tensor may own fewer than four elements (cnt = 1, 2 or 3).
-// It loads element min(j, cnt - 1) in place of element j, so that its loads are
-// as independent of each other as the other lanes' are, goes through the same
-// arithmetic, and stores the elements it owns.
-template <bool TAIL, bool NT>
-__device__ __forceinline__ V4 ldv(const float *p, int cnt) {
-  if constexpr (TAIL) {
-    const SLOWMO_GLOBAL float *q = as_global<float>(p);
-    V4 r;
-    r.x = q[0];
-    r.y = q[cnt > 1 ? 1 : 0];
-    r.z = q[cnt > 2 ? 2 : 0];
-    r.w = r.x;
-    return r;
+template <bool ONE, bool NT>
+__device__ __forceinline__ V4 ldv(const float *p) {
+  if constexpr (ONE) {
+    const float f = *as_global<float>(p);
+    return V4{f, f, f, f};
   } else {
     return ld4<NT>(p);
   }
 }
-template <bool TAIL, bool NT>
-__device__ __forceinline__ void stv(float *p, V4 v, int cnt) {
-  if constexpr (TAIL) {
-    SLOWMO_GLOBAL float *q = as_global<float>(p);
-    q[0] = v.x;
-    if (cnt > 1) q[1] = v.y;
-    if (cnt > 2) q[2] = v.z;
+template <bool ONE, bool NT>
+__device__ __forceinline__ void stv(float *p, V4 v) {
+  if constexpr (ONE) {
+    *as_global<float>(p) = v.x;
   } else {
     st4<NT>(p, v);
   }
 }
 
 // Gradients: fp32 as is, bf16 widened exactly (the 16 bits become the high half
-// of an fp32 word).  Elements [e0, e0 + cnt) of g.
-template <bool BF16, bool TAIL, bool NT>
-__device__ __forceinline__ V4 ldgv(const void *g, int e0, int cnt) {
+// of an fp32 word).  The vector (ONE: the element) at element e0 of g.
+template <bool BF16, bool ONE, bool NT>
+__device__ __forceinline__ V4 ldgv(const void *g, int e0) {
   if constexpr (BF16) {
     V4 r;
-    if constexpr (TAIL) {
-      const SLOWMO_GLOBAL uint16_t *q = as_global<uint16_t>(g) + e0;
-      r.x = __uint_as_float(static_cast<uint32_t>(q[0]) << 16);
-      r.y = __uint_as_float(static_cast<uint32_t>(q[cnt > 1 ? 1 : 0]) << 16);
-      r.z = __uint_as_float(static_cast<uint32_t>(q[cnt > 2 ? 2 : 0]) << 16);
-      r.w = r.x;
+    if constexpr (ONE) {
+      const float f =
+          __uint_as_float(static_cast<uint32_t>(as_global<uint16_t>(g)[e0]) << 16);
+      r = V4{f, f, f, f};
     } else {
       const GU2 *q = reinterpret_cast<const GU2 *>(as_global<uint16_t>(g) + e0);
       const U2 w = NT ? __builtin_nontemporal_load(q) : *q;
@@ -202,7 +199,7 @@ __device__ __forceinline__ V4 ldgv(const void *g, int e0, int cnt) {
     }
     return r;
   } else {
-    return ldv<TAIL, NT>(static_cast<const float *>(g) + e0, cnt);
+    return ldv<ONE, NT>(static_cast<const float *>(g) + e0);
   }
 }
 template <bool BF16>
@@ -324,8 +321,7 @@ __device__ __forceinline__ void have_now(const T &a) {
 }
 
 // ---- local step ---------------------------------------------------------------
-// One workgroup = one tile = up to 4 * blockDim elements of one (worker,
-// tensor).  Lane t owns elements [4t, 4t + 4) of the tile.
+// One workgroup = one tile = up to 4 * blockDim elements of one (worker, tensor).
 
 // FIRST: the stored buffers are to be read as zero (not loaded).  LAST: the
 // buffers are dead after this step (the reset policy discards them before
@@ -353,43 +349,39 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
   float *v = BASE == 1 ? vbase + s.so + go : nullptr;
   const int64_t left = s.numel - go;
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   V4 xv, hv, vv, gv;
-  if (cnt >= 4) {
+  if (n >= 4) {
+    const int e0 = lane_element(n);
     xv = ld4<NT>(x + e0);
     // With only two loads per wave (buffers read as zero) the step measures 2.5 %
     // faster when the second load is issued after the first has returned
     // (2.125 -> 2.072 ms, m = 32, 25.6 M elements, four alternating runs); with
     // three or four loads the same wait changes nothing or costs 1-2 %.
     if constexpr (FIRST) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xv)::"memory");
-    gv = ldgv<BF16, false, NT>(g, e0, 4);
+    gv = ldgv<BF16, false, NT>(g, e0);
     if constexpr (!FIRST) hv = ld4<NT>(h + e0);
     if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
-  } else {
-    const int et = tail_offset(e0);
-    xv = ldv<true, NT>(x + et, cnt);
-    if constexpr (!FIRST) hv = ldv<true, NT>(h + et, cnt);
-    if constexpr (!FIRST && BASE == 1) vv = ldv<true, NT>(v + et, cnt);
-    gv = ldgv<BF16, true, NT>(g, et, cnt);
-  }
-  step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
-  if (cnt >= 4) {
+    step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
     st4_at<NT>(x, e0, xv);
     if constexpr (!LAST) st4_arena<NT>(h, e0, hv);
     if constexpr (!LAST && BASE == 1) st4_arena<NT>(v, e0, vv);
   } else {
-    const int et = tail_offset(e0);
-    stv<true, NT>(x + et, xv, cnt);
-    if constexpr (!LAST) stv<true, NT>(h + et, hv, cnt);
-    if constexpr (!LAST && BASE == 1) stv<true, NT>(v + et, vv, cnt);
+    const int e0 = static_cast<int>(threadIdx.x);
+    xv = ldv<true, NT>(x + e0);
+    if constexpr (!FIRST) hv = ldv<true, NT>(h + e0);
+    if constexpr (!FIRST && BASE == 1) vv = ldv<true, NT>(v + e0);
+    gv = ldgv<BF16, true, NT>(g, e0);
+    step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+    stv<true, NT>(x + e0, xv);
+    if constexpr (!LAST) stv<true, NT>(h + e0, hv);
+    if constexpr (!LAST && BASE == 1) stv<true, NT>(v + e0, vv);
   }
 }
 
 // ---- outer step -----------------------------------------------------------------
-// One workgroup = one tile = up to 4 * blockDim elements of one tensor; lane t
-// owns elements [4t, 4t + 4) in all m replicas, x0 and u.
+// One workgroup = one tile = up to 4 * blockDim elements of one tensor; a lane owns
+// the same elements in all m replicas, x0 and u.
 
 #ifndef SLOWMO_OUTER_UNROLL
 #define SLOWMO_OUTER_UNROLL 8
@@ -406,40 +398,40 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
 
 // Buffer strategy "average" for this lane's elements of one arena (h or v):
 // every worker's value becomes the ordered mean over the workers.
-template <bool TAIL, bool NTL, bool NTS>
+template <bool ONE, bool NTL, bool NTS>
 __device__ __forceinline__ void average_arena(float *__restrict__ b0, int64_t stride, int m,
-                                              float m_f, int e0, int cnt) {
-  V4 acc = ldv<TAIL, NTL>(b0 + e0, cnt);
+                                              float m_f, int e0) {
+  V4 acc = ldv<ONE, NTL>(b0 + e0);
   SLOWMO_PRAGMA_UNROLL_OUTER
-  for (int i = 1; i < m; ++i) acc = acc + ldv<TAIL, NTL>(b0 + i * stride + e0, cnt);
+  for (int i = 1; i < m; ++i) acc = acc + ldv<ONE, NTL>(b0 + i * stride + e0);
   V4 mean;
 #pragma unroll
   for (int c = 0; c < 4; ++c) mean[c] = acc[c] / m_f;
   SLOWMO_PRAGMA_UNROLL_OUTER
-  for (int i = 0; i < m; ++i) stv<TAIL, NTS>(b0 + i * stride + e0, mean, cnt);
+  for (int i = 0; i < m; ++i) stv<ONE, NTS>(b0 + i * stride + e0, mean);
 }
 
-// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor; xp:
+// One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor; xp:
 // its m replicas; x0, u, h0, v0: the tile's place in the arenas.
-template <bool NT, int AVG, bool TAIL>
+template <bool NT, int AVG, bool ONE>
 __device__ __forceinline__ void outer_lane(float *const *__restrict__ xp, int64_t eo, float *x0,
                                            float *u, float *h0, float *v0, int64_t d_pad, int m,
-                                           const OuterP &p, int e0, int cnt) {
+                                           const OuterP &p, int e0) {
   constexpr bool NTL = NT && SLOWMO_OUTER_NTL, NTS = NT && SLOWMO_OUTER_NTS;
   // line 6: ordered sum over the replicas, i = 0, 1, ..., m-1
-  V4 acc = ldv<TAIL, NTL>(xp[0] + eo + e0, cnt);
+  V4 acc = ldv<ONE, NTL>(xp[0] + eo + e0);
   SLOWMO_PRAGMA_UNROLL_OUTER
-  for (int i = 1; i < m; ++i) acc = acc + ldv<TAIL, NTL>(xp[i] + eo + e0, cnt);
-  const V4 x0v = ldv<TAIL, NTL>(x0 + e0, cnt);
-  V4 uv = ldv<TAIL, NTL>(u + e0, cnt);
+  for (int i = 1; i < m; ++i) acc = acc + ldv<ONE, NTL>(xp[i] + eo + e0);
+  const V4 x0v = ldv<ONE, NTL>(x0 + e0);
+  V4 uv = ldv<ONE, NTL>(u + e0);
   const V4 xn = outer4(acc, x0v, uv, p);
-  stv<TAIL, NTS>(u + e0, uv, cnt);
-  stv<TAIL, NTS>(x0 + e0, xn, cnt);
+  stv<ONE, NTS>(u + e0, uv);
+  stv<ONE, NTS>(x0 + e0, xn);
   SLOWMO_PRAGMA_UNROLL_OUTER
-  for (int i = 0; i < m; ++i) stv<TAIL, NTS>(xp[i] + eo + e0, xn, cnt);
+  for (int i = 0; i < m; ++i) stv<ONE, NTS>(xp[i] + eo + e0, xn);
   // line 2 of the next outer iteration, strategy "average"
-  if constexpr (AVG >= 1) average_arena<TAIL, NTL, NTS>(h0, d_pad, m, p.m_f, e0, cnt);
-  if constexpr (AVG >= 2) average_arena<TAIL, NTL, NTS>(v0, d_pad, m, p.m_f, e0, cnt);
+  if constexpr (AVG >= 1) average_arena<ONE, NTL, NTS>(h0, d_pad, m, p.m_f, e0);
+  if constexpr (AVG >= 2) average_arena<ONE, NTL, NTS>(v0, d_pad, m, p.m_f, e0);
 }
 
 // AVG: 0 = lines 6-8 only; 1 = also average h over the workers; 2 = h and v.
@@ -458,15 +450,13 @@ __global__ __launch_bounds__(kOuterBlock) void k_outer_step(
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   float *x0 = x0base + ti.fo + eo, *u = ubase + ti.fo + eo;
   float *h0 = AVG >= 1 ? hbase + ti.fo + eo : nullptr, *v0 = AVG >= 2 ? vbase + ti.fo + eo : nullptr;
-  if (cnt >= 4) {
-    outer_lane<NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, e0, 4);
+  if (n >= 4) {
+    outer_lane<NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, lane_element(n));
   } else {
-    outer_lane<NT, AVG, true>(xp, eo, x0, u, h0, v0, d_pad, m, p, tail_offset(e0), cnt);
+    outer_lane<NT, AVG, true>(xp, eo, x0, u, h0, v0, d_pad, m, p, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -485,21 +475,20 @@ __global__ __launch_bounds__(kOuterBlock) void k_init_broadcast(
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   float *x0 = x0base + ti.fo + eo;
-  if (cnt >= 4) {
+  if (n >= 4) {
+    const int e0 = lane_element(n);
     const V4 v = ld4<NT>(xp[0] + eo + e0);
     for (int c = 0; c < x0_copies; ++c) st4<NT>(x0 + c * d_pad + e0, v);
 #pragma unroll 8
     for (int i = 1; i < m; ++i) st4<NT>(xp[i] + eo + e0, v);
   } else {
-    const int et = tail_offset(e0);
-    const V4 v = ldv<true, NT>(xp[0] + eo + et, cnt);
-    for (int c = 0; c < x0_copies; ++c) stv<true, NT>(x0 + c * d_pad + et, v, cnt);
-    for (int i = 1; i < m; ++i) stv<true, NT>(xp[i] + eo + et, v, cnt);
+    const int e0 = static_cast<int>(threadIdx.x);
+    const V4 v = ldv<true, NT>(xp[0] + eo + e0);
+    for (int c = 0; c < x0_copies; ++c) stv<true, NT>(x0 + c * d_pad + e0, v);
+    for (int i = 1; i < m; ++i) stv<true, NT>(xp[i] + eo + e0, v);
   }
 }
 
@@ -523,30 +512,23 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   float *u = ubase + s.so + go;
   const int64_t left = s.numel - go;
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
-  V4 xv, x0v, uv;
-  if (cnt >= 4) {
-    xv = ld4<NT>(x + e0);
-    x0v = ld4<NT>(x0 + e0);
-    uv = ld4<NT>(u + e0);
-  } else {
-    const int et = tail_offset(e0);
-    xv = ldv<true, NT>(x + et, cnt);
-    x0v = ldv<true, NT>(x0 + et, cnt);
-    uv = ldv<true, NT>(u + et, cnt);
-  }
-  const V4 xn = outer4(xv, x0v, uv, p);
-  if (cnt >= 4) {
+  if (lane_idle(n)) return;
+  if (n >= 4) {
+    const int e0 = lane_element(n);
+    const V4 xv = ld4<NT>(x + e0), x0v = ld4<NT>(x0 + e0);
+    V4 uv = ld4<NT>(u + e0);
+    const V4 xn = outer4(xv, x0v, uv, p);
     st4_arena<NT>(u, e0, uv);
     st4_arena<NT>(x0, e0, xn);
     st4_at<NT>(x, e0, xn);
   } else {
-    const int et = tail_offset(e0);
-    stv<true, NT>(u + et, uv, cnt);
-    stv<true, NT>(x0 + et, xn, cnt);
-    stv<true, NT>(x + et, xn, cnt);
+    const int e0 = static_cast<int>(threadIdx.x);
+    const V4 xv = ldv<true, NT>(x + e0), x0v = ldv<true, NT>(x0 + e0);
+    V4 uv = ldv<true, NT>(u + e0);
+    const V4 xn = outer4(xv, x0v, uv, p);
+    stv<true, NT>(u + e0, uv);
+    stv<true, NT>(x0 + e0, xn);
+    stv<true, NT>(x + e0, xn);
   }
 }
 
@@ -564,31 +546,31 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
 #ifndef SLOWMO_FUSED_UNROLL
 #define SLOWMO_FUSED_UNROLL 8
 #endif
-// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor; xp:
+// One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor; xp:
 // its replicas, gp: its gradients (worker i: gp[i * n_tensors]); x0, u, h0, v0:
 // the tile's place in the arenas (worker i's buffers: + i * d_pad).
-template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool TAIL>
+template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool ONE>
 __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
                                                  const void *const *__restrict__ gp, int64_t eo,
                                                  float *x0, float *u, float *h0, float *v0,
                                                  int64_t d_pad, int n_tensors, int m,
                                                  const SgdP &sp, const AdamP &ap, const OuterP &p,
-                                                 int e0, int cnt) {
+                                                 int e0) {
   constexpr bool NTL = NT && SLOWMO_FUSED_NTL;
   V4 acc, acch, accv;
   _Pragma(SLOWMO_STR(unroll SLOWMO_FUSED_UNROLL))
   for (int i = 0; i < m; ++i) {
     float *hi = h0 + i * d_pad + e0;
     float *vi = BASE == 1 ? v0 + i * d_pad + e0 : nullptr;
-    V4 xv = ldv<TAIL, NTL>(xp[i] + eo + e0, cnt), hv, vv;
-    if constexpr (!FIRST) hv = ldv<TAIL, NTL>(hi, cnt);
-    if constexpr (!FIRST && BASE == 1) vv = ldv<TAIL, NTL>(vi, cnt);
+    V4 xv = ldv<ONE, NTL>(xp[i] + eo + e0), hv, vv;
+    if constexpr (!FIRST) hv = ldv<ONE, NTL>(hi);
+    if constexpr (!FIRST && BASE == 1) vv = ldv<ONE, NTL>(vi);
     const V4 gv =
-        ldgv<BF16, TAIL, NTL>(grad_at<BF16>(gp[static_cast<int64_t>(i) * n_tensors], eo), e0, cnt);
+        ldgv<BF16, ONE, NTL>(grad_at<BF16>(gp[static_cast<int64_t>(i) * n_tensors], eo), e0);
     step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
     if constexpr (POLICY == 1) {
-      stv<TAIL, NT>(hi, hv, cnt);
-      if constexpr (BASE == 1) stv<TAIL, NT>(vi, vv, cnt);
+      stv<ONE, NT>(hi, hv);
+      if constexpr (BASE == 1) stv<ONE, NT>(vi, vv);
     }
     if constexpr (POLICY == 2) {
       acch = (i == 0) ? hv : acch + hv;
@@ -596,13 +578,13 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
     }
     acc = (i == 0) ? xv : acc + xv;
   }
-  const V4 x0v = ldv<TAIL, NT>(x0 + e0, cnt);
-  V4 uv = ldv<TAIL, NT>(u + e0, cnt);
+  const V4 x0v = ldv<ONE, NT>(x0 + e0);
+  V4 uv = ldv<ONE, NT>(u + e0);
   const V4 xn = outer4(acc, x0v, uv, p);
-  stv<TAIL, NT>(u + e0, uv, cnt);
-  stv<TAIL, NT>(x0 + e0, xn, cnt);
+  stv<ONE, NT>(u + e0, uv);
+  stv<ONE, NT>(x0 + e0, xn);
 #pragma unroll 8
-  for (int i = 0; i < m; ++i) stv<TAIL, NT>(xp[i] + eo + e0, xn, cnt);
+  for (int i = 0; i < m; ++i) stv<ONE, NT>(xp[i] + eo + e0, xn);
   if constexpr (POLICY == 2) {
     V4 mh, mv;
 #pragma unroll
@@ -612,8 +594,8 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
     }
 #pragma unroll 8
     for (int i = 0; i < m; ++i) {
-      stv<TAIL, NT>(h0 + i * d_pad + e0, mh, cnt);
-      if constexpr (BASE == 1) stv<TAIL, NT>(v0 + i * d_pad + e0, mv, cnt);
+      stv<ONE, NT>(h0 + i * d_pad + e0, mh);
+      if constexpr (BASE == 1) stv<ONE, NT>(v0 + i * d_pad + e0, mv);
     }
   }
 }
@@ -637,21 +619,19 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   const void *const *__restrict__ gp = gtab + t.owner;
   float *x0 = x0base + ti.fo + eo;
   float *u = ubase + ti.fo + eo;
   float *h0 = hbase + ti.fo + eo;
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
-  if (cnt >= 4) {
+  if (n >= 4) {
     local_outer_lane<BASE, BF16, FIRST, POLICY, NT, false>(xp, gp, eo, x0, u, h0, v0, d_pad,
-                                                           n_tensors, m, sp, ap, p, e0, 4);
+                                                           n_tensors, m, sp, ap, p, lane_element(n));
   } else {
     local_outer_lane<BASE, BF16, FIRST, POLICY, NT, true>(
-        xp, gp, eo, x0, u, h0, v0, d_pad, n_tensors, m, sp, ap, p, tail_offset(e0), cnt);
+        xp, gp, eo, x0, u, h0, v0, d_pad, n_tensors, m, sp, ap, p, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -756,7 +736,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
         xv[v] = ld4<true>(xi + off + lane);
         if constexpr (!FIRST) hv[v] = ld4<true>(hi + off + lane);
         if constexpr (!FIRST && BASE == 1) vv[v] = ld4<true>(vi + off + lane);
-        gv[v] = ldgv<BF16, false, true>(gi + static_cast<int64_t>(off) * gsize, lane, 4);
+        gv[v] = ldgv<BF16, false, true>(gi + static_cast<int64_t>(off) * gsize, lane);
       }
 #pragma unroll
       for (int v = 0; v < SUB; ++v) {
@@ -847,12 +827,12 @@ __device__ __forceinline__ bool mix_src_in_register(int32_t flags) {
   return (flags & (kMixSrcFromS | kMixSrcFromFirst)) || mix_src_saved(flags);
 }
 
-// One lane's elements [e0, e0 + cnt) of the tile at element eo of a tensor whose
+// One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor whose
 // replicas are xp.
-template <bool NT, bool TAIL>
+template <bool NT, bool ONE>
 __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
                                          const MixEntry *__restrict__ seq, int len, int64_t eo,
-                                         int e0, int cnt) {
+                                         int e0) {
   V4 S = {0.f, 0.f, 0.f, 0.f}, first = S;
   SavedRegs H;
   H.clear(S);
@@ -864,9 +844,9 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
       if (base + q < len) {
         const MixEntry en = seq[base + q];
         ptr[q] = xp[en.node] + eo + e0;
-        if (!mix_own_in_register(en.flags)) own[q] = ldv<TAIL, NT && SLOWMO_MIX_OWN_NT>(ptr[q], cnt);
+        if (!mix_own_in_register(en.flags)) own[q] = ldv<ONE, NT && SLOWMO_MIX_OWN_NT>(ptr[q]);
         if (!(en.flags & kMixNoSrc) && !mix_src_in_register(en.flags))
-          sv[q] = ldv<TAIL, NT && SLOWMO_MIX_SRC_NT>(xp[en.src] + eo + e0, cnt);
+          sv[q] = ldv<ONE, NT && SLOWMO_MIX_SRC_NT>(xp[en.src] + eo + e0);
       }
     }
 #pragma unroll
@@ -876,7 +856,7 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
         const V4 o = (en.flags & kMixOwnFromS) ? S : H.get(mix_own_saved(en.flags), own[q]);
         if (en.flags & kMixSaveFirst) first = o;
         if (en.flags & kMixNoSrc) {
-          stv<TAIL, NT>(ptr[q], en.a * o, cnt);
+          stv<ONE, NT>(ptr[q], en.a * o);
         } else {
           H.put(mix_save(en.flags), S);
           if (en.flags & kMixSrcFromFirst) {
@@ -884,7 +864,7 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
           } else if (!(en.flags & kMixSrcFromS)) {
             S = H.get(mix_src_saved(en.flags), sv[q]);
           }
-          stv<TAIL, NT>(ptr[q], en.a * o + en.b * S, cnt);
+          stv<ONE, NT>(ptr[q], en.a * o + en.b * S);
         }
       }
     }
@@ -903,14 +883,12 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
-  if (cnt >= 4) {
-    mix_lane<NT, false>(xp, seq, len, eo, e0, 4);
+  if (n >= 4) {
+    mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
   } else {
-    mix_lane<NT, true>(xp, seq, len, eo, tail_offset(e0), cnt);
+    mix_lane<NT, true>(xp, seq, len, eo, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -925,24 +903,24 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
 // whose stepped value is needed as a source before its own turn, and is not
 // the next in the order, is stepped again from memory at its own turn: its x,
 // h and v in memory stay untouched until then.
-template <int BASE, bool BF16, bool FIRST, bool NT, bool TAIL>
+template <int BASE, bool BF16, bool FIRST, bool NT, bool ONE>
 __device__ __forceinline__ void step_from_memory(const float *xi, const float *hi, const float *vi,
-                                                 const void *gi, int e0, int cnt, const SgdP &sp,
+                                                 const void *gi, int e0, const SgdP &sp,
                                                  const AdamP &ap, V4 &xv, V4 &hv, V4 &vv) {
-  xv = ldv<TAIL, NT>(xi + e0, cnt);
-  if constexpr (!FIRST) hv = ldv<TAIL, NT>(hi + e0, cnt);
-  if constexpr (!FIRST && BASE == 1) vv = ldv<TAIL, NT>(vi + e0, cnt);
-  const V4 gv = ldgv<BF16, TAIL, NT>(gi, e0, cnt);
+  xv = ldv<ONE, NT>(xi + e0);
+  if constexpr (!FIRST) hv = ldv<ONE, NT>(hi + e0);
+  if constexpr (!FIRST && BASE == 1) vv = ldv<ONE, NT>(vi + e0);
+  const V4 gv = ldgv<BF16, ONE, NT>(gi, e0);
   step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
 }
 
-// One lane's elements [e0, e0 + cnt) of a tile; pointers as in local_outer_lane.
-template <int BASE, bool BF16, bool FIRST, bool NT, bool TAIL>
+// One lane's vector (ONE: element) at e0 of a tile; pointers as in local_outer_lane.
+template <int BASE, bool BF16, bool FIRST, bool NT, bool ONE>
 __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
                                                const void *const *__restrict__ gp, int64_t eo,
                                                float *h0, float *v0, int64_t d_pad, int n_tensors,
                                                const MixEntry *__restrict__ seq, int len,
-                                               const SgdP &sp, const AdamP &ap, int e0, int cnt) {
+                                               const SgdP &sp, const AdamP &ap, int e0) {
   V4 Sx = {0.f, 0.f, 0.f, 0.f}, Sh = Sx, Sv = Sx, first = Sx;
   SavedRegs Hx, Hh, Hv;           // saved stepped workers: new x, h and v
   Hx.clear(Sx);
@@ -961,13 +939,13 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
       vo = Hv.get(mix_own_saved(en.flags), Sv);
     } else {
       const void *gi = grad_at<BF16>(gp[static_cast<int64_t>(en.node) * n_tensors], eo);
-      step_from_memory<BASE, BF16, FIRST, NT, TAIL>(xi, hi, vi, gi, e0, cnt, sp, ap, xo, ho, vo);
+      step_from_memory<BASE, BF16, FIRST, NT, ONE>(xi, hi, vi, gi, e0, sp, ap, xo, ho, vo);
     }
-    stv<TAIL, NT>(hi + e0, ho, cnt);
-    if constexpr (BASE == 1) stv<TAIL, NT>(vi + e0, vo, cnt);
+    stv<ONE, NT>(hi + e0, ho);
+    if constexpr (BASE == 1) stv<ONE, NT>(vi + e0, vo);
     if (en.flags & kMixSaveFirst) first = xo;
     if (en.flags & kMixNoSrc) {
-      stv<TAIL, NT>(xi + e0, en.a * xo, cnt);
+      stv<ONE, NT>(xi + e0, en.a * xo);
     } else {
       Hx.put(mix_save(en.flags), Sx);
       Hh.put(mix_save(en.flags), Sh);
@@ -980,11 +958,11 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
         Sv = Hv.get(mix_src_saved(en.flags), Sv);
       } else if (!(en.flags & kMixSrcFromS)) {
         const void *gs = grad_at<BF16>(gp[static_cast<int64_t>(en.src) * n_tensors], eo);
-        step_from_memory<BASE, BF16, FIRST, NT, TAIL>(
+        step_from_memory<BASE, BF16, FIRST, NT, ONE>(
             xp[en.src] + eo, h0 + en.src * d_pad, BASE == 1 ? v0 + en.src * d_pad : nullptr, gs,
-            e0, cnt, sp, ap, Sx, Sh, Sv);
+            e0, sp, ap, Sx, Sh, Sv);
       }
-      stv<TAIL, NT>(xi + e0, en.a * xo + en.b * Sx, cnt);
+      stv<ONE, NT>(xi + e0, en.a * xo + en.b * Sx);
     }
   }
 }
@@ -1006,19 +984,17 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
+  if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   const void *const *__restrict__ gp = gtab + t.owner;       // worker i: gp[i * n_tensors]
   float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
-  if (cnt >= 4) {
+  if (n >= 4) {
     local_mix_lane<BASE, BF16, FIRST, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len,
-                                                 sp, ap, e0, 4);
+                                                 sp, ap, lane_element(n));
   } else {
     local_mix_lane<BASE, BF16, FIRST, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len, sp,
-                                                ap, tail_offset(e0), cnt);
+                                                ap, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -1109,7 +1085,7 @@ __device__ __forceinline__ void paced_load(PV &r, const float *p, int lane) {
 template <bool BF16>
 __device__ __forceinline__ void paced_load_grad(PV &r, const void *g, int lane) {
 #pragma unroll
-  for (int k = 0; k < kPV; ++k) r.v[k] = ldgv<BF16, false, true>(grad_at<BF16>(g, k * kPacedStride), lane, 4);
+  for (int k = 0; k < kPV; ++k) r.v[k] = ldgv<BF16, false, true>(grad_at<BF16>(g, k * kPacedStride), lane);
   burst_end();
 }
 __device__ __forceinline__ void paced_store(float *p, int lane, const PV &r) {
@@ -1249,20 +1225,19 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   float *z = ztab[t.owner] + go;
   const int64_t left = s.numel - go;
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
-  const int e0 = 4 * static_cast<int>(threadIdx.x);
-  if (e0 >= n) return;
-  const int cnt = n - e0;             // 4 or more: a whole vector
-  if (cnt >= 4) {
+  if (lane_idle(n)) return;
+  if (n >= 4) {
+    const int e0 = lane_element(n);
     V4 xv = ld4<NT>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
     st4_at<NT>(z, e0, xv);
   } else {
-    const int et = tail_offset(e0);
-    V4 xv = ldv<true, NT>(x + et, cnt);
+    const int e0 = static_cast<int>(threadIdx.x);
+    V4 xv = ldv<true, NT>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
-    stv<true, NT>(z + et, xv, cnt);
+    stv<true, NT>(z + e0, xv);
   }
 }
 

@@ -192,8 +192,9 @@ def run_library(w, layouts, step, **knobs):
             prob.fill_grads(0, r * w.tau + k)
             step(opt, prob.grads[0], k)
     nt = len(prob.numel)
-    state = {"x": [t for p in prob.params for t in p],
-             "x0": [opt.buffer("x0", j) for j in range(nt)], "u": [opt.buffer("u", j) for j in range(nt)]}
+    state = {"x": [t for p in prob.params for t in p]}
+    for key in ("x0", "u"):      # one of each worker's own without the exact average
+        state[key] = [opt.buffer(key, j, i) for i in range(1 if w.exact_average else w.m) for j in range(nt)]
     if w.policy != "reset":      # under "reset" the buffers mean nothing after an outer step
         for key in ("h", "v") if w.base == "adam" else ("h",):
             state[key] = [opt.buffer(key, j, i) for i in range(w.m) for j in range(nt)]
