@@ -94,6 +94,16 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const int64_t 
       static_cast<size_t>(count_paced_pieces(c.m, n_tensors, numel, paced_mode() >= 2)));
 }
 
+// Whether streaming stores that are written through the L2 at once pay for a kernel
+// that touches `bytes` of memory.  Up to nearly twice what the eight L2s hold (32 MB)
+// the next kernel finds lines of this one there if they were not written out; beyond,
+// the memory takes the local step's mix of reads and writes better this way.  Local
+// step, with against without: working set 20-30 MB 1.3-1.6 times, 40 MB 1.03-1.30,
+// 48-56 MB 0.99-1.07, 60-64 MB 0.96-1.00, 70-120 MB 0.92-0.98, 1 GB and more
+// 0.98-1.00 (ResNet-50-shaped, m = 32: 2584 -> 2546 us).
+constexpr int64_t kWriteThroughBytes = int64_t{54} << 20;
+bool write_through_pays(int64_t bytes) { return bytes > kWriteThroughBytes; }
+
 bool finite_pos(float v) { return std::isfinite(v) && v > 0.f; }
 bool unit_interval(float v) { return std::isfinite(v) && v >= 0.f && v < 1.f; }
 
@@ -474,6 +484,16 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->tune.xcd_remap = env_flag("SLOWMO_XCD_REMAP", 1) ? 1 : 0;
   ctx->tune.xcd_run = std::max(env_flag("SLOWMO_XCD_RUN", 0), 0);
   ctx->tune.nontemporal = env_flag("SLOWMO_NT", 1) ? 1 : 0;
+  // write-through stores: -1 = by the rule, 0 = never, 1 = always
+  const int32_t through = env_flag("SLOWMO_WRITE_THROUGH", -1);
+  const int64_t elements = static_cast<int64_t>(m) * ctx->layout.d;
+  const int64_t grad_bytes = cfg->grad_dtype == SLOWMO_BF16 ? 2 : 4;
+  const int64_t buffer_bytes = cfg->base == SLOWMO_ADAM ? 8 : 4;
+  ctx->tune.write_through =
+      through < 0 ? write_through_pays(elements * (4 + buffer_bytes + grad_bytes)) : through != 0;
+  // the outer step without the average reads what it writes: twice the size (24 MB
+  // 1.10-1.12 times, 60 MB 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00)
+  ctx->tune.noavg_through = through < 0 ? write_through_pays(elements * 12 / 2) : through != 0;
   ctx->tune.fuse_last = env_flag("SLOWMO_FUSE_LAST", 1) ? 1 : 0;
   ctx->tune.fuse_mix = env_flag("SLOWMO_FUSE_MIX", 1) ? 1 : 0;
   // 160 KiB / 8 KiB: at most 20 single-wave workgroups per CU.  With all 32 the

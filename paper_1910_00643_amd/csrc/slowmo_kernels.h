@@ -91,6 +91,8 @@ struct LaunchTuning {
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
   int32_t paced;        // 1: kernels that store inside a walk over all workers take paced tiles
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
+  int32_t write_through;  // 1: the local step writes through the L2 (nt sc1 stores)
+  int32_t noavg_through;  // the same for the outer step without the average
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
                         // outer step without the average: caps the wavefronts per CU
   int32_t outer_lds;    // the same for the outer step and the fused last step (160 KiB / outer_lds

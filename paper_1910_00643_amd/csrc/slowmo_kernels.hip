@@ -112,16 +112,16 @@ __device__ __forceinline__ void st4(float *p, V4 v) {
 }
 
 // Stores one vector per lane to p + e0 (p uniform over the wave, e0 the lane's
-// element).  Where the wave's vectors cover whole 128-byte lines the store is "nt
-// sc1": streaming, and written through the XCD's L2 at once instead of when the
-// line is evicted, which the local step's mix of reads and writes likes better
-// (ResNet-18-shaped round, m = 8: 3.472 -> 3.452 ms).  Lines that two waves share
-// must stay in the L2 until both halves are there (tensors packed back to back:
-// 2.61 ms "nt", 3.00 ms "nt sc1").  Only the buffer form lets a builtin ask for it.
+// element).  With THROUGH, and where the wave's vectors cover whole 128-byte lines,
+// the store is "nt sc1": streaming, and written through the XCD's L2 at once instead
+// of when the line is evicted (the rule that sets it: write_through_pays).  Lines
+// that two waves share must stay in the L2 until both halves are there (tensors
+// packed back to back: 2.61 ms "nt", 3.00 ms "nt sc1").  Only the buffer form lets a
+// builtin ask for it.
 constexpr int kWriteThrough = 18;   // bits of the buffer store's cache policy: nt = 2, sc1 = 16
-template <bool NT>
+template <bool NT, bool THROUGH>
 __device__ __forceinline__ void st4_at(float *p, int e0, V4 v) {
-  if (NT && (reinterpret_cast<uintptr_t>(p) & 127) == 0) {
+  if (THROUGH && (reinterpret_cast<uintptr_t>(p) & 127) == 0) {
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
@@ -129,16 +129,17 @@ __device__ __forceinline__ void st4_at(float *p, int e0, V4 v) {
     st4<NT>(p + e0, v);
   }
 }
+
 // The same for a place in a state arena, every slice of which starts at a
 // multiple of 256 bytes.
-template <bool NT>
+template <bool NT, bool THROUGH>
 __device__ __forceinline__ void st4_arena(float *p, int e0, V4 v) {
-  if constexpr (NT) {
+  if constexpr (THROUGH) {
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
   } else {
-    st4<false>(p + e0, v);
+    st4<NT>(p + e0, v);
   }
 }
 
@@ -326,7 +327,7 @@ __device__ __forceinline__ void have_now(const T &a) {
 // FIRST: the stored buffers are to be read as zero (not loaded).  LAST: the
 // buffers are dead after this step (the reset policy discards them before
 // their next use), so they are not stored.
-template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT>
+template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT, bool THROUGH>
 __global__ __launch_bounds__(kLocalBlock) void k_local_step(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
@@ -363,9 +364,9 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
     if constexpr (!FIRST) hv = ld4<NT>(h + e0);
     if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
     step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
-    st4_at<NT>(x, e0, xv);
-    if constexpr (!LAST) st4_arena<NT>(h, e0, hv);
-    if constexpr (!LAST && BASE == 1) st4_arena<NT>(v, e0, vv);
+    st4_at<NT, THROUGH>(x, e0, xv);
+    if constexpr (!LAST) st4_arena<NT, THROUGH>(h, e0, hv);
+    if constexpr (!LAST && BASE == 1) st4_arena<NT, THROUGH>(v, e0, vv);
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
     xv = ldv<true, NT>(x + e0);
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_init_broadcast(
 // Same tiling as the local step: one workgroup = 256 elements of one (worker,
 // tensor); 3 streams read, 3 written.  "xbar" is the worker's own replica
 // (a one-term sum divided by 1, which is exact).
-template <bool NT>
+template <bool NT, bool THROUGH>
 __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *__restrict__ x0base, float *__restrict__ ubase, int ntiles, int chunk, int remap,
@@ -518,9 +519,9 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
     const V4 xv = ld4<NT>(x + e0), x0v = ld4<NT>(x0 + e0);
     V4 uv = ld4<NT>(u + e0);
     const V4 xn = outer4(xv, x0v, uv, p);
-    st4_arena<NT>(u, e0, uv);
-    st4_arena<NT>(x0, e0, xn);
-    st4_at<NT>(x, e0, xn);
+    st4_arena<NT, THROUGH>(u, e0, uv);
+    st4_arena<NT, THROUGH>(x0, e0, xn);
+    st4_at<NT, THROUGH>(x, e0, xn);
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
     const V4 xv = ldv<true, NT>(x + e0), x0v = ldv<true, NT>(x0 + e0);
@@ -1231,7 +1232,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
     V4 xv = ld4<NT>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
-    st4_at<NT>(z, e0, xv);
+    st4_at<NT, NT>(z, e0, xv);
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
     V4 xv = ldv<true, NT>(x + e0);
@@ -1275,14 +1276,16 @@ hipError_t launch_local_t(const LocalArgs &a, const LaunchTuning &t, hipStream_t
   const unsigned lds = !FIRST ? t.local_lds : BASE == 1 ? t.local_lds * 3 / 4 : 0;
   const SgdP sp{a.lr, a.mu, a.wd};
   const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
-  if (t.nontemporal) {
-    hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, true>), dim3(g.blocks),
-                       dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
-                       g.chunk, g.run, sp, ap);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab,
+                       a.h, a.v, a.ntiles, g.chunk, g.run, sp, ap);
+  };
+  if (!t.nontemporal) {
+    launch(k_local_step<BASE, BF16, FIRST, LAST, false, false>);
+  } else if (t.write_through) {
+    launch(k_local_step<BASE, BF16, FIRST, LAST, true, true>);
   } else {
-    hipLaunchKernelGGL((k_local_step<BASE, BF16, FIRST, LAST, false>), dim3(g.blocks),
-                       dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab, a.h, a.v, a.ntiles,
-                       g.chunk, g.run, sp, ap);
+    launch(k_local_step<BASE, BF16, FIRST, LAST, true, false>);
   }
   return hipGetLastError();
 }
@@ -1559,12 +1562,16 @@ hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &
   if (a.ntiles <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   const OuterP p{a.lr, 0.f, a.beta, 1.0f, a.alpha};
-  if (t.nontemporal) {
-    hipLaunchKernelGGL((k_outer_noavg<true>), dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles,
-                       a.slots, a.x0, a.u, a.ntiles, g.chunk, g.run, p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots,
+                       a.x0, a.u, a.ntiles, g.chunk, g.run, p);
+  };
+  if (!t.nontemporal) {
+    launch(k_outer_noavg<false, false>);
+  } else if (t.noavg_through) {
+    launch(k_outer_noavg<true, true>);
   } else {
-    hipLaunchKernelGGL((k_outer_noavg<false>), dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles,
-                       a.slots, a.x0, a.u, a.ntiles, g.chunk, g.run, p);
+    launch(k_outer_noavg<true, false>);
   }
   return hipGetLastError();
 }

@@ -102,3 +102,16 @@ def test_debias_of_short_tensors(layout):
         for x, t in zip(prob.params[i], z[i]):
             assert torch.equal(t, x / torch.tensor(weights[i], device="cuda:0"))
     opt.close()
+
+
+@pytest.mark.parametrize("layout", ["arena", "flat"])
+@pytest.mark.parametrize("base,grad_dtype,policy,average", [
+    ("sgd_nesterov", "f32", "reset", True), ("sgd_nesterov", "bf16", "maintain", False),
+    ("adam", "bf16", "maintain", True), ("adam", "f32", "maintain", False)])
+def test_stores_that_are_written_through(base, grad_dtype, policy, average, layout):
+    """By itself the library writes through only on lists larger than these."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy=policy, m=3), tau=3,
+                            exact_average=average)
+    w = dataclasses.replace(w, shapes=w.shapes + tuple((f"t{n}", (n,)) for n in LENGTHS))
+    PU.assert_same_bits(*(PU.run_library(w, (layout, "padded"), _outer(w), SLOWMO_WRITE_THROUGH=v)
+                          for v in ("1", "0")))
