@@ -505,11 +505,19 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
   // 30 % slower with the cap.
   ctx->tune.local_lds = std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", 8192), 0), 64 * 1024);
-  // at most 16 single-wave workgroups per CU in the outer step and the fused last
-  // step, for the same reason: Lookahead with Adam (m = 1) 643 -> 637 us, odd-width
-  // layers packed back to back 2.66 -> 2.64 ms, Transformer-big-shaped round 86.1 ->
-  // 85.9 ms; with 8 the first two are back where they were.
-  ctx->tune.outer_lds = std::min(std::max(env_flag("SLOWMO_OUTER_LDS", 10240), 0), 64 * 1024);
+  // At most 16 single-wave workgroups per CU in the outer step and the fused last step,
+  // for the same reason, as long as a wave walks few workers; with many its own
+  // streams are what opens the pages, and fewer waves only leave requests out.  With
+  // the cap over without, lists of 12 to 51 M elements and 1, 2, 4, 8, 16, 32 workers:
+  // outer step 0.96-0.97, 0.96-0.97, 0.97-0.98, 0.97-0.98, 0.99-1.01, 1.00; with the
+  // buffers averaged 0.97-0.98, 0.95-0.97, 0.97-0.98, 0.97-0.98, 1.00, 1.00-1.01; fused
+  // last step 0.95-1.01, 0.96-1.00, 0.97-1.01, 0.99-1.01, 0.99-1.02, 1.00-1.01.
+  const int32_t outer_lds = env_flag("SLOWMO_OUTER_LDS", -1);
+  const auto waves_cap = [&](int32_t below) {
+    return outer_lds >= 0 ? std::min(outer_lds, 64 * 1024) : m < below ? 10240 : 0;
+  };
+  ctx->tune.outer_lds = waves_cap(16);
+  ctx->tune.last_lds = waves_cap(8);
   // big tiles: -1 = by the worker count (see kBigFusedFromWorkers), 0 = never, 1 = always
   const int32_t big = env_flag("SLOWMO_BIG_TILES", -1);
   ctx->tune.big_tiles =

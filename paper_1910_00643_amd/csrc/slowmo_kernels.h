@@ -95,8 +95,9 @@ struct LaunchTuning {
   int32_t noavg_through;  // the same for the outer step without the average
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
                         // outer step without the average: caps the wavefronts per CU
-  int32_t outer_lds;    // the same for the outer step and the fused last step (160 KiB / outer_lds
-                        // wavefronts per CU; 0 = no cap)
+  int32_t outer_lds;    // the same for the outer step (160 KiB / outer_lds wavefronts per CU; 0 = no
+                        // cap)
+  int32_t last_lds;     // the same for the fused last step
 };
 
 // base: 0 SGD-Nesterov, 1 Adam.  bf16: gradient dtype.  first: the stored

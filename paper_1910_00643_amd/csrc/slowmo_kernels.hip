@@ -1399,12 +1399,12 @@ hipError_t launch_fused_t(const LocalArgs &l, const OuterArgs &o, int n_tensors,
   const OuterP p{o.lr, 0.f, o.beta, o.m_f, o.alpha};
   if (t.nontemporal) {
     hipLaunchKernelGGL((k_local_outer_step<BASE, BF16, FIRST, POLICY, true>), dim3(g.blocks),
-                       dim3(kOuterBlock), t.outer_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0, o.u, l.h,
-                       l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
+                       dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0,
+                       o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
   } else {
     hipLaunchKernelGGL((k_local_outer_step<BASE, BF16, FIRST, POLICY, false>), dim3(g.blocks),
-                       dim3(kOuterBlock), t.outer_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0, o.u, l.h,
-                       l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
+                       dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0,
+                       o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
   }
   return hipGetLastError();
 }
