@@ -489,8 +489,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const int64_t elements = static_cast<int64_t>(m) * ctx->layout.d;
   const int64_t grad_bytes = cfg->grad_dtype == SLOWMO_BF16 ? 2 : 4;
   const int64_t buffer_bytes = cfg->base == SLOWMO_ADAM ? 8 : 4;
-  ctx->tune.write_through =
-      through < 0 ? write_through_pays(elements * (4 + buffer_bytes + grad_bytes)) : through != 0;
+  const bool past_caches = write_through_pays(elements * (4 + buffer_bytes + grad_bytes));
+  ctx->tune.write_through = through < 0 ? past_caches : through != 0;
   // the outer step without the average reads what it writes: twice the size (24 MB
   // 1.10-1.12 times, 60 MB 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00)
   ctx->tune.noavg_through = through < 0 ? write_through_pays(elements * 12 / 2) : through != 0;
@@ -503,8 +503,12 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // 3.440 with 20, 3.446 with 17 wavefronts; tensors packed back to back 2.82 ->
   // 2.65 ms; Adam with bf16 gradients 0.669 -> 0.643 ms; outer step without the
   // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
-  // 30 % slower with the cap.
-  ctx->tune.local_lds = std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", 8192), 0), 64 * 1024);
+  // 30 % slower with the cap.  Where the working set stays in the caches (the line of
+  // the write-through stores) there are no pages to spare: 3 to 4.5 M elements, time
+  // over that before any cap, with it / without: steps 0.95-1.02 / 0.92-1.00, the last
+  // one under "reset" 1.02-1.09 / 0.96-1.03.
+  ctx->tune.local_lds = std::min(
+      std::max(env_flag("SLOWMO_LOCAL_LDS", past_caches ? 8192 : 0), 0), 64 * 1024);
   // At most 16 single-wave workgroups per CU in the outer step and the fused last step,
   // for the same reason, as long as a wave walks few workers; with many its own
   // streams are what opens the pages, and fewer waves only leave requests out.  With
