@@ -559,7 +559,12 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
                                                  int e0) {
   constexpr bool NTL = NT && SLOWMO_FUSED_NTL;
   V4 acc, acch, accv;
-  _Pragma(SLOWMO_STR(unroll SLOWMO_FUSED_UNROLL))
+  // Adam with fp32 gradients and averaged buffers holds the most per worker: 8 of them
+  // are 135 VGPRs, 3 waves per SIMD (lists that fit the caches, 4 workers of 1 M
+  // elements: 21.7 us); 6 are 94 and 5 waves (19.2 us).
+  constexpr int kUnroll =
+      BASE == 1 && !BF16 && !FIRST && POLICY == 2 ? 6 : SLOWMO_FUSED_UNROLL;
+#pragma unroll kUnroll
   for (int i = 0; i < m; ++i) {
     float *hi = h0 + i * d_pad + e0;
     float *vi = BASE == 1 ? v0 + i * d_pad + e0 : nullptr;
