@@ -130,7 +130,8 @@ typedef enum { SLOWMO_BUF_X0 = 0, SLOWMO_BUF_U = 1, SLOWMO_BUF_H = 2, SLOWMO_BUF
 /*
  * Bytes of device workspace a context needs for this configuration and
  * tensor list: x0 and u (one copy each; one per worker with cfg.no_average),
- * h (and v for Adam) per worker, and the tiling and pointer tables.  Returns 0 if the arguments are invalid.  Host-only.
+ * h (and v for Adam) per worker, and the tiling and pointer tables.  Returns 0 if
+ * the arguments are invalid.  Host-only.
  */
 size_t slowmo_state_bytes(const slowmo_config *cfg, int32_t n_tensors, const int64_t *numel);
 
@@ -191,10 +192,11 @@ slowmo_status slowmo_outer_step(slowmo_ctx *ctx, float lr, void *stream);
  * the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_outer_step(ctx, outer_lr, stream);
- * but when cfg.no_average is 0 both run in ONE kernel that keeps the stepped replicas in registers for the average: the replicas are
- * read and written once instead of twice (8 m bytes less traffic per element),
- * and the per-worker buffers of this step are not written under the RESET and
- * AVERAGE policies.  Otherwise the two kernels are launched back to back.
+ * but when cfg.no_average is 0 both run in ONE kernel that keeps the stepped
+ * replicas in registers for the average: the replicas are read and written once
+ * instead of twice (8 m bytes less traffic per element), and the per-worker
+ * buffers of this step are not written under the RESET and AVERAGE policies.
+ * Otherwise the two kernels are launched back to back.
  * Errors: as for the two calls; STATE unless exactly tau-1 local steps were
  * taken since the previous outer step.
  */
@@ -229,10 +231,10 @@ slowmo_status slowmo_mix_step(slowmo_ctx *ctx, const int32_t *in_peer, void *str
  * outer iteration): the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_mix_step(ctx, in_peer, stream);
- * but when every replica pointer is 16-byte aligned both run in ONE kernel that keeps the stepped replicas in
- * registers for the mix: the replicas are read and written once instead of
- * twice (8 bytes less traffic per worker and element).  Otherwise the two
- * kernels are launched back to back.
+ * but when every replica pointer is 16-byte aligned both run in ONE kernel that
+ * keeps the stepped replicas in registers for the mix: the replicas are read and
+ * written once instead of twice (8 bytes less traffic per worker and element).
+ * Otherwise the two kernels are launched back to back.
  * Errors: as for the two calls.
  */
 slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, float lr,
@@ -295,9 +297,9 @@ slowmo_status slowmo_get_pushsum_weights(const slowmo_ctx *ctx, float *w);
  * The de-biased parameters of Algorithm C.1 (last line): z^{(i)} = x^{(i)} / w_i,
  * the point at which worker i evaluates its next gradient.
  *   z : host array of m * n_tensors DEVICE pointers, laid out like `params` of
- *       slowmo_create; z[i * n_tensors + j] receives numel[j] floats.  4-byte
- *       alignment is enough (16 enables vector stores).  The destinations
- *       must not overlap the replicas, the workspace or each other.
+ *       slowmo_create; z[i * n_tensors + j] receives numel[j] floats, 4-byte
+ *       aligned.  The destinations must not overlap the replicas, the workspace
+ *       or each other.
  * Reads the replicas and the current w_i; changes no state.  The pointer array
  * is copied before the call returns.  Asynchronous on `stream`.
  * Errors: ARG (NULL), ALIGN, HIP.

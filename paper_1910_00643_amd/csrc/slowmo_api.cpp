@@ -1045,7 +1045,9 @@ struct StagedMix {
 // many of them.  Measured with one tensor of 330 to 1555 paced tiles (SGD with fp32
 // and Adam with bf16 gradients, time against single waves): groups of 8 or more
 // workers 0.83-0.98; groups of 4 0.92-1.01 with 16 or 32 workers, 0.93-1.06 with 8;
-// groups of 2 0.93-1.06.  With 4 workers 0.95-1.12.
+// groups of 2 0.93-1.06.  With 4 workers 0.95-1.12.  One large group and pairs, 512 and
+// 1536 tiles: 18 workers and 7 pairs 0.91-0.93, 24 and 4 pairs 0.88-0.91, 10 and 3
+// pairs 0.92-0.96; random maps of 16 and 32 workers 0.86-0.98.
 bool paced_mix(const slowmo_ctx *ctx, const std::vector<MixEntry> &seq) {
   if (ctx->paced.ntiles <= 0) return false;
   if (ctx->tune.paced >= 2) return true;
@@ -1153,7 +1155,9 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
   const bool bf16 = c.grad_dtype == SLOWMO_BF16;
-  // replicas that are not 16-byte aligned: documented (and tested) to be two kernels
+  // The fused kernels take replicas at any element; whether the lines that two workgroups
+  // share then cost more than the 8 bytes per element saved has not been measured, so
+  // such replicas keep the two kernels.
   const bool two_kernels = !ctx->params_aligned || !ctx->tune.fuse_mix || ctx->n_otiles == 0;
   // both tables are on their way to the device before the first kernel is launched
   StagedMix sm;

@@ -89,7 +89,8 @@ struct LaunchTuning {
   int32_t nontemporal;  // 1: streaming (non-temporal) loads and stores
   int32_t fuse_last;    // 1: slowmo_local_outer_step runs one fused kernel when it can
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
-  int32_t paced;        // 1: kernels that store inside a walk over all workers take paced tiles
+  int32_t paced;        // the fused gossip step on paced tiles: 0 never, 1 by the rule, 2 wherever
+                        // the kernel allows
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
   int32_t write_through;  // 1: the local step writes through the L2 (nt sc1 stores)
   int32_t noavg_through;  // the same for the outer step without the average

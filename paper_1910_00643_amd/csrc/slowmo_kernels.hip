@@ -22,7 +22,10 @@
 //     stores do not hold a wave slot, reads and writes of neighbouring
 //     workgroups interleave, and the set of addresses in flight is a compact
 //     window that moves through memory in order;
-//   * 16 to 20 of them per CU, not all 32: fewer places in memory at a time;
+//   * on lists past the caches fewer of them per CU than the 32 that fit: 20 in the
+//     local step (its first step under "reset": 26 with Adam, no cap with SGD) and the
+//     outer step without the average, 16 in the outer step and the fused last step
+//     with few workers.  The kernels that copy, mix or de-bias have no cap;
 //   * non-temporal loads and stores (nothing is reused);
 //   * workgroup -> tile mapping that gives each XCD one contiguous range of
 //     tiles (workgroups are dealt to the 8 XCDs round-robin);

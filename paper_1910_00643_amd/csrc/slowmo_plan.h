@@ -19,17 +19,12 @@ namespace slowmo {
 // aligned (tiles start at multiples of 4 elements of their tensor).
 constexpr int64_t kArenaAlign = 64;
 
-#ifndef SLOWMO_LOCAL_BLOCK
-#define SLOWMO_LOCAL_BLOCK 64
-#endif
-#ifndef SLOWMO_OUTER_BLOCK
-#define SLOWMO_OUTER_BLOCK 64
-#endif
-// Threads per workgroup; a tile is one vec4 per lane.  Single-wavefront
-// workgroups measured best for both kernels (64 > 128 > 256 > 512).
-constexpr int32_t kLocalBlock = SLOWMO_LOCAL_BLOCK;
+// Threads per workgroup; a tile is one vec4 per lane.  Single-wavefront workgroups
+// measured best for both kernels (64 > 128 > 256 > 512), and the lanes of a tile's end
+// rely on them.
+constexpr int32_t kLocalBlock = 64;
 constexpr int32_t kLocalTile = 4 * kLocalBlock;
-constexpr int32_t kOuterBlock = SLOWMO_OUTER_BLOCK;
+constexpr int32_t kOuterBlock = 64;
 constexpr int32_t kOuterTile = 4 * kOuterBlock;
 
 // Big tiles of the outer step and of the fused last step: one 1024-thread
@@ -56,12 +51,16 @@ constexpr int32_t kBigOuterFromWorkers = 16;
 constexpr int32_t kBigMinTiles = 160;
 static_assert(kBigTile % kOuterTile == 0, "a big tile is a whole number of ordinary tiles");
 
-// Paced tiles of the kernels that walk all workers and store inside the walk: one
-// 512-thread workgroup per CU, 8 vectors per lane, 64 KiB of a stream per tile.
+// Paced tiles of the fused gossip step: one 512-thread workgroup per CU, 8 vectors per
+// lane, 64 KiB of a stream per tile.
 constexpr int32_t kPacedBlock = 512;
 constexpr int32_t kPacedVpt = 8;
 constexpr int32_t kPacedTile = 4 * kPacedBlock * kPacedVpt;
 constexpr int32_t kPacedFromWorkers = 8;
+// Pieces a list must have: a full row and some to go with its second launch (300 pieces
+// 0.83-0.95 of the time in single waves, 8 to 32 workers).  128 pieces gain nothing
+// (0.98-1.05); single rows of 192 to 256 would (0.82-1.00, with SLOWMO_PACED=2) and are
+// not taken so far.
 constexpr int32_t kPacedMinTiles = 300;
 constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMixSaved in single waves)
 constexpr int32_t kPaceStride = 128;    // words between the counters of two XCDs
@@ -115,7 +114,7 @@ struct PlanRun {  // host description of a tile (mirrors slowmo_plan_run)
 // needed; the members of a cycle follow each other, each before its source,
 // and the last one takes the first one's old value from a register.  Where an
 // operand is the previous entry's source it is taken from a register too.
-// Two more registers ("saved" operands) keep a sender whose later receivers or
+// kMixSaved more registers ("saved" operands) keep a sender whose later receivers or
 // own turn come only after other senders have passed through the source
 // register, so that it is not read (in the fused kernel: stepped) again.
 constexpr int32_t kMixSaved = 4;

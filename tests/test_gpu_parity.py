@@ -362,7 +362,7 @@ def test_export_import_resumes_bit_for_bit(base, policy, exact_average):
     ("adam", "bf16", "maintain", 5, ("separate", "padded")),
     ("adam", "f32", "reset", 3, ("separate", "separate")),
     ("adam", "bf16", "average", 4, ("separate", "padded")),
-    ("sgd_nesterov", "f32", "reset", 5, ("flat", "flat")),             # unaligned: two kernels
+    ("sgd_nesterov", "f32", "reset", 5, ("flat", "flat")),             # unaligned
 ])
 def test_fused_last_local_and_outer_step(base, grad_dtype, policy, tau, layouts):
     """slowmo_local_outer_step == slowmo_local_step + slowmo_outer_step, bit
