@@ -94,16 +94,6 @@ Sections make_sections(const slowmo_config &c, int32_t n_tensors, const int64_t 
       static_cast<size_t>(count_paced_pieces(c.m, n_tensors, numel, paced_mode() >= 2)));
 }
 
-// Whether streaming stores that are written through the L2 at once pay for a kernel
-// that touches `bytes` of memory.  Up to nearly twice what the eight L2s hold (32 MB)
-// the next kernel finds lines of this one there if they were not written out; beyond,
-// the memory takes the local step's mix of reads and writes better this way.  Local
-// step, with against without: working set 20-30 MB 1.3-1.6 times, 40 MB 1.03-1.30,
-// 48-56 MB 0.99-1.07, 60-64 MB 0.96-1.00, 70-120 MB 0.92-0.98, 1 GB and more
-// 0.98-1.00 (ResNet-50-shaped, m = 32: 2584 -> 2546 us).
-constexpr int64_t kWriteThroughBytes = int64_t{54} << 20;
-bool write_through_pays(int64_t bytes) { return bytes > kWriteThroughBytes; }
-
 bool finite_pos(float v) { return std::isfinite(v) && v > 0.f; }
 bool unit_interval(float v) { return std::isfinite(v) && v >= 0.f && v < 1.f; }
 
@@ -301,6 +291,7 @@ struct slowmo_ctx {
   int64_t fail_launch_at = 0, launches = 0;
 
   LaunchTuning tune{};
+  bool turning = true;  // sweeps over the tiles change direction (tune.backward)
   std::string err;
 };
 
@@ -325,6 +316,11 @@ template <typename F>
 hipError_t guarded(slowmo_ctx *ctx, F &&launch) {
   if (ctx->fail_launch_at > 0 && ++ctx->launches == ctx->fail_launch_at) return hipErrorLaunchFailure;
   return launch();
+}
+
+// The launches of one sweep over the tiles are out: the next sweep goes the other way.
+void swept(slowmo_ctx *ctx) {
+  if (ctx->turning) ctx->tune.backward ^= 1;
 }
 
 // Failure after at least one kernel of a multi-kernel call was launched.
@@ -354,6 +350,7 @@ slowmo_status run_tiled(slowmo_ctx *ctx, bool use_big, int *launched, const char
     if (e != hipSuccess) return *launched ? fail_midway(ctx, e, what) : fail_hip(ctx, e, what);
     ++*launched;
   }
+  swept(ctx);
   return SLOWMO_OK;
 }
 
@@ -484,16 +481,27 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->tune.xcd_remap = env_flag("SLOWMO_XCD_REMAP", 1) ? 1 : 0;
   ctx->tune.xcd_run = std::max(env_flag("SLOWMO_XCD_RUN", 0), 0);
   ctx->tune.nontemporal = env_flag("SLOWMO_NT", 1) ? 1 : 0;
-  // write-through stores: -1 = by the rule, 0 = never, 1 = always
+  // write-through stores, streaming accesses of the local step: -1 = by the rule,
+  // 0 = never, 1 = always; kept MB: -1 = by the rule
   const int32_t through = env_flag("SLOWMO_WRITE_THROUGH", -1);
+  const int32_t local_nt = env_flag("SLOWMO_LOCAL_NT", -1);
+  const int32_t kept_mb = env_flag("SLOWMO_KEPT", -1);
   const int64_t elements = static_cast<int64_t>(m) * ctx->layout.d;
   const int64_t grad_bytes = cfg->grad_dtype == SLOWMO_BF16 ? 2 : 4;
   const int64_t buffer_bytes = cfg->base == SLOWMO_ADAM ? 8 : 4;
-  const bool past_caches = write_through_pays(elements * (4 + buffer_bytes + grad_bytes));
-  ctx->tune.write_through = through < 0 ? past_caches : through != 0;
-  // the outer step without the average reads what it writes: twice the size (24 MB
-  // 1.10-1.12 times, 60 MB 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00)
-  ctx->tune.noavg_through = through < 0 ? write_through_pays(elements * 12 / 2) : through != 0;
+  const int64_t touched_state = elements * (4 + buffer_bytes);
+  const int64_t touched = touched_state + elements * grad_bytes;
+  const bool past_l2 = touched > int64_t{54} << 20;
+  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes);
+  if (kept_mb >= 0) {
+    const double share = kept_mb * 1e6 / static_cast<double>(std::max<int64_t>(touched_state, 1));
+    caches.kept = static_cast<uint64_t>(std::min(share, 1.0) * 4294967296.0);
+  }
+  ctx->tune.local_nt = ctx->tune.nontemporal && (local_nt < 0 ? caches.streaming : local_nt != 0);
+  ctx->tune.write_through = through < 0 ? caches.write_through : through != 0;
+  // the outer step without the average: written through 24 MB 1.10-1.12 times, 60 MB
+  // 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00
+  ctx->tune.noavg_through = through < 0 ? elements * 12 > (int64_t{108} << 20) : through != 0;
   ctx->tune.fuse_last = env_flag("SLOWMO_FUSE_LAST", 1) ? 1 : 0;
   ctx->tune.fuse_mix = env_flag("SLOWMO_FUSE_MIX", 1) ? 1 : 0;
   // 160 KiB / 8 KiB: at most 20 single-wave workgroups per CU.  With all 32 the
@@ -503,12 +511,19 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // 3.440 with 20, 3.446 with 17 wavefronts; tensors packed back to back 2.82 ->
   // 2.65 ms; Adam with bf16 gradients 0.669 -> 0.643 ms; outer step without the
   // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
-  // 30 % slower with the cap.  Where the working set stays in the caches (the line of
-  // the write-through stores) there are no pages to spare: 3 to 4.5 M elements, time
+  // 30 % slower with the cap.  Where the working set stays in the L2s
+  // there are no pages to spare: 3 to 4.5 M elements, time
   // over that before any cap, with it / without: steps 0.95-1.02 / 0.92-1.00, the last
   // one under "reset" 1.02-1.09 / 0.96-1.03.
-  ctx->tune.local_lds = std::min(
-      std::max(env_flag("SLOWMO_LOCAL_LDS", past_caches ? 8192 : 0), 0), 64 * 1024);
+  // SGD with kept tiles: part of its requests never reach the memory, and up to 4 GB it
+  // takes 28 (300-500 MB 0.96-0.97 of the time with 20, 1 GB 0.97-1.00, 2 GB 0.98-1.00, 5 GB
+  // 1.00; Adam 0.99-1.02).
+  const bool more_waves = caches.kept > 0 && cfg->base == SLOWMO_SGD_NESTEROV && touched < int64_t{4} << 30;
+  const auto local_cap = [&](int32_t by_rule) {
+    return std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", by_rule), 0), 64 * 1024);
+  };
+  ctx->tune.local_lds = local_cap(!past_l2 ? 0 : more_waves ? 5800 : 8192);
+  ctx->tune.noavg_lds = local_cap(past_l2 ? 8192 : 0);
   // At most 16 single-wave workgroups per CU in the outer step and the fused last step,
   // for the same reason, as long as a wave walks few workers; with many its own
   // streams are what opens the pages, and fewer waves only leave requests out.  With
@@ -529,6 +544,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->big_outer = ctx->tune.big_tiles && (big > 0 || m >= kBigOuterFromWorkers);
   ctx->big_forced = big > 0;
   ctx->tune.paced = paced_mode();
+  ctx->turning = env_flag("SLOWMO_TURN", 1) != 0;
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
@@ -622,10 +638,17 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   std::vector<TileRef> lt, lists;  // lists: the ordinary tiles and what is chosen from them
   lt.reserve(static_cast<size_t>(n_ltiles));
   lists.reserve(static_cast<size_t>(n_otiles));
-  for (int32_t w = 0; w < m; ++w)
-    for (int32_t j = 0; j < n_tensors; ++j)
-      for (int64_t k = 0; k * kLocalTile < numel[j]; ++k)
-        lt.push_back({w * n_tensors + j, static_cast<int32_t>(k)});
+  for (int32_t w = 0; w < m; ++w) {
+    for (int32_t j = 0; j < n_tensors; ++j) {
+      for (int64_t k = 0; k * kLocalTile < numel[j];) {
+        constexpr int64_t per = kKeptUnit / kLocalTile;
+        const int32_t flag =
+            unit_kept(L.arena_off[j] / kKeptUnit + k / per, caches.kept) ? kTileKept : 0;
+        for (const int64_t end = k + per; k < end && k * kLocalTile < numel[j]; ++k)
+          lt.push_back({w * n_tensors + j, static_cast<int32_t>(k) | flag});
+      }
+    }
+  }
   for (int32_t j = 0; j < n_tensors; ++j)
     for (int64_t k = 0; k * kOuterTile < numel[j]; ++k) lists.push_back({j, static_cast<int32_t>(k)});
   if (!lt.empty())
@@ -816,6 +839,7 @@ slowmo_status slowmo_local_step(slowmo_ctx *ctx, const void *const *grads, float
                              ctx->tune, stream);
   });
   if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
+  swept(ctx);
   finish_local(ctx);
   return SLOWMO_OK;
 }
@@ -865,6 +889,7 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
       return *launched ? fail_midway(ctx, e, "outer-step kernel launch")
                        : fail_hip(ctx, e, "outer-step kernel launch");
     ++*launched;
+    swept(ctx);
     return SLOWMO_OK;
   }
   OuterArgs a = outer_args(ctx, lr);
@@ -919,6 +944,7 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
                                ctx->tune, stream);
     });
     if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
+    swept(ctx);
     int launched = 1;
     st = run_outer(ctx, outer_lr, &launched, stream);
     if (st != SLOWMO_OK) return st;
@@ -1099,6 +1125,7 @@ slowmo_status run_mix(slowmo_ctx *ctx, const StagedMix &sm, int launched, hipStr
                       : fail_hip(ctx, e, "mixing kernel launch");
     ++launched;
   }
+  swept(ctx);
   return SLOWMO_OK;
 }
 
@@ -1170,6 +1197,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
       return launch_local_step(a, c.base, bf16, ctx->buffers_zero, dead_after, ctx->tune, stream);
     });
     if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
+    swept(ctx);
     st = run_mix(ctx, sm, 1, stream);
     if (st != SLOWMO_OK) return st;
   } else {
@@ -1204,6 +1232,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
                         : fail_hip(ctx, e, "fused local+mixing kernel launch");
       ++launched;
     }
+    swept(ctx);
   }
   // counters and weights move only after the last launch was accepted
   finish_local(ctx);
@@ -1282,6 +1311,7 @@ slowmo_status debias_into(slowmo_ctx *ctx, float *const *z, void *table_dev, hip
   a.n_tensors = nt;
   e = guarded(ctx, [&] { return launch_debias(a, ctx->tune, stream); });
   if (e != hipSuccess) return fail_hip(ctx, e, "de-bias kernel launch");
+  swept(ctx);
   return SLOWMO_OK;
 }
 

@@ -86,16 +86,20 @@ struct LaunchTuning {
   int32_t xcd_remap;    // 1: consecutive tiles go to the same XCD
   int32_t xcd_run;      // tiles an XCD takes in a row before the next XCD's run; 0 = one
                         // contiguous eighth of all tiles per XCD
+  int32_t backward;     // 1: every XCD walks its contiguous eighth from the end to the start;
+                        // changes with every sweep over the tiles
   int32_t nontemporal;  // 1: streaming (non-temporal) loads and stores
   int32_t fuse_last;    // 1: slowmo_local_outer_step runs one fused kernel when it can
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
   int32_t paced;        // the fused gossip step on paced tiles: 0 never, 1 by the rule, 2 wherever
                         // the kernel allows
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
+  int32_t local_nt;     // the same for the local step (0: its working set stays in the caches)
   int32_t write_through;  // 1: the local step writes through the L2 (nt sc1 stores)
   int32_t noavg_through;  // the same for the outer step without the average
-  int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step and of the
-                        // outer step without the average: caps the wavefronts per CU
+  int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step: caps the
+                        // wavefronts per CU
+  int32_t noavg_lds;    // the same for the outer step without the average
   int32_t outer_lds;    // the same for the outer step (160 KiB / outer_lds wavefronts per CU; 0 = no
                         // cap)
   int32_t last_lds;     // the same for the fused last step

@@ -26,7 +26,8 @@
 //     local step (its first step under "reset": 26 with Adam, no cap with SGD) and the
 //     outer step without the average, 16 in the outer step and the fused last step
 //     with few workers.  The kernels that copy, mix or de-bias have no cap;
-//   * non-temporal loads and stores (nothing is reused);
+//   * non-temporal loads and stores, but for what the next call can find in a cache (the
+//     local step on lists that fit the last-level cache, and a part of longer ones);
 //   * workgroup -> tile mapping that gives each XCD one contiguous range of
 //     tiles (workgroups are dealt to the 8 XCDs round-robin);
 //   * tile descriptors and pointer tables read with scalar loads: they are
@@ -121,13 +122,13 @@ __device__ __forceinline__ void st4(float *p, V4 v) {
 // that two waves share must stay in the L2 until both halves are there (tensors
 // packed back to back: 2.61 ms "nt", 3.00 ms "nt sc1").  Only the buffer form lets a
 // builtin ask for it.
-constexpr int kWriteThrough = 18;   // bits of the buffer store's cache policy: nt = 2, sc1 = 16
+constexpr int kNt = 2, kSc1 = 16;   // bits of the buffer store's cache policy
 template <bool NT, bool THROUGH>
 __device__ __forceinline__ void st4_at(float *p, int e0, V4 v) {
   if (THROUGH && (reinterpret_cast<uintptr_t>(p) & 127) == 0) {
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kSc1 + (NT ? kNt : 0));
   } else {
     st4<NT>(p + e0, v);
   }
@@ -140,7 +141,7 @@ __device__ __forceinline__ void st4_arena(float *p, int e0, V4 v) {
   if constexpr (THROUGH) {
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p, 0, 0x7ffffff0, 0x00027000);
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kWriteThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), rsrc, 4 * e0, 0, kSc1 + (NT ? kNt : 0));
   } else {
     st4<NT>(p + e0, v);
   }
@@ -211,18 +212,24 @@ __device__ __forceinline__ const void *grad_at(const void *g, int64_t j) {
   return static_cast<const char *>(g) + j * (BF16 ? 2 : 4);
 }
 
+__device__ __forceinline__ int piece_of(const TileRef &t) { return t.k & ~kTileKept; }
+__device__ __forceinline__ bool is_kept(const TileRef &t) { return (t.k & kTileKept) != 0; }
+
 // Tile of workgroup b.  Workgroup b runs on XCD b mod 8; with the remap, XCD c
 // walks the contiguous tile range [c * chunk, (c + 1) * chunk), so each XCD's
 // L2 and TLB see one compact window of every stream instead of a 1-in-8 comb.
 __device__ __forceinline__ int tile_of(int b, int chunk, int run) {
   // run == 0: workgroup b takes tile b.  run == chunk: every XCD has one
   // contiguous eighth of the tiles (the default; no division, which would be a
-  // chain of some 40 instructions in front of a wave's first load).  Otherwise
+  // chain of some 40 instructions in front of a wave's first load).  Else, if > 0,
   // the workgroups of one XCD (b % 8) take runs of `run` consecutive tiles, the
   // 8 XCDs side by side.
   if (run == 0) return b;
   const unsigned q = static_cast<unsigned>(b) / kXcd, x = static_cast<unsigned>(b) % kXcd;
   if (run == chunk) return static_cast<int>(x * static_cast<unsigned>(chunk) + q);
+  // The same eighths from their ends (run == -chunk).  Every sweep over the tiles goes the
+  // other way than the one before it: what that one touched last is still in the caches.
+  if (run < 0) return static_cast<int>((x + 1) * static_cast<unsigned>(chunk) - 1 - q);
   const unsigned r = static_cast<unsigned>(run);
   return static_cast<int>((q / r) * (kXcd * r) + x * r + q % r);
 }
@@ -324,12 +331,45 @@ __device__ __forceinline__ void have_now(const T &a) {
   asm volatile("" ::"s"(a));
 }
 
+// Makes the accesses through p of one branch others than those of the next: the
+// compiler would merge a plain and a non-temporal load of the same address into one
+// plain load in front of the branch.
+template <typename T>
+__device__ __forceinline__ void own_path(T *&p) {
+  asm volatile("" : "+s"(p));
+}
+
 // ---- local step ---------------------------------------------------------------
 // One workgroup = one tile = up to 4 * blockDim elements of one (worker, tensor).
 
-// FIRST: the stored buffers are to be read as zero (not loaded).  LAST: the
-// buffers are dead after this step (the reset policy discards them before
-// their next use), so they are not stored.
+// One lane's vector at e0 of a tile.  FIRST: the stored buffers are to be read as
+// zero (not loaded).  LAST: the buffers are dead after this step (the reset policy
+// discards them before their next use), so they are not stored.  NT, THROUGH: the
+// accesses to the replica and the buffers; NTG: those to the gradient.
+template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT, bool THROUGH, bool NTG>
+__device__ __forceinline__ void local_lane(float *x, float *h, float *v, const void *g, int e0,
+                                           const SgdP &sp, const AdamP &ap) {
+  V4 xv = ld4<NT>(x + e0), hv, vv;
+  // With only two loads per wave (buffers read as zero) the step measures 2.5 %
+  // faster when the second load is issued after the first has returned
+  // (2.125 -> 2.072 ms, m = 32, 25.6 M elements, four alternating runs); with
+  // three or four loads the same wait changes nothing or costs 1-2 %.
+  if constexpr (FIRST) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xv)::"memory");
+  const V4 gv = ldgv<BF16, false, NTG>(g, e0);
+  if constexpr (!FIRST) hv = ld4<NT>(h + e0);
+  if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
+  step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+  st4_at<NT, THROUGH>(x, e0, xv);
+  if constexpr (!LAST) st4_arena<NT, THROUGH>(h, e0, hv);
+  if constexpr (!LAST && BASE == 1) st4_arena<NT, THROUGH>(v, e0, vv);
+}
+
+// Bound by memory.  What a call finds in the 256 MB last-level cache is what the call
+// before left there, and non-temporal loads leave nothing: a call over a list that
+// fits reads it through plain loads, and one over a longer list reads the kept tiles
+// (kTileKept, see cache_rule) through plain loads and everything else past the cache,
+// so that the kept lines are still there when the next call comes.  The kept tiles lie
+// between the others, so that cache and memory serve the call side by side.
 template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT, bool THROUGH>
 __global__ __launch_bounds__(kLocalBlock) void k_local_step(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
@@ -346,7 +386,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
   sp.wd = s.wd;
   ap.lr = ap.lr * s.lr_scale;
   ap.wd = s.wd;
-  const int64_t go = static_cast<int64_t>(t.k) * kLocalTile;  // offset of the tile in its tensor
+  const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;  // offset in the tensor
   const void *g = grad_at<BF16>(g0, go);
   float *x = s.x + go;
   float *h = hbase + s.so + go;
@@ -354,28 +394,21 @@ __global__ __launch_bounds__(kLocalBlock) void k_local_step(
   const int64_t left = s.numel - go;
   const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
   if (lane_idle(n)) return;
-  V4 xv, hv, vv, gv;
   if (n >= 4) {
     const int e0 = lane_element(n);
-    xv = ld4<NT>(x + e0);
-    // With only two loads per wave (buffers read as zero) the step measures 2.5 %
-    // faster when the second load is issued after the first has returned
-    // (2.125 -> 2.072 ms, m = 32, 25.6 M elements, four alternating runs); with
-    // three or four loads the same wait changes nothing or costs 1-2 %.
-    if constexpr (FIRST) asm volatile("s_waitcnt vmcnt(0)" : "+v"(xv)::"memory");
-    gv = ldgv<BF16, false, NT>(g, e0);
-    if constexpr (!FIRST) hv = ld4<NT>(h + e0);
-    if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
-    step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
-    st4_at<NT, THROUGH>(x, e0, xv);
-    if constexpr (!LAST) st4_arena<NT, THROUGH>(h, e0, hv);
-    if constexpr (!LAST && BASE == 1) st4_arena<NT, THROUGH>(v, e0, vv);
+    if (NT && THROUGH && is_kept(t)) {
+      own_path(x), own_path(h);
+      if constexpr (BASE == 1) own_path(v);
+      local_lane<BASE, BF16, FIRST, LAST, false, THROUGH, NT>(x, h, v, g, e0, sp, ap);
+    } else {
+      local_lane<BASE, BF16, FIRST, LAST, NT, THROUGH, NT>(x, h, v, g, e0, sp, ap);
+    }
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
-    xv = ldv<true, NT>(x + e0);
+    V4 xv = ldv<true, NT>(x + e0), hv, vv;
     if constexpr (!FIRST) hv = ldv<true, NT>(h + e0);
     if constexpr (!FIRST && BASE == 1) vv = ldv<true, NT>(v + e0);
-    gv = ldgv<BF16, true, NT>(g, e0);
+    const V4 gv = ldgv<BF16, true, NT>(g, e0);
     step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
     stv<true, NT>(x + e0, xv);
     if constexpr (!LAST) stv<true, NT>(h + e0, hv);
@@ -510,7 +543,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   const TileRef t = tiles[tile];
   const SlotInfo s = slots[t.owner];
   const OuterP p = for_tensor(p0, s.lr_scale);
-  const int64_t go = static_cast<int64_t>(t.k) * kLocalTile;
+  const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;
   float *x = s.x + go;
   float *x0 = x0base + s.so + go;
   float *u = ubase + s.so + go;
@@ -1229,7 +1262,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   const TileRef t = tiles[tile];
   const SlotInfo s = slots[t.owner];
   const float wi = w[t.owner / n_tensors];
-  const int64_t go = static_cast<int64_t>(t.k) * kLocalTile;
+  const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;
   const float *x = s.x + go;
   float *z = ztab[t.owner] + go;
   const int64_t left = s.numel - go;
@@ -1252,14 +1285,17 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
 
 struct Grid {
   int chunk;
-  int run;  // tiles per XCD turn; 0 = no remap
+  int run;  // tiles per XCD turn; 0 = no remap, -chunk = each XCD's eighth backward
   unsigned blocks;
 };
 Grid make_grid(int ntiles, const LaunchTuning &t) {
   Grid g;
   g.chunk = (ntiles + kXcd - 1) / kXcd;
   g.run = !t.xcd_remap ? 0 : (t.xcd_run > 0 && t.xcd_run < g.chunk ? t.xcd_run : g.chunk);
-  if (g.run == 0) {
+  if (t.backward && g.run == g.chunk) {
+    g.run = -g.chunk;
+    g.blocks = static_cast<unsigned>(kXcd) * static_cast<unsigned>(g.chunk);
+  } else if (g.run == 0) {
     g.blocks = static_cast<unsigned>(ntiles);
   } else {
     int64_t span = static_cast<int64_t>(kXcd) * g.run;
@@ -1288,8 +1324,12 @@ hipError_t launch_local_t(const LocalArgs &a, const LaunchTuning &t, hipStream_t
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), lds, s, a.tiles, a.slots, a.gtab,
                        a.h, a.v, a.ntiles, g.chunk, g.run, sp, ap);
   };
-  if (!t.nontemporal) {
-    launch(k_local_step<BASE, BF16, FIRST, LAST, false, false>);
+  if (!t.local_nt) {
+    if (t.write_through) {
+      launch(k_local_step<BASE, BF16, FIRST, LAST, false, true>);
+    } else {
+      launch(k_local_step<BASE, BF16, FIRST, LAST, false, false>);
+    }
   } else if (t.write_through) {
     launch(k_local_step<BASE, BF16, FIRST, LAST, true, true>);
   } else {
@@ -1571,7 +1611,7 @@ hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &
   const Grid g = make_grid(a.ntiles, t);
   const OuterP p{a.lr, 0.f, a.beta, 1.0f, a.alpha};
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.local_lds, s, a.tiles, a.slots,
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.noavg_lds, s, a.tiles, a.slots,
                        a.x0, a.u, a.ntiles, g.chunk, g.run, p);
   };
   if (!t.nontemporal) {

@@ -17,6 +17,39 @@ Layout make_layout(int32_t n_tensors, const int64_t *numel) {
   return L;
 }
 
+// The lines, from the time of one local step among others, over the time with streaming
+// accesses everywhere and all sweeps in one direction; 1, 8 and 32 workers in 1 and 20 tensors each, SGD and Adam, fp32
+// and bf16 gradients, 0.1 to 800 M elements.
+CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size) {
+  constexpr int64_t MiB = int64_t{1} << 20;
+  const int64_t all = state_bytes + grad_bytes;
+  CacheRule r{true, false, 0};
+  // Plain accesses, gradients included, as long as all of it fits the last-level cache:
+  // 21-28 MB 0.76-1.07, 30-60 MB 0.73-0.90, 60-250 MB 0.72-0.83, 256-266 MB 0.80-0.92.
+  // Below, in the L2s, streaming is as good or better (18 MB: plain 0.84-1.02, streaming
+  // 0.81-0.91).
+  r.streaming = !(all > 20 * MiB && all <= 240 * MiB);
+  // Written through: where the L2s cannot hold much of it for the next call anyway, the
+  // memory takes stores better when they come at once.  With against without, plain
+  // accesses: 30-50 MB 1.00-1.25; fp32 gradients 56-64 MB 0.96-1.02, 72-230 MB 0.92-0.98;
+  // bf16 gradients 60-70 MB 1.04-1.06, 80-84 MB 0.99-1.03, 100-224 MB 0.96-0.99.
+  // Streaming accesses on longer lists: 0.98-1.00.
+  r.write_through = all > (grad_size == 2 ? 80 : 54) * MiB;
+  // Longer lists keep a part of the replicas and buffers: a kept byte saves a read and a
+  // write, a gradient's only a read.  224 MB of it, 0.6 of the state where that is less
+  // (what is not kept comes from memory at the same time): 260-360 MB 0.79-0.88, 400-560
+  // MB 0.80-0.90, 1 GB 0.85-0.89, 2 GB 0.90-0.92, 5 GB 0.95-0.97, 10 GB 0.98.  With 128 MB
+  // 0.02 more at 1 to 2 GB; with all of the state up to 0.14 more at 300 MB.  Plain
+  // accesses on such lists: 0.84-0.96 up to 500 MB, 1.03-1.10 from 2 GB on.  All of this
+  // where steps follow each other; where something else has passed through the cache in
+  // between, a call with kept tiles takes as long as one without.
+  if (r.streaming && r.write_through) {
+    const double keep = std::min(224e6, 0.6 * static_cast<double>(state_bytes));
+    r.kept = static_cast<uint64_t>(keep / static_cast<double>(state_bytes) * 4294967296.0);
+  }
+  return r;
+}
+
 static int64_t tiles_of(int64_t n, int64_t tile) { return (n + tile - 1) / tile; }
 
 int64_t count_local_tiles(int32_t m, int32_t n_tensors, const int64_t *numel) {

@@ -70,12 +70,32 @@ static_assert(kPacedTile % kOuterTile == 0, "a paced tile is a whole number of o
 
 // One tile of either kernel: the k-th piece of a tensor.  For the local step
 // `owner` is the slot (worker * n_tensors + tensor); for the outer step it is
-// the tensor.  8 bytes, read with one scalar load.
+// the tensor.  8 bytes, read with one scalar load.  In the list of the local step
+// kTileKept is set in k for a kept tile (a tensor has at most 2^28 pieces).
+constexpr int32_t kTileKept = INT32_MIN;
 struct TileRef {
   int32_t owner;
   int32_t k;
 };
 static_assert(sizeof(TileRef) == 8, "TileRef layout");
+
+// How the local step goes through the caches: 8 L2s of 4 MB and one last-level cache of
+// 256 MB in front of the memory.
+struct CacheRule {
+  bool streaming;      // non-temporal accesses (but for the kept tiles)
+  bool write_through;  // stores leave the L2 at once
+  uint64_t kept;       // share of the units that is kept, times 2^32
+};
+// For a step that touches state_bytes of replicas and buffers and grad_bytes of
+// gradients (grad_size bytes per element).
+CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size);
+// Kept tiles come in units of 16 384 elements of every worker.  Units are numbered along
+// the tensors; the multiples of the golden ratio spread the kept ones evenly over any
+// stretch of them, and so over the sets of the cache.
+constexpr int32_t kKeptUnit = 16384;
+inline bool unit_kept(int64_t unit, uint64_t kept) {
+  return static_cast<uint32_t>(unit) * 2654435769u < kept;
+}
 
 // Per (worker, tensor), fixed at create.
 struct SlotInfo {

@@ -1,0 +1,69 @@
+"""How a sweep over the tiles goes through the caches (streaming or plain accesses, tiles
+that are kept in the last-level cache, the direction of the sweep) changes no bit of any
+result.  By itself the library chooses by sizes far above these."""
+import dataclasses
+import gc
+
+import pytest
+
+from slowmo_inputs import workloads as W
+
+import parity_utils as PU
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _free_gpu_memory():
+    yield
+    import torch
+    gc.collect()
+    torch.cuda.empty_cache()
+
+
+# kept tiles come in units of 16 384 elements: one short of a unit, one, a few more, some
+LENGTHS = (16383, 16384, 16387, 3, 49152, 1, 70001, 257)
+MAPS = ([1, 2, 0], [0, 0, 1], [2, 0, 1])
+STREAMING = {"SLOWMO_LOCAL_NT": "1", "SLOWMO_WRITE_THROUGH": "0", "SLOWMO_KEPT": "0", "SLOWMO_TURN": "0"}
+
+
+def _separate(w):
+    def step(opt, grads, k):
+        opt.local_step(grads, w.lr)
+        if k == w.tau - 1:
+            opt.outer_step(w.lr)
+    return step
+
+
+def _fused(w):
+    def step(opt, grads, k):
+        if k == w.tau - 1:
+            opt.local_outer_step(grads, w.lr)
+        else:
+            opt.local_step(grads, w.lr)
+    return step
+
+
+def _gossip(w):
+    def step(opt, grads, k):
+        opt.local_mix_step(grads, w.lr, MAPS[k])
+        if k == w.tau - 1:
+            opt.outer_step(w.lr)
+    return step
+
+
+@pytest.mark.parametrize("layout", ["arena", "flat"])
+@pytest.mark.parametrize("base,grad_dtype,policy,calls,average", [
+    ("sgd_nesterov", "f32", "reset", _fused, True), ("sgd_nesterov", "bf16", "maintain", _separate, True),
+    ("adam", "bf16", "maintain", _fused, True), ("adam", "f32", "average", _separate, True),
+    ("sgd_nesterov", "f32", "maintain", _separate, False), ("adam", "bf16", "reset", _gossip, True)])
+def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layout):
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy=policy, m=3), tau=3,
+                            exact_average=average,
+                            shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
+    want = PU.run_library(w, (layout, "padded"), calls(w), **STREAMING)
+    for other in ({"SLOWMO_LOCAL_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_WRITE_THROUGH": "1"},
+                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1"},
+                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1000"}):
+        PU.assert_same_bits(want, PU.run_library(w, (layout, "padded"), calls(w),
+                                                 **{**STREAMING, "SLOWMO_TURN": "1", **other}))
