@@ -481,10 +481,11 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->tune.xcd_remap = env_flag("SLOWMO_XCD_REMAP", 1) ? 1 : 0;
   ctx->tune.xcd_run = std::max(env_flag("SLOWMO_XCD_RUN", 0), 0);
   ctx->tune.nontemporal = env_flag("SLOWMO_NT", 1) ? 1 : 0;
-  // write-through stores, streaming accesses of the local step: -1 = by the rule,
-  // 0 = never, 1 = always; kept MB: -1 = by the rule
+  // write-through stores, streaming accesses of the local and of the outer step: -1 = by
+  // the rule, 0 = never, 1 = always; kept MB: -1 = by the rule
   const int32_t through = env_flag("SLOWMO_WRITE_THROUGH", -1);
   const int32_t local_nt = env_flag("SLOWMO_LOCAL_NT", -1);
+  const int32_t outer_nt = env_flag("SLOWMO_OUTER_NT", -1);
   const int32_t kept_mb = env_flag("SLOWMO_KEPT", -1);
   const int64_t elements = static_cast<int64_t>(m) * ctx->layout.d;
   const int64_t grad_bytes = cfg->grad_dtype == SLOWMO_BF16 ? 2 : 4;
@@ -492,12 +493,14 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const int64_t touched_state = elements * (4 + buffer_bytes);
   const int64_t touched = touched_state + elements * grad_bytes;
   const bool past_l2 = touched > int64_t{54} << 20;
-  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes);
+  const int64_t outer_bytes = 8 * ctx->layout.d * (cfg->no_average ? m : 1);
+  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes, outer_bytes);
   if (kept_mb >= 0) {
     const double share = kept_mb * 1e6 / static_cast<double>(std::max<int64_t>(touched_state, 1));
     caches.kept = static_cast<uint64_t>(std::min(share, 1.0) * 4294967296.0);
   }
   ctx->tune.local_nt = ctx->tune.nontemporal && (local_nt < 0 ? caches.streaming : local_nt != 0);
+  ctx->tune.outer_nt = ctx->tune.nontemporal && (outer_nt < 0 ? caches.outer_streaming : outer_nt != 0);
   ctx->tune.write_through = through < 0 ? caches.write_through : through != 0;
   // the outer step without the average: written through 24 MB 1.10-1.12 times, 60 MB
   // 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00

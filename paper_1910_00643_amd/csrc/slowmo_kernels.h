@@ -94,7 +94,9 @@ struct LaunchTuning {
   int32_t paced;        // the fused gossip step on paced tiles: 0 never, 1 by the rule, 2 wherever
                         // the kernel allows
   int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
-  int32_t local_nt;     // the same for the local step (0: its working set stays in the caches)
+  int32_t local_nt;     // the same for the local step, the gossip kernels in single waves and the
+                        // loads of the de-biasing (0: their working set stays in the caches)
+  int32_t outer_nt;     // the same for the outer step and the fused last step in single waves
   int32_t write_through;  // 1: the local step writes through the L2 (nt sc1 stores)
   int32_t noavg_through;  // the same for the outer step without the average
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step: caps the

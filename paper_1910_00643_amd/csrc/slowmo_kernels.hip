@@ -1251,8 +1251,9 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
   Pacer::leave(pace, gridDim.x);
 }
 
-// z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.
-template <bool NT>
+// z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.  NTL:
+// the loads; NT: the stores.
+template <bool NTL, bool NT>
 __global__ __launch_bounds__(kLocalBlock) void k_debias(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *const *__restrict__ ztab, const float *__restrict__ w, int n_tensors, int ntiles,
@@ -1270,13 +1271,13 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   if (lane_idle(n)) return;
   if (n >= 4) {
     const int e0 = lane_element(n);
-    V4 xv = ld4<NT>(x + e0);
+    V4 xv = ld4<NTL>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
     st4_at<NT, NT>(z, e0, xv);
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
-    V4 xv = ldv<true, NT>(x + e0);
+    V4 xv = ldv<true, NTL>(x + e0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
     stv<true, NT>(z + e0, xv);
@@ -1375,7 +1376,7 @@ hipError_t launch_outer_t(const OuterArgs &a, const LaunchTuning &t, hipStream_t
 hipError_t launch_outer_step(const OuterArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   const int avg = a.avg_h ? (a.avg_v ? 2 : 1) : 0;
-  if (t.nontemporal) {
+  if (t.outer_nt) {
     return avg == 0 ? launch_outer_t<true, 0>(a, t, s)
                     : avg == 1 ? launch_outer_t<true, 1>(a, t, s) : launch_outer_t<true, 2>(a, t, s);
   }
@@ -1445,7 +1446,7 @@ hipError_t launch_fused_t(const LocalArgs &l, const OuterArgs &o, int n_tensors,
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   const OuterP p{o.lr, 0.f, o.beta, o.m_f, o.alpha};
-  if (t.nontemporal) {
+  if (t.outer_nt) {
     hipLaunchKernelGGL((k_local_outer_step<BASE, BF16, FIRST, POLICY, true>), dim3(g.blocks),
                        dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0,
                        o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
@@ -1507,7 +1508,7 @@ hipError_t launch_init_broadcast(const OuterArgs &a, int32_t x0_copies, const La
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0 || a.len <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
-  if (t.nontemporal) {
+  if (t.local_nt) {
     hipLaunchKernelGGL((k_mix_step<true>), dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles,
                        a.tensors, a.xtab_t, a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
   } else {
@@ -1525,7 +1526,7 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const Grid g = make_grid(x.ntiles, t);
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
-  if (t.nontemporal) {
+  if (t.local_nt) {
     hipLaunchKernelGGL((k_local_mix_step<BASE, BF16, FIRST, true>), dim3(g.blocks),
                        dim3(kOuterBlock), 0, s, x.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
                        x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m, sp, ap);
@@ -1596,12 +1597,16 @@ hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t 
 hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
-  if (t.nontemporal) {
-    hipLaunchKernelGGL((k_debias<true>), dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles, a.slots,
-                       a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles, a.slots, a.ztab,
+                       a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
+  };
+  if (!t.nontemporal) {
+    launch(k_debias<false, false>);
+  } else if (t.local_nt) {
+    launch(k_debias<true, true>);
   } else {
-    hipLaunchKernelGGL((k_debias<false>), dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles, a.slots,
-                       a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
+    launch(k_debias<false, true>);
   }
   return hipGetLastError();
 }
@@ -1614,7 +1619,7 @@ hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.noavg_lds, s, a.tiles, a.slots,
                        a.x0, a.u, a.ntiles, g.chunk, g.run, p);
   };
-  if (!t.nontemporal) {
+  if (!t.outer_nt) {
     launch(k_outer_noavg<false, false>);
   } else if (t.noavg_through) {
     launch(k_outer_noavg<true, true>);

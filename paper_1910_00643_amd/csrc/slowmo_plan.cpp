@@ -20,15 +20,22 @@ Layout make_layout(int32_t n_tensors, const int64_t *numel) {
 // The lines, from the time of one local step among others, over the time with streaming
 // accesses everywhere and all sweeps in one direction; 1, 8 and 32 workers in 1 and 20 tensors each, SGD and Adam, fp32
 // and bf16 gradients, 0.1 to 800 M elements.
-CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size) {
+CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
+                     int64_t outer_bytes) {
   constexpr int64_t MiB = int64_t{1} << 20;
   const int64_t all = state_bytes + grad_bytes;
-  CacheRule r{true, false, 0};
+  CacheRule r{true, true, false, 0};
   // Plain accesses, gradients included, as long as all of it fits the last-level cache:
   // 21-28 MB 0.76-1.07, 30-60 MB 0.73-0.90, 60-250 MB 0.72-0.83, 256-266 MB 0.80-0.92.
   // Below, in the L2s, streaming is as good or better (18 MB: plain 0.84-1.02, streaming
   // 0.81-0.91).
   r.streaming = !(all > 20 * MiB && all <= 240 * MiB);
+  // The outer step and the fused last step, plain with x0 and u in the cache as well; time
+  // of rounds of 4 steps over that with only the local step plain, 1, 4 and 16 workers: 24 MB
+  // 0.82-1.09 (worst under "reset"), 40-230 MB with x0 and u 0.77-0.99; 255-290 MB
+  // 0.95-1.10, 330-400 MB 1.00-1.09.  The gossip kernels, rounds by the line of the local
+  // step: 24 MB 0.88-0.99, 40-120 MB 0.87-0.95, 200-245 MB 0.82-0.95.
+  r.outer_streaming = !(all > 28 * MiB && all + outer_bytes <= 240 * MiB);
   // Written through: where the L2s cannot hold much of it for the next call anyway, the
   // memory takes stores better when they come at once.  With against without, plain
   // accesses: 30-50 MB 1.00-1.25; fp32 gradients 56-64 MB 0.96-1.02, 72-230 MB 0.92-0.98;

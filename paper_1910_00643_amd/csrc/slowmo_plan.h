@@ -79,16 +79,18 @@ struct TileRef {
 };
 static_assert(sizeof(TileRef) == 8, "TileRef layout");
 
-// How the local step goes through the caches: 8 L2s of 4 MB and one last-level cache of
+// How the kernels go through the caches: 8 L2s of 4 MB and one last-level cache of
 // 256 MB in front of the memory.
 struct CacheRule {
   bool streaming;      // non-temporal accesses (but for the kept tiles)
+  bool outer_streaming;  // the same for the outer step and the fused last step
   bool write_through;  // stores leave the L2 at once
   uint64_t kept;       // share of the units that is kept, times 2^32
 };
 // For a step that touches state_bytes of replicas and buffers and grad_bytes of
-// gradients (grad_size bytes per element).
-CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size);
+// gradients (grad_size bytes per element); x0 and u are outer_bytes.
+CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
+                     int64_t outer_bytes);
 // Kept tiles come in units of 16 384 elements of every worker.  Units are numbered along
 // the tensors; the multiples of the golden ratio spread the kept ones evenly over any
 // stretch of them, and so over the sets of the cache.

@@ -24,7 +24,8 @@ def _free_gpu_memory():
 # kept tiles come in units of 16 384 elements: one short of a unit, one, a few more, some
 LENGTHS = (16383, 16384, 16387, 3, 49152, 1, 70001, 257)
 MAPS = ([1, 2, 0], [0, 0, 1], [2, 0, 1])
-STREAMING = {"SLOWMO_LOCAL_NT": "1", "SLOWMO_WRITE_THROUGH": "0", "SLOWMO_KEPT": "0", "SLOWMO_TURN": "0"}
+STREAMING = {"SLOWMO_LOCAL_NT": "1", "SLOWMO_OUTER_NT": "1", "SLOWMO_WRITE_THROUGH": "0",
+             "SLOWMO_KEPT": "0", "SLOWMO_TURN": "0"}
 
 
 def _separate(w):
@@ -62,8 +63,27 @@ def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layou
                             exact_average=average,
                             shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
     want = PU.run_library(w, (layout, "padded"), calls(w), **STREAMING)
-    for other in ({"SLOWMO_LOCAL_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_WRITE_THROUGH": "1"},
+    for other in ({"SLOWMO_LOCAL_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_OUTER_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_WRITE_THROUGH": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1000"}):
         PU.assert_same_bits(want, PU.run_library(w, (layout, "padded"), calls(w),
                                                  **{**STREAMING, "SLOWMO_TURN": "1", **other}))
+
+
+def test_debias_of_a_list_that_stays_in_the_caches():
+    import torch
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = dataclasses.replace(W.ragged_mini(m=3, policy="maintain"), tau=3,
+                            shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
+    prob = GpuProblem(w, "cuda:0", param_layout="flat", grad_layout="flat")
+    with PU.environment(SLOWMO_LOCAL_NT="0"):
+        opt = PU.make_gpu(w, prob)
+    prob.fill_grads(0, 0)
+    opt.local_mix_step(prob.grads[0], w.lr, MAPS[1])
+    z = [[torch.full((n,), 7.0, device="cuda:0") for n in LENGTHS] for _ in range(w.m)]
+    opt.debias(z)
+    weights = opt.pushsum_weights()
+    for i in range(w.m):
+        for x, t in zip(prob.params[i], z[i], strict=True):
+            assert torch.equal(t, x / torch.tensor(weights[i], device="cuda:0"))
+    opt.close()
