@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -495,10 +496,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const bool past_l2 = touched > int64_t{54} << 20;
   const int64_t outer_bytes = 8 * ctx->layout.d * (cfg->no_average ? m : 1);
   CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes, outer_bytes);
-  if (kept_mb >= 0) {
-    const double share = kept_mb * 1e6 / static_cast<double>(std::max<int64_t>(touched_state, 1));
-    caches.kept = static_cast<uint64_t>(std::min(share, 1.0) * 4294967296.0);
-  }
+  if (kept_mb >= 0) caches.kept_bytes = kept_mb * 1e6;
   ctx->tune.local_nt = ctx->tune.nontemporal && (local_nt < 0 ? caches.streaming : local_nt != 0);
   ctx->tune.outer_nt = ctx->tune.nontemporal && (outer_nt < 0 ? caches.outer_streaming : outer_nt != 0);
   ctx->tune.write_through = through < 0 ? caches.write_through : through != 0;
@@ -521,7 +519,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // SGD with kept tiles: part of its requests never reach the memory, and up to 4 GB it
   // takes 28 (300-500 MB 0.96-0.97 of the time with 20, 1 GB 0.97-1.00, 2 GB 0.98-1.00, 5 GB
   // 1.00; Adam 0.99-1.02).
-  const bool more_waves = caches.kept > 0 && cfg->base == SLOWMO_SGD_NESTEROV && touched < int64_t{4} << 30;
+  const bool more_waves = caches.kept_bytes > 0 && cfg->base == SLOWMO_SGD_NESTEROV &&
+                          touched < int64_t{4} << 30;
   const auto local_cap = [&](int32_t by_rule) {
     return std::min(std::max(env_flag("SLOWMO_LOCAL_LDS", by_rule), 0), 64 * 1024);
   };
@@ -637,34 +636,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
       }
     }
   }
-  // tiles in launch order: worker-major, tensors in list order, pieces ascending
-  std::vector<TileRef> lt, lists;  // lists: the ordinary tiles and what is chosen from them
-  lt.reserve(static_cast<size_t>(n_ltiles));
-  lists.reserve(static_cast<size_t>(n_otiles));
-  for (int32_t w = 0; w < m; ++w) {
-    for (int32_t j = 0; j < n_tensors; ++j) {
-      for (int64_t k = 0; k * kLocalTile < numel[j];) {
-        constexpr int64_t per = kKeptUnit / kLocalTile;
-        const int32_t flag =
-            unit_kept(L.arena_off[j] / kKeptUnit + k / per, caches.kept) ? kTileKept : 0;
-        for (const int64_t end = k + per; k < end && k * kLocalTile < numel[j]; ++k)
-          lt.push_back({w * n_tensors + j, static_cast<int32_t>(k) | flag});
-      }
-    }
-  }
-  for (int32_t j = 0; j < n_tensors; ++j)
-    for (int64_t k = 0; k * kOuterTile < numel[j]; ++k) lists.push_back({j, static_cast<int32_t>(k)});
-  if (!lt.empty())
-    CREATE_HIP(hipMemcpyAsync(ctx->d_ltiles, lt.data(), lt.size() * sizeof(TileRef),
-                              hipMemcpyHostToDevice, stream),
-               "upload of the local-step tiles");
-  // appends one more list to the upload; returns its place on the device
-  auto append = [&](const std::vector<TileRef> &v) {
-    TileRef *at = ctx->d_otiles + lists.size();
-    lists.insert(lists.end(), v.begin(), v.end());
-    return at;
-  };
-  std::vector<TileRef> bt, rt;
+  std::vector<TileRef> bt, rt;  // big tiles and the ordinary tiles they leave over
   if (ctx->tune.big_tiles) {
     constexpr int64_t per_big = kBigTile / kOuterTile;
     for (int32_t j = 0; j < n_tensors; ++j) {
@@ -673,8 +645,62 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
       for (int64_t k = n_big * per_big; k * kOuterTile < numel[j]; ++k)
         rt.push_back({j, static_cast<int32_t>(k)});
     }
+    if (big < 0 && static_cast<int64_t>(bt.size()) < kBigMinTiles) bt.clear();
   }
-  if (bt.empty() || (big < 0 && static_cast<int64_t>(bt.size()) < kBigMinTiles)) {
+  // Kept tiles: a share of the units of every worker.  But big tiles run best while the
+  // whole chip is on one worker, and lose that when some of them come from the cache and
+  // others do not: the fused last step takes 2.49-2.61 instead of 2.20 ms then (m = 32, 25.6
+  // M elements), 322 instead of 275 us (m = 8, 11.7 M).  Where big tiles are in use, the local
+  // step keeps whole workers, or, if one is too large, units of the first.
+  const bool big_in_use = !bt.empty() && !cfg->no_average &&
+                          (cfg->policy == SLOWMO_BUF_RESET || ctx->big_outer);
+  const double worker_bytes = static_cast<double>(touched_state) / m;
+  const int32_t whole = kept_workers(m, caches.kept_bytes, worker_bytes);
+  const auto share_of = [&](int32_t w) {
+    if (!big_in_use) return kept_share(caches.kept_bytes, static_cast<double>(touched_state));
+    if (whole > 0) return kept_share(w < whole ? worker_bytes : 0.0, worker_bytes);
+    return kept_share(w == 0 ? caches.kept_bytes : 0.0, worker_bytes);
+  };
+  const auto flag_at = [&](int32_t j, int64_t element, uint64_t share) {
+    return unit_kept(L.arena_off[j] / kKeptUnit + element / kKeptUnit, share) ? kTileKept : 0;
+  };
+  // to the kernels that walk all workers only a tile that is kept of each of them is one
+  const uint64_t walk_share = big_in_use ? 0 : share_of(0);
+  ctx->tune.kept_tiles = walk_share > 0;
+  // tiles in launch order: worker-major, tensors in list order, pieces ascending
+  static_assert(kLocalTile == kOuterTile, "a worker's local tiles are the outer tiles");
+  const auto fill = [&](TileRef *out, int32_t first_owner, uint64_t share) {
+    constexpr int64_t per_unit = kKeptUnit / kOuterTile;
+    for (int32_t j = 0; j < n_tensors; ++j) {
+      const int64_t tiles = (numel[j] + kOuterTile - 1) / kOuterTile;
+      for (int64_t k = 0; k < tiles;) {
+        const int32_t flag = flag_at(j, k * kOuterTile, share);
+        for (const int64_t end = std::min(k + per_unit, tiles); k < end; ++k)
+          *out++ = {first_owner + j, static_cast<int32_t>(k) | flag};
+      }
+    }
+    return out;
+  };
+  const std::unique_ptr<TileRef[]> lt(new (std::nothrow) TileRef[static_cast<size_t>(n_ltiles) + 1]);
+  if (!lt) {
+    release(ctx);
+    return fail(nullptr, SLOWMO_ERR_NOMEM, "host allocation failed");
+  }
+  TileRef *next = lt.get();
+  for (int32_t w = 0; w < m; ++w) next = fill(next, w * n_tensors, share_of(w));
+  std::vector<TileRef> lists(static_cast<size_t>(n_otiles));  // the ordinary tiles and what is chosen from them
+  fill(lists.data(), 0, walk_share);
+  if (n_ltiles > 0)
+    CREATE_HIP(hipMemcpyAsync(ctx->d_ltiles, lt.get(), static_cast<size_t>(n_ltiles) * sizeof(TileRef),
+                              hipMemcpyHostToDevice, stream),
+               "upload of the local-step tiles");
+  // appends one more list to the upload; returns its place on the device
+  auto append = [&](const std::vector<TileRef> &v) {
+    TileRef *at = ctx->d_otiles + lists.size();
+    lists.insert(lists.end(), v.begin(), v.end());
+    return at;
+  };
+  if (bt.empty()) {
     ctx->d_rtiles = ctx->d_otiles;
     ctx->n_rtiles = ctx->n_otiles;
   } else {
@@ -694,6 +720,9 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     ctx->paced.spins = env_flag("SLOWMO_TEST_PACE_SPINS", kPaceSpins);
     std::vector<TileRef> pt, prt;
     plan_paced(m, n_tensors, numel, cus % 8 == 0 ? cus : 0, ctx->tune.paced >= 2, pt, prt);
+    // The paced kernel itself keeps nothing: with plain accesses to kept units or to kept
+    // workers it takes 0.99-1.01 of the time (5 to 26 M elements, 8 to 32 workers).
+    for (TileRef &t : prt) t.k |= flag_at(t.owner, int64_t{t.k} * kOuterTile, walk_share);
     ctx->paced.tiles = append(pt);
     ctx->paced.ntiles = static_cast<int32_t>(pt.size());
     ctx->d_prtiles = append(prt);

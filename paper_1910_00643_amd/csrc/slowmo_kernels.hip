@@ -234,6 +234,15 @@ __device__ __forceinline__ int tile_of(int b, int chunk, int run) {
   return static_cast<int>((q / r) * (kXcd * r) + x * r + q % r);
 }
 
+// Keep the accesses of one branch apart from those of the other: the compiler would merge
+// a plain and a non-temporal load into one plain load, in front of the branch (own_path, on
+// the pointer before the accesses) or behind it (own_value, on what was loaded).
+template <typename P>
+__device__ __forceinline__ void own_path(P &p) {
+  asm volatile("" : "+s"(p));
+}
+__device__ __forceinline__ void own_value(V4 &v) { asm volatile("" : "+v"(v)); }
+
 // ---- per-element arithmetic -------------------------------------------------
 
 struct SgdP {
@@ -329,14 +338,6 @@ __device__ __forceinline__ V4 outer4(V4 s, V4 x0, V4 &u, const OuterP &p) {
 template <typename T>
 __device__ __forceinline__ void have_now(const T &a) {
   asm volatile("" ::"s"(a));
-}
-
-// Makes the accesses through p of one branch others than those of the next: the
-// compiler would merge a plain and a non-temporal load of the same address into one
-// plain load in front of the branch.
-template <typename T>
-__device__ __forceinline__ void own_path(T *&p) {
-  asm volatile("" : "+s"(p));
 }
 
 // ---- local step ---------------------------------------------------------------
@@ -449,8 +450,10 @@ __device__ __forceinline__ void average_arena(float *__restrict__ b0, int64_t st
 }
 
 // One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor; xp:
-// its m replicas; x0, u, h0, v0: the tile's place in the arenas.
-template <bool NT, int AVG, bool ONE>
+// its m replicas; x0, u, h0, v0: the tile's place in the arenas.  NT: the accesses to the
+// replicas and buffers (in a kept tile they are plain, as the local step's); NTO: those to
+// x0 and u.
+template <bool NT, bool NTO, int AVG, bool ONE>
 __device__ __forceinline__ void outer_lane(float *const *__restrict__ xp, int64_t eo, float *x0,
                                            float *u, float *h0, float *v0, int64_t d_pad, int m,
                                            const OuterP &p, int e0) {
@@ -459,11 +462,11 @@ __device__ __forceinline__ void outer_lane(float *const *__restrict__ xp, int64_
   V4 acc = ldv<ONE, NTL>(xp[0] + eo + e0);
   SLOWMO_PRAGMA_UNROLL_OUTER
   for (int i = 1; i < m; ++i) acc = acc + ldv<ONE, NTL>(xp[i] + eo + e0);
-  const V4 x0v = ldv<ONE, NTL>(x0 + e0);
-  V4 uv = ldv<ONE, NTL>(u + e0);
+  const V4 x0v = ldv<ONE, NTO>(x0 + e0);
+  V4 uv = ldv<ONE, NTO>(u + e0);
   const V4 xn = outer4(acc, x0v, uv, p);
-  stv<ONE, NTS>(u + e0, uv);
-  stv<ONE, NTS>(x0 + e0, xn);
+  stv<ONE, NTO>(u + e0, uv);
+  stv<ONE, NTO>(x0 + e0, xn);
   SLOWMO_PRAGMA_UNROLL_OUTER
   for (int i = 0; i < m; ++i) stv<ONE, NTS>(xp[i] + eo + e0, xn);
   // line 2 of the next outer iteration, strategy "average"
@@ -471,8 +474,10 @@ __device__ __forceinline__ void outer_lane(float *const *__restrict__ xp, int64_
   if constexpr (AVG >= 2) average_arena<ONE, NTL, NTS>(v0, d_pad, m, p.m_f, e0);
 }
 
-// AVG: 0 = lines 6-8 only; 1 = also average h over the workers; 2 = h and v.
-template <bool NT, int AVG>
+// AVG: 0 = lines 6-8 only; 1 = also average h over the workers; 2 = h and v.  KEPT: some
+// of the tiles are kept (an instance of its own: with both walks in one the others would
+// pay with registers, fused last step 64 -> 94).
+template <bool NT, int AVG, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_outer_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, float *__restrict__ x0base, float *__restrict__ ubase,
@@ -484,16 +489,23 @@ __global__ __launch_bounds__(kOuterBlock) void k_outer_step(
   const TensorInfo ti = tensors[t.owner];
   const OuterP p = for_tensor(p0, ti.lr_scale);
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;  // m replica pointers
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
+  const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
   float *x0 = x0base + ti.fo + eo, *u = ubase + ti.fo + eo;
   float *h0 = AVG >= 1 ? hbase + ti.fo + eo : nullptr, *v0 = AVG >= 2 ? vbase + ti.fo + eo : nullptr;
   if (n >= 4) {
-    outer_lane<NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, lane_element(n));
+    if (NT && KEPT && is_kept(t)) {
+      own_path(xp);
+      if constexpr (AVG >= 1) own_path(h0);
+      if constexpr (AVG >= 2) own_path(v0);
+      outer_lane<false, NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, lane_element(n));
+    } else {
+      outer_lane<NT, NT, AVG, false>(xp, eo, x0, u, h0, v0, d_pad, m, p, lane_element(n));
+    }
   } else {
-    outer_lane<NT, AVG, true>(xp, eo, x0, u, h0, v0, d_pad, m, p, static_cast<int>(threadIdx.x));
+    outer_lane<NT, NT, AVG, true>(xp, eo, x0, u, h0, v0, d_pad, m, p, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -509,7 +521,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_init_broadcast(
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const TensorInfo ti = tensors[t.owner];
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
+  const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
@@ -552,12 +564,24 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   if (lane_idle(n)) return;
   if (n >= 4) {
     const int e0 = lane_element(n);
-    const V4 xv = ld4<NT>(x + e0), x0v = ld4<NT>(x0 + e0);
+    V4 xv;
+    if (NT && is_kept(t)) {
+      own_path(x);
+      xv = ld4<false>(x + e0);
+      own_value(xv);
+    } else {
+      xv = ld4<NT>(x + e0);
+    }
+    const V4 x0v = ld4<NT>(x0 + e0);
     V4 uv = ld4<NT>(u + e0);
     const V4 xn = outer4(xv, x0v, uv, p);
     st4_arena<NT, THROUGH>(u, e0, uv);
     st4_arena<NT, THROUGH>(x0, e0, xn);
-    st4_at<NT, THROUGH>(x, e0, xn);
+    if (NT && is_kept(t)) {
+      st4_at<false, THROUGH>(x, e0, xn);
+    } else {
+      st4_at<NT, THROUGH>(x, e0, xn);
+    }
   } else {
     const int e0 = static_cast<int>(threadIdx.x);
     const V4 xv = ldv<true, NT>(x + e0), x0v = ldv<true, NT>(x0 + e0);
@@ -585,8 +609,9 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
 #endif
 // One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor; xp:
 // its replicas, gp: its gradients (worker i: gp[i * n_tensors]); x0, u, h0, v0:
-// the tile's place in the arenas (worker i's buffers: + i * d_pad).
-template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool ONE>
+// the tile's place in the arenas (worker i's buffers: + i * d_pad).  NT: the accesses to
+// the replicas and buffers (plain in a kept tile); NTO: those to the gradients, x0 and u.
+template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool NTO, bool ONE>
 __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
                                                  const void *const *__restrict__ gp, int64_t eo,
                                                  float *x0, float *u, float *h0, float *v0,
@@ -608,7 +633,7 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
     if constexpr (!FIRST) hv = ldv<ONE, NTL>(hi);
     if constexpr (!FIRST && BASE == 1) vv = ldv<ONE, NTL>(vi);
     const V4 gv =
-        ldgv<BF16, ONE, NTL>(grad_at<BF16>(gp[static_cast<int64_t>(i) * n_tensors], eo), e0);
+        ldgv<BF16, ONE, NTO>(grad_at<BF16>(gp[static_cast<int64_t>(i) * n_tensors], eo), e0);
     step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
     if constexpr (POLICY == 1) {
       stv<ONE, NT>(hi, hv);
@@ -620,11 +645,11 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
     }
     acc = (i == 0) ? xv : acc + xv;
   }
-  const V4 x0v = ldv<ONE, NT>(x0 + e0);
-  V4 uv = ldv<ONE, NT>(u + e0);
+  const V4 x0v = ldv<ONE, NTO>(x0 + e0);
+  V4 uv = ldv<ONE, NTO>(u + e0);
   const V4 xn = outer4(acc, x0v, uv, p);
-  stv<ONE, NT>(u + e0, uv);
-  stv<ONE, NT>(x0 + e0, xn);
+  stv<ONE, NTO>(u + e0, uv);
+  stv<ONE, NTO>(x0 + e0, xn);
 #pragma unroll 8
   for (int i = 0; i < m; ++i) stv<ONE, NT>(xp[i] + eo + e0, xn);
   if constexpr (POLICY == 2) {
@@ -642,7 +667,7 @@ __device__ __forceinline__ void local_outer_lane(float *const *__restrict__ xp,
   }
 }
 
-template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT>
+template <int BASE, bool BF16, bool FIRST, int POLICY, bool NT, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
@@ -658,7 +683,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
   sp.wd = ti.wd;
   ap.lr = ap.lr * ti.lr_scale;
   ap.wd = ti.wd;
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
+  const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
@@ -669,10 +694,18 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
   float *h0 = hbase + ti.fo + eo;
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
   if (n >= 4) {
-    local_outer_lane<BASE, BF16, FIRST, POLICY, NT, false>(xp, gp, eo, x0, u, h0, v0, d_pad,
-                                                           n_tensors, m, sp, ap, p, lane_element(n));
+    const int e0 = lane_element(n);
+    if (NT && KEPT && is_kept(t)) {
+      own_path(xp), own_path(h0);
+      if constexpr (BASE == 1) own_path(v0);
+      local_outer_lane<BASE, BF16, FIRST, POLICY, false, NT, false>(xp, gp, eo, x0, u, h0, v0, d_pad,
+                                                                    n_tensors, m, sp, ap, p, e0);
+    } else {
+      local_outer_lane<BASE, BF16, FIRST, POLICY, NT, NT, false>(xp, gp, eo, x0, u, h0, v0, d_pad,
+                                                                 n_tensors, m, sp, ap, p, e0);
+    }
   } else {
-    local_outer_lane<BASE, BF16, FIRST, POLICY, NT, true>(
+    local_outer_lane<BASE, BF16, FIRST, POLICY, NT, NT, true>(
         xp, gp, eo, x0, u, h0, v0, d_pad, n_tensors, m, sp, ap, p, static_cast<int>(threadIdx.x));
   }
 }
@@ -689,6 +722,11 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
 // scalar registers: the 128 vector registers a 1024-thread workgroup can have
 // per lane hold the 16 accumulators and the operands of a few vectors.
 constexpr int kBigStride = 4 * kBigBlock;  // floats between a lane's consecutive vectors
+
+// The waves of a workgroup begin each worker together: one that runs ahead opens another
+// region's pages for its 16 KiB only.  Fused last step, m = 32 2247 -> 2203 us, m = 8
+// (11.7 M elements) 289 -> 280 us.
+__device__ __forceinline__ void together() { __builtin_amdgcn_s_barrier(); }
 
 __global__ __launch_bounds__(kBigBlock) void k_outer_big(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
@@ -707,6 +745,7 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
   constexpr int HALF = kBigVpt / 2;
   V4 acc[kBigVpt];
   for (int i = 0; i < m; ++i) {       // line 6: ordered sum, i = 0, 1, ..., m-1
+    together();
     const float *x = xp[i] + eo;
 #pragma unroll
     for (int v0 = 0; v0 < kBigVpt; v0 += HALF) {
@@ -765,6 +804,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
   const int lane = 4 * static_cast<int>(threadIdx.x);
   V4 acc[kBigVpt];
   for (int i = 0; i < m; ++i) {
+    together();
     const float *xi = xp[i] + eo;
     float *hi = h0 + i * d_pad;
     float *vi = BASE == 1 ? v0 + i * d_pad : nullptr;
@@ -922,13 +962,18 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const TensorInfo ti = tensors[t.owner];
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
+  const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   if (n >= 4) {
-    mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
+    if (NT && is_kept(t)) {
+      own_path(xp);
+      mix_lane<false, false>(xp, seq, len, eo, lane_element(n));
+    } else {
+      mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
+    }
   } else {
     mix_lane<NT, true>(xp, seq, len, eo, static_cast<int>(threadIdx.x));
   }
@@ -945,19 +990,20 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
 // whose stepped value is needed as a source before its own turn, and is not
 // the next in the order, is stepped again from memory at its own turn: its x,
 // h and v in memory stay untouched until then.
-template <int BASE, bool BF16, bool FIRST, bool NT, bool ONE>
+template <int BASE, bool BF16, bool FIRST, bool NT, bool NTG, bool ONE>
 __device__ __forceinline__ void step_from_memory(const float *xi, const float *hi, const float *vi,
                                                  const void *gi, int e0, const SgdP &sp,
                                                  const AdamP &ap, V4 &xv, V4 &hv, V4 &vv) {
   xv = ldv<ONE, NT>(xi + e0);
   if constexpr (!FIRST) hv = ldv<ONE, NT>(hi + e0);
   if constexpr (!FIRST && BASE == 1) vv = ldv<ONE, NT>(vi + e0);
-  const V4 gv = ldgv<BF16, ONE, NT>(gi, e0);
+  const V4 gv = ldgv<BF16, ONE, NTG>(gi, e0);
   step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
 }
 
-// One lane's vector (ONE: element) at e0 of a tile; pointers as in local_outer_lane.
-template <int BASE, bool BF16, bool FIRST, bool NT, bool ONE>
+// One lane's vector (ONE: element) at e0 of a tile; pointers as in local_outer_lane.  NT:
+// the accesses to the replicas and buffers (plain in a kept tile); NTG: the gradients'.
+template <int BASE, bool BF16, bool FIRST, bool NT, bool NTG, bool ONE>
 __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
                                                const void *const *__restrict__ gp, int64_t eo,
                                                float *h0, float *v0, int64_t d_pad, int n_tensors,
@@ -981,7 +1027,7 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
       vo = Hv.get(mix_own_saved(en.flags), Sv);
     } else {
       const void *gi = grad_at<BF16>(gp[static_cast<int64_t>(en.node) * n_tensors], eo);
-      step_from_memory<BASE, BF16, FIRST, NT, ONE>(xi, hi, vi, gi, e0, sp, ap, xo, ho, vo);
+      step_from_memory<BASE, BF16, FIRST, NT, NTG, ONE>(xi, hi, vi, gi, e0, sp, ap, xo, ho, vo);
     }
     stv<ONE, NT>(hi + e0, ho);
     if constexpr (BASE == 1) stv<ONE, NT>(vi + e0, vo);
@@ -1000,7 +1046,7 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
         Sv = Hv.get(mix_src_saved(en.flags), Sv);
       } else if (!(en.flags & kMixSrcFromS)) {
         const void *gs = grad_at<BF16>(gp[static_cast<int64_t>(en.src) * n_tensors], eo);
-        step_from_memory<BASE, BF16, FIRST, NT, ONE>(
+        step_from_memory<BASE, BF16, FIRST, NT, NTG, ONE>(
             xp[en.src] + eo, h0 + en.src * d_pad, BASE == 1 ? v0 + en.src * d_pad : nullptr, gs,
             e0, sp, ap, Sx, Sh, Sv);
       }
@@ -1023,7 +1069,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   sp.wd = ti.wd;
   ap.lr = ap.lr * ti.lr_scale;
   ap.wd = ti.wd;
-  const int64_t eo = static_cast<int64_t>(t.k) * kOuterTile;  // offset of the tile in its tensor
+  const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;  // offset of the tile in its tensor
   const int64_t left = ti.numel - eo;
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
@@ -1032,10 +1078,18 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
   if (n >= 4) {
-    local_mix_lane<BASE, BF16, FIRST, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len,
-                                                 sp, ap, lane_element(n));
+    const int e0 = lane_element(n);
+    if (NT && is_kept(t)) {
+      own_path(xp), own_path(h0);
+      if constexpr (BASE == 1) own_path(v0);
+      local_mix_lane<BASE, BF16, FIRST, false, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq,
+                                                          len, sp, ap, e0);
+    } else {
+      local_mix_lane<BASE, BF16, FIRST, NT, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len,
+                                                       sp, ap, e0);
+    }
   } else {
-    local_mix_lane<BASE, BF16, FIRST, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len, sp,
+    local_mix_lane<BASE, BF16, FIRST, NT, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len, sp,
                                                 ap, static_cast<int>(threadIdx.x));
   }
 }
@@ -1271,7 +1325,14 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   if (lane_idle(n)) return;
   if (n >= 4) {
     const int e0 = lane_element(n);
-    V4 xv = ld4<NTL>(x + e0);
+    V4 xv;
+    if (NTL && is_kept(t)) {
+      own_path(x);
+      xv = ld4<false>(x + e0);
+      own_value(xv);
+    } else {
+      xv = ld4<NTL>(x + e0);
+    }
 #pragma unroll
     for (int c = 0; c < 4; ++c) xv[c] = xv[c] / wi;
     st4_at<NT, NT>(z, e0, xv);
@@ -1363,25 +1424,28 @@ hipError_t launch_local_step(const LocalArgs &a, int base, bool bf16, bool first
               : launch_local_b<1, false>(a, first, last, t, s);
 }
 
-template <bool NT, int AVG>
+template <int AVG>
 hipError_t launch_outer_t(const OuterArgs &a, const LaunchTuning &t, hipStream_t s) {
   const Grid g = make_grid(a.ntiles, t);
   const OuterP p{a.lr, 0.f, a.beta, a.m_f, a.alpha};
-  hipLaunchKernelGGL((k_outer_step<NT, AVG>), dim3(g.blocks), dim3(kOuterBlock), t.outer_lds, s,
-                     a.tiles, a.tensors, a.xtab_t, a.x0, a.u, a.avg_h, a.avg_v, a.d_pad, a.ntiles,
-                     g.chunk, g.run, a.m, p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), t.outer_lds, s, a.tiles, a.tensors,
+                       a.xtab_t, a.x0, a.u, a.avg_h, a.avg_v, a.d_pad, a.ntiles, g.chunk, g.run, a.m, p);
+  };
+  if (!t.outer_nt) {
+    launch(k_outer_step<false, AVG, false>);
+  } else if (t.kept_tiles) {
+    launch(k_outer_step<true, AVG, true>);
+  } else {
+    launch(k_outer_step<true, AVG, false>);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_outer_step(const OuterArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0) return hipSuccess;
-  const int avg = a.avg_h ? (a.avg_v ? 2 : 1) : 0;
-  if (t.outer_nt) {
-    return avg == 0 ? launch_outer_t<true, 0>(a, t, s)
-                    : avg == 1 ? launch_outer_t<true, 1>(a, t, s) : launch_outer_t<true, 2>(a, t, s);
-  }
-  return avg == 0 ? launch_outer_t<false, 0>(a, t, s)
-                  : avg == 1 ? launch_outer_t<false, 1>(a, t, s) : launch_outer_t<false, 2>(a, t, s);
+  if (!a.avg_h) return launch_outer_t<0>(a, t, s);
+  return a.avg_v ? launch_outer_t<2>(a, t, s) : launch_outer_t<1>(a, t, s);
 }
 
 hipError_t launch_outer_big(const OuterArgs &a, const LaunchTuning &t, hipStream_t s) {
@@ -1446,14 +1510,17 @@ hipError_t launch_fused_t(const LocalArgs &l, const OuterArgs &o, int n_tensors,
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   const OuterP p{o.lr, 0.f, o.beta, o.m_f, o.alpha};
-  if (t.outer_nt) {
-    hipLaunchKernelGGL((k_local_outer_step<BASE, BF16, FIRST, POLICY, true>), dim3(g.blocks),
-                       dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0,
-                       o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors,
+                       o.xtab_t, l.gtab, o.x0, o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk,
+                       g.run, o.m, sp, ap, p);
+  };
+  if (!t.outer_nt) {
+    launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, false, false>);
+  } else if (t.kept_tiles) {
+    launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, true, true>);
   } else {
-    hipLaunchKernelGGL((k_local_outer_step<BASE, BF16, FIRST, POLICY, false>), dim3(g.blocks),
-                       dim3(kOuterBlock), t.last_lds, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0,
-                       o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
+    launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, true, false>);
   }
   return hipGetLastError();
 }

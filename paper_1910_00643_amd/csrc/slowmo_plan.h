@@ -70,8 +70,8 @@ static_assert(kPacedTile % kOuterTile == 0, "a paced tile is a whole number of o
 
 // One tile of either kernel: the k-th piece of a tensor.  For the local step
 // `owner` is the slot (worker * n_tensors + tensor); for the outer step it is
-// the tensor.  8 bytes, read with one scalar load.  In the list of the local step
-// kTileKept is set in k for a kept tile (a tensor has at most 2^28 pieces).
+// the tensor.  8 bytes, read with one scalar load.  In k
+// kTileKept is set for a kept tile (a tensor has at most 2^28 pieces).
 constexpr int32_t kTileKept = INT32_MIN;
 struct TileRef {
   int32_t owner;
@@ -85,19 +85,24 @@ struct CacheRule {
   bool streaming;      // non-temporal accesses (but for the kept tiles)
   bool outer_streaming;  // the same for the outer step and the fused last step
   bool write_through;  // stores leave the L2 at once
-  uint64_t kept;       // share of the units that is kept, times 2^32
+  double kept_bytes;   // of the replicas and buffers: kept in the last-level cache
 };
 // For a step that touches state_bytes of replicas and buffers and grad_bytes of
 // gradients (grad_size bytes per element); x0 and u are outer_bytes.
 CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
                      int64_t outer_bytes);
-// Kept tiles come in units of 16 384 elements of every worker.  Units are numbered along
-// the tensors; the multiples of the golden ratio spread the kept ones evenly over any
-// stretch of them, and so over the sets of the cache.
+// Kept units: 16 384 elements of every worker.  Units are numbered along the tensors; the
+// multiples of the golden ratio spread the kept ones evenly over any stretch of them, and
+// so over the XCDs and the sets of the cache.
 constexpr int32_t kKeptUnit = 16384;
-inline bool unit_kept(int64_t unit, uint64_t kept) {
-  return static_cast<uint32_t>(unit) * 2654435769u < kept;
+inline bool unit_kept(int64_t unit, uint64_t share) {
+  return static_cast<uint32_t>(unit) * 2654435769u < share;
 }
+// The share of the units, times 2^32, that is kept_bytes of state_bytes.
+uint64_t kept_share(double kept_bytes, double state_bytes);
+// Where the local step keeps whole workers instead: how many of m are about kept_bytes,
+// worker_bytes of replica and buffers each (0: not even the first one is).
+int32_t kept_workers(int32_t m, double kept_bytes, double worker_bytes);
 
 // Per (worker, tensor), fixed at create.
 struct SlotInfo {

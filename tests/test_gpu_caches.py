@@ -65,7 +65,10 @@ def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layou
     want = PU.run_library(w, (layout, "padded"), calls(w), **STREAMING)
     for other in ({"SLOWMO_LOCAL_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_OUTER_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_WRITE_THROUGH": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1"},
-                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1000"}):
+                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1000"},
+                  # whole workers kept, and a part of the first one: where big tiles are in use
+                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "3", "SLOWMO_BIG_TILES": "1"},
+                  {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1", "SLOWMO_BIG_TILES": "1"}):
         PU.assert_same_bits(want, PU.run_library(w, (layout, "padded"), calls(w),
                                                  **{**STREAMING, "SLOWMO_TURN": "1", **other}))
 
