@@ -87,12 +87,24 @@ def fused_bytes_per_element(w) -> int:
     return reads + writes
 
 
-BIG_TILE = 65536                # elements of a big tile (kBigTile of the library)
+def big_tile(w, cus=256):
+    """Elements of a big tile (the library's rule for the vectors per lane: what fills
+    the rounds of one tile per CU best), 0 where there are fewer than 160 of them."""
+    best = (None, 0)
+    for vpt, loss in ((16, 1.0), (14, 1.01), (12, 1.06)):
+        n = sum(v // (4096 * vpt) for v in w.numel)
+        if n < 160:
+            continue
+        f = n % cus / cus
+        cost = loss * vpt * (n // cus + (f if f <= 0.05 else max(f, 0.42 + 0.46 * f)))
+        if best[0] is None or cost < best[0]:
+            best = (cost, 4096 * vpt)
+    return best[1]
 
 
 def big_elements(w, fused: bool) -> int:
     """Elements that the big-tile kernels take in the outer step (fused with
-    the last local step or not): the whole 65 536-element pieces of every
+    the last local step or not): the whole big tiles of every
     tensor, from 8 workers on for the fused kernel and from 16 for the plain
     outer step, if there are at least 160 such pieces; the fused kernel only
     under the "reset" buffer strategy, the plain one unless the buffers are
@@ -102,8 +114,8 @@ def big_elements(w, fused: bool) -> int:
         return 0
     if fused and w.policy != "reset":
         return 0
-    tiles = sum(n // BIG_TILE for n in w.numel)
-    return tiles * BIG_TILE if tiles >= 160 else 0
+    tile = big_tile(w)
+    return sum(n // tile for n in w.numel) * tile if tile else 0
 
 
 def fusable(w) -> bool:

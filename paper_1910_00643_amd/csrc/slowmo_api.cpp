@@ -253,7 +253,7 @@ struct slowmo_ctx {
   TileRef *d_otiles = nullptr;
   int32_t n_ltiles = 0, n_otiles = 0;
   // With big tiles in use, the outer step and the fused last step run twice:
-  // over the big tiles (whole kBigTile pieces of the tensors all of whose
+  // over the big tiles (whole pieces of the tensors all of whose
   // replicas are 16-byte aligned) and over the ordinary tiles these leave
   // over.  Otherwise n_btiles = 0 and the rest list is the whole ordinary list.
   TileRef *d_btiles = nullptr, *d_rtiles = nullptr;
@@ -616,6 +616,10 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // the library's static scratch array (the create call runs with it current)
   CREATE_HIP(static_scratch(ctx->device, &ctx->static_table), "address of the static scratch array");
 
+  int cus = 0;
+  CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
+             "number of CUs");
+
   // device tables
   const Layout &L = ctx->layout;
   std::vector<SlotInfo> &slots = ctx->slots;
@@ -638,14 +642,20 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   }
   std::vector<TileRef> bt, rt;  // big tiles and the ordinary tiles they leave over
   if (ctx->tune.big_tiles) {
-    constexpr int64_t per_big = kBigTile / kOuterTile;
-    for (int32_t j = 0; j < n_tensors; ++j) {
-      const int64_t n_big = tinfo[j].unaligned ? 0 : numel[j] / kBigTile;
+    std::vector<int64_t> usable(numel, numel + n_tensors);
+    for (int32_t j = 0; j < n_tensors; ++j)
+      if (tinfo[j].unaligned) usable[j] = 0;
+    // forced big tiles have 16 vectors, unless a test asks for another size
+    const int32_t asked = env_flag("SLOWMO_TEST_BIG_VPT", kBigVpt);
+    ctx->tune.big_vpt = big <= 0 ? choose_big_vpt(n_tensors, usable.data(), cus)
+                                 : asked == 14 || asked == 12 ? asked : kBigVpt;
+    const int64_t tile = big_tile(ctx->tune.big_vpt), per_big = tile / kOuterTile;
+    for (int32_t j = 0; j < n_tensors && tile > 0; ++j) {
+      const int64_t n_big = usable[j] / tile;
       for (int64_t k = 0; k < n_big; ++k) bt.push_back({j, static_cast<int32_t>(k)});
       for (int64_t k = n_big * per_big; k * kOuterTile < numel[j]; ++k)
         rt.push_back({j, static_cast<int32_t>(k)});
     }
-    if (big < 0 && static_cast<int64_t>(bt.size()) < kBigMinTiles) bt.clear();
   }
   // Kept tiles: a share of the units of every worker.  But big tiles run best while the
   // whole chip is on one worker, and lose that when some of them come from the cache and
@@ -712,9 +722,6 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // paced tiles, for contexts whose fused gossip step is one pass
   if (ctx->tune.paced != 0 && ctx->tune.nontemporal && ctx->tune.fuse_mix && ctx->params_aligned &&
       count_paced_pieces(m, n_tensors, numel, ctx->tune.paced >= 2) > 0) {
-    int cus = 0;
-    CREATE_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
-               "number of CUs");
     ctx->paced.members = cus / 8;
     // test hook: a limit that the workgroups reach, to run on out of step
     ctx->paced.spins = env_flag("SLOWMO_TEST_PACE_SPINS", kPaceSpins);

@@ -93,7 +93,8 @@ struct LaunchTuning {
   int32_t fuse_mix;     // 1: slowmo_local_mix_step runs one fused kernel when it can
   int32_t paced;        // the fused gossip step on paced tiles: 0 never, 1 by the rule, 2 wherever
                         // the kernel allows
-  int32_t big_tiles;    // 1: whole kBigTile pieces of aligned tensors go to the big-tile kernels
+  int32_t big_tiles;    // 1: whole big tiles of aligned tensors go to the big-tile kernels
+  int32_t big_vpt;      // vectors per lane of a big tile: 16, 14 or 12
   int32_t local_nt;     // the same for the local step, the gossip kernels in single waves and the
                         // loads of the de-biasing (0: their working set stays in the caches)
   int32_t outer_nt;     // the same for the outer step and the fused last step in single waves
@@ -121,8 +122,8 @@ hipError_t launch_outer_step(const OuterArgs &a, const LaunchTuning &tune, hipSt
 hipError_t launch_local_outer_step(const LocalArgs &l, const OuterArgs &o, int32_t n_tensors,
                                    int base, bool bf16, bool first, int policy,
                                    const LaunchTuning &tune, hipStream_t stream);
-// The same two operations on BIG tiles (a.tiles / o.tiles list whole kBigTile
-// pieces, every one full, of tensors all of whose replicas are 16-byte aligned).  Results are
+// The same two operations on BIG tiles (a.tiles / o.tiles list whole pieces of
+// big_tile(tune.big_vpt) elements, every one full, of tensors all of whose replicas are 16-byte aligned).  Results are
 // bit-identical to the ordinary tiles'.  launch_outer_big handles no buffer
 // average (a.avg_h must be NULL); launch_local_outer_big handles policies 0 and 1.
 hipError_t launch_outer_big(const OuterArgs &a, const LaunchTuning &tune, hipStream_t stream);

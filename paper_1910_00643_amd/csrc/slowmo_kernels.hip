@@ -711,8 +711,8 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_outer_step(
 }
 
 // ---- big tiles: the two kernels above on whole 65 536-element pieces ---------------
-// One 1024-thread workgroup = kBigTile elements of one tensor, all workers;
-// lane t owns the vectors [v * 4096 + 4t, + 4), v = 0..15, of every stream.  All
+// One 1024-thread workgroup = 4096 VPT elements of one tensor, all workers;
+// lane t owns the vectors [v * 4096 + 4t, + 4), v = 0..VPT-1, of every stream.  All
 // 16 waves of the workgroup read 256 KiB of replica 0, then of replica 1, ...:
 // measured, a memory region that is visited in pieces of this size serves the
 // many-stream walk about 10 % faster than 1 KiB pieces from unrelated waves
@@ -728,6 +728,7 @@ constexpr int kBigStride = 4 * kBigBlock;  // floats between a lane's consecutiv
 // (11.7 M elements) 289 -> 280 us.
 __device__ __forceinline__ void together() { __builtin_amdgcn_s_barrier(); }
 
+template <int VPT>
 __global__ __launch_bounds__(kBigBlock) void k_outer_big(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, float *__restrict__ x0base, float *__restrict__ ubase,
@@ -737,18 +738,18 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
   const TileRef t = tiles[tile];
   const TensorInfo ti = tensors[t.owner];
   const OuterP p = for_tensor(p0, ti.lr_scale);
-  const int64_t eo = static_cast<int64_t>(t.k) * kBigTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * big_tile(VPT);
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   float *x0 = x0base + ti.fo + eo;
   float *u = ubase + ti.fo + eo;
   const int lane = 4 * static_cast<int>(threadIdx.x);
-  constexpr int HALF = kBigVpt / 2;
-  V4 acc[kBigVpt];
+  constexpr int HALF = VPT / 2;
+  V4 acc[VPT];
   for (int i = 0; i < m; ++i) {       // line 6: ordered sum, i = 0, 1, ..., m-1
     together();
     const float *x = xp[i] + eo;
 #pragma unroll
-    for (int v0 = 0; v0 < kBigVpt; v0 += HALF) {
+    for (int v0 = 0; v0 < VPT; v0 += HALF) {
       V4 xv[HALF];
 #pragma unroll
       for (int v = 0; v < HALF; ++v) xv[v] = ld4<true>(x + (v0 + v) * kBigStride + lane);
@@ -757,7 +758,7 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
     }
   }
 #pragma unroll
-  for (int v = 0; v < kBigVpt; ++v) {
+  for (int v = 0; v < VPT; ++v) {
     const V4 x0v = ld4<true>(x0 + v * kBigStride + lane);
     V4 uv = ld4<true>(u + v * kBigStride + lane);
     const V4 xn = outer4(acc[v], x0v, uv, p);
@@ -768,14 +769,14 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
   for (int i = 0; i < m; ++i) {
     float *x = xp[i] + eo;
 #pragma unroll
-    for (int v = 0; v < kBigVpt; ++v) st4<true>(x + v * kBigStride + lane, acc[v]);
+    for (int v = 0; v < VPT; ++v) st4<true>(x + v * kBigStride + lane, acc[v]);
   }
 }
 
 // POLICY 0 (reset: the buffers of this step are not stored) or 1 (maintain).
 // A worker's step runs over SUB vectors at a time: their operands are loaded,
 // stepped, added to the sum and dropped before the next SUB are loaded.
-template <int BASE, bool BF16, bool FIRST, int POLICY>
+template <int BASE, bool BF16, bool FIRST, int POLICY, int VPT>
 __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
@@ -792,7 +793,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
   sp.wd = ti.wd;
   ap.lr = ap.lr * ti.lr_scale;
   ap.wd = ti.wd;
-  const int64_t eo = static_cast<int64_t>(t.k) * kBigTile;
+  const int64_t eo = static_cast<int64_t>(t.k) * big_tile(VPT);
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   const void *const *__restrict__ gp = gtab + t.owner;       // worker i: gp[i * n_tensors]
   float *x0 = x0base + ti.fo + eo;
@@ -802,7 +803,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
   constexpr int gsize = BF16 ? 2 : 4;
   constexpr int SUB = 2;
   const int lane = 4 * static_cast<int>(threadIdx.x);
-  V4 acc[kBigVpt];
+  V4 acc[VPT];
   for (int i = 0; i < m; ++i) {
     together();
     const float *xi = xp[i] + eo;
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
     float *vi = BASE == 1 ? v0 + i * d_pad : nullptr;
     const char *gi = static_cast<const char *>(gp[static_cast<int64_t>(i) * n_tensors]) + eo * gsize;
 #pragma unroll
-    for (int s0 = 0; s0 < kBigVpt; s0 += SUB) {
+    for (int s0 = 0; s0 < VPT; s0 += SUB) {
       V4 xv[SUB], hv[SUB], vv[SUB], gv[SUB];
 #pragma unroll
       for (int v = 0; v < SUB; ++v) {
@@ -833,7 +834,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
     }
   }
 #pragma unroll
-  for (int v = 0; v < kBigVpt; ++v) {
+  for (int v = 0; v < VPT; ++v) {
     const V4 x0v = ld4<true>(x0 + v * kBigStride + lane);
     V4 uv = ld4<true>(u + v * kBigStride + lane);
     const V4 xn = outer4(acc[v], x0v, uv, p);
@@ -844,7 +845,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
   for (int i = 0; i < m; ++i) {
     float *x = xp[i] + eo;
 #pragma unroll
-    for (int v = 0; v < kBigVpt; ++v) st4<true>(x + v * kBigStride + lane, acc[v]);
+    for (int v = 0; v < VPT; ++v) st4<true>(x + v * kBigStride + lane, acc[v]);
   }
 }
 
@@ -1453,8 +1454,16 @@ hipError_t launch_outer_big(const OuterArgs &a, const LaunchTuning &t, hipStream
   if (a.avg_h || a.avg_v || !t.nontemporal) return hipErrorInvalidValue;
   const Grid g = make_grid(a.ntiles, t);
   const OuterP p{a.lr, 0.f, a.beta, a.m_f, a.alpha};
-  hipLaunchKernelGGL(k_outer_big, dim3(g.blocks), dim3(kBigBlock), 0, s, a.tiles, a.tensors,
-                     a.xtab_t, a.x0, a.u, a.ntiles, g.chunk, g.run, a.m, p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kBigBlock), 0, s, a.tiles, a.tensors, a.xtab_t,
+                       a.x0, a.u, a.ntiles, g.chunk, g.run, a.m, p);
+  };
+  switch (t.big_vpt) {
+    case 16: launch(k_outer_big<16>); break;
+    case 14: launch(k_outer_big<14>); break;
+    case 12: launch(k_outer_big<12>); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -1467,14 +1476,21 @@ hipError_t launch_fused_big_t(const LocalArgs &l, const OuterArgs &o, int n_tens
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   const OuterP p{o.lr, 0.f, o.beta, o.m_f, o.alpha};
-  if (policy == 0) {
-    hipLaunchKernelGGL((k_local_outer_big<BASE, BF16, FIRST, 0>), dim3(g.blocks), dim3(kBigBlock),
-                       0, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0, o.u, l.h, l.v, o.d_pad,
-                       n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
-  } else {
-    hipLaunchKernelGGL((k_local_outer_big<BASE, BF16, FIRST, 1>), dim3(g.blocks), dim3(kBigBlock),
-                       0, s, o.tiles, o.tensors, o.xtab_t, l.gtab, o.x0, o.u, l.h, l.v, o.d_pad,
-                       n_tensors, o.ntiles, g.chunk, g.run, o.m, sp, ap, p);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kBigBlock), 0, s, o.tiles, o.tensors, o.xtab_t,
+                       l.gtab, o.x0, o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk, g.run, o.m,
+                       sp, ap, p);
+  };
+  if (policy != 0) {
+    if (t.big_vpt != kBigVpt) return hipErrorInvalidValue;
+    launch(k_local_outer_big<BASE, BF16, FIRST, 1, kBigVpt>);
+    return hipGetLastError();
+  }
+  switch (t.big_vpt) {
+    case 16: launch(k_local_outer_big<BASE, BF16, FIRST, 0, 16>); break;
+    case 14: launch(k_local_outer_big<BASE, BF16, FIRST, 0, 14>); break;
+    case 12: launch(k_local_outer_big<BASE, BF16, FIRST, 0, 12>); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 #include "slowmo_plan.h"
 
 #include <algorithm>
+#include <utility>
 
 namespace slowmo {
 
@@ -89,7 +90,31 @@ int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece) {
 }
 
 int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel) {
-  return count_pieces(n_tensors, numel, kBigTile);
+  return count_pieces(n_tensors, numel, big_tile(kBigVptMin));
+}
+
+// A big tile keeps one CU busy, and all of them take about the same time, so a launch runs
+// in rounds of one tile per CU.  A last round that fills a part f of the CUs is bound by what
+// their loads can have in flight: it takes 0.46 of a whole one at f = 0.11-0.14, 0.59 at
+// 0.33, 0.65 at 0.5, 0.70 at 0.6, 0.73 at 0.7, 0.81 at 0.8, 0.93 at 0.93 (m = 8), and up to
+// 0.05 next to nothing, because the rounds are not that even.  Smaller tiles cost 1 % (14
+// vectors) and 3-6 % (12) per element; 10 and 8 would cost 7-8 %.  Fused last step with 16, 14,
+// 12 vectors: 25.6 M elements, m = 32 2205, 2145, 2163 us, m = 16 (first step) 930, 885, 889;
+// 11.7 M, m = 8 287, 278, 276; 20.0 M, m = 16 1057, 982, 913; 16.8 M, m = 8 394, 504, 469; 76 M,
+// m = 8 2608, 2646, 2750.
+int32_t choose_big_vpt(int32_t n_tensors, const int64_t *numel, int32_t cus) {
+  if (cus <= 0) return 0;
+  int32_t best = 0;
+  double best_cost = 0;
+  for (const auto &[vpt, loss] : {std::pair{16, 1.0}, std::pair{14, 1.01}, std::pair{12, 1.06}}) {
+    const int64_t n = count_pieces(n_tensors, numel, big_tile(vpt));
+    if (n < kBigMinTiles) continue;
+    const double f = static_cast<double>(n % cus) / cus;
+    const double part = f <= 0.05 ? f : std::max(f, 0.42 + 0.46 * f);
+    const double cost = loss * vpt * (static_cast<double>(n / cus) + part);
+    if (best == 0 || cost < best_cost) best = vpt, best_cost = cost;
+  }
+  return best;
 }
 
 int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, bool forced) {

@@ -42,6 +42,10 @@ constexpr int32_t kOuterTile = 4 * kOuterBlock;
 constexpr int32_t kBigBlock = 1024;
 constexpr int32_t kBigVpt = 16;
 constexpr int32_t kBigTile = 4 * kBigBlock * kBigVpt;
+// Tiles of 14 or 12 vectors per lane instead of 16, where they fill the chip's rounds
+// better (choose_big_vpt).
+constexpr int32_t kBigVptMin = 12;
+constexpr int32_t big_tile(int32_t vpt) { return 4 * kBigBlock * vpt; }
 constexpr int32_t kBigFusedFromWorkers = 8;
 constexpr int32_t kBigOuterFromWorkers = 16;
 // ... and only when there are enough of them to occupy the chip: one big tile
@@ -49,7 +53,7 @@ constexpr int32_t kBigOuterFromWorkers = 16;
 // and 32): twice as slow as single-wave tiles at k = 64, 6-17 % slower at
 // k = 128, 4-15 % faster from k = 173 on.
 constexpr int32_t kBigMinTiles = 160;
-static_assert(kBigTile % kOuterTile == 0, "a big tile is a whole number of ordinary tiles");
+static_assert(big_tile(1) % kOuterTile == 0, "a big tile is a whole number of ordinary tiles");
 
 // Paced tiles of the fused gossip step: one 512-thread workgroup per CU, 8 vectors per
 // lane, 64 KiB of a stream per tile.
@@ -190,8 +194,12 @@ Layout make_layout(int32_t n_tensors, const int64_t *numel);
 // Number of tiles of each kind (no allocation).
 int64_t count_local_tiles(int32_t m, int32_t n_tensors, const int64_t *numel);
 int64_t count_outer_tiles(int32_t n_tensors, const int64_t *numel);
-// Whole kBigTile pieces over all tensors (an upper bound on the big tiles in use).
+// Whole pieces of the smallest big tile over all tensors (an upper bound on the big tiles
+// in use).
 int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel);
+// Vectors per lane of the big tiles for a list (numel: its tensors, those that cannot take
+// big tiles as 0) on a chip with `cus` CUs; 0: not enough of them.
+int32_t choose_big_vpt(int32_t n_tensors, const int64_t *numel, int32_t cus);
 int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
 // Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
 // worker count is too small (with `forced`, only when no tensor has such a piece).

@@ -1,0 +1,62 @@
+// The rules that say how the kernels go through the caches, and which big tiles a list gets.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "slowmo_plan.h"
+
+using namespace slowmo;
+
+static void check(bool ok, const char *what, double at) {
+  if (ok) return;
+  std::printf("FAILED: %s (%g)\n", what, at);
+  std::exit(1);
+}
+
+int main() {
+  const int64_t MiB = int64_t{1} << 20;
+  for (int64_t size : {int64_t{1}, 20 * MiB, 20 * MiB + 3, 54 * MiB, 240 * MiB, 240 * MiB + 3, int64_t{1} << 40}) {
+    for (int64_t grad : {2, 4}) {
+      const int64_t g = size / (8 + grad) * grad, s = size - g;
+      const CacheRule r = cache_rule(s, g, grad, size / 4);
+      check(r.streaming == !(size > 20 * MiB && size <= 240 * MiB), "plain in the caches only", size);
+      check(r.outer_streaming || !r.streaming, "the outer step plain only where the local step is", size);
+      check(r.outer_streaming || size + size / 4 <= 240 * MiB, "x0 and u fit too", size);
+      check((r.kept_bytes > 0) == (r.streaming && r.write_through), "kept on long lists", size);
+      check(r.kept_bytes <= 0.6 * s && r.kept_bytes <= 224e6, "no more kept than fits", size);
+      check(r.write_through == (size > (grad == 2 ? 80 : 54) * MiB), "written through", size);
+    }
+  }
+  // the kept share of any stretch of units is near the share asked for
+  for (double share : {0.0, 0.004, 0.1, 0.37, 0.6, 1.0}) {
+    const uint64_t of = kept_share(share * 1e9, 1e9);
+    for (int64_t from : {int64_t{0}, int64_t{7777}, int64_t{1} << 33}) {
+      int64_t n = 0;
+      for (int64_t u = from; u < from + 1000; ++u) n += unit_kept(u, of);
+      check(std::abs(n - 1000 * share) <= 8, "kept units of a stretch", share);
+    }
+  }
+  check(kept_share(0, 1e9) == 0 && kept_share(1e9, 0) == 0, "nothing kept", 0);
+  check(unit_kept(123, kept_share(5e9, 1e9)), "everything kept", 0);
+  check(kept_workers(8, 224e6, 94e6) == 2 && kept_workers(32, 224e6, 204e6) == 1, "whole workers", 0);
+  check(kept_workers(8, 224e6, 306e6) == 1 && kept_workers(8, 224e6, 2.5e9) == 0, "large workers", 0);
+  check(kept_workers(2, 1e12, 1e6) == 2 && kept_workers(4, 0, 1e6) == 0, "limits", 0);
+  // big tiles: none below 160, never more than the workspace has room for
+  for (int64_t n = 0; n < 4000; n += 37) {
+    const std::vector<int64_t> list = {n * 20000 + 11, 65536 * (n % 90), 5};
+    const int32_t v = choose_big_vpt(3, list.data(), 256);
+    check(v == 0 || v == 16 || v == 14 || v == 12, "size", n);
+    if (v == 0) {
+      check(count_pieces(3, list.data(), big_tile(kBigVptMin)) < kBigMinTiles, "enough of the smallest", n);
+    } else {
+      const int64_t tiles = count_pieces(3, list.data(), big_tile(v));
+      check(tiles >= kBigMinTiles && tiles <= count_big_tiles(3, list.data()), "number of tiles", n);
+    }
+  }
+  const int64_t full = 256 * int64_t{65536};
+  check(choose_big_vpt(1, &full, 256) == 16, "one full round", 0);
+  check(choose_big_vpt(1, &full, 0) == 0, "no CUs", 0);
+  std::puts("ok");
+  return 0;
+}
