@@ -676,6 +676,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   };
   // to the kernels that walk all workers only a tile that is kept of each of them is one
   const uint64_t walk_share = big_in_use ? 0 : share_of(0);
+  ctx->tune.kept_local = caches.kept_bytes > 0;
   ctx->tune.kept_tiles = walk_share > 0;
   // tiles in launch order: worker-major, tensors in list order, pieces ascending
   static_assert(kLocalTile == kOuterTile, "a worker's local tiles are the outer tiles");

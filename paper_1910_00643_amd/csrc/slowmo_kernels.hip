@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_init_broadcast(
 // Same tiling as the local step: one workgroup = 256 elements of one (worker,
 // tensor); 3 streams read, 3 written.  "xbar" is the worker's own replica
 // (a one-term sum divided by 1, which is exact).
-template <bool NT, bool THROUGH>
+template <bool NT, bool THROUGH, bool KEPT>
 __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *__restrict__ x0base, float *__restrict__ ubase, int ntiles, int chunk, int remap,
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   if (n >= 4) {
     const int e0 = lane_element(n);
     V4 xv;
-    if (NT && is_kept(t)) {
+    if (NT && KEPT && is_kept(t)) {
       own_path(x);
       xv = ld4<false>(x + e0);
       own_value(xv);
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
     const V4 xn = outer4(xv, x0v, uv, p);
     st4_arena<NT, THROUGH>(u, e0, uv);
     st4_arena<NT, THROUGH>(x0, e0, xn);
-    if (NT && is_kept(t)) {
+    if (NT && KEPT && is_kept(t)) {
       st4_at<false, THROUGH>(x, e0, xn);
     } else {
       st4_at<NT, THROUGH>(x, e0, xn);
@@ -954,7 +954,7 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
   }
 }
 
-template <bool NT>
+template <bool NT, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const MixEntry *__restrict__ seq, int len, int ntiles,
@@ -969,7 +969,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   if (n >= 4) {
-    if (NT && is_kept(t)) {
+    if (NT && KEPT && is_kept(t)) {
       own_path(xp);
       mix_lane<false, false>(xp, seq, len, eo, lane_element(n));
     } else {
@@ -1056,7 +1056,7 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
   }
 }
 
-template <int BASE, bool BF16, bool FIRST, bool NT>
+template <int BASE, bool BF16, bool FIRST, bool NT, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
@@ -1080,7 +1080,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
   if (n >= 4) {
     const int e0 = lane_element(n);
-    if (NT && is_kept(t)) {
+    if (NT && KEPT && is_kept(t)) {
       own_path(xp), own_path(h0);
       if constexpr (BASE == 1) own_path(v0);
       local_mix_lane<BASE, BF16, FIRST, false, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq,
@@ -1308,7 +1308,7 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
 
 // z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.  NTL:
 // the loads; NT: the stores.
-template <bool NTL, bool NT>
+template <bool NTL, bool NT, bool KEPT>
 __global__ __launch_bounds__(kLocalBlock) void k_debias(
     const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *const *__restrict__ ztab, const float *__restrict__ w, int n_tensors, int ntiles,
@@ -1327,7 +1327,7 @@ __global__ __launch_bounds__(kLocalBlock) void k_debias(
   if (n >= 4) {
     const int e0 = lane_element(n);
     V4 xv;
-    if (NTL && is_kept(t)) {
+    if (NTL && KEPT && is_kept(t)) {
       own_path(x);
       xv = ld4<false>(x + e0);
       own_value(xv);
@@ -1591,12 +1591,16 @@ hipError_t launch_init_broadcast(const OuterArgs &a, int32_t x0_copies, const La
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0 || a.len <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
-  if (t.local_nt) {
-    hipLaunchKernelGGL((k_mix_step<true>), dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles,
-                       a.tensors, a.xtab_t, a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles, a.tensors, a.xtab_t,
+                       a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
+  };
+  if (!t.local_nt) {
+    launch(k_mix_step<false, false>);
+  } else if (t.kept_tiles) {
+    launch(k_mix_step<true, true>);
   } else {
-    hipLaunchKernelGGL((k_mix_step<false>), dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles,
-                       a.tensors, a.xtab_t, a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
+    launch(k_mix_step<true, false>);
   }
   return hipGetLastError();
 }
@@ -1609,14 +1613,17 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const Grid g = make_grid(x.ntiles, t);
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
-  if (t.local_nt) {
-    hipLaunchKernelGGL((k_local_mix_step<BASE, BF16, FIRST, true>), dim3(g.blocks),
-                       dim3(kOuterBlock), 0, s, x.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
-                       x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m, sp, ap);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), 0, s, x.tiles, x.tensors, x.xtab_t,
+                       l.gtab, l.h, l.v, x.seq, x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m,
+                       sp, ap);
+  };
+  if (!t.local_nt) {
+    launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
+  } else if (t.kept_tiles) {
+    launch(k_local_mix_step<BASE, BF16, FIRST, true, true>);
   } else {
-    hipLaunchKernelGGL((k_local_mix_step<BASE, BF16, FIRST, false>), dim3(g.blocks),
-                       dim3(kOuterBlock), 0, s, x.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
-                       x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m, sp, ap);
+    launch(k_local_mix_step<BASE, BF16, FIRST, true, false>);
   }
   return hipGetLastError();
 }
@@ -1685,11 +1692,13 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
                        a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
   };
   if (!t.nontemporal) {
-    launch(k_debias<false, false>);
-  } else if (t.local_nt) {
-    launch(k_debias<true, true>);
+    launch(k_debias<false, false, false>);
+  } else if (!t.local_nt) {
+    launch(k_debias<false, true, false>);
+  } else if (t.kept_local) {
+    launch(k_debias<true, true, true>);
   } else {
-    launch(k_debias<false, true>);
+    launch(k_debias<true, true, false>);
   }
   return hipGetLastError();
 }
@@ -1703,11 +1712,13 @@ hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &
                        a.x0, a.u, a.ntiles, g.chunk, g.run, p);
   };
   if (!t.outer_nt) {
-    launch(k_outer_noavg<false, false>);
-  } else if (t.noavg_through) {
-    launch(k_outer_noavg<true, true>);
+    launch(k_outer_noavg<false, false, false>);
+  } else if (!t.noavg_through) {
+    launch(k_outer_noavg<true, false, false>);
+  } else if (t.kept_local) {
+    launch(k_outer_noavg<true, true, true>);
   } else {
-    launch(k_outer_noavg<true, false>);
+    launch(k_outer_noavg<true, true, false>);
   }
   return hipGetLastError();
 }
