@@ -735,6 +735,12 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     ctx->paced.ntiles = static_cast<int32_t>(pt.size());
     ctx->d_prtiles = append(prt);
     ctx->n_prtiles = static_cast<int32_t>(prt.size());
+    if (const int32_t ride = env_flag("SLOWMO_PACED_REST", -1);
+        ride < 0 ? rest_rides(ctx->paced.ntiles, ctx->n_prtiles, cus) : ride != 0) {
+      ctx->paced.rest = ctx->d_prtiles;
+      ctx->paced.nrest = ctx->n_prtiles;
+      ctx->n_prtiles = 0;
+    }
     // A launch per connected group walks only its replicas, but each has a tail of its
     // own.  Groups of 4 workers (m = 16 and 32, both base optimizers, one to four rows
     // of paced tiles), time over all in single waves, in one launch / one per group, by

@@ -68,6 +68,8 @@ struct PacedArgs {
   const TileRef *tiles;        // device: whole kPacedTile pieces (owner = tensor)
   int32_t ntiles;
   int32_t members;             // workgroups per XCD: its number of CUs
+  const TileRef *rest;         // device: ordinary tiles for the workgroups without a piece in the
+  int32_t nrest;               // last row (0: they run as a launch of their own)
   int32_t spins;               // polls after which a workgroup stops waiting for the others
   uint32_t *counters;          // device: kPaceWords words, zero between launches
 };

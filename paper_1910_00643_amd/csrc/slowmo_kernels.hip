@@ -157,14 +157,14 @@ __device__ __forceinline__ void st4_arena(float *p, int e0, V4 v) {
 // gradients, gossip step 68 -> 51 us.)  Both lanes read before either writes because they are lanes
 // of one wave: a workgroup must be a single one.  n < 4 (ONE): one element per lane.
 static_assert(kLocalBlock == 64 && kOuterBlock == 64, "a tile belongs to one wave");
+// (t: the lane, which is the thread except where a workgroup's waves take tiles of their
+// own.)
+__device__ __forceinline__ int lane_element(int n, int t) { return 4 * t < n - 4 ? 4 * t : n - 4; }
 __device__ __forceinline__ int lane_element(int n) {
-  const int e = 4 * static_cast<int>(threadIdx.x);
-  return e < n - 4 ? e : n - 4;
+  return lane_element(n, static_cast<int>(threadIdx.x));
 }
-__device__ __forceinline__ bool lane_idle(int n) {
-  const int t = static_cast<int>(threadIdx.x);
-  return (n >= 4 ? 4 * t : t) >= n;
-}
+__device__ __forceinline__ bool lane_idle(int n, int t) { return (n >= 4 ? 4 * t : t) >= n; }
+__device__ __forceinline__ bool lane_idle(int n) { return lane_idle(n, static_cast<int>(threadIdx.x)); }
 
 template <bool ONE, bool NT>
 __device__ __forceinline__ V4 ldv(const float *p) {
@@ -1217,6 +1217,7 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
     float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
     float *__restrict__ hbase, float *__restrict__ vbase, const MixEntry *__restrict__ seq, int len,
     int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int spins, int m,
+    const TileRef *__restrict__ rest, int nrest,
     uint32_t *pace, SgdP sp0, AdamP ap0) {
   static_assert(kPacedSaved == 2, "one saved value in LDS, one in registers");
   __shared__ V4 kept[2][kPV][kPacedBlock];     // [0]: opened the cycle, [1]: saved value 1
@@ -1301,6 +1302,40 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
         for (int q = 0; q < kPV; ++q) mixed.v[q] = mixed.v[q] + en.b * S.v[q];
       }
       paced_store(xi, lane, mixed);
+    }
+  }
+  // The ordinary tiles that the pieces leave over go, one per wave, to the workgroups that
+  // have no piece in the last row (if all have one: to all), an eighth to each XCD.
+  const int busy = (mine > 0 ? mine : 0) % members;  // workgroups with a piece in the last row
+  if (nrest > 0 && rank >= busy) {
+    const int share = (nrest + kXcd - 1) / kXcd, end = nrest < (xcd + 1) * share ? nrest : (xcd + 1) * share;
+    constexpr int kWaves = kPacedBlock / 64;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+    const int t64 = static_cast<int>(threadIdx.x) % 64;
+    for (int r = xcd * share + (rank - busy) * kWaves + wave; r < end; r += (members - busy) * kWaves) {
+      const TileRef t = rest[r];
+      const TensorInfo ti = tensors[t.owner];
+      SgdP sp = sp0;
+      AdamP ap = ap0;
+      sp.lr = sp.lr * ti.lr_scale;
+      sp.wd = ti.wd;
+      ap.lr = ap.lr * ti.lr_scale;
+      ap.wd = ti.wd;
+      const int64_t eo = static_cast<int64_t>(piece_of(t)) * kOuterTile;
+      const int64_t left = ti.numel - eo;
+      const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
+      if (lane_idle(n, t64)) continue;
+      float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+      const void *const *__restrict__ gp = gtab + t.owner;
+      float *h0 = hbase + ti.fo + eo;
+      float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
+      if (n >= 4) {
+        local_mix_lane<BASE, BF16, FIRST, true, true, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq,
+                                                             len, sp, ap, lane_element(n, t64));
+      } else {
+        local_mix_lane<BASE, BF16, FIRST, true, true, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq,
+                                                            len, sp, ap, t64);
+      }
     }
   }
   Pacer::leave(pace, gridDim.x);
@@ -1659,7 +1694,7 @@ hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
                      dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
                      x.len, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members,
-                     p.spins, x.m, p.counters, sp, ap);
+                     p.spins, x.m, p.rest, p.nrest, p.counters, sp, ap);
   return hipGetLastError();
 }
 
