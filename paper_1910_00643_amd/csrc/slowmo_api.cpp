@@ -495,7 +495,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const int64_t touched = touched_state + elements * grad_bytes;
   const bool past_l2 = touched > int64_t{54} << 20;
   const int64_t outer_bytes = 8 * ctx->layout.d * (cfg->no_average ? m : 1);
-  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes, outer_bytes);
+  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes, outer_bytes, cfg->tau);
   if (kept_mb >= 0) caches.kept_bytes = kept_mb * 1e6;
   ctx->tune.local_nt = ctx->tune.nontemporal && (local_nt < 0 ? caches.streaming : local_nt != 0);
   ctx->tune.outer_nt = ctx->tune.nontemporal && (outer_nt < 0 ? caches.outer_streaming : outer_nt != 0);

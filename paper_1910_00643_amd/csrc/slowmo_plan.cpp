@@ -22,21 +22,27 @@ Layout make_layout(int32_t n_tensors, const int64_t *numel) {
 // accesses everywhere and all sweeps in one direction; 1, 8 and 32 workers in 1 and 20 tensors each, SGD and Adam, fp32
 // and bf16 gradients, 0.1 to 800 M elements.
 CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
-                     int64_t outer_bytes) {
+                     int64_t outer_bytes, int32_t tau) {
   constexpr int64_t MiB = int64_t{1} << 20;
   const int64_t all = state_bytes + grad_bytes;
   CacheRule r{true, true, false, 0.0};
   // Plain accesses, gradients included, as long as all of it fits the last-level cache:
-  // 21-28 MB 0.76-1.07, 30-60 MB 0.73-0.90, 60-250 MB 0.72-0.83, 256-266 MB 0.80-0.92.
-  // Below, in the L2s, streaming is as good or better (18 MB: plain 0.84-1.02, streaming
-  // 0.81-0.91).
-  r.streaming = !(all > 20 * MiB && all <= 240 * MiB);
+  // 30-60 MB 0.73-0.90, 60-250 MB 0.72-0.83, 256-266 MB 0.80-0.92.  Below, in the L2s,
+  // streaming is as good or better (18 MB: plain 0.84-1.02, streaming 0.81-0.91), or plain
+  // accesses gain only while nothing else runs (24 MB 0.76-1.07; three optimizers in turn,
+  // rounds of 2 steps 0.84-1.41).  A round of one step finds nothing in the cache but what
+  // the last round left there: three optimizers in turn, tau = 1, 40 MB 0.85-1.10, 70 MB
+  // 0.82-1.01, 120 MB 0.96-1.13, 200 MB 0.97-1.17; tau = 2 0.79-1.00 from 40 MB on.
+  const int64_t fits = (tau > 1 ? 240 : 72) * MiB;
+  r.streaming = !(all > 32 * MiB && all <= fits);
   // The outer step and the fused last step, plain with x0 and u in the cache as well; time
   // of rounds of 4 steps over that with only the local step plain, 1, 4 and 16 workers: 24 MB
   // 0.82-1.09 (worst under "reset"), 40-230 MB with x0 and u 0.77-0.99; 255-290 MB
   // 0.95-1.10, 330-400 MB 1.00-1.09.  The gossip kernels, rounds by the line of the local
   // step: 24 MB 0.88-0.99, 40-120 MB 0.87-0.95, 200-245 MB 0.82-0.95.
-  r.outer_streaming = !(all > 28 * MiB && all + outer_bytes <= 240 * MiB);
+  // Three optimizers in turn, tau = 1, fused step under "reset": 35 MB 1.00-1.13, 45 MB
+  // 1.00-1.04, 60 MB 0.94-1.00.
+  r.outer_streaming = !(all > (tau > 1 ? 32 : 48) * MiB && all + outer_bytes <= fits);
   // Written through: where the L2s cannot hold much of it for the next call anyway, the
   // memory takes stores better when they come at once.  With against without, plain
   // accesses: 30-50 MB 1.00-1.25; fp32 gradients 56-64 MB 0.96-1.02, 72-230 MB 0.92-0.98;
@@ -51,7 +57,8 @@ CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
   // accesses on such lists: 0.84-0.96 up to 500 MB, 1.03-1.10 from 2 GB on.  All of this
   // where steps follow each other; where something else has passed through the cache in
   // between, a call with kept tiles takes as long as one without.
-  if (r.streaming && r.write_through) {
+  // With tau = 1 nothing is kept: three optimizers in turn 0.96-1.08 (tau = 2 0.89-0.98).
+  if (r.streaming && r.write_through && tau > 1) {
     r.kept_bytes = std::min(224e6, 0.6 * static_cast<double>(state_bytes));
   }
   return r;

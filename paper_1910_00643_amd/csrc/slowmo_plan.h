@@ -93,9 +93,10 @@ struct CacheRule {
   double kept_bytes;   // of the replicas and buffers: kept in the last-level cache
 };
 // For a step that touches state_bytes of replicas and buffers and grad_bytes of
-// gradients (grad_size bytes per element); x0 and u are outer_bytes.
+// gradients (grad_size bytes per element); x0 and u are outer_bytes, tau steps follow each
+// other in an outer iteration.
 CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
-                     int64_t outer_bytes);
+                     int64_t outer_bytes, int32_t tau);
 // Kept units: 16 384 elements of every worker.  Units are numbered along the tensors; the
 // multiples of the golden ratio spread the kept ones evenly over any stretch of them, and
 // so over the XCDs and the sets of the cache.

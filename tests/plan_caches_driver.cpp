@@ -16,16 +16,20 @@ static void check(bool ok, const char *what, double at) {
 
 int main() {
   const int64_t MiB = int64_t{1} << 20;
-  for (int64_t size : {int64_t{1}, 20 * MiB, 20 * MiB + 3, 54 * MiB, 240 * MiB, 240 * MiB + 3, int64_t{1} << 40}) {
+  for (int64_t size : {int64_t{1}, 32 * MiB, 32 * MiB + 3, 54 * MiB, 72 * MiB, 72 * MiB + 3, 240 * MiB,
+                       240 * MiB + 3, int64_t{1} << 40}) {
     for (int64_t grad : {2, 4}) {
-      const int64_t g = size / (8 + grad) * grad, s = size - g;
-      const CacheRule r = cache_rule(s, g, grad, size / 4);
-      check(r.streaming == !(size > 20 * MiB && size <= 240 * MiB), "plain in the caches only", size);
-      check(r.outer_streaming || !r.streaming, "the outer step plain only where the local step is", size);
-      check(r.outer_streaming || size + size / 4 <= 240 * MiB, "x0 and u fit too", size);
-      check((r.kept_bytes > 0) == (r.streaming && r.write_through), "kept on long lists", size);
-      check(r.kept_bytes <= 0.6 * s && r.kept_bytes <= 224e6, "no more kept than fits", size);
-      check(r.write_through == (size > (grad == 2 ? 80 : 54) * MiB), "written through", size);
+      for (int32_t tau : {1, 2, 48}) {
+        const int64_t g = size / (8 + grad) * grad, s = size - g, fits = (tau > 1 ? 240 : 72) * MiB;
+        const CacheRule r = cache_rule(s, g, grad, size / 4, tau);
+        check(r.streaming == !(size > 32 * MiB && size <= fits), "plain in the caches only", size);
+        check(r.outer_streaming || !r.streaming, "the outer step plain only where the local step is", size);
+        check(r.outer_streaming == !(size > (tau > 1 ? 32 : 48) * MiB && size + size / 4 <= fits),
+              "the outer step plain where x0 and u fit too", size);
+        check((r.kept_bytes > 0) == (r.streaming && r.write_through && tau > 1), "kept on long lists", size);
+        check(r.kept_bytes <= 0.6 * s && r.kept_bytes <= 224e6, "no more kept than fits", size);
+        check(r.write_through == (size > (grad == 2 ? 80 : 54) * MiB), "written through", size);
+      }
     }
   }
   // the kept share of any stretch of units is near the share asked for
