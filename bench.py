@@ -363,8 +363,7 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
              "outer": "k_outer_noavg" if not w.exact_average else
                       "k_outer_big + k_outer_step (whole big tiles + rest)"
                       if big_elements(w, False) else "k_outer_step",
-             "fused_last_outer": "k_local_outer_big + k_local_outer_step (whole 65 536-element "
-                                 "pieces + rest)" if big_elements(w, True) else "k_local_outer_step",
+             "fused_last_outer": "k_local_outer_big + k_local_outer_step (whole big tiles + rest)" if big_elements(w, True) else "k_local_outer_step",
              "debias": "k_debias"}
     kernels = {}
     for kind, ms in kern_ms.items():

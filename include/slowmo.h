@@ -52,11 +52,11 @@
  *    kernel per connected group of workers; slowmo_local_mix_step launches
  *    the local step and the mixing step one after the other when a replica
  *    pointer is not 16-byte aligned, and from 8 workers on, for long tensor
- *    lists, one kernel for whole 16 384-element pieces and one, or one per
- *    connected group, for the rest;
+ *    lists, one kernel for whole 16 384-element pieces and, where the rest does
+ *    not ride with it, one, or one per connected group, for the rest;
  *    slowmo_outer_step and slowmo_local_outer_step launch one kernel for the
- *    whole 65 536-element pieces of the tensors and one for the rest when the
- *    tensor list has at least 160 such pieces -- the former from 16 workers
+ *    whole pieces of 65 536, 57 344 or 49 152 elements of the tensors and one for
+ *    the rest when the tensor list has at least 160 such pieces -- the former from 16 workers
  *    on, the latter from 8 on under SLOWMO_BUF_RESET;
  *    slowmo_import_state copies up to four arrays).  If the HIP
  *    runtime refuses one of them after an earlier one was issued, device

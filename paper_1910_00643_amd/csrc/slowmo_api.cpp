@@ -512,10 +512,9 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // 3.440 with 20, 3.446 with 17 wavefronts; tensors packed back to back 2.82 ->
   // 2.65 ms; Adam with bf16 gradients 0.669 -> 0.643 ms; outer step without the
   // average 4 % faster.  The de-biasing kernel (one read, one write) needs all 32:
-  // 30 % slower with the cap.  Where the working set stays in the L2s
-  // there are no pages to spare: 3 to 4.5 M elements, time
-  // over that before any cap, with it / without: steps 0.95-1.02 / 0.92-1.00, the last
-  // one under "reset" 1.02-1.09 / 0.96-1.03.
+  // 30 % slower with the cap.  Where the working set stays in the L2s there are no pages to
+  // spare: 3 to 4.5 M elements, time over that before any cap, with it / without: steps
+  // 0.95-1.02 / 0.92-1.00, the last one under "reset" 1.02-1.09 / 0.96-1.03.
   // SGD with kept tiles: part of its requests never reach the memory, and up to 4 GB it
   // takes 28 (300-500 MB 0.96-0.97 of the time with 20, 1 GB 0.97-1.00, 2 GB 0.98-1.00, 5 GB
   // 1.00; Adam 0.99-1.02).

@@ -97,12 +97,12 @@ struct LaunchTuning {
                         // the kernel allows
   int32_t big_tiles;    // 1: whole big tiles of aligned tensors go to the big-tile kernels
   int32_t big_vpt;      // vectors per lane of a big tile: 16, 14 or 12
-  int32_t local_nt;     // the same for the local step, the gossip kernels in single waves and the
+  int32_t local_nt;     // 1: streaming accesses in the local step, the gossip kernels in single waves and the
                         // loads of the de-biasing (0: their working set stays in the caches)
   int32_t outer_nt;     // the same for the outer step and the fused last step in single waves
   int32_t kept_local;   // 1: some of the local-step tiles are kept (kTileKept)
   int32_t kept_tiles;   // 1: some of the outer-step tiles are kept
-  int32_t write_through;  // 1: the local step writes through the L2 (nt sc1 stores)
+  int32_t write_through;  // 1: the local step writes through the L2 (sc1 stores)
   int32_t noavg_through;  // the same for the outer step without the average
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step: caps the
                         // wavefronts per CU

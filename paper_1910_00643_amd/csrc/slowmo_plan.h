@@ -28,8 +28,8 @@ constexpr int32_t kOuterBlock = 64;
 constexpr int32_t kOuterTile = 4 * kOuterBlock;
 
 // Big tiles of the outer step and of the fused last step: one 1024-thread
-// workgroup takes kBigVpt vectors per lane, i.e. 256 KiB of every stream it
-// walks (its 16 waves start together and move from replica to replica
+// workgroup takes kBigVpt vectors per lane (or a few less), i.e. 256 KiB of every stream
+// it walks (its 16 waves start together and move from replica to replica
 // together).  Measured in one process on the same replicas against the
 // single-wave tiles: the fused last step is 10-14 % faster at m = 32, 6-7 % at
 // m = 16, 3-5 % at m = 8 and no faster at m = 4; the plain outer step 8 % faster
@@ -37,11 +37,9 @@ constexpr int32_t kOuterTile = 4 * kOuterBlock;
 // and workgroup) gain half of that or nothing.  Under "maintain" the fused
 // kernel stores every worker's buffers inside the walk and is 2-10 % slower in
 // this shape than in single waves, so it takes big tiles only under "reset".
-// Used for the whole kBigTile pieces of aligned tensors from these worker
-// counts on:
+// Used for the whole pieces of aligned tensors from these worker counts on:
 constexpr int32_t kBigBlock = 1024;
 constexpr int32_t kBigVpt = 16;
-constexpr int32_t kBigTile = 4 * kBigBlock * kBigVpt;
 // Tiles of 14 or 12 vectors per lane instead of 16, where they fill the chip's rounds
 // better (choose_big_vpt).
 constexpr int32_t kBigVptMin = 12;

@@ -125,7 +125,7 @@ def algorithmic_bytes(kernel, w, rounds, dispatches):
         calls = rounds * w.tau
         return 4 * md * calls, 4 * md * calls, calls
     # the outer step and the fused last step run as two kernels when big tiles
-    # are in use: the whole 65 536-element pieces, and the rest
+    # are in use: the whole big tiles, and the rest
     if name in ("k_local_outer_step", "k_local_outer_big"):
         first = a[2] == "true"
         r = w.m * (4 + (0 if first else 4 * nbuf) + g) + 8
