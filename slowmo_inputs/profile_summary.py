@@ -67,7 +67,9 @@ def _merge_gossip(values):
     """The fused gossip step runs as paced tiles plus the ordinary kernel for the rest of the
     list (and for maps of small groups): both under the paced kernel's name."""
     for k in [k for k in values if k.startswith("k_local_mix_paced")]:
-        values[k] += values.pop("k_local_mix_step" + k[len("k_local_mix_paced"):-1] + ", true>", [])
+        rest = "k_local_mix_step" + k[len("k_local_mix_paced"):-1] + ","
+        for r in [r for r in values if r.startswith(rest)]:
+            values[k] += values.pop(r)
     return values
 
 
