@@ -678,7 +678,10 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // to the kernels that walk all workers only a tile that is kept of each of them is one
   const uint64_t walk_share = big_in_use ? 0 : share_of(0);
   ctx->tune.kept_local = caches.kept_bytes > 0;
-  ctx->tune.kept_tiles = walk_share > 0;
+  const bool asked_to_keep = kept_mb >= 0;  // by SLOWMO_KEPT: in every kernel
+  ctx->tune.kept_tiles = walk_share == 0 ? 0 : asked_to_keep ? 2 : 1;
+  ctx->tune.kept_outer = walk_share > 0 && (asked_to_keep ||
+                                            outer_keeps(m, touched, cfg->policy == SLOWMO_BUF_AVERAGE));
   // tiles in launch order: worker-major, tensors in list order, pieces ascending
   static_assert(kLocalTile == kOuterTile, "a worker's local tiles are the outer tiles");
   const auto fill = [&](TileRef *out, int32_t first_owner, uint64_t share) {

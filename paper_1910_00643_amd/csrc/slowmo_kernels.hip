@@ -959,7 +959,10 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
   }
 }
 
-template <bool NT, bool KEPT>
+// Kept tiles go like the others.  Read and written as such they cost this kernel, which moves
+// nothing but replicas, 1.05-1.29 times its time up to 1 GB (rounds of 4 local and 4 gossip steps,
+// 2 to 32 workers, 1.00-1.10; 2 GB 0.99-1.02) and gain nothing beyond (5 to 20 GB 0.99-1.00).
+template <bool NT>
 __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
     float *const *__restrict__ xtab_t, const MixEntry *__restrict__ seq, int len, int ntiles,
@@ -974,12 +977,7 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
   if (n >= 4) {
-    if (NT && KEPT && is_kept(t)) {
-      own_path(xp);
-      mix_lane<false, false>(xp, seq, len, eo, lane_element(n));
-    } else {
-      mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
-    }
+    mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
   } else {
     mix_lane<NT, true>(xp, seq, len, eo, static_cast<int>(threadIdx.x));
   }
@@ -1475,7 +1473,7 @@ hipError_t launch_outer_t(const OuterArgs &a, const LaunchTuning &t, hipStream_t
   };
   if (!t.outer_nt) {
     launch(k_outer_step<false, AVG, false>);
-  } else if (t.kept_tiles) {
+  } else if (t.kept_outer) {
     launch(k_outer_step<true, AVG, true>);
   } else {
     launch(k_outer_step<true, AVG, false>);
@@ -1573,7 +1571,7 @@ hipError_t launch_fused_t(const LocalArgs &l, const OuterArgs &o, int n_tensors,
   };
   if (!t.outer_nt) {
     launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, false, false>);
-  } else if (t.kept_tiles) {
+  } else if (t.kept_tiles > 1 || (t.kept_tiles && last_keeps(o.ntiles, POLICY == 1))) {
     launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, true, true>);
   } else {
     launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, true, false>);
@@ -1635,12 +1633,10 @@ hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t 
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles, a.tensors, a.xtab_t,
                        a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
   };
-  if (!t.local_nt) {
-    launch(k_mix_step<false, false>);
-  } else if (t.kept_tiles) {
-    launch(k_mix_step<true, true>);
+  if (t.local_nt) {
+    launch(k_mix_step<true>);
   } else {
-    launch(k_mix_step<true, false>);
+    launch(k_mix_step<false>);
   }
   return hipGetLastError();
 }
@@ -1660,7 +1656,7 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   };
   if (!t.local_nt) {
     launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
-  } else if (t.kept_tiles) {
+  } else if (t.kept_tiles > 1 || (t.kept_tiles && mix_keeps(x.ntiles, BASE == 1))) {
     launch(k_local_mix_step<BASE, BF16, FIRST, true, true>);
   } else {
     launch(k_local_mix_step<BASE, BF16, FIRST, true, false>);

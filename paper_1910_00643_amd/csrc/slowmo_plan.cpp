@@ -69,6 +69,30 @@ uint64_t kept_share(double kept_bytes, double state_bytes) {
   return static_cast<uint64_t>(std::min(kept_bytes / state_bytes, 1.0) * 4294967296.0);
 }
 
+// The instances for kept tiles have both walks in them and up to 46 registers more: 4 or 5 waves
+// per SIMD, 4096 to 5120 on the chip.  Without them a shorter list is on its way at once, and a
+// tile that is back early makes room for no other.  Rounds of 4 steps, 16 to 64 workers, kept
+// tiles read as such over streamed (the local step keeps them in both).  Gossip step, SGD / Adam:
+// 1500 tiles 1.32 / 1.25-1.30, 2500 1.14 / 1.01-1.08, 3000 1.05-1.10 / 0.97-1.01, 3500 0.99-1.04 /
+// 0.91-0.98, 4500 0.92-0.95 / 0.86-0.95, 8000 0.88-0.95 / 0.87-0.97; in groups of 2 to 8 workers
+// 2500 0.98-1.13 / 0.97-1.08, 3500 1.02-1.07 / 0.98-1.04, 4500 0.98-1.04 / 0.96-1.05, 6000
+// 0.94-1.02 / 0.95-1.04 (above 1.02 with 64 workers only).  Fused last step: "maintain" 0.95-1.01 on
+// 1500 to 4000 tiles, 0.95-0.98 beyond; "reset" 1.00-1.05, averaged buffers 1.01-1.07, from 4500 on
+// 0.98-1.01 and 0.97-1.02.  A small share is no reason against them: at 5 and 12 GB, where 6 and 3
+// % are kept, the fused last step takes 0.94-0.98 and 0.97-0.99 of its time, the gossip step
+// 0.95-0.96 and 0.97-0.99: kept lines that are streamed over are not there for the next call.
+bool last_keeps(int64_t tiles, bool maintains) { return maintains || tiles >= 4096; }
+bool mix_keeps(int64_t tiles, bool adam) { return tiles >= (adam ? 3000 : 4096); }
+
+// The plain outer step moves only the replicas, of which a third to a half of the kept part is, and
+// has 56 registers instead of 40 then.  Its time with kept tiles over streamed, 2 to 8 workers:
+// 270-500 MB 0.96-1.12, 600 MB 0.94-1.08, 800 MB 0.94-1.02, 1 GB 0.91-0.94, 5 GB 0.97; one worker
+// 0.91-1.00 at all of them, 16 and 32 workers 0.97-1.03 at 270 MB, 0.87-0.97 beyond.  With averaged
+// buffers 0.84-1.00 from 260 MB to 20 GB.
+bool outer_keeps(int32_t m, int64_t touched_bytes, bool averages) {
+  return averages || m == 1 || m >= 16 || touched_bytes > int64_t{700} << 20;
+}
+
 // To the nearest number that is not much more than the cache holds: 306 MB still are good
 // (Adam, m = 8, 25.6 M elements: 866 -> 789 us, units of every worker 804).
 int32_t kept_workers(int32_t m, double kept_bytes, double worker_bytes) {

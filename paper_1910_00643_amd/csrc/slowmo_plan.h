@@ -104,6 +104,14 @@ inline bool unit_kept(int64_t unit, uint64_t share) {
 }
 // The share of the units, times 2^32, that is kept_bytes of state_bytes.
 uint64_t kept_share(double kept_bytes, double state_bytes);
+// Whether a launch over `tiles` tiles, some of them kept, reads those through plain accesses
+// (in an instance of its own): the fused last step (its buffers are maintained), and the gossip
+// step fused with the local step.
+bool last_keeps(int64_t tiles, bool maintains);
+bool mix_keeps(int64_t tiles, bool adam);
+// The same for the outer step: m workers, touched_bytes as a local step touches them; the
+// buffers are averaged along with the replicas.
+bool outer_keeps(int32_t m, int64_t touched_bytes, bool averages);
 // Where the local step keeps whole workers instead: how many of m are about kept_bytes,
 // worker_bytes of replica and buffers each (0: not even the first one is).
 int32_t kept_workers(int32_t m, double kept_bytes, double worker_bytes);

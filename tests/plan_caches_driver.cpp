@@ -46,6 +46,17 @@ int main() {
   check(kept_workers(8, 224e6, 94e6) == 2 && kept_workers(32, 224e6, 204e6) == 1, "whole workers", 0);
   check(kept_workers(8, 224e6, 306e6) == 1 && kept_workers(8, 224e6, 2.5e9) == 0, "large workers", 0);
   check(kept_workers(2, 1e12, 1e6) == 2 && kept_workers(4, 0, 1e6) == 0, "limits", 0);
+  // instances for kept tiles: none on lists that are on their way at once, whatever the share
+  for (bool other : {false, true}) {
+    check(last_keeps(4095, other) == other && last_keeps(4096, other), "fused last step", other);
+    check(!mix_keeps(2999, other) && mix_keeps(3000, other) == other && mix_keeps(4096, other), "gossip", other);
+    check(last_keeps(int64_t{1} << 31, other) && mix_keeps(int64_t{1} << 31, other), "small shares", other);
+  }
+  for (int32_t m : {1, 2, 8, 15, 16, 32}) {
+    check(outer_keeps(m, 250 * MiB, true) && outer_keeps(m, 20000 * MiB, true), "averaged buffers", m);
+    check(outer_keeps(m, 500 * MiB, false) == (m == 1 || m >= 16) && outer_keeps(m, 701 * MiB, false),
+          "plain outer step", m);
+  }
   // big tiles: none below 160, never more than the workspace has room for
   for (int64_t n = 0; n < 4000; n += 37) {
     const std::vector<int64_t> list = {n * 20000 + 11, 65536 * (n % 90), 5};
