@@ -264,8 +264,7 @@ struct slowmo_ctx {
   TileRef *d_prtiles = nullptr;
   int32_t n_prtiles = 0;
   bool prtiles_by_group = false;  // the left-over tiles run once per connected group
-  bool big_outer = false;  // the plain outer step uses them too (it gains only with many workers)
-  bool big_forced = false; // SLOWMO_BIG_TILES=1: wherever the kernels allow
+  bool last_big = false, outer_big = false;  // the fused last step, the outer step take big tiles
 
   TableRing<kGradSlots> gtab;  // gradient-pointer tables of recent calls (m * n_tensors each)
   TableRing<kSlots> mixtab;  // update order of the current mixing step (at most m entries)
@@ -542,8 +541,6 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const int32_t big = env_flag("SLOWMO_BIG_TILES", -1);
   ctx->tune.big_tiles =
       ((big < 0 ? m >= kBigFusedFromWorkers : big != 0) && ctx->tune.nontemporal) ? 1 : 0;
-  ctx->big_outer = ctx->tune.big_tiles && (big > 0 || m >= kBigOuterFromWorkers);
-  ctx->big_forced = big > 0;
   ctx->tune.paced = paced_mode();
   // a list that the L2s hold in any order has nothing to turn for (18 MB 0.84-0.98 of the
   // time, 9-15 MB 0.98-1.04)
@@ -661,10 +658,16 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // Kept tiles: a share of the units of every worker.  But big tiles run best while the
   // whole chip is on one worker, and lose that when some of them come from the cache and
   // others do not: the fused last step takes 2.49-2.61 instead of 2.20 ms then (m = 32, 25.6
-  // M elements), 322 instead of 275 us (m = 8, 11.7 M).  Where big tiles are in use, the local
-  // step keeps whole workers, or, if one is too large, units of the first.
-  const bool big_in_use = !bt.empty() && !cfg->no_average &&
-                          (cfg->policy == SLOWMO_BUF_RESET || ctx->big_outer);
+  // M elements), 322 instead of 275 us (m = 8, 11.7 M).  Where an outer step or a fused last step
+  // takes big tiles, the local step keeps whole workers, or, if one is too large, units of the
+  // first.  (Where none does, units for all: rounds with averaged buffers, m = 16, 2-3 GB 0.95-0.99 of
+  // the time with whole workers, m = 16 and 32, 6-12 GB 0.97-1.00.)
+  static_assert(SLOWMO_BUF_RESET == 0 && SLOWMO_BUF_MAINTAIN == 1 && SLOWMO_BUF_AVERAGE == 2,
+                "the policies as the kernels and the rules name them");
+  const bool any_big = !bt.empty() && !cfg->no_average;
+  ctx->last_big = any_big && ctx->tune.fuse_last && last_takes_big(cfg->policy, big > 0);
+  ctx->outer_big = any_big && outer_takes_big(m, cfg->policy, big > 0);
+  const bool big_in_use = ctx->last_big || ctx->outer_big;
   const double worker_bytes = static_cast<double>(touched_state) / m;
   const int32_t whole = kept_workers(m, caches.kept_bytes, worker_bytes);
   const auto share_of = [&](int32_t w) {
@@ -675,12 +678,17 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const auto flag_at = [&](int32_t j, int64_t element, uint64_t share) {
     return unit_kept(L.arena_off[j] / kKeptUnit + element / kKeptUnit, share) ? kTileKept : 0;
   };
-  // to the kernels that walk all workers only a tile that is kept of each of them is one
-  const uint64_t walk_share = big_in_use ? 0 : share_of(0);
+  // To the kernels that walk all workers only a tile that is kept of each of them is one: the
+  // outer step and the fused last step take units as such where the local step keeps them.  The
+  // gossip step fused with the local step follows others of its kind and keeps units in any
+  // case (rounds of 4 of them and an outer step, against streaming where big tiles are in use: m = 8
+  // and 12, 0.8-2 GB 0.86-0.96, 4 GB 0.95-0.98, 12 GB 0.98-1.00; m = 16 and 32 0.94-1.01).
+  const uint64_t walk_share = kept_share(caches.kept_bytes, static_cast<double>(touched_state));
   ctx->tune.kept_local = caches.kept_bytes > 0;
   const bool asked_to_keep = kept_mb >= 0;  // by SLOWMO_KEPT: in every kernel
-  ctx->tune.kept_tiles = walk_share == 0 ? 0 : asked_to_keep ? 2 : 1;
-  ctx->tune.kept_outer = walk_share > 0 && (asked_to_keep ||
+  ctx->tune.kept_mix = walk_share == 0 ? 0 : asked_to_keep ? 2 : 1;
+  ctx->tune.kept_tiles = big_in_use ? 0 : ctx->tune.kept_mix;
+  ctx->tune.kept_outer = ctx->tune.kept_tiles && (asked_to_keep ||
                                             outer_keeps(m, touched, cfg->policy == SLOWMO_BUF_AVERAGE));
   // tiles in launch order: worker-major, tensors in list order, pieces ascending
   static_assert(kLocalTile == kOuterTile, "a worker's local tiles are the outer tiles");
@@ -948,10 +956,8 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
     a.ntiles = n;
     return a;
   };
-  // the big-tile kernel has no buffer average
-  const bool use_big = ctx->n_btiles > 0 && ctx->big_outer && !a.avg_h;
   return run_tiled(
-      ctx, use_big, launched, "outer-step kernel launch",
+      ctx, ctx->outer_big, launched, "outer-step kernel launch",
       [&](const TileRef *t, int32_t n) { return launch_outer_big(with(t, n), ctx->tune, stream); },
       [&](const TileRef *t, int32_t n) { return launch_outer_step(with(t, n), ctx->tune, stream); });
 }
@@ -1006,15 +1012,8 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
       return o;
     };
     int launched = 0;
-    // big tiles pay when the buffers of this step are dropped ("reset"); stores of
-    // every worker's buffers inside the walk cost them their gain (measured: 2-10 %
-    // slower than single-wave tiles under "maintain"), and the buffer average does
-    // not fit their registers
-    const bool use_big =
-        ctx->n_btiles > 0 && (c.policy == SLOWMO_BUF_RESET ||
-                              (ctx->big_forced && c.policy == SLOWMO_BUF_MAINTAIN));
     st = run_tiled(
-        ctx, use_big, &launched, "fused local+outer kernel launch",
+        ctx, ctx->last_big, &launched, "fused local+outer kernel launch",
         [&](const TileRef *t, int32_t n) {
           return launch_local_outer_big(a, with(t, n), ctx->n_tensors, c.base, bf16,
                                         ctx->buffers_zero, c.policy, ctx->tune, stream);

@@ -101,8 +101,9 @@ struct LaunchTuning {
                         // loads of the de-biasing (0: their working set stays in the caches)
   int32_t outer_nt;     // the same for the outer step and the fused last step in single waves
   int32_t kept_local;   // 1: some of the local-step tiles are kept (kTileKept)
-  int32_t kept_tiles;   // 1: some of the outer-step tiles are kept; the kernels that walk all workers
-                        // read them as such where last_keeps, mix_keeps say so (2: on every list)
+  int32_t kept_tiles;   // 1: the fused last step reads kept outer-step tiles as such where
+                        // last_keeps says so (2: on every list)
+  int32_t kept_mix;     // the same for the gossip step fused with the local step (mix_keeps)
   int32_t kept_outer;   // 1: the outer step reads them as such
   int32_t write_through;  // 1: the local step writes through the L2 (sc1 stores)
   int32_t noavg_through;  // the same for the outer step without the average

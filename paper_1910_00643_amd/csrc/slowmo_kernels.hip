@@ -1656,7 +1656,7 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   };
   if (!t.local_nt) {
     launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
-  } else if (t.kept_tiles > 1 || (t.kept_tiles && mix_keeps(x.ntiles, BASE == 1))) {
+  } else if (t.kept_mix > 1 || (t.kept_mix && mix_keeps(x.ntiles, BASE == 1))) {
     launch(k_local_mix_step<BASE, BF16, FIRST, true, true>);
   } else {
     launch(k_local_mix_step<BASE, BF16, FIRST, true, false>);

@@ -124,6 +124,14 @@ int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel) {
   return count_pieces(n_tensors, numel, big_tile(kBigVptMin));
 }
 
+// Big tiles pay in the fused last step when its buffers are dropped ("reset"); stores of every
+// worker's buffers inside the walk cost them their gain (2-10 % slower than single-wave tiles
+// under "maintain").  Averages of the buffers are in neither kernel: they do not fit the registers.
+bool last_takes_big(int policy, bool asked) { return policy == 0 || (asked && policy == 1); }
+bool outer_takes_big(int32_t m, int policy, bool asked) {
+  return policy != 2 && (asked || m >= kBigOuterFromWorkers);
+}
+
 // A big tile keeps one CU busy, and all of them take about the same time, so a launch runs
 // in rounds of one tile per CU.  A last round that fills a part f of the CUs is bound by what
 // their loads can have in flight: it takes 0.46 of a whole one at f = 0.11-0.14, 0.59 at

@@ -208,6 +208,11 @@ int64_t count_big_tiles(int32_t n_tensors, const int64_t *numel);
 // Vectors per lane of the big tiles for a list (numel: its tensors, those that cannot take
 // big tiles as 0) on a chip with `cus` CUs; 0: not enough of them.
 int32_t choose_big_vpt(int32_t n_tensors, const int64_t *numel, int32_t cus);
+// Which calls take the big tiles of a list that has some (policy: 0 reset, 1 maintain, 2
+// average; asked: SLOWMO_BIG_TILES=1, wherever the kernels allow): the fused last step, and the
+// outer step by itself.
+bool last_takes_big(int policy, bool asked);
+bool outer_takes_big(int32_t m, int policy, bool asked);
 int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
 // Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
 // worker count is too small (with `forced`, only when no tensor has such a piece).

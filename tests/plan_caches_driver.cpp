@@ -57,6 +57,15 @@ int main() {
     check(outer_keeps(m, 500 * MiB, false) == (m == 1 || m >= 16) && outer_keeps(m, 701 * MiB, false),
           "plain outer step", m);
   }
+  // calls that take big tiles: never with averaged buffers, however many workers there are
+  for (bool asked : {false, true}) {
+    for (int32_t m : {8, 15, 16, 32}) {
+      check(!outer_takes_big(m, 2, asked) && !last_takes_big(2, asked), "averaged buffers", m);
+      check(outer_takes_big(m, 0, asked) == (asked || m >= 16), "outer step", m);
+      check(outer_takes_big(m, 1, asked) == (asked || m >= 16), "outer step", m);
+    }
+    check(last_takes_big(0, asked) && last_takes_big(1, asked) == asked, "fused last step", asked);
+  }
   // big tiles: none below 160, never more than the workspace has room for
   for (int64_t n = 0; n < 4000; n += 37) {
     const std::vector<int64_t> list = {n * 20000 + 11, 65536 * (n % 90), 5};
