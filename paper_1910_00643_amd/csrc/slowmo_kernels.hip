@@ -780,7 +780,8 @@ __global__ __launch_bounds__(kBigBlock) void k_outer_big(
 
 // POLICY 0 (reset: the buffers of this step are not stored) or 1 (maintain).
 // A worker's step runs over SUB vectors at a time: their operands are loaded,
-// stepped, added to the sum and dropped before the next SUB are loaded.
+// stepped, added to the sum and dropped before the next SUB are loaded.  No instance that the
+// rules choose uses scratch memory.
 template <int BASE, bool BF16, bool FIRST, int POLICY, int VPT>
 __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
     const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
@@ -806,7 +807,14 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
   float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
   constexpr int gsize = BF16 ? 2 : 4;
-  constexpr int SUB = 2;
+  // With two narrow streams and registers to spare the compiler would issue most loads of a worker
+  // first, take all 128 registers and spill up to 32 bytes per lane: it stays within SUB then.  Fused
+  // last step at tau = 1, bf16 gradients: 12 vectors (8.2 and 20 M elements) SGD m = 8 144 -> 139
+  // and 358 -> 347 us, m = 32 489 -> 477 and 1182 -> 1148, Adam m = 32 543 -> 517 and 1233 -> 1182
+  // (3 vectors at a time; 2 are 4-9 % slower); 14 vectors (25.6 M) SGD m = 8 453 -> 428, m = 32
+  // 1492 -> 1443, Adam m = 32 1528 -> 1486.
+  constexpr bool APART = FIRST && BF16 && VPT < kBigVpt;
+  constexpr int SUB = APART && VPT % 3 == 0 ? 3 : 2;
   const int lane = 4 * static_cast<int>(threadIdx.x);
   V4 acc[VPT];
   for (int i = 0; i < m; ++i) {
@@ -818,6 +826,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
 #pragma unroll
     for (int s0 = 0; s0 < VPT; s0 += SUB) {
       V4 xv[SUB], hv[SUB], vv[SUB], gv[SUB];
+      if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int v = 0; v < SUB; ++v) {
         const int off = (s0 + v) * kBigStride;
@@ -826,6 +835,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
         if constexpr (!FIRST && BASE == 1) vv[v] = ld4<true>(vi + off + lane);
         gv[v] = ldgv<BF16, false, true>(gi + static_cast<int64_t>(off) * gsize, lane);
       }
+      if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int v = 0; v < SUB; ++v) {
         step4<BASE, FIRST>(xv[v], hv[v], vv[v], gv[v], sp, ap);
