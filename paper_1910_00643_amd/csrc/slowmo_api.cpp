@@ -319,8 +319,8 @@ hipError_t guarded(slowmo_ctx *ctx, F &&launch) {
 }
 
 // The launches of one sweep over the tiles are out: the next sweep goes the other way.
-void swept(slowmo_ctx *ctx) {
-  if (ctx->turning) ctx->tune.backward ^= 1;
+void swept(slowmo_ctx *ctx, bool paced = false) {
+  if (ctx->turning) ctx->tune.backward = next_sweep(ctx->tune.backward, paced);
 }
 
 // Failure after at least one kernel of a multi-kernel call was launched.
@@ -1174,7 +1174,7 @@ slowmo_status run_mix(slowmo_ctx *ctx, const StagedMix &sm, int launched, hipStr
                       : fail_hip(ctx, e, "mixing kernel launch");
     ++launched;
   }
-  swept(ctx);
+  if (!sm.ranges.empty()) swept(ctx);
   return SLOWMO_OK;
 }
 
@@ -1281,7 +1281,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
                         : fail_hip(ctx, e, "fused local+mixing kernel launch");
       ++launched;
     }
-    swept(ctx);
+    swept(ctx, sm.paced);
   }
   // counters and weights move only after the last launch was accepted
   finish_local(ctx);

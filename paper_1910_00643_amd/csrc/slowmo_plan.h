@@ -95,6 +95,9 @@ struct CacheRule {
 // other in an outer iteration.
 CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
                      int64_t outer_bytes, int32_t tau);
+// Direction of the next sweep over the tiles (1: backward) after one that went `backward`: the
+// other one.  A paced walk goes forward in any case.
+inline int32_t next_sweep(int32_t backward, bool paced) { return paced ? 1 : backward ^ 1; }
 // Kept units: 16 384 elements of every worker.  Units are numbered along the tensors; the
 // multiples of the golden ratio spread the kept ones evenly over any stretch of them, and
 // so over the XCDs and the sets of the cache.

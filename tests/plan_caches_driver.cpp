@@ -66,6 +66,8 @@ int main() {
     }
     check(last_takes_big(0, asked) && last_takes_big(1, asked) == asked, "fused last step", asked);
   }
+  // sweeps: the other way than the one before, and backward after a paced walk
+  for (int32_t was : {0, 1}) check(next_sweep(was, false) == 1 - was && next_sweep(was, true) == 1, "sweep", was);
   // big tiles: none below 160, never more than the workspace has room for
   for (int64_t n = 0; n < 4000; n += 37) {
     const std::vector<int64_t> list = {n * 20000 + 11, 65536 * (n % 90), 5};
