@@ -163,13 +163,16 @@ int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, b
 
 // The CUs without a piece in the last row have its whole time for the left-over tiles, one
 // per wave: a wave takes about 1.2 us per worker for one (nothing overlaps in it), a row
-// about 14, and 8 waves work side by side.  Gossip step with the tiles riding against a
-// launch of their own: m = 16, 11.7 M elements (240 tiles) 657 -> 640 us, m = 32, 25.6 M
-// elements (1552 tiles, 8 per wave) 2809 -> 2803 us.
+// about 14, and 8 waves work side by side.  A launch of their own has the whole chip instead, which
+// tells from about 1500 tiles on.  Gossip step with the tiles riding over a launch of their own; m = 8,
+// 16 and 32, SGD and Adam, groups of 4 to 32 workers, 2 and 4 rows; by tiles per wave: 1 of 32 CUs idle 3
+// 0.95-0.99, 6 0.96-1.00, 9 1.02-1.07, 13 1.08-1.22; 2 idle 3 0.96-0.99, 6 0.97-1.01, 9 1.03-1.08; 6 idle
+// 0.9 (345 tiles) 0.96-0.99, 3 (1209) 0.98-1.00, 6 (2419) 1.00-1.05, 9 (3456) 1.03-1.10; 12 idle 0.9
+// (691) 0.95-0.99, 3 (2419) 0.99-1.01, 6 (4838) 0.99-1.04, 9 (6912) 1.01-1.06.
 bool rest_rides(int64_t paced, int64_t rest, int64_t row) {
   if (row < 8 || paced <= 0) return false;
   const int64_t members = row / 8, busy = (paced + 7) / 8 % members;
-  return busy > 0 && rest <= (members - busy) * 8 * 8 * kRestPerWave;
+  return busy > 0 && rest <= kRestMost && rest <= (members - busy) * 8 * 8 * kRestPerWave;
 }
 
 void plan_paced(int32_t m, int32_t n_tensors, const int64_t *numel, int64_t row, bool forced,

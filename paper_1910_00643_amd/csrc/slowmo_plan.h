@@ -68,7 +68,8 @@ constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMix
 constexpr int32_t kPaceStride = 128;    // words between the counters of two XCDs
 constexpr int32_t kPaceWords = 8 * kPaceStride + kPaceStride;
 constexpr int32_t kPaceSpins = 300;
-constexpr int32_t kRestPerWave = 9;     // left-over tiles that a wave takes during a last row
+constexpr int32_t kRestPerWave = 6;     // left-over tiles that a wave takes during a last row
+constexpr int32_t kRestMost = 1200;     // ... and that all of them take
 static_assert(kPacedTile % kOuterTile == 0, "a paced tile is a whole number of ordinary tiles");
 
 // One tile of either kernel: the k-th piece of a tensor.  For the local step
@@ -220,10 +221,10 @@ int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
 // Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
 // worker count is too small (with `forced`, only when no tensor has such a piece).
 int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, bool forced);
-// The pieces a paced walk takes (owner = tensor) on a chip with `row` CUs, and the
-// ordinary tiles they leave over; both empty when it takes none.
 // `rest` left-over tiles ride with `paced` pieces in the same launch, on `row` CUs.
 bool rest_rides(int64_t paced, int64_t rest, int64_t row);
+// The pieces a paced walk takes (owner = tensor) on a chip with `row` CUs, and the
+// ordinary tiles they leave over; both empty when it takes none.
 void plan_paced(int32_t m, int32_t n_tensors, const int64_t *numel, int64_t row, bool forced,
                 std::vector<TileRef> &paced, std::vector<TileRef> &rest);
 

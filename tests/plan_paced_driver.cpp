@@ -130,8 +130,19 @@ static void paced_rule() {
         "forced: all whole pieces", 0);
 }
 
+// Left-over tiles that ride: up to 6 per wave of the CUs without a piece in the last row, and 1200.
+static void riding_rule() {
+  check(!rest_rides(512, 1, 256) && !rest_rides(505, 1, 256), "a full row: no CU to spare", 0);
+  check(rest_rides(504, 384, 256) && !rest_rides(504, 385, 256), "one CU of each XCD", 0);
+  check(rest_rides(256 + 240, 768, 256) && !rest_rides(256 + 240, 769, 256), "two CUs of each XCD", 0);
+  check(rest_rides(256 + 160, 1200, 256) && !rest_rides(256 + 160, 1201, 256), "many CUs", 0);
+  check(rest_rides(497, 384, 256) && !rest_rides(497, 385, 256), "by the XCD with the most pieces", 0);
+  check(!rest_rides(0, 10, 256) && !rest_rides(400, 10, 0) && !rest_rides(400, 10, 7), "no pieces, few CUs", 0);
+}
+
 int main() {
   paced_rule();
+  riding_rule();
   std::mt19937 rng(7);
   int reads = 0, workers = 0;
   for (int m = 1; m <= 40; ++m) {
