@@ -90,3 +90,46 @@ def test_debias_of_a_list_that_stays_in_the_caches():
         for x, t in zip(prob.params[i], z[i], strict=True):
             assert torch.equal(t, x / torch.tensor(weights[i], device="cuda:0"))
     opt.close()
+
+
+KEPT = {"SLOWMO_LOCAL_NT": "1", "SLOWMO_OUTER_NT": "1", "SLOWMO_WRITE_THROUGH": "1", "SLOWMO_TURN": "1"}
+
+
+@pytest.mark.parametrize("megabytes", ["1", "1000"])
+@pytest.mark.parametrize("layout", ["arena", "flat"])
+def test_debias_of_kept_tiles(layout, megabytes):
+    """A part of the units and all of them: z = x / w in every element."""
+    import torch
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = dataclasses.replace(W.ragged_mini(m=3, policy="maintain"), tau=3,
+                            shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
+    prob = GpuProblem(w, "cuda:0", param_layout=layout, grad_layout="flat")
+    with PU.environment(SLOWMO_KEPT=megabytes, **KEPT):
+        opt = PU.make_gpu(w, prob)
+    prob.fill_grads(0, 0)
+    opt.local_mix_step(prob.grads[0], w.lr, MAPS[1])
+    z = [[torch.full((n,), 7.0, device="cuda:0") for n in LENGTHS] for _ in range(w.m)]
+    opt.debias(z)
+    weights = opt.pushsum_weights()
+    assert len(set(weights)) > 1
+    for i in range(w.m):
+        for x, t in zip(prob.params[i], z[i], strict=True):
+            assert torch.equal(t, x / torch.tensor(weights[i], device="cuda:0"))
+    opt.close()
+
+
+@pytest.mark.parametrize("layout", ["arena", "flat"])
+@pytest.mark.parametrize("base,grad_dtype,average", [("sgd_nesterov", "f32", True), ("adam", "bf16", False)])
+def test_gossip_kernel_on_kept_tiles(base, grad_dtype, average, layout):
+    """The gossip step by itself reads and writes kept tiles like the others."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy="maintain", m=3), tau=3,
+                            exact_average=average, shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
+
+    def step(opt, grads, k):
+        opt.local_step(grads, w.lr)
+        opt.mix_step(MAPS[k])
+        if k == w.tau - 1:
+            opt.outer_step(w.lr)
+
+    PU.assert_same_bits(PU.run_library(w, (layout, "padded"), step, **STREAMING),
+                        PU.run_library(w, (layout, "padded"), step, SLOWMO_KEPT="1", **KEPT))
