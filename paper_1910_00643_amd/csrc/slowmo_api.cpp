@@ -291,6 +291,8 @@ struct slowmo_ctx {
   int64_t fail_launch_at = 0, launches = 0;
 
   LaunchTuning tune{};
+  bool gossip_outer_nt = true;  // tune.outer_nt for an outer step after a fused gossip step
+  bool after_gossip = false;    // the last inner step was one
   bool turning = true;  // sweeps over the tiles change direction (tune.backward)
   std::string err;
 };
@@ -494,10 +496,19 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   const int64_t touched = touched_state + elements * grad_bytes;
   const bool past_l2 = touched > int64_t{54} << 20;
   const int64_t outer_bytes = 8 * ctx->layout.d * (cfg->no_average ? m : 1);
-  CacheRule caches = cache_rule(touched_state, elements * grad_bytes, grad_bytes, outer_bytes, cfg->tau);
+  const bool one_step = cfg->tau == 1 && cfg->policy == SLOWMO_BUF_RESET && !cfg->no_average;
+  CacheRule caches = cache_rule({touched_state, elements * grad_bytes, grad_bytes, outer_bytes,
+                                 one_step ? elements * buffer_bytes : 0, cfg->tau,
+                                 cfg->base == SLOWMO_ADAM, cfg->policy == SLOWMO_BUF_AVERAGE});
   if (kept_mb >= 0) caches.kept_bytes = kept_mb * 1e6;
-  ctx->tune.local_nt = ctx->tune.nontemporal && (local_nt < 0 ? caches.streaming : local_nt != 0);
-  ctx->tune.outer_nt = ctx->tune.nontemporal && (outer_nt < 0 ? caches.outer_streaming : outer_nt != 0);
+  const auto streams = [&](int32_t asked, bool by_rule) {
+    return ctx->tune.nontemporal && (asked < 0 ? by_rule : asked != 0);
+  };
+  ctx->tune.local_nt = streams(local_nt, caches.streaming);
+  ctx->tune.mix_nt = streams(local_nt, caches.gossip_streaming);
+  ctx->tune.outer_nt = streams(outer_nt, caches.outer_streaming);
+  ctx->tune.last_nt = streams(outer_nt, caches.last_streaming);
+  ctx->gossip_outer_nt = streams(outer_nt, caches.gossip_outer_streaming);
   ctx->tune.write_through = through < 0 ? caches.write_through : through != 0;
   // the outer step without the average: written through 24 MB 1.10-1.12 times, 60 MB
   // 1.02-1.04, 84 MB 1.01-1.02, from 120 MB on 0.98-1.00
@@ -542,8 +553,8 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->tune.big_tiles =
       ((big < 0 ? m >= kBigFusedFromWorkers : big != 0) && ctx->tune.nontemporal) ? 1 : 0;
   ctx->tune.paced = paced_mode();
-  // a list that the L2s hold in any order has nothing to turn for (18 MB 0.84-0.98 of the
-  // time, 9-15 MB 0.98-1.04)
+  // a list of half the L2s' 32 MB is found there in any order and has nothing to turn for
+  // (18 MB 0.84-0.98 of the time, 9-15 MB 0.98-1.04)
   ctx->turning = env_flag("SLOWMO_TURN", touched > int64_t{16} << 20) != 0;
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
@@ -861,7 +872,8 @@ slowmo_status prepare_local(slowmo_ctx *ctx, const void *const *grads, float lr,
   return SLOWMO_OK;
 }
 
-void finish_local(slowmo_ctx *ctx) {
+void finish_local(slowmo_ctx *ctx, bool gossip = false) {
+  ctx->after_gossip = gossip;
   ctx->k += 1;
   ctx->l += 1;
   ctx->buffers_zero = false;
@@ -931,6 +943,8 @@ OuterArgs outer_args(const slowmo_ctx *ctx, float lr) {
 // call already issued (a failure is then a failure halfway).
 slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t stream) {
   const slowmo_config &c = ctx->cfg;
+  LaunchTuning tune = ctx->tune;
+  if (ctx->after_gossip) tune.outer_nt = ctx->gossip_outer_nt;
   if (c.no_average) {  // Section 6: lines 7-8 per worker, no line 6
     OuterNoAvgArgs na{};
     na.tiles = ctx->d_ltiles;
@@ -942,7 +956,7 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
     na.alpha = c.alpha;
     na.beta = c.beta;
     const hipError_t e =
-        guarded(ctx, [&] { return launch_outer_noavg_step(na, ctx->tune, stream); });
+        guarded(ctx, [&] { return launch_outer_noavg_step(na, tune, stream); });
     if (e != hipSuccess)
       return *launched ? fail_midway(ctx, e, "outer-step kernel launch")
                        : fail_hip(ctx, e, "outer-step kernel launch");
@@ -958,8 +972,8 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
   };
   return run_tiled(
       ctx, ctx->outer_big, launched, "outer-step kernel launch",
-      [&](const TileRef *t, int32_t n) { return launch_outer_big(with(t, n), ctx->tune, stream); },
-      [&](const TileRef *t, int32_t n) { return launch_outer_step(with(t, n), ctx->tune, stream); });
+      [&](const TileRef *t, int32_t n) { return launch_outer_big(with(t, n), tune, stream); },
+      [&](const TileRef *t, int32_t n) { return launch_outer_step(with(t, n), tune, stream); });
 }
 
 }  // namespace
@@ -1284,7 +1298,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
     swept(ctx, sm.paced);
   }
   // counters and weights move only after the last launch was accepted
-  finish_local(ctx);
+  finish_local(ctx, /*gossip=*/!two_kernels);
   mix_weights(ctx, in_peer);
   return SLOWMO_OK;
 }

@@ -97,9 +97,11 @@ struct LaunchTuning {
                         // the kernel allows
   int32_t big_tiles;    // 1: whole big tiles of aligned tensors go to the big-tile kernels
   int32_t big_vpt;      // vectors per lane of a big tile: 16, 14 or 12
-  int32_t local_nt;     // 1: streaming accesses in the local step, the gossip kernels in single waves and the
-                        // loads of the de-biasing (0: their working set stays in the caches)
-  int32_t outer_nt;     // the same for the outer step and the fused last step in single waves
+  int32_t local_nt;     // 1: streaming accesses in the local step and k_mix_step (0: their working set
+                        // stays in the caches)
+  int32_t mix_nt;       // the same for k_local_mix_step and the loads of the de-biasing
+  int32_t outer_nt;     // ... for the outer step in single waves
+  int32_t last_nt;      // ... for the fused last step in single waves
   int32_t kept_local;   // 1: some of the local-step tiles are kept (kTileKept)
   int32_t kept_tiles;   // 1: the fused last step reads kept outer-step tiles as such where
                         // last_keeps says so (2: on every list)

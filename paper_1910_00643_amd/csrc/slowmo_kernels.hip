@@ -1579,7 +1579,7 @@ hipError_t launch_fused_t(const LocalArgs &l, const OuterArgs &o, int n_tensors,
                        o.xtab_t, l.gtab, o.x0, o.u, l.h, l.v, o.d_pad, n_tensors, o.ntiles, g.chunk,
                        g.run, o.m, sp, ap, p);
   };
-  if (!t.outer_nt) {
+  if (!t.last_nt) {
     launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, false, false>);
   } else if (t.kept_tiles > 1 || (t.kept_tiles && last_keeps(o.ntiles, POLICY == 1))) {
     launch(k_local_outer_step<BASE, BF16, FIRST, POLICY, true, true>);
@@ -1664,7 +1664,7 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
                        l.gtab, l.h, l.v, x.seq, x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m,
                        sp, ap);
   };
-  if (!t.local_nt) {
+  if (!t.mix_nt) {
     launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
   } else if (t.kept_mix > 1 || (t.kept_mix && mix_keeps(x.ntiles, BASE == 1))) {
     launch(k_local_mix_step<BASE, BF16, FIRST, true, true>);
@@ -1739,7 +1739,7 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
   };
   if (!t.nontemporal) {
     launch(k_debias<false, false, false>);
-  } else if (!t.local_nt) {
+  } else if (!t.mix_nt) {
     launch(k_debias<false, true, false>);
   } else if (t.kept_local) {
     launch(k_debias<true, true, true>);

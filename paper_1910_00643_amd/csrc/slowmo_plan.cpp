@@ -21,11 +21,10 @@ Layout make_layout(int32_t n_tensors, const int64_t *numel) {
 // The lines, from the time of one local step among others, over the time with streaming
 // accesses everywhere and all sweeps in one direction; 1, 8 and 32 workers in 1 and 20 tensors each, SGD and Adam, fp32
 // and bf16 gradients, 0.1 to 800 M elements.
-CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
-                     int64_t outer_bytes, int32_t tau) {
+CacheRule cache_rule(const Touched &t) {
   constexpr int64_t MiB = int64_t{1} << 20;
-  const int64_t all = state_bytes + grad_bytes;
-  CacheRule r{true, true, false, 0.0};
+  const int64_t all = t.state_bytes + t.grad_bytes;
+  CacheRule r{};
   // Plain accesses, gradients included, as long as all of it fits the last-level cache:
   // 30-60 MB 0.73-0.90, 60-250 MB 0.72-0.83, 256-266 MB 0.80-0.92.  Below, in the L2s,
   // streaming is as good or better (18 MB: plain 0.84-1.02, streaming 0.81-0.91), or plain
@@ -33,22 +32,39 @@ CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
   // rounds of 2 steps 0.84-1.41).  A round of one step finds nothing in the cache but what
   // the last round left there: three optimizers in turn, tau = 1, 40 MB 0.85-1.10, 70 MB
   // 0.82-1.01, 120 MB 0.96-1.13, 200 MB 0.97-1.17; tau = 2 0.79-1.00 from 40 MB on.
-  const int64_t fits = (tau > 1 ? 240 : 72) * MiB;
-  r.streaming = !(all > 32 * MiB && all <= fits);
+  const int64_t fits = (t.tau > 1 ? 240 : 72) * MiB;
+  const bool plain = all > 32 * MiB && all <= fits;
   // The outer step and the fused last step, plain with x0 and u in the cache as well; time
   // of rounds of 4 steps over that with only the local step plain, 1, 4 and 16 workers: 24 MB
   // 0.82-1.09 (worst under "reset"), 40-230 MB with x0 and u 0.77-0.99; 255-290 MB
   // 0.95-1.10, 330-400 MB 1.00-1.09.  The gossip kernels, rounds by the line of the local
   // step: 24 MB 0.88-0.99, 40-120 MB 0.87-0.95, 200-245 MB 0.82-0.95.
-  // Three optimizers in turn, tau = 1, fused step under "reset": 35 MB 1.00-1.13, 45 MB
-  // 1.00-1.04, 60 MB 0.94-1.00.
-  r.outer_streaming = !(all > (tau > 1 ? 32 : 48) * MiB && all + outer_bytes <= fits);
+  // With tau = 1 plain accesses in the local step alone cost where x0 and u are a small part (11
+  // workers, 35-74 MB 1.05-1.24; 6 with de-biasing 1.00-1.10) and gain where they are a large one (1 to
+  // 3 workers, 52-70 MB 0.84-0.99): a small part does not count, but where the outer step takes
+  // the buffers as well (8 workers, 74 MB, plain over streaming outer step 1.05-1.15).
+  const bool small_outer = t.tau == 1 && !t.averages && t.outer_bytes < all / 8;
+  const bool with_outer = plain && (small_outer || all + t.outer_bytes <= fits);
+  r.streaming = r.gossip_streaming = !plain;
+  r.outer_streaming = r.last_streaming = r.gossip_outer_streaming = !with_outer;
+  if (t.idle_bytes > 0) {
+    // tau = 1 under "reset": calls share x, x0 and u only, and as long as what they touch at all
+    // is in the L2s, plain accesses cost.  Local and outer step, plain over streaming, one optimizer
+    // or three in turn, 11 workers, by what is touched: 18-31 MB 0.96-1.33, 32-33 MB 0.92-1.05,
+    // 34-40 MB 0.90-1.06, 41 MB and more 0.83-0.93.  The fused step is the whole round: SGD, touching 28
+    // to 47 MB, 0.89-1.10, worst with fp32 gradients from 35 MB on; Adam, 50-70 MB with the buffers,
+    // 0.85-1.02.
+    if (all - t.idle_bytes + t.outer_bytes <= 30 * MiB) r.streaming = r.outer_streaming = true;
+    if (!t.adam || all <= 48 * MiB) r.last_streaming = true;
+  }
+  // SGD with averaged buffers, fused step, 8 workers, 43-50 MB 1.04-1.08 or, three in turn, 0.96-0.97.
+  if (t.tau == 1 && t.averages && !t.adam && all <= 48 * MiB) r.last_streaming = true;
   // Written through: where the L2s cannot hold much of it for the next call anyway, the
   // memory takes stores better when they come at once.  With against without, plain
   // accesses: 30-50 MB 1.00-1.25; fp32 gradients 56-64 MB 0.96-1.02, 72-230 MB 0.92-0.98;
   // bf16 gradients 60-70 MB 1.04-1.06, 80-84 MB 0.99-1.03, 100-224 MB 0.96-0.99.
   // Streaming accesses on longer lists: 0.98-1.00.
-  r.write_through = all > (grad_size == 2 ? 80 : 54) * MiB;
+  r.write_through = all > (t.grad_size == 2 ? 80 : 54) * MiB;
   // Longer lists keep a part of the replicas and buffers: a kept byte saves a read and a
   // write, a gradient's only a read.  224 MB of it, 0.6 of the state where that is less
   // (what is not kept comes from memory at the same time): 260-360 MB 0.79-0.88, 400-560
@@ -58,8 +74,8 @@ CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
   // where steps follow each other; where something else has passed through the cache in
   // between, a call with kept tiles takes as long as one without.
   // With tau = 1 nothing is kept: three optimizers in turn 0.96-1.08 (tau = 2 0.89-0.98).
-  if (r.streaming && r.write_through && tau > 1) {
-    r.kept_bytes = std::min(224e6, 0.6 * static_cast<double>(state_bytes));
+  if (r.streaming && r.write_through && t.tau > 1) {
+    r.kept_bytes = std::min(224e6, 0.6 * static_cast<double>(t.state_bytes));
   }
   return r;
 }

@@ -86,16 +86,24 @@ static_assert(sizeof(TileRef) == 8, "TileRef layout");
 // How the kernels go through the caches: 8 L2s of 4 MB and one last-level cache of
 // 256 MB in front of the memory.
 struct CacheRule {
-  bool streaming;      // non-temporal accesses (but for the kept tiles)
-  bool outer_streaming;  // the same for the outer step and the fused last step
+  bool streaming;      // non-temporal accesses (but for the kept tiles): local step, k_mix_step
+  bool outer_streaming;  // the same for the outer step
+  bool last_streaming;   // ... for the fused last step
+  bool gossip_streaming;        // ... for the gossip step fused with the local step, de-biasing
+  bool gossip_outer_streaming;  // ... for the outer step after such a gossip step
   bool write_through;  // stores leave the L2 at once
   double kept_bytes;   // of the replicas and buffers: kept in the last-level cache
 };
-// For a step that touches state_bytes of replicas and buffers and grad_bytes of
-// gradients (grad_size bytes per element); x0 and u are outer_bytes, tau steps follow each
-// other in an outer iteration.
-CacheRule cache_rule(int64_t state_bytes, int64_t grad_bytes, int64_t grad_size,
-                     int64_t outer_bytes, int32_t tau);
+// A step touches state_bytes of replicas and buffers and grad_bytes of gradients (grad_size
+// bytes per element); x0 and u are outer_bytes, tau steps follow each other in an outer
+// iteration.  idle_bytes of the state are buffers that no call of a round touches: under
+// "reset" with tau = 1 all of them, but for the gossip step's.
+struct Touched {
+  int64_t state_bytes, grad_bytes, grad_size, outer_bytes, idle_bytes;
+  int32_t tau;
+  bool adam, averages;  // the base optimizer; the buffers are averaged
+};
+CacheRule cache_rule(const Touched &t);
 // Direction of the next sweep over the tiles (1: backward) after one that went `backward`: the
 // other one.  A paced walk goes forward in any case.
 inline int32_t next_sweep(int32_t backward, bool paced) { return paced ? 1 : backward ^ 1; }

@@ -201,6 +201,10 @@ def summarize(directory, bench_args, out_md, title, extra_note=""):
             f"FETCH_SIZE reads {sum(fetch[cal]) / len(fetch[cal]):.2f} for it (factor {fs:.5f}), "
             f"WRITE_SIZE {sum(write[cal]) / len(write[cal]):.2f} (factor {ws:.5f}).\n") if counters
            else "Kernel trace only: the HBM counters were not collected for this command.\n",
+           "Both counters count what leaves the L2s, the requests that the 256 MB last-level cache "
+           "answers among them.  Where a kernel finds a part of its list there (plain accesses or kept "
+           "tiles), \"GB/s\" and \"of 8 TB/s\" are therefore rates of cache and memory together; that "
+           "a call was faster for it shows in its time only.\n",
            "A library call may launch its kernel several times (the gossip kernels run once per "
            "connected group of workers, or as paced tiles and a rest, listed here under "
            "`k_local_mix_paced`): durations, traffic and algorithmic bytes below are "

@@ -16,19 +16,34 @@ static void check(bool ok, const char *what, double at) {
 
 int main() {
   const int64_t MiB = int64_t{1} << 20;
-  for (int64_t size : {int64_t{1}, 32 * MiB, 32 * MiB + 3, 54 * MiB, 72 * MiB, 72 * MiB + 3, 240 * MiB,
+  for (int64_t size : {int64_t{1}, 32 * MiB, 32 * MiB + 3, 48 * MiB, 54 * MiB, 72 * MiB, 72 * MiB + 3, 240 * MiB,
                        240 * MiB + 3, int64_t{1} << 40}) {
     for (int64_t grad : {2, 4}) {
       for (int32_t tau : {1, 2, 48}) {
-        const int64_t g = size / (8 + grad) * grad, s = size - g, fits = (tau > 1 ? 240 : 72) * MiB;
-        const CacheRule r = cache_rule(s, g, grad, size / 4, tau);
-        check(r.streaming == !(size > 32 * MiB && size <= fits), "plain in the caches only", size);
-        check(r.outer_streaming || !r.streaming, "the outer step plain only where the local step is", size);
-        check(r.outer_streaming == !(size > (tau > 1 ? 32 : 48) * MiB && size + size / 4 <= fits),
-              "the outer step plain where x0 and u fit too", size);
-        check((r.kept_bytes > 0) == (r.streaming && r.write_through && tau > 1), "kept on long lists", size);
-        check(r.kept_bytes <= 0.6 * s && r.kept_bytes <= 224e6, "no more kept than fits", size);
-        check(r.write_through == (size > (grad == 2 ? 80 : 54) * MiB), "written through", size);
+        for (int64_t idle : {int64_t{0}, size / 3}) {
+          for (bool adam : {false, true}) {
+            if (idle && tau > 1) continue;
+            const int64_t g = size / (8 + grad) * grad, s = size - g, fits = (tau > 1 ? 240 : 72) * MiB;
+            const CacheRule r = cache_rule({s, g, grad, size / 4, idle, tau, adam, false});
+            const bool in = size > 32 * MiB && size <= fits, both = in && size + size / 4 <= fits;
+            // x0 and u of many workers: small, and with one step per round no reason to stream
+            const CacheRule many = cache_rule({s, g, grad, size / 10, 0, tau, adam, false});
+            check(many.outer_streaming == !(in && (tau == 1 || size + size / 10 <= fits)), "a small part", size);
+            const CacheRule avg = cache_rule({s, g, grad, size / 10, 0, tau, adam, true});
+            check(avg.outer_streaming == !(in && size + size / 10 <= fits), "averaged buffers", size);
+            check(avg.last_streaming == (avg.outer_streaming || (tau == 1 && !adam && size <= 48 * MiB)),
+                  "averaged buffers", size);
+            const bool l2 = idle && size - idle + size / 4 <= 30 * MiB;
+            check(r.streaming == (!in || l2), "plain in the caches only", size);
+            check(r.outer_streaming == (!both || l2), "the outer step plain where x0 and u fit too", size);
+            check(r.outer_streaming || !r.streaming, "the outer step plain only where the local step is", size);
+            check(r.gossip_streaming == !in && r.gossip_outer_streaming == !both, "after gossip", size);
+            check(r.last_streaming == (!both || (idle && (!adam || size <= 48 * MiB))), "fused last step", size);
+            check((r.kept_bytes > 0) == (r.streaming && r.write_through && tau > 1), "kept on long lists", size);
+            check(r.kept_bytes <= 0.6 * s && r.kept_bytes <= 224e6, "no more kept than fits", size);
+            check(r.write_through == (size > (grad == 2 ? 80 : 54) * MiB), "written through", size);
+          }
+        }
       }
     }
   }
