@@ -1015,6 +1015,7 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
     });
     if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
     swept(ctx);
+    ctx->after_gossip = false;
     int launched = 1;
     st = run_outer(ctx, outer_lr, &launched, stream);
     if (st != SLOWMO_OK) return st;

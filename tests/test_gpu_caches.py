@@ -133,3 +133,24 @@ def test_gossip_kernel_on_kept_tiles(base, grad_dtype, average, layout):
 
     PU.assert_same_bits(PU.run_library(w, (layout, "padded"), step, **STREAMING),
                         PU.run_library(w, (layout, "padded"), step, SLOWMO_KEPT="1", **KEPT))
+
+
+@pytest.mark.parametrize("policy", ["reset", "maintain"])
+@pytest.mark.parametrize("calls", [_separate, _fused, _gossip])
+def test_one_step_rounds_by_the_rule(calls, policy):
+    """tau = 1, 36 and 50 MB with 11 workers: each call pattern has lines of its own there, and
+    an outer step goes by the step before it."""
+    maps = [(i + 3) % 11 for i in range(11)]
+
+    def gossip(w):
+        def step(opt, grads, k):
+            opt.local_mix_step(grads, w.lr, maps)
+            opt.outer_step(w.lr)
+        return step
+
+    for elements in (270_001, 380_003):
+        w = dataclasses.replace(W.ragged_mini(policy=policy, m=11), tau=1,
+                                shapes=(("a", (elements,)), ("b", (16387,)), ("c", (3,))))
+        step = gossip(w) if calls is _gossip else calls(w)
+        PU.assert_same_bits(PU.run_library(w, ("arena", "flat"), step, **STREAMING),
+                            PU.run_library(w, ("arena", "flat"), step))
