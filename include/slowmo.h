@@ -39,17 +39,18 @@
  *    correctly any number of times; one of the Adam base does not (its bias
  *    correction changes every step).  The context's counters advance when the
  *    calls are recorded, not when the graph is replayed.  slowmo_mix_step,
- *    slowmo_local_mix_step and slowmo_debias upload a small table with every
- *    call (from a staging buffer that later calls reuse) and keep the push-sum
- *    weights on the host: do not record them into a graph.
+ *    slowmo_local_mix_step and slowmo_debias keep the push-sum weights on the
+ *    host, and upload a small table (the former two with more than 64 workers)
+ *    from a staging buffer that later calls reuse: do not record them into a
+ *    graph.
  *  - Errors: every entry point returns a slowmo_status; nothing aborts or
  *    throws.  Arguments, call order and alignment are checked, and every table
  *    a call needs is planned and on its way to the device, before the call's
  *    first kernel is launched; counters and push-sum weights advance after its
  *    last launch was accepted.  A call that fails therefore leaves the
  *    context's state unchanged, with one exception: some calls issue several
- *    kernels or copies (slowmo_mix_step and slowmo_local_mix_step launch one
- *    kernel per connected group of workers; slowmo_local_mix_step launches
+ *    kernels or copies (slowmo_mix_step may launch one kernel per connected
+ *    group of workers; slowmo_local_mix_step launches
  *    the local step and the mixing step one after the other when a replica
  *    pointer is not 16-byte aligned, and from 8 workers on, for long tensor
  *    lists, one kernel for whole 16 384-element pieces and, where the rest does
@@ -263,7 +264,7 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
  * written.  Idle workers (no sender, no receiver) have no entry.  Entries of
  * one connected group of workers are consecutive and the first of them carries
  * GROUP_START; no HELD / IS_FIRST / SAVED flag refers across a group start, and the
- * library runs the groups as separate kernel launches.
+ * library runs the groups side by side or as separate kernel launches.
  * Writes at most m entries to `out` (host) and returns their number, or -1
  * for bad arguments.  Host-only.
  */

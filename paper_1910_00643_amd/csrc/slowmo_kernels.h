@@ -53,14 +53,32 @@ struct OuterNoAvgArgs {
   float lr, alpha, beta;
 };
 
+// The mixing order as the kernels read it: one entry is one 16-byte scalar load.
+struct MixSend {
+  uint16_t node, src;
+  float a, b;
+  uint32_t flags;
+};
+static_assert(sizeof(MixSend) == 16, "MixSend layout");
+// It travels with the launch, in the kernel's arguments, where it has at most kMixInline
+// entries; a longer one is a table in the workspace (the entries, then the groups).
+constexpr int32_t kMixInline = 64;
+struct MixInline {
+  MixSend entry[kMixInline];
+  uint32_t group[kMixInline];  // connected groups of workers: first entry, number of entries << 16
+};
+
 struct MixArgs {
   const TileRef *tiles;        // device: outer-step tiles (owner = tensor)
   const TensorInfo *tensors;   // device
   float *const *xtab_t;        // device: replica pointers, tensor-major
   int32_t ntiles;
   int32_t m;
-  const MixEntry *seq;         // device: len entries
-  int32_t len;
+  const MixInline *order;      // host: the mixing order, or ...
+  const MixSend *table;        // ... device: its entries
+  const uint32_t *groups;      // ... and its groups (nullptr: one range from `first` on)
+  int32_t n_groups;            // groups to run side by side in one launch (0: the entries
+  int32_t first, len;          // [first, first + len))
 };
 
 // Tiles of a paced walk (see kPacedTile), and what its workgroups pace each other with.
@@ -144,12 +162,12 @@ hipError_t launch_init_broadcast(const OuterArgs &a, int32_t x0_copies, const La
                                  hipStream_t stream);
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &tune,
                               hipStream_t stream);
-// The local step and the mixing step that follows it in one kernel; x.seq must
+// The local step and the mixing step that follows it in one kernel; the order must
 // list EVERY worker (plan_mix with idle workers).
 hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                  int32_t n_tensors, int base, bool bf16, bool first,
                                  const LaunchTuning &tune, hipStream_t stream);
-// The same on paced tiles (whole kPacedTile pieces of any tensors); x.seq must come
+// The same on paced tiles (whole kPacedTile pieces of any tensors); the order must come
 // from plan_mix with saved_limit = kPacedSaved.
 hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                   int32_t n_tensors, int base, bool bf16, bool first,

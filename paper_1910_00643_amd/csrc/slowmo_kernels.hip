@@ -40,6 +40,7 @@
 // in the order written here, which is the order of Table C.1 and Eq. (2)-(3).
 #include "slowmo_kernels.h"
 
+#include <cstddef>
 #include <mutex>
 
 // Device memory of the allocation-free entry point (slowmo_debias_static): the
@@ -866,7 +867,7 @@ __global__ __launch_bounds__(kBigBlock) void k_local_outer_big(
 
 // ---- mixing step of stochastic gradient push (Algorithm C.1) ---------------------
 // x^{(i)} <- p(i,i) x^{(i)} + p(i,j) x^{(j)}, j = in_peer(i), in place; one
-// workgroup = 256 elements of one tensor, all workers.  See MixEntry.  Every entry overwrites one worker
+// workgroup = 256 elements of one tensor, all workers.  See MixEntry, MixSend.  Every entry overwrites one worker
 // with a * own + b * src, both operands being values from before the step.
 // An operand that the previous entry already loaded (it is the previous
 // entry's source) or that opened the current cycle is taken from a register
@@ -925,11 +926,49 @@ __device__ __forceinline__ bool mix_src_in_register(int32_t flags) {
   return (flags & (kMixSrcFromS | kMixSrcFromFirst)) || mix_src_saved(flags);
 }
 
+// The entries a workgroup takes.  They lie in the kernel's arguments (a MixInline that is its first
+// one) or, from more than kMixInline workers on, in a table; constant memory in both cases, so
+// that an entry is a scalar load.  Blocks of one launch are dealt group after group (blockIdx.y).
+// An upload of the entries in front of every launch was 2-4 us of copy and 13-18 us of gaps on
+// the stream, and a wait of the host for the one four calls before.
+typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) U4 MixSendC;
+typedef const __attribute__((address_space(4))) uint32_t WordC;
+struct MixRange {
+  MixSendC *seq;
+  int len;
+};
+struct MixStep {
+  int node, src;
+  float a, b;
+  int32_t flags;
+};
+__device__ __forceinline__ MixStep mix_entry(MixSendC *seq, int i) {
+  const U4 w = seq[i];
+  return {static_cast<int>(w.x & 0xffffu), static_cast<int>(w.x >> 16), __uint_as_float(w.y),
+          __uint_as_float(w.z), static_cast<int32_t>(w.w)};
+}
+struct MixPlace {              // the part of a MixArgs that the kernels get beside the MixInline
+  const MixSend *table;
+  const uint32_t *groups;
+  int32_t n_groups, first, len;
+};
+__device__ __forceinline__ MixRange mix_range(const MixPlace &p) {
+  const uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+  MixSendC *seq = (MixSendC *)(p.table ? reinterpret_cast<uintptr_t>(p.table)
+                                       : args + offsetof(MixInline, entry));
+  if (p.n_groups == 0) return {seq + p.first, p.len};
+  WordC *groups = (WordC *)(p.table ? reinterpret_cast<uintptr_t>(p.groups)
+                                    : args + offsetof(MixInline, group));
+  const uint32_t g = groups[blockIdx.y];
+  return {seq + (g & 0xffffu), static_cast<int>(g >> 16)};
+}
+
 // One lane's vector (ONE: element) at e0 of the tile at element eo of a tensor whose
 // replicas are xp.
 template <bool NT, bool ONE>
 __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
-                                         const MixEntry *__restrict__ seq, int len, int64_t eo,
+                                         MixSendC *seq, int len, int64_t eo,
                                          int e0) {
   V4 S = {0.f, 0.f, 0.f, 0.f}, first = S;
   SavedRegs H;
@@ -940,7 +979,7 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
 #pragma unroll
     for (int q = 0; q < kMixBatch; ++q) {
       if (base + q < len) {
-        const MixEntry en = seq[base + q];
+        const MixStep en = mix_entry(seq, base + q);
         ptr[q] = xp[en.node] + eo + e0;
         if (!mix_own_in_register(en.flags)) own[q] = ldv<ONE, NT && SLOWMO_MIX_OWN_NT>(ptr[q]);
         if (!(en.flags & kMixNoSrc) && !mix_src_in_register(en.flags))
@@ -950,7 +989,7 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
 #pragma unroll
     for (int q = 0; q < kMixBatch; ++q) {
       if (base + q < len) {
-        const MixEntry en = seq[base + q];
+        const MixStep en = mix_entry(seq, base + q);
         const V4 o = (en.flags & kMixOwnFromS) ? S : H.get(mix_own_saved(en.flags), own[q]);
         if (en.flags & kMixSaveFirst) first = o;
         if (en.flags & kMixNoSrc) {
@@ -974,8 +1013,8 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
 // 2 to 32 workers, 1.00-1.10; 2 GB 0.99-1.02) and gain nothing beyond (5 to 20 GB 0.99-1.00).
 template <bool NT>
 __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
-    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
-    float *const *__restrict__ xtab_t, const MixEntry *__restrict__ seq, int len, int ntiles,
+    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
+    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t, int ntiles,
     int chunk, int remap, int m) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
@@ -986,10 +1025,11 @@ __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
   const int n = left < kOuterTile ? static_cast<int>(left) : kOuterTile;
   if (lane_idle(n)) return;
   float *const *__restrict__ xp = xtab_t + static_cast<int64_t>(t.owner) * m;
+  const MixRange r = mix_range(place);
   if (n >= 4) {
-    mix_lane<NT, false>(xp, seq, len, eo, lane_element(n));
+    mix_lane<NT, false>(xp, r.seq, r.len, eo, lane_element(n));
   } else {
-    mix_lane<NT, true>(xp, seq, len, eo, static_cast<int>(threadIdx.x));
+    mix_lane<NT, true>(xp, r.seq, r.len, eo, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -1021,8 +1061,8 @@ template <int BASE, bool BF16, bool FIRST, bool NT, bool NTG, bool ONE>
 __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
                                                const void *const *__restrict__ gp, int64_t eo,
                                                float *h0, float *v0, int64_t d_pad, int n_tensors,
-                                               const MixEntry *__restrict__ seq, int len,
-                                               const SgdP &sp, const AdamP &ap, int e0) {
+                                               MixSendC *seq, int len, const SgdP &sp,
+                                               const AdamP &ap, int e0) {
   V4 Sx = {0.f, 0.f, 0.f, 0.f}, Sh = Sx, Sv = Sx, first = Sx;
   SavedRegs Hx, Hh, Hv;           // saved stepped workers: new x, h and v
   Hx.clear(Sx);
@@ -1030,7 +1070,7 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
   Hv.clear(Sx);
 #pragma unroll 1
   for (int i = 0; i < len; ++i) {
-    const MixEntry en = seq[i];
+    const MixStep en = mix_entry(seq, i);
     float *xi = xp[en.node] + eo;
     float *hi = h0 + en.node * d_pad;
     float *vi = BASE == 1 ? v0 + en.node * d_pad : nullptr;
@@ -1071,9 +1111,9 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
 
 template <int BASE, bool BF16, bool FIRST, bool NT, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
-    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
-    float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
-    float *__restrict__ hbase, float *__restrict__ vbase, const MixEntry *__restrict__ seq, int len,
+    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
+    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t,
+    const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
     int64_t d_pad, int n_tensors, int ntiles, int chunk, int remap, int m, SgdP sp, AdamP ap) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
@@ -1091,20 +1131,21 @@ __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
   const void *const *__restrict__ gp = gtab + t.owner;       // worker i: gp[i * n_tensors]
   float *h0 = hbase + ti.fo + eo;                              // worker i: h0 + i * d_pad
   float *v0 = BASE == 1 ? vbase + ti.fo + eo : nullptr;
+  const MixRange r = mix_range(place);
   if (n >= 4) {
     const int e0 = lane_element(n);
     if (NT && KEPT && is_kept(t)) {
       own_path(xp), own_path(h0);
       if constexpr (BASE == 1) own_path(v0);
-      local_mix_lane<BASE, BF16, FIRST, false, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq,
-                                                          len, sp, ap, e0);
+      local_mix_lane<BASE, BF16, FIRST, false, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, r.seq,
+                                                          r.len, sp, ap, e0);
     } else {
-      local_mix_lane<BASE, BF16, FIRST, NT, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len,
-                                                       sp, ap, e0);
+      local_mix_lane<BASE, BF16, FIRST, NT, NT, false>(xp, gp, eo, h0, v0, d_pad, n_tensors, r.seq,
+                                                       r.len, sp, ap, e0);
     }
   } else {
-    local_mix_lane<BASE, BF16, FIRST, NT, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, seq, len, sp,
-                                                ap, static_cast<int>(threadIdx.x));
+    local_mix_lane<BASE, BF16, FIRST, NT, NT, true>(xp, gp, eo, h0, v0, d_pad, n_tensors, r.seq, r.len,
+                                                    sp, ap, static_cast<int>(threadIdx.x));
   }
 }
 
@@ -1226,9 +1267,9 @@ __device__ __forceinline__ void paced_step(PV &x, PV &h, PV &v, const float *xi,
 // first saved value in LDS (64 KiB each), the second saved value in registers.
 template <int BASE, bool BF16, bool FIRST>
 __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
-    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
-    float *const *__restrict__ xtab_t, const void *const *__restrict__ gtab,
-    float *__restrict__ hbase, float *__restrict__ vbase, const MixEntry *__restrict__ seq, int len,
+    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
+    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t,
+    const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
     int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int spins, int m,
     const TileRef *__restrict__ rest, int nrest,
     uint32_t *pace, SgdP sp0, AdamP ap0) {
@@ -1238,6 +1279,9 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
   const int lane = 4 * static_cast<int>(threadIdx.x);
   const int mine = ntiles - xcd * chunk < chunk ? ntiles - xcd * chunk : chunk;  // this XCD's tiles
   Pacer pacer(pace, xcd, members, spins);
+  const MixRange order = mix_range(place);
+  MixSendC *const seq = order.seq;
+  const int len = order.len;
   for (int at = 0; at + rank < mine; at += members) {
     const bool paced = at + members <= mine;   // the last, partly filled row of tiles runs free
     const TileRef t = tiles[xcd * chunk + at + rank];
@@ -1256,7 +1300,7 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
     PV S, saved2, x, h, v;
 #pragma unroll 1
     for (int i = 0; i < len; ++i) {
-      const MixEntry en = seq[i];
+      const MixStep en = mix_entry(seq, i);
       if (paced) pacer.next();
       float *xi = xp[en.node] + eo;
       PV mixed;                                // a * own, then + b * source
@@ -1636,12 +1680,27 @@ hipError_t launch_init_broadcast(const OuterArgs &a, int32_t x0_copies, const La
   return hipGetLastError();
 }
 
+namespace {
+
+MixPlace mix_place(const MixArgs &a) { return {a.table, a.groups, a.n_groups, a.first, a.len}; }
+const MixInline &mix_inline(const MixArgs &a) {
+  static const MixInline none{};
+  return a.order ? *a.order : none;
+}
+// x: the blocks of one group (a multiple of the XCDs, so that every group is dealt to them
+// alike), y: the groups
+dim3 mix_blocks(const MixArgs &a, const Grid &g) {
+  return dim3(g.blocks, static_cast<unsigned>(a.n_groups > 0 ? a.n_groups : 1));
+}
+
+}  // namespace
+
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t s) {
-  if (a.ntiles <= 0 || a.len <= 0) return hipSuccess;
+  if (a.ntiles <= 0 || (a.len <= 0 && a.n_groups <= 0)) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), 0, s, a.tiles, a.tensors, a.xtab_t,
-                       a.seq, a.len, a.ntiles, g.chunk, g.run, a.m);
+    hipLaunchKernelGGL(kernel, mix_blocks(a, g), dim3(kOuterBlock), 0, s, mix_inline(a), mix_place(a),
+                       a.tiles, a.tensors, a.xtab_t, a.ntiles, g.chunk, g.run, a.m);
   };
   if (t.local_nt) {
     launch(k_mix_step<true>);
@@ -1660,9 +1719,9 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kOuterBlock), 0, s, x.tiles, x.tensors, x.xtab_t,
-                       l.gtab, l.h, l.v, x.seq, x.len, d_pad, n_tensors, x.ntiles, g.chunk, g.run, x.m,
-                       sp, ap);
+    hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(kOuterBlock), 0, s, mix_inline(x), mix_place(x),
+                       x.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, d_pad, n_tensors, x.ntiles,
+                       g.chunk, g.run, x.m, sp, ap);
   };
   if (!t.mix_nt) {
     launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
@@ -1686,7 +1745,7 @@ hipError_t launch_local_mix_f(const LocalArgs &l, const MixArgs &x, int64_t d_pa
 hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                  int32_t n_tensors, int base, bool bf16, bool first,
                                  const LaunchTuning &t, hipStream_t s) {
-  if (x.ntiles <= 0 || x.len <= 0) return hipSuccess;
+  if (x.ntiles <= 0 || (x.len <= 0 && x.n_groups <= 0)) return hipSuccess;
   if (base == 0) {
     return bf16 ? launch_local_mix_f<0, true>(l, x, d_pad, n_tensors, first, t, s)
                 : launch_local_mix_f<0, false>(l, x, d_pad, n_tensors, first, t, s);
@@ -1703,8 +1762,8 @@ hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
-                     dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, x.seq,
-                     x.len, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members,
+                     dim3(kPacedBlock), 0, s, mix_inline(x), mix_place(x), p.tiles, x.tensors,
+                     x.xtab_t, l.gtab, l.h, l.v, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members,
                      p.spins, x.m, p.rest, p.nrest, p.counters, sp, ap);
   return hipGetLastError();
 }
