@@ -40,7 +40,8 @@
  *    correction changes every step).  The context's counters advance when the
  *    calls are recorded, not when the graph is replayed.  slowmo_mix_step,
  *    slowmo_local_mix_step and slowmo_debias keep the push-sum weights on the
- *    host, and upload a small table (the former two with more than 64 workers)
+ *    host, and may upload a small table (the former two with more than 64
+ *    workers, slowmo_debias for new destinations or with more than 64 workers)
  *    from a staging buffer that later calls reuse: do not record them into a
  *    graph.
  *  - Errors: every entry point returns a slowmo_status; nothing aborts or

@@ -92,12 +92,16 @@ struct PacedArgs {
   uint32_t *counters;          // device: kPaceWords words, zero between launches
 };
 
+struct DebiasWeights {
+  float w[kMixInline];
+};
 // De-biased parameters of push-sum: z^{(i)} = x^{(i)} / w_i, over the local tiles.
 struct DebiasArgs {
   const TileRef *tiles;        // device (owner = slot)
   const SlotInfo *slots;       // device
   float *const *ztab;          // device: m * n_tensors destination pointers (worker-major)
-  const float *w;              // device: m push-sum weights
+  const float *w;              // device: m push-sum weights, or nullptr:
+  const DebiasWeights *inl;    // host: the weights travel with the launch
   int32_t ntiles;
   int32_t n_tensors;
 };

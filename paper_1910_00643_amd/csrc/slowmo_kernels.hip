@@ -1399,17 +1399,21 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
 }
 
 // z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.  NTL:
-// the loads; NT: the stores.
+// the loads; NT: the stores.  The weights change with every gossip step and lie in the kernel's
+// arguments (the DebiasWeights that is its first one) where there are at most kMixInline of them,
+// so that only new destinations are uploaded.
 template <bool NTL, bool NT, bool KEPT>
 __global__ __launch_bounds__(kLocalBlock) void k_debias(
-    const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
+    DebiasWeights, const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *const *__restrict__ ztab, const float *__restrict__ w, int n_tensors, int ntiles,
     int chunk, int remap) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const SlotInfo s = slots[t.owner];
-  const float wi = w[t.owner / n_tensors];
+  WordC *weights = (WordC *)(w ? reinterpret_cast<uintptr_t>(w)
+                               : (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr());
+  const float wi = __uint_as_float(weights[t.owner / n_tensors]);
   const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;
   const float *x = s.x + go;
   float *z = ztab[t.owner] + go;
@@ -1793,8 +1797,8 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
   if (a.ntiles <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), 0, s, a.tiles, a.slots, a.ztab,
-                       a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), 0, s,
+                       a.inl ? *a.inl : DebiasWeights{}, a.tiles, a.slots, a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
   };
   if (!t.nontemporal) {
     launch(k_debias<false, false, false>);

@@ -25,3 +25,28 @@ def test_limit_of_the_inline_order_every_element(m, mix, fused_mix):
     PU.compare_run(w, prob, opt, np.arange(w.d, dtype=np.int64), w.rounds, bitwise_f32=True,
                    fused_mix=fused_mix)
     opt.close()
+
+
+@pytest.mark.parametrize("m", [3, 64, 65])
+def test_debias_into_more_destinations_than_are_remembered(m):
+    """The weights change with every gossip step and the destinations take turns, six sets of them;
+    up to 64 workers only new destinations are uploaded."""
+    import torch
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = dataclasses.replace(W.ragged_mini(m=m, policy="maintain"), mix="random", tau=14, rounds=1,
+                            shapes=(("a", (300,)), ("b", (3,))))
+    prob = GpuProblem(w, "cuda:0", grad_layout="separate")
+    opt = PU.make_gpu(w, prob)
+    sets = [[[torch.zeros_like(t) for t in p] for p in prob.params] for _ in range(6)]
+    for k in range(w.tau):
+        prob.fill_grads(0, k)
+        opt.local_mix_step(prob.grads[0], w.lr, W.in_peers(w, k).tolist())
+        z = sets[k % 6 if k != 1 else 0]
+        opt.debias(z)
+        weights = opt.pushsum_weights()
+        assert len(set(weights)) > 1
+        for i in range(m):
+            for zt, xt in zip(z[i], prob.params[i], strict=True):
+                # a division by an fp32 tensor rounds once, as the kernel's
+                assert torch.equal(zt, xt / torch.tensor(weights[i], dtype=torch.float32, device=xt.device))
+    opt.close()
