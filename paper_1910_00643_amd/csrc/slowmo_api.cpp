@@ -297,6 +297,7 @@ struct slowmo_ctx {
   LaunchTuning tune{};
   bool gossip_outer_nt = true;  // tune.outer_nt for an outer step after a fused gossip step
   bool after_gossip = false;    // the last inner step was one
+  int64_t team_waves = 0;  // waves of a gossip step by teams, at most (SLOWMO_TEAM)
   bool turning = true;  // sweeps over the tiles change direction (tune.backward)
   std::string err;
 };
@@ -327,6 +328,19 @@ hipError_t guarded(slowmo_ctx *ctx, F &&launch) {
 // The launches of one sweep over the tiles are out: the next sweep goes the other way.
 void swept(slowmo_ctx *ctx, bool paced = false) {
   if (ctx->turning) ctx->tune.backward = next_sweep(ctx->tune.backward, paced);
+}
+
+// Whether the gossip step goes by teams (a wave per worker), from 2 to kTeamMost workers up to
+// 65 536 waves in all.  Beyond, memory is what bounds it and the walk from worker to worker
+// is the better order.  Fused step, team over walk, SGD / Adam: cycle of all workers, 16 to 1024
+// tiles, m = 2 0.74-0.80, 4 0.55-0.80, 8 0.36-0.70, 16 0.23-0.52, 32 0.17-0.58; 32 768 and 65 536
+// waves 0.84-1.04, worst m = 2 with Adam; 131 072 waves 0.98-1.14; 262 144 1.05-1.29.  Pairs and
+// groups of 4: 0.71-0.98 up to 65 536 waves, 1.1-1.4 from 131 072 on.  By itself: cycle of 8 to 32
+// workers 0.24-0.93 (m = 8, 4096 tiles 1.07), pairs 0.88-1.08; 131 072 waves 1.05-1.32.  Lists with
+// kept tiles (Adam with fp32 gradients, 65 536 waves) 1.02-1.25: a team streams them.
+bool mix_by_team(const slowmo_ctx *ctx) {
+  const int32_t m = ctx->cfg.m;
+  return m > 1 && m <= kTeamMost && ctx->tune.kept_mix == 0 && static_cast<int64_t>(ctx->n_otiles) * m <= ctx->team_waves;
 }
 
 // Failure after at least one kernel of a multi-kernel call was launched.
@@ -560,6 +574,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // a list of half the L2s' 32 MB is found there in any order and has nothing to turn for
   // (18 MB 0.84-0.98 of the time, 9-15 MB 0.98-1.04)
   ctx->turning = env_flag("SLOWMO_TURN", touched > int64_t{16} << 20) != 0;
+  ctx->team_waves = env_flag("SLOWMO_TEAM", 65536);
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
@@ -1131,6 +1146,7 @@ struct StagedMix {
   std::vector<int32_t> starts;         // first entry of each connected group of workers
   int32_t len = 0;                     // entries of all groups together
   bool paced = false;                  // planned for the paced kernel
+  int32_t team = 0;                    // > 0: a team's order, entries of its largest group
 };
 
 // Whether the fused gossip step takes the paced tiles.  They keep the chip on one
@@ -1178,6 +1194,27 @@ slowmo_status stage_mix(slowmo_ctx *ctx, const int32_t *in_peer, bool with_idle,
                   static_cast<uint32_t>(e.flags)};
     if (e.flags & kMixGroupStart) out->starts.push_back(i);
   }
+  // (maps that move at most four workers keep a launch per group: see run_mix)
+  if ((with_idle || out->len > 4) && !out->paced && mix_by_team(ctx)) {
+    // On the shortest lists of many workers a workgroup takes one connected group of them, else
+    // all: 16 tiles, pairs and groups of 4 and 8, 16 workers 0.92-0.99 and 32 workers 0.70-0.78 of
+    // the time; 256 tiles 1.01-1.09.
+    if (ctx->cfg.m < 16 || static_cast<int64_t>(ctx->n_otiles) * ctx->cfg.m > 1024) out->starts.assign(1, 0);
+    for (size_t g = 0; g < out->starts.size(); ++g) {
+      const int32_t at = out->starts[g], end = g + 1 < out->starts.size() ? out->starts[g + 1] : out->len;
+      out->team = std::max(out->team, end - at);
+    }
+    if (out->team <= kTeamMost) {
+      std::vector<uint16_t> place(ctx->cfg.m, 0);
+      for (size_t g = 0; g < out->starts.size(); ++g) {
+        const int32_t at = out->starts[g], end = g + 1 < out->starts.size() ? out->starts[g + 1] : out->len;
+        for (int32_t i = at; i < end; ++i) place[entries[i].node] = static_cast<uint16_t>(i - at);
+      }
+      for (int32_t i = 0; i < out->len; ++i) entries[i].src = place[entries[i].src];
+    } else {
+      out->team = 0;
+    }
+  }
   for (size_t g = 0; g < out->starts.size(); ++g) {
     const int32_t end = g + 1 < out->starts.size() ? out->starts[g + 1] : out->len;
     groups[g] = static_cast<uint32_t>(out->starts[g]) |
@@ -1206,6 +1243,7 @@ MixArgs mix_args(const slowmo_ctx *ctx, const StagedMix &sm) {
   a.table = sm.d_entries;
   a.groups = sm.d_groups;
   a.len = sm.len;
+  a.team = sm.team;
   return a;
 }
 
@@ -1243,7 +1281,11 @@ slowmo_status run_mix(slowmo_ctx *ctx, const StagedMix &sm, int launched, hipStr
   // its own (a call that fails halfway is tested there).
   const slowmo_status st = run_groups(
       ctx, sm, mix_args(ctx, sm), sm.len > 4, &launched, "mixing kernel launch",
-      [&](const MixArgs &a) { return launch_mix_step(a, ctx->tune, stream); });
+      [&](const MixArgs &a) {
+        return a.team ? launch_team_mix(nullptr, a, ctx->layout.d_pad, ctx->n_tensors, 0, false, false,
+                                        ctx->tune, stream)
+                      : launch_mix_step(a, ctx->tune, stream);
+      });
   if (st == SLOWMO_OK && sm.len > 0) swept(ctx);
   return st;
 }
@@ -1338,6 +1380,9 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
     if (x.ntiles > 0) {
       st = run_groups(ctx, sm, x, one_launch, &launched, "fused local+mixing kernel launch",
                       [&](const MixArgs &r) {
+                        if (r.team)
+                          return launch_team_mix(&a, r, ctx->layout.d_pad, ctx->n_tensors, c.base,
+                                                 bf16, ctx->buffers_zero, ctx->tune, stream);
                         return launch_local_mix_step(a, r, ctx->layout.d_pad, ctx->n_tensors, c.base,
                                                      bf16, ctx->buffers_zero, ctx->tune, stream);
                       });

@@ -63,6 +63,7 @@ static_assert(sizeof(MixSend) == 16, "MixSend layout");
 // It travels with the launch, in the kernel's arguments, where it has at most kMixInline
 // entries; a longer one is a table in the workspace (the entries, then the groups).
 constexpr int32_t kMixInline = 64;
+constexpr int32_t kTeamMost = 32;  // workers that a team takes
 struct MixInline {
   MixSend entry[kMixInline];
   uint32_t group[kMixInline];  // connected groups of workers: first entry, number of entries << 16
@@ -79,6 +80,7 @@ struct MixArgs {
   const uint32_t *groups;      // ... and its groups (nullptr: one range from `first` on)
   int32_t n_groups;            // groups to run side by side in one launch (0: the entries
   int32_t first, len;          // [first, first + len))
+  int32_t team;                // > 0: a team's order (see launch_team_mix), entries of its largest group
 };
 
 // Tiles of a paced walk (see kPacedTile), and what its workgroups pace each other with.
@@ -176,6 +178,12 @@ hipError_t launch_local_mix_step(const LocalArgs &l, const MixArgs &x, int64_t d
 hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t d_pad,
                                   int32_t n_tensors, int base, bool bf16, bool first,
                                   const PacedArgs &p, hipStream_t stream);
+// The gossip step by itself (l = nullptr) or fused with the local step, with a wave per worker on
+// every tile, for short lists.  In a team's order src is the place of the source in its group
+// (x.team <= kTeamMost).
+hipError_t launch_team_mix(const LocalArgs *l, const MixArgs &x, int64_t d_pad, int32_t n_tensors,
+                           int base, bool bf16, bool first, const LaunchTuning &tune,
+                           hipStream_t stream);
 hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &tune, hipStream_t stream);
 
 // Static device memory for the entry point that allocates nothing: room for

@@ -1,0 +1,61 @@
+"""Teams, a wave per worker on every tile of a short list, against the walk from worker to worker
+(SLOWMO_TEAM=0), bit for bit: tensors whose ends fall on every side of a tile's edge, worker counts
+around one and two workers per wave, teams of all workers and of one connected group."""
+import dataclasses
+import gc
+
+import numpy as np
+import pytest
+
+from slowmo_inputs import workloads as W
+
+import parity_utils as PU
+
+pytestmark = pytest.mark.gpu
+
+# one lane alone, one lane and a few, a full tile less or more a few, two tiles
+LENGTHS = list(range(1, 10)) + list(range(251, 262)) + [511, 512, 513, 515]
+SHORT = tuple((f"t{j}", (n,)) for j, n in enumerate(LENGTHS))
+LONGER = SHORT + (("long", (60_001,)),)      # beyond the line of the teams of one group
+
+
+@pytest.fixture(autouse=True)
+def _free_gpu_memory():
+    yield
+    import torch
+    gc.collect()
+    torch.cuda.empty_cache()
+
+
+def _maps(m):
+    cycle = [(i - 1) % m for i in range(m)]
+    pairs = [i ^ 1 if i ^ 1 < m else i for i in range(m)]
+    return [cycle, pairs, np.random.default_rng(m).integers(0, m, size=m).tolist(), [0] * m,
+            list(range(m))]
+
+
+def _gossip(w, fused):
+    def step(opt, grads, k):
+        peers = _maps(w.m)[k]
+        if fused:
+            opt.local_mix_step(grads, w.lr, peers)
+        else:
+            opt.local_step(grads, w.lr)
+            opt.mix_step(peers)
+        if k == w.tau - 1:
+            opt.outer_step(w.lr)
+    return step
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("m,shapes,base,grad_dtype,policy", [
+    (2, LONGER, "sgd_nesterov", "f32", "reset"), (5, SHORT, "adam", "bf16", "maintain"),
+    (16, SHORT, "sgd_nesterov", "bf16", "maintain"), (16, LONGER, "adam", "f32", "reset"),
+    (17, LONGER, "sgd_nesterov", "f32", "reset"), (32, SHORT, "adam", "f32", "maintain"),
+    (32, LONGER, "sgd_nesterov", "bf16", "average"), (33, SHORT, "sgd_nesterov", "f32", "reset")])
+def test_gossip_by_teams(m, shapes, base, grad_dtype, policy, fused):
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=m, policy=policy),
+                            shapes=shapes, tau=5, rounds=2)
+    for layouts in (("separate", "separate"), ("flat", "flat")) if not fused else (("separate", "flat"),):
+        PU.assert_same_bits(PU.run_library(w, layouts, _gossip(w, fused)),
+                            PU.run_library(w, layouts, _gossip(w, fused), SLOWMO_TEAM="0"))
