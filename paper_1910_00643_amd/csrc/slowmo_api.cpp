@@ -297,7 +297,7 @@ struct slowmo_ctx {
   LaunchTuning tune{};
   bool gossip_outer_nt = true;  // tune.outer_nt for an outer step after a fused gossip step
   bool after_gossip = false;    // the last inner step was one
-  int64_t team_waves = 0;  // waves of a gossip step by teams, at most (SLOWMO_TEAM)
+  bool teams = true;    // short lists by teams, a wave per worker
   bool turning = true;  // sweeps over the tiles change direction (tune.backward)
   std::string err;
 };
@@ -340,7 +340,22 @@ void swept(slowmo_ctx *ctx, bool paced = false) {
 // kept tiles (Adam with fp32 gradients, 65 536 waves) 1.02-1.25: a team streams them.
 bool mix_by_team(const slowmo_ctx *ctx) {
   const int32_t m = ctx->cfg.m;
-  return m > 1 && m <= kTeamMost && ctx->tune.kept_mix == 0 && static_cast<int64_t>(ctx->n_otiles) * m <= ctx->team_waves;
+  return ctx->teams && m > 1 && m <= kTeamMost && ctx->tune.kept_mix == 0 &&
+         static_cast<int64_t>(ctx->n_otiles) * m <= 65536;
+}
+
+// Whether the outer step, by itself or fused with the last local step, goes by teams (a wave per
+// worker).  Team over walk: 16 to 512 tiles, 4 to 6 workers 0.80-0.96 (fused) and 0.61-0.96 (by
+// itself, with the local step before it), 8 and 12 0.53-0.96, 16 to 32 0.37-0.94; 768 and 1024 tiles
+// up to 16 384 waves 0.66-0.98 and 0.70-1.02, but "reset" at 1024 tiles 1.03-1.09; beyond 1024 tiles,
+// or 16 384 waves, 0.8-1.29.  2 workers 1.0-1.1, 3 workers 0.93-1.06; by itself with averaged
+// buffers 3 workers 0.80-1.01.
+bool outer_by_team(const slowmo_ctx *ctx, bool fused) {
+  const int32_t m = ctx->cfg.m, policy = ctx->cfg.policy;
+  const int32_t fewest = policy == SLOWMO_BUF_AVERAGE && !fused ? 3 : 4;
+  const int32_t tiles = policy == SLOWMO_BUF_RESET && fused ? 768 : 1024;
+  return ctx->teams && m >= fewest && m <= kTeamMost && ctx->n_otiles <= tiles &&
+         static_cast<int64_t>(ctx->n_otiles) * m <= 16384;
 }
 
 // Failure after at least one kernel of a multi-kernel call was launched.
@@ -574,7 +589,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   // a list of half the L2s' 32 MB is found there in any order and has nothing to turn for
   // (18 MB 0.84-0.98 of the time, 9-15 MB 0.98-1.04)
   ctx->turning = env_flag("SLOWMO_TURN", touched > int64_t{16} << 20) != 0;
-  ctx->team_waves = env_flag("SLOWMO_TEAM", 65536);
+  ctx->teams = env_flag("SLOWMO_TEAM", 1) != 0;
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
@@ -985,6 +1000,7 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
     return SLOWMO_OK;
   }
   OuterArgs a = outer_args(ctx, lr);
+  const bool team = outer_by_team(ctx, false);
   auto with = [&](const TileRef *tiles, int32_t n) {
     a.tiles = tiles;
     a.ntiles = n;
@@ -993,7 +1009,10 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
   return run_tiled(
       ctx, ctx->outer_big, launched, "outer-step kernel launch",
       [&](const TileRef *t, int32_t n) { return launch_outer_big(with(t, n), tune, stream); },
-      [&](const TileRef *t, int32_t n) { return launch_outer_step(with(t, n), tune, stream); });
+      [&](const TileRef *t, int32_t n) {
+        return team ? launch_team_outer(nullptr, with(t, n), ctx->n_tensors, 0, false, false, 0, tune, stream)
+                    : launch_outer_step(with(t, n), tune, stream);
+      });
 }
 
 }  // namespace
@@ -1054,6 +1073,9 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
                                         ctx->buffers_zero, c.policy, ctx->tune, stream);
         },
         [&](const TileRef *t, int32_t n) {
+          if (outer_by_team(ctx, true))
+            return launch_team_outer(&a, with(t, n), ctx->n_tensors, c.base, bf16, ctx->buffers_zero,
+                                     c.policy, ctx->tune, stream);
           return launch_local_outer_step(a, with(t, n), ctx->n_tensors, c.base, bf16,
                                          ctx->buffers_zero, c.policy, ctx->tune, stream);
         });

@@ -184,6 +184,10 @@ hipError_t launch_local_mix_paced(const LocalArgs &l, const MixArgs &x, int64_t 
 hipError_t launch_team_mix(const LocalArgs *l, const MixArgs &x, int64_t d_pad, int32_t n_tensors,
                            int base, bool bf16, bool first, const LaunchTuning &tune,
                            hipStream_t stream);
+// The outer step, after the last local step or by itself (l = nullptr), in the same way.
+hipError_t launch_team_outer(const LocalArgs *l, const OuterArgs &o, int32_t n_tensors, int base,
+                             bool bf16, bool first, int policy, const LaunchTuning &tune,
+                             hipStream_t stream);
 hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &tune, hipStream_t stream);
 
 // Static device memory for the entry point that allocates nothing: room for

@@ -59,3 +59,39 @@ def test_gossip_by_teams(m, shapes, base, grad_dtype, policy, fused):
     for layouts in (("separate", "separate"), ("flat", "flat")) if not fused else (("separate", "flat"),):
         PU.assert_same_bits(PU.run_library(w, layouts, _gossip(w, fused)),
                             PU.run_library(w, layouts, _gossip(w, fused), SLOWMO_TEAM="0"))
+
+
+def _outer(w, fused):
+    def step(opt, grads, k):
+        if fused and k == w.tau - 1:
+            opt.local_outer_step(grads, w.lr)
+        else:
+            opt.local_step(grads, w.lr)
+            if k == w.tau - 1:
+                opt.outer_step(w.lr)
+    return step
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("m,base,grad_dtype,policy,tau", [
+    (3, "adam", "bf16", "average", 2), (4, "sgd_nesterov", "f32", "reset", 2),
+    (5, "adam", "f32", "maintain", 1), (16, "sgd_nesterov", "bf16", "average", 2),
+    (17, "adam", "f32", "average", 1), (31, "sgd_nesterov", "f32", "maintain", 2),
+    (32, "adam", "f32", "average", 2), (32, "adam", "bf16", "reset", 1)])
+def test_outer_step_by_teams(m, base, grad_dtype, policy, tau, fused):
+    """Two workers per wave from 17 on; three rows of LDS per worker with Adam's averages (96 KiB
+    with 32 workers)."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=m, policy=policy),
+                            shapes=LONGER, tau=tau, rounds=2)
+    for layouts in (("separate", "separate"), ("flat", "flat")):
+        PU.assert_same_bits(PU.run_library(w, layouts, _outer(w, fused)),
+                            PU.run_library(w, layouts, _outer(w, fused), SLOWMO_TEAM="0"))
+
+
+@pytest.mark.parametrize("tiles", [768, 769, 1024, 1025])
+@pytest.mark.parametrize("policy", ["reset", "maintain"])
+def test_both_sides_of_the_line_of_the_teams(tiles, policy):
+    w = dataclasses.replace(W.ragged_mini(m=5, policy=policy), tau=2, rounds=2,
+                            shapes=(("a", (256 * tiles - 300,)), ("b", (1,)),))
+    PU.assert_same_bits(PU.run_library(w, ("separate", "flat"), _outer(w, True)),
+                        PU.run_library(w, ("separate", "flat"), _outer(w, True), SLOWMO_TEAM="0"))
