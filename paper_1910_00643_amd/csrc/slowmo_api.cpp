@@ -778,8 +778,10 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
     ctx->n_btiles = static_cast<int32_t>(bt.size());
     ctx->n_rtiles = static_cast<int32_t>(rt.size());
   }
-  // paced tiles, for contexts whose fused gossip step is one pass
-  if (ctx->tune.paced != 0 && ctx->tune.nontemporal && ctx->tune.fuse_mix && ctx->params_aligned &&
+  // paced tiles
+  const bool pays = ctx->tune.paced >= 2 ||
+                    paced_pays(count_paced_pieces(m, n_tensors, numel, false), cus, touched, ctx->params_aligned);
+  if (ctx->tune.paced != 0 && pays && ctx->tune.nontemporal && ctx->tune.fuse_mix &&
       count_paced_pieces(m, n_tensors, numel, ctx->tune.paced >= 2) > 0) {
     ctx->paced.members = cus / 8;
     // test hook: a limit that the workgroups reach, to run on out of step

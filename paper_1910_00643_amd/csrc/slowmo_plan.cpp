@@ -177,6 +177,20 @@ int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, b
   return forced || (m >= kPacedFromWorkers && n >= kPacedMinTiles) ? n : 0;
 }
 
+// The paced kernel keeps nothing in the last-level cache, single waves keep 224 MB there, which
+// tells on lists of a few GB.  Time paced over in single waves (4 steps on random maps and the
+// outer step, m = 8, 12, 16, 24 and 32), by the bytes that a step reads.  SGD, fp32 gradients: 1.2 GB
+// 1.02-1.10, 1.6 1.01-1.06, 1.9 1.01-1.03, 2.3 0.98-1.01, 2.6 0.95-1.00, 3.8 0.93-1.00; bf16: 1.3 GB
+// 1.01-1.08, 1.9 0.97-1.03, 2.2 0.97-1.01, 3.2 0.94-1.00; Adam, fp32: 1.6 GB 1.02-1.04, 2.1
+// 1.01-1.03, 2.6 0.99-1.01, 3.0 0.93-1.00, 5.1 0.92-0.99.  On tensors packed back to back single waves
+// lose more: SGD, fp32 1.2 GB 1.02-1.04, 1.6 1.00-1.02, 1.9 0.98-1.00, 2.3 0.94-1.00, 3.8 0.89-0.99;
+// bf16 1.3 GB 1.00-1.05, 1.6 1.00-1.01, 1.9 0.96-1.00; Adam 1.6 GB 1.00-1.03, 2.1 0.98-1.00, 5.1
+// 0.89-0.98.  An aligned list of less than two rows is paced in any case (1.00-1.10 times single
+// waves): what its launches leave behind when one of them fails is tested there.
+bool paced_pays(int64_t pieces, int64_t row, int64_t read_bytes, bool aligned) {
+  return (aligned && pieces < 2 * row) || read_bytes >= (aligned ? kPacedFromBytes : kPacedPackedFromBytes);
+}
+
 // The CUs without a piece in the last row have its whole time for the left-over tiles, one
 // per wave: a wave takes about 1.2 us per worker for one (nothing overlaps in it), a row
 // about 14, and 8 waves work side by side.  A launch of their own has the whole chip instead, which

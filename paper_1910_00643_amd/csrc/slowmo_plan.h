@@ -64,6 +64,8 @@ constexpr int32_t kPacedFromWorkers = 8;
 // (0.98-1.05); single rows of 192 to 256 would (0.82-1.00, with SLOWMO_PACED=2) and are
 // not taken so far.
 constexpr int32_t kPacedMinTiles = 300;
+constexpr int64_t kPacedFromBytes = 2200000000;        // bytes that a step reads, from which pacing pays,
+constexpr int64_t kPacedPackedFromBytes = 1750000000;  // ... on replicas that are not 16-byte aligned
 constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMixSaved in single waves)
 constexpr int32_t kPaceStride = 128;    // words between the counters of two XCDs
 constexpr int32_t kPaceWords = 8 * kPaceStride + kPaceStride;
@@ -226,6 +228,9 @@ int32_t choose_big_vpt(int32_t n_tensors, const int64_t *numel, int32_t cus);
 bool last_takes_big(int policy, bool asked);
 bool outer_takes_big(int32_t m, int policy, bool asked);
 int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
+// Whether a list of `pieces` paced tiles, of whose workers a step reads `read_bytes`, is paced on a chip of
+// `row` CUs.
+bool paced_pays(int64_t pieces, int64_t row, int64_t read_bytes, bool aligned);
 // Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
 // worker count is too small (with `forced`, only when no tensor has such a piece).
 int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, bool forced);
