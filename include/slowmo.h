@@ -52,9 +52,9 @@
  *    context's state unchanged, with one exception: some calls issue several
  *    kernels or copies (slowmo_mix_step may launch one kernel per connected
  *    group of workers; slowmo_local_mix_step launches
- *    the local step and the mixing step one after the other when a replica
- *    pointer is not 16-byte aligned, and from 8 workers on, for long tensor
- *    lists, one kernel for whole 16 384-element pieces and, where the rest does
+ *    the local step and the mixing step one after the other for four workers on
+ *    a short list with a replica that is not 16-byte aligned and a map that is no
+ *    permutation, and from 8 workers on, for long tensor lists, one kernel for whole 16 384-element pieces and, where the rest does
  *    not ride with it, one, or one per connected group, for the rest;
  *    slowmo_outer_step and slowmo_local_outer_step launch one kernel for the
  *    whole pieces of 65 536, 57 344 or 49 152 elements of the tensors and one for
@@ -233,10 +233,10 @@ slowmo_status slowmo_mix_step(slowmo_ctx *ctx, const int32_t *in_peer, void *str
  * outer iteration): the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_mix_step(ctx, in_peer, stream);
- * but when every replica pointer is 16-byte aligned both run in ONE kernel that
- * keeps the stepped replicas in registers for the mix: the replicas are read and
- * written once instead of twice (8 bytes less traffic per worker and element).
- * Otherwise the two kernels are launched back to back.
+ * but both run in ONE kernel that keeps the stepped replicas in registers for the
+ * mix: the replicas are read and written once instead of twice (8 bytes less
+ * traffic per worker and element).  A map that moves nobody leaves the local step
+ * alone.  (One exception: the notes on errors at the top.)
  * Errors: as for the two calls.
  */
 slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, float lr,
