@@ -929,8 +929,8 @@ __device__ __forceinline__ bool mix_src_in_register(int32_t flags) {
   return (flags & (kMixSrcFromS | kMixSrcFromFirst)) || mix_src_saved(flags);
 }
 
-// The entries a workgroup takes.  They lie in the kernel's arguments (a MixInline that is its first
-// one) or, from more than kMixInline workers on, in a table; constant memory in both cases, so
+// The entries a workgroup takes.  They lie in the kernel's arguments (a MixInline behind the first
+// kMixHead bytes, which are the same in all gossip kernels) or, from more than kMixInline workers on, in a table; constant memory in both cases, so
 // that an entry is a scalar load.  Blocks of one launch are dealt group after group (blockIdx.y).
 // An upload of the entries in front of every launch was 2-4 us of copy and 13-18 us of gaps on
 // the stream, and a wait of the host for the one four calls before.
@@ -956,8 +956,9 @@ struct MixPlace {              // the part of a MixArgs that the kernels get bes
   const uint32_t *groups;
   int32_t n_groups, first, len;
 };
+constexpr uintptr_t kMixHead = 3 * sizeof(void *) + 4 * sizeof(int);  // tiles, tensors, xtab_t, ntiles ... m
 __device__ __forceinline__ MixRange mix_range(const MixPlace &p) {
-  const uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+  const uintptr_t args = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + kMixHead;
   MixSendC *seq = (MixSendC *)(p.table ? reinterpret_cast<uintptr_t>(p.table)
                                        : args + offsetof(MixInline, entry));
   if (p.n_groups == 0) return {seq + p.first, p.len};
@@ -1016,9 +1017,9 @@ __device__ __forceinline__ void mix_lane(float *const *__restrict__ xp,
 // 2 to 32 workers, 1.00-1.10; 2 GB 0.99-1.02) and gain nothing beyond (5 to 20 GB 0.99-1.00).
 template <bool NT>
 __global__ __launch_bounds__(kOuterBlock) void k_mix_step(
-    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
-    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t, int ntiles,
-    int chunk, int remap, int m) {
+    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
+    float *const *__restrict__ xtab_t, int ntiles, int chunk, int remap, int m, MixInline,
+    MixPlace place) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
@@ -1114,10 +1115,10 @@ __device__ __forceinline__ void local_mix_lane(float *const *__restrict__ xp,
 
 template <int BASE, bool BF16, bool FIRST, bool NT, bool KEPT>
 __global__ __launch_bounds__(kOuterBlock) void k_local_mix_step(
-    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
-    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t,
-    const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
-    int64_t d_pad, int n_tensors, int ntiles, int chunk, int remap, int m, SgdP sp, AdamP ap) {
+    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
+    float *const *__restrict__ xtab_t, int ntiles, int chunk, int remap, int m, MixInline,
+    MixPlace place, const void *const *__restrict__ gtab, float *__restrict__ hbase,
+    float *__restrict__ vbase, int64_t d_pad, int n_tensors, SgdP sp, AdamP ap) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
@@ -1208,10 +1209,10 @@ __device__ __forceinline__ void team_mix_lane(V4 (*shared)[64], float *const *__
 
 template <int BASE, bool BF16, bool FIRST, bool NT, int R>
 __global__ __launch_bounds__(64 * kTeamWaves) void k_team_mix(
-    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
-    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t,
-    const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
-    int64_t d_pad, int n_tensors, int ntiles, int chunk, int remap, int m, SgdP sp, AdamP ap) {
+    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
+    float *const *__restrict__ xtab_t, int ntiles, int chunk, int remap, int m, MixInline,
+    MixPlace place, const void *const *__restrict__ gtab, float *__restrict__ hbase,
+    float *__restrict__ vbase, int64_t d_pad, int n_tensors, SgdP sp, AdamP ap) {
   extern __shared__ V4 team_rows[];      // one row of 64 vectors per worker of the team
   V4 (*const shared)[64] = reinterpret_cast<V4 (*)[64]>(team_rows);
   const int tile = tile_of(blockIdx.x, chunk, remap);
@@ -1492,12 +1493,11 @@ __device__ __forceinline__ void paced_step(PV &x, PV &h, PV &v, const float *xi,
 // first saved value in LDS (64 KiB each), the second saved value in registers.
 template <int BASE, bool BF16, bool FIRST>
 __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
-    MixInline, MixPlace place, const TileRef *__restrict__ tiles,
-    const TensorInfo *__restrict__ tensors, float *const *__restrict__ xtab_t,
-    const void *const *__restrict__ gtab, float *__restrict__ hbase, float *__restrict__ vbase,
-    int64_t d_pad, int n_tensors, int ntiles, int chunk, int members, int spins, int m,
-    const TileRef *__restrict__ rest, int nrest,
-    uint32_t *pace, SgdP sp0, AdamP ap0) {
+    const TileRef *__restrict__ tiles, const TensorInfo *__restrict__ tensors,
+    float *const *__restrict__ xtab_t, int ntiles, int chunk, int members, int m, MixInline,
+    MixPlace place, int spins, const void *const *__restrict__ gtab, float *__restrict__ hbase,
+    float *__restrict__ vbase, int64_t d_pad, int n_tensors, const TileRef *__restrict__ rest,
+    int nrest, uint32_t *pace, SgdP sp0, AdamP ap0) {
   static_assert(kPacedSaved == 2, "one saved value in LDS, one in registers");
   __shared__ V4 kept[2][kPV][kPacedBlock];     // [0]: opened the cycle, [1]: saved value 1
   const int xcd = static_cast<int>(blockIdx.x) % kXcd, rank = static_cast<int>(blockIdx.x) / kXcd;
@@ -1625,19 +1625,20 @@ __global__ __launch_bounds__(kPacedBlock) void k_local_mix_paced(
 
 // z^{(i)} = x^{(i)} / w_i (Algorithm C.1, last line), one workgroup per local tile.  NTL:
 // the loads; NT: the stores.  The weights change with every gossip step and lie in the kernel's
-// arguments (the DebiasWeights that is its first one) where there are at most kMixInline of them,
+// arguments (a DebiasWeights behind the first kDebiasHead bytes) where there are at most kMixInline of them,
 // so that only new destinations are uploaded.
+constexpr uintptr_t kDebiasHead = 4 * sizeof(void *) + 4 * sizeof(int);
 template <bool NTL, bool NT, bool KEPT>
 __global__ __launch_bounds__(kLocalBlock) void k_debias(
-    DebiasWeights, const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
+    const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
     float *const *__restrict__ ztab, const float *__restrict__ w, int n_tensors, int ntiles,
-    int chunk, int remap) {
+    int chunk, int remap, DebiasWeights) {
   const int tile = tile_of(blockIdx.x, chunk, remap);
   if (tile >= ntiles) return;
   const TileRef t = tiles[tile];
   const SlotInfo s = slots[t.owner];
   WordC *weights = (WordC *)(w ? reinterpret_cast<uintptr_t>(w)
-                               : (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr());
+                               : (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + kDebiasHead);
   const float wi = __uint_as_float(weights[t.owner / n_tensors]);
   const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;
   const float *x = s.x + go;
@@ -1928,8 +1929,8 @@ hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t 
   if (a.ntiles <= 0 || (a.len <= 0 && a.n_groups <= 0)) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, mix_blocks(a, g), dim3(kOuterBlock), 0, s, mix_inline(a), mix_place(a),
-                       a.tiles, a.tensors, a.xtab_t, a.ntiles, g.chunk, g.run, a.m);
+    hipLaunchKernelGGL(kernel, mix_blocks(a, g), dim3(kOuterBlock), 0, s, a.tiles, a.tensors,
+                       a.xtab_t, a.ntiles, g.chunk, g.run, a.m, mix_inline(a), mix_place(a));
   };
   if (t.local_nt) {
     launch(k_mix_step<true>);
@@ -1948,9 +1949,9 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(kOuterBlock), 0, s, mix_inline(x), mix_place(x),
-                       x.tiles, x.tensors, x.xtab_t, l.gtab, l.h, l.v, d_pad, n_tensors, x.ntiles,
-                       g.chunk, g.run, x.m, sp, ap);
+    hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(kOuterBlock), 0, s, x.tiles, x.tensors,
+                       x.xtab_t, x.ntiles, g.chunk, g.run, x.m, mix_inline(x), mix_place(x), l.gtab,
+                       l.h, l.v, d_pad, n_tensors, sp, ap);
   };
   if (!t.mix_nt) {
     launch(k_local_mix_step<BASE, BF16, FIRST, false, false>);
@@ -1991,9 +1992,9 @@ hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
-                     dim3(kPacedBlock), 0, s, mix_inline(x), mix_place(x), p.tiles, x.tensors,
-                     x.xtab_t, l.gtab, l.h, l.v, d_pad, n_tensors, p.ntiles, (p.ntiles + kXcd - 1) / kXcd, p.members,
-                     p.spins, x.m, p.rest, p.nrest, p.counters, sp, ap);
+                     dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, p.ntiles,
+                     (p.ntiles + kXcd - 1) / kXcd, p.members, x.m, mix_inline(x), mix_place(x), p.spins,
+                     l.gtab, l.h, l.v, d_pad, n_tensors, p.rest, p.nrest, p.counters, sp, ap);
   return hipGetLastError();
 }
 
@@ -2034,9 +2035,8 @@ hipError_t launch_team_mix_t(const LocalArgs *l, const MixArgs &x, int64_t d_pad
   const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
   auto launch = [&](auto kernel, int R) {
     hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(64 * team_waves(x.team, R)), team_lds(x.team),
-                       s, mix_inline(x),
-                       mix_place(x), x.tiles, x.tensors, x.xtab_t, a.gtab, a.h, a.v, d_pad, n_tensors,
-                       x.ntiles, g.chunk, g.run, x.m, sp, ap);
+                       s, x.tiles, x.tensors, x.xtab_t, x.ntiles, g.chunk, g.run, x.m, mix_inline(x),
+                       mix_place(x), a.gtab, a.h, a.v, d_pad, n_tensors, sp, ap);
   };
   const bool nt = BASE == 2 ? t.local_nt : t.mix_nt;
   if (x.team <= kTeamWaves) {
@@ -2132,7 +2132,8 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), 0, s,
-                       a.inl ? *a.inl : DebiasWeights{}, a.tiles, a.slots, a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run);
+                       a.tiles, a.slots, a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run,
+                       a.inl ? *a.inl : DebiasWeights{});
   };
   if (!t.nontemporal) {
     launch(k_debias<false, false, false>);
