@@ -41,7 +41,7 @@
  *    calls are recorded, not when the graph is replayed.  slowmo_mix_step,
  *    slowmo_local_mix_step and slowmo_debias keep the push-sum weights on the
  *    host, and may upload a small table (the former two with more than 64
- *    workers, slowmo_debias for new destinations or with more than 64 workers)
+ *    workers, slowmo_debias for new destinations or with more than 32 workers)
  *    from a staging buffer that later calls reuse: do not record them into a
  *    graph.
  *  - Errors: every entry point returns a slowmo_status; nothing aborts or

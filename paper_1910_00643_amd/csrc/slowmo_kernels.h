@@ -61,8 +61,10 @@ struct MixSend {
 };
 static_assert(sizeof(MixSend) == 16, "MixSend layout");
 // It travels with the launch, in the kernel's arguments, where it has at most kMixInline
-// entries; a longer one is a table in the workspace (the entries, then the groups).
-constexpr int32_t kMixInline = 64;
+// entries; a longer one is a table in the workspace (the entries, then the groups).  Every launch
+// copies room for all of them: 64 instead of 32 take 0.1 us more on the host (rounds of 12 steps on
+// 4 to 8 workers 73-78 -> 72-76 us, with the de-biased parameters after each 128-133 -> 124-130).
+constexpr int32_t kMixInline = 32;
 constexpr int32_t kTeamMost = 32;  // workers that a team takes
 struct MixInline {
   MixSend entry[kMixInline];

@@ -1,4 +1,4 @@
-"""The mixing order of a gossip step travels in the kernel's arguments up to 64 workers and as
+"""The mixing order of a gossip step travels in the kernel's arguments up to 32 workers and as
 a table beyond, and one launch runs all connected groups of workers: both sides of the limit,
 from one group to one pair of workers per group (64 of them)."""
 import dataclasses
@@ -14,9 +14,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fused_mix", [False, True])
-@pytest.mark.parametrize("m,mix", [(64, "expgraph"), (64, "random"), (65, "random"), (128, "expgraph")])
+@pytest.mark.parametrize("m,mix", [(32, "expgraph"), (32, "random"), (33, "random"), (64, "expgraph"), (64, "random"), (65, "random"), (128, "expgraph")])
 def test_limit_of_the_inline_order_every_element(m, mix, fused_mix):
-    """128 workers on the exponential graph: hops 1 to 64, 1 to 64 groups; 64: 1 to 32."""
+    """128 workers on the exponential graph: hops 1 to 64, 1 to 64 groups; 32: 1 to 16."""
     from slowmo_inputs.gpu_problem import GpuProblem
     w = dataclasses.replace(W.ragged_mini(m=m, policy="maintain"), mix=mix, tau=7, rounds=1,
                             shapes=(("a", (300,)), ("b", (3,)), ("c", (1030,))))
@@ -27,10 +27,10 @@ def test_limit_of_the_inline_order_every_element(m, mix, fused_mix):
     opt.close()
 
 
-@pytest.mark.parametrize("m", [3, 64, 65])
+@pytest.mark.parametrize("m", [3, 32, 33, 64, 65])
 def test_debias_into_more_destinations_than_are_remembered(m):
     """The weights change with every gossip step and the destinations take turns, six sets of them;
-    up to 64 workers only new destinations are uploaded."""
+    up to 32 workers only new destinations are uploaded."""
     import torch
     from slowmo_inputs.gpu_problem import GpuProblem
     w = dataclasses.replace(W.ragged_mini(m=m, policy="maintain"), mix="random", tau=14, rounds=1,
