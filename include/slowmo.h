@@ -40,7 +40,7 @@
  *    correction changes every step).  The context's counters advance when the
  *    calls are recorded, not when the graph is replayed.  slowmo_mix_step,
  *    slowmo_local_mix_step and slowmo_debias keep the push-sum weights on the
- *    host, and may upload a small table (the former two with more than 64
+ *    host, and may upload a small table (the former two with more than 32
  *    workers, slowmo_debias for new destinations or with more than 32 workers)
  *    from a staging buffer that later calls reuse: do not record them into a
  *    graph.
@@ -194,11 +194,10 @@ slowmo_status slowmo_outer_step(slowmo_ctx *ctx, float lr, void *stream);
  * the same results, bit for bit, as
  *     slowmo_local_step(ctx, grads, lr, stream);
  *     slowmo_outer_step(ctx, outer_lr, stream);
- * but when cfg.no_average is 0 both run in ONE kernel that keeps the stepped
- * replicas in registers for the average: the replicas are read and written once
- * instead of twice (8 m bytes less traffic per element), and the per-worker
- * buffers of this step are not written under the RESET and AVERAGE policies.
- * Otherwise the two kernels are launched back to back.
+ * but both run in ONE kernel that keeps the stepped replicas in registers for the
+ * outer step: the replicas are read and written once instead of twice (8 m bytes
+ * less traffic per element), and the per-worker buffers of this step are not
+ * written under the RESET and AVERAGE policies.
  * Errors: as for the two calls; STATE unless exactly tau-1 local steps were
  * taken since the previous outer step.
  */

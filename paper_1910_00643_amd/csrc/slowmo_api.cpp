@@ -976,6 +976,19 @@ OuterArgs outer_args(const slowmo_ctx *ctx, float lr) {
   return a;
 }
 
+OuterNoAvgArgs noavg_args(const slowmo_ctx *ctx, float lr) {
+  OuterNoAvgArgs na{};
+  na.tiles = ctx->d_ltiles;
+  na.slots = ctx->d_slots;
+  na.ntiles = ctx->n_ltiles;
+  na.x0 = ctx->x0;
+  na.u = ctx->u;
+  na.lr = lr;
+  na.alpha = ctx->cfg.alpha;
+  na.beta = ctx->cfg.beta;
+  return na;
+}
+
 // Lines 6-8 and the copy into the replicas.  *launched: kernels of the same
 // call already issued (a failure is then a failure halfway).
 slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t stream) {
@@ -983,15 +996,7 @@ slowmo_status run_outer(slowmo_ctx *ctx, float lr, int *launched, hipStream_t st
   LaunchTuning tune = ctx->tune;
   if (ctx->after_gossip) tune.outer_nt = ctx->gossip_outer_nt;
   if (c.no_average) {  // Section 6: lines 7-8 per worker, no line 6
-    OuterNoAvgArgs na{};
-    na.tiles = ctx->d_ltiles;
-    na.slots = ctx->d_slots;
-    na.ntiles = ctx->n_ltiles;
-    na.x0 = ctx->x0;
-    na.u = ctx->u;
-    na.lr = lr;
-    na.alpha = c.alpha;
-    na.beta = c.beta;
+    const OuterNoAvgArgs na = noavg_args(ctx, lr);
     const hipError_t e =
         guarded(ctx, [&] { return launch_outer_noavg_step(na, tune, stream); });
     if (e != hipSuccess)
@@ -1048,7 +1053,14 @@ slowmo_status slowmo_local_outer_step(slowmo_ctx *ctx, const void *const *grads,
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
   const bool bf16 = c.grad_dtype == SLOWMO_BF16;
-  if (c.no_average || !ctx->tune.fuse_last) {
+  if (c.no_average && ctx->tune.fuse_last) {
+    const hipError_t e = guarded(ctx, [&] {
+      return launch_local_noavg_step(a, noavg_args(ctx, outer_lr), c.base, bf16, ctx->buffers_zero,
+                                     c.policy == SLOWMO_BUF_RESET, ctx->tune, stream);
+    });
+    if (e != hipSuccess) return fail_hip(ctx, e, "fused local+outer kernel launch");
+    swept(ctx);
+  } else if (!ctx->tune.fuse_last) {
     // same two kernels as the separate calls
     hipError_t e = guarded(ctx, [&] {
       return launch_local_step(a, c.base, bf16, ctx->buffers_zero, c.policy == SLOWMO_BUF_RESET,

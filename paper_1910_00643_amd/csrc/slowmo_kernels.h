@@ -205,5 +205,9 @@ constexpr size_t kStaticScratchBytes =
 hipError_t static_scratch(int device, void **ptr);
 hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &tune,
                                    hipStream_t stream);
+// The last local step and the outer step without the average in one pass (first, last: as for
+// launch_local_step).
+hipError_t launch_local_noavg_step(const LocalArgs &l, const OuterNoAvgArgs &o, int base, bool bf16,
+                                   bool first, bool last, const LaunchTuning &tune, hipStream_t stream);
 
 }  // namespace slowmo

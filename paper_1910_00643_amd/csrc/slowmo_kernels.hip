@@ -602,6 +602,83 @@ __global__ __launch_bounds__(kLocalBlock) void k_outer_noavg(
   }
 }
 
+// ---- last local step + outer step without the average, fused ----------------------
+// The local step's tiles, the arithmetic of both kernels; the stepped x stays in registers.  Bound by
+// memory: 8 of the pair's 34 to 52 bytes per worker and element less, and a launch.  Rounds with tau = 1
+// and 3, one kernel over two, SGD and Adam, both gradient types: up to 1.6 M elements of all workers
+// 0.45-0.86 and 0.80-0.96, 3 to 10 M 0.60-0.89 and 0.87-0.94, 25 to 160 M 0.74-0.92 and 0.84-0.96
+// (4 x 40 M, SGD, tau = 1 908 -> 730 us).  NTO: the accesses to x0 and u.
+template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT, bool NTO, bool THROUGH, bool NTG>
+__device__ __forceinline__ void local_noavg_lane(float *x, float *h, float *v, const void *g, float *x0,
+                                                 float *u, int e0, const SgdP &sp, const AdamP &ap,
+                                                 const OuterP &p) {
+  V4 xv = ld4<NT>(x + e0), hv, vv;
+  if constexpr (!FIRST) hv = ld4<NT>(h + e0);
+  if constexpr (!FIRST && BASE == 1) vv = ld4<NT>(v + e0);
+  const V4 gv = ldgv<BF16, false, NTG>(g, e0);
+  const V4 x0v = ld4<NTO>(x0 + e0);
+  V4 uv = ld4<NTO>(u + e0);
+  step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+  const V4 xn = outer4(xv, x0v, uv, p);
+  if constexpr (!LAST) st4_arena<NT, THROUGH>(h, e0, hv);
+  if constexpr (!LAST && BASE == 1) st4_arena<NT, THROUGH>(v, e0, vv);
+  st4_arena<NTO, THROUGH>(u, e0, uv);
+  st4_arena<NTO, THROUGH>(x0, e0, xn);
+  st4_at<NT, THROUGH>(x, e0, xn);
+}
+
+template <int BASE, bool BF16, bool FIRST, bool LAST, bool NT, bool NTO, bool THROUGH>
+__global__ __launch_bounds__(kLocalBlock) void k_local_noavg(
+    const TileRef *__restrict__ tiles, const SlotInfo *__restrict__ slots,
+    const void *const *__restrict__ gtab, int ntiles, int chunk, int remap,
+    float *__restrict__ hbase, float *__restrict__ vbase, float *__restrict__ x0base,
+    float *__restrict__ ubase, SgdP sp, AdamP ap, OuterP p0) {
+  const int tile = tile_of(blockIdx.x, chunk, remap);
+  if (tile >= ntiles) return;
+  const TileRef t = tiles[tile];
+  const SlotInfo s = slots[t.owner];
+  const void *const g0 = gtab[t.owner];
+  have_now(s.x), have_now(s.so), have_now(s.lr_scale), have_now(g0);
+  const OuterP p = for_tensor(p0, s.lr_scale);
+  sp.lr = sp.lr * s.lr_scale;
+  sp.wd = s.wd;
+  ap.lr = ap.lr * s.lr_scale;
+  ap.wd = s.wd;
+  const int64_t go = static_cast<int64_t>(piece_of(t)) * kLocalTile;
+  const void *g = grad_at<BF16>(g0, go);
+  float *x = s.x + go;
+  float *h = hbase + s.so + go;
+  float *v = BASE == 1 ? vbase + s.so + go : nullptr;
+  float *x0 = x0base + s.so + go, *u = ubase + s.so + go;
+  const int64_t left = s.numel - go;
+  const int n = left < kLocalTile ? static_cast<int>(left) : kLocalTile;
+  if (lane_idle(n)) return;
+  if (n >= 4) {
+    const int e0 = lane_element(n);
+    if (NT && THROUGH && is_kept(t)) {
+      own_path(x), own_path(h);
+      if constexpr (BASE == 1) own_path(v);
+      local_noavg_lane<BASE, BF16, FIRST, LAST, false, NTO, THROUGH, NT>(x, h, v, g, x0, u, e0, sp, ap, p);
+    } else {
+      local_noavg_lane<BASE, BF16, FIRST, LAST, NT, NTO, THROUGH, NT>(x, h, v, g, x0, u, e0, sp, ap, p);
+    }
+  } else {
+    const int e0 = static_cast<int>(threadIdx.x);
+    V4 xv = ldv<true, NT>(x + e0), hv, vv;
+    if constexpr (!FIRST) hv = ldv<true, NT>(h + e0);
+    if constexpr (!FIRST && BASE == 1) vv = ldv<true, NT>(v + e0);
+    const V4 gv = ldgv<BF16, true, NT>(g, e0), x0v = ldv<true, NTO>(x0 + e0);
+    V4 uv = ldv<true, NTO>(u + e0);
+    step4<BASE, FIRST>(xv, hv, vv, gv, sp, ap);
+    const V4 xn = outer4(xv, x0v, uv, p);
+    if constexpr (!LAST) stv<true, NT>(h + e0, hv);
+    if constexpr (!LAST && BASE == 1) stv<true, NT>(v + e0, vv);
+    stv<true, NTO>(u + e0, uv);
+    stv<true, NTO>(x0 + e0, xn);
+    stv<true, NT>(x + e0, xn);
+  }
+}
+
 // ---- last local step + outer step, fused ---------------------------------------
 // For one tile (256 elements of one tensor): for every worker in order, the
 // base-optimizer step on that worker's (x, h[, v], g) -- the same arithmetic
@@ -2145,6 +2222,54 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
     launch(k_debias<true, true, false>);
   }
   return hipGetLastError();
+}
+
+namespace {
+
+template <int BASE, bool BF16, bool FIRST, bool LAST>
+hipError_t launch_local_noavg_t(const LocalArgs &a, const OuterNoAvgArgs &o, const LaunchTuning &t,
+                                hipStream_t s) {
+  const Grid g = make_grid(a.ntiles, t);
+  const SgdP sp{a.lr, a.mu, a.wd};
+  const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
+  const OuterP p{o.lr, 0.f, o.beta, 1.0f, o.alpha};
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.noavg_lds, s, a.tiles, a.slots,
+                       a.gtab, a.ntiles, g.chunk, g.run, a.h, a.v, o.x0, o.u, sp, ap, p);
+  };
+  if (t.local_nt) {
+    t.noavg_through ? launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, true>)
+                    : launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, false>);
+  } else if (t.outer_nt) {
+    launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, true, true>);
+  } else {
+    launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, false, false>);
+  }
+  return hipGetLastError();
+}
+
+template <int BASE, bool BF16>
+hipError_t launch_local_noavg_b(const LocalArgs &a, const OuterNoAvgArgs &o, bool first, bool last,
+                                const LaunchTuning &t, hipStream_t s) {
+  if (first) {
+    return last ? launch_local_noavg_t<BASE, BF16, true, true>(a, o, t, s)
+                : launch_local_noavg_t<BASE, BF16, true, false>(a, o, t, s);
+  }
+  return last ? launch_local_noavg_t<BASE, BF16, false, true>(a, o, t, s)
+              : launch_local_noavg_t<BASE, BF16, false, false>(a, o, t, s);
+}
+
+}  // namespace
+
+hipError_t launch_local_noavg_step(const LocalArgs &a, const OuterNoAvgArgs &o, int base, bool bf16,
+                                   bool first, bool last, const LaunchTuning &t, hipStream_t s) {
+  if (a.ntiles <= 0) return hipSuccess;
+  if (base == 0) {
+    return bf16 ? launch_local_noavg_b<0, true>(a, o, first, last, t, s)
+                : launch_local_noavg_b<0, false>(a, o, first, last, t, s);
+  }
+  return bf16 ? launch_local_noavg_b<1, true>(a, o, first, last, t, s)
+              : launch_local_noavg_b<1, false>(a, o, first, last, t, s);
 }
 
 hipError_t launch_outer_noavg_step(const OuterNoAvgArgs &a, const LaunchTuning &t, hipStream_t s) {
