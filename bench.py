@@ -126,9 +126,7 @@ def round_bytes(w, fused: bool = False, fused_mix: bool = False) -> int:
     """Algorithmic HBM bytes of one outer iteration as it is executed."""
     reset = w.policy == "reset"
     steps = range(w.tau - 1) if fused else range(w.tau)
-    # the fused local+gossip kernel always stores the buffers
-    per_worker_elem = sum(local_bytes_per_update(w, reset and k == 0,
-                                                 reset and k == w.tau - 1 and not fused_mix)
+    per_worker_elem = sum(local_bytes_per_update(w, reset and k == 0, reset and k == w.tau - 1)
                           for k in steps)
     if w.mix != "none" and not fused_mix:   # every replica read and written once per gossip step
         per_worker_elem += 8 * w.tau
@@ -209,7 +207,8 @@ def run_rounds(w, opt, arrays, rounds, events=None, marks=None, fused=False, fus
                     opt.local_outer_step(arrays[k % ring], w.lr)
                 break
             if peers is not None and fused_mix:     # local step + gossip step, one call
-                with _bracket(events, "local_mix_first" if (reset and k == 0) else "local_mix"):
+                with _bracket(events, "local_mix_last" if (reset and k == w.tau - 1) else
+                              "local_mix_first" if (reset and k == 0) else "local_mix"):
                     opt.local_mix_step(arrays[k % ring], w.lr, peers[k % len(peers)])
                 if z is not None:
                     with _bracket(events, "debias"):
@@ -254,7 +253,7 @@ def time_workload(w, steps, warmup, ring=None, fused=False, fused_mix=False, ker
     round_ms = [a.elapsed_time(b) for a, b in zip(marks[:-1], marks[1:])]
     # second pass: per-kernel durations from HIP events around every launch
     events = {"local": [], "local_first": [], "local_last": [], "outer": [], "mix": [],
-              "fused_last_outer": [], "local_mix": [], "local_mix_first": [], "debias": []}
+              "fused_last_outer": [], "local_mix": [], "local_mix_first": [], "local_mix_last": [], "debias": []}
     run_rounds(w, opt, arrays, kernel_rounds or steps, events, fused=fused, fused_mix=fused_mix,
                z=z)
     torch.cuda.synchronize()
@@ -350,6 +349,7 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
         # the fused local+gossip kernel moves the local step's bytes (gossip adds none)
         "local_mix": local_bytes_per_update(w, False) * w.m * w.d,
         "local_mix_first": local_bytes_per_update(w, True) * w.m * w.d,
+        "local_mix_last": local_bytes_per_update(w, reset and w.tau == 1, True) * w.m * w.d,
         "mix": 8 * w.m * w.d,
         "outer": outer_bytes_per_element(w) * w.d,
         "fused_last_outer": fused_bytes_per_element(w) * w.d,
@@ -359,6 +359,7 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
              "local_last": "k_local_step (buffers not stored)",
              "local_mix": "k_local_mix_step / k_local_mix_paced (steady state; all launches of one step)",
              "local_mix_first": "k_local_mix_step / k_local_mix_paced (buffers read as zero)",
+             "local_mix_last": "k_local_mix_step / k_local_mix_paced (buffers not stored)",
              "mix": "k_mix_step (all launches of one step)",
              "outer": "k_outer_noavg" if not w.exact_average else
                       "k_outer_big + k_outer_step (whole big tiles + rest)"
@@ -374,7 +375,7 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
                              "algorithmic_bytes_per_launch": per_launch[kind]}
     # the kernel kind the round spends most of its time in
     calls = {"local": w.tau - (2 if reset else 0) - (1 if fused and not reset else 0),
-             "local_mix": w.tau - (1 if reset else 0)}
+             "local_mix": w.tau - (2 if reset else 0)}
     dominant = "local_mix" if "local_mix" in kernels else "local" if "local" in kernels else \
         max(kernels, key=lambda k: kernels[k]["ms"] * calls.get(k, 1))
     dom = kernels[dominant]

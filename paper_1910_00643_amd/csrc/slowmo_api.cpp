@@ -891,6 +891,9 @@ slowmo_status prepare_local(slowmo_ctx *ctx, const void *const *grads, float lr,
   a.gtab = static_cast<const void *const *>(ctx->gtab.d[slot]);
   a.h = ctx->h;
   a.v = ctx->v;
+  // Under the reset policy the buffers written by the last step of an outer iteration are discarded
+  // before they are read again: skip those stores.
+  a.keep = !(c.policy == SLOWMO_BUF_RESET && ctx->k == c.tau - 1);
   a.lr = lr;
   a.wd = c.weight_decay;
   a.mu = c.momentum;
@@ -938,11 +941,8 @@ slowmo_status slowmo_local_step(slowmo_ctx *ctx, const void *const *grads, float
   slowmo_status st = prepare_local(ctx, grads, lr, stream, &a);
   if (st != SLOWMO_OK) return st;
   const slowmo_config &c = ctx->cfg;
-  // Under the reset policy the buffers written by the last step of an outer
-  // iteration are discarded before they are read again: skip those stores.
-  const bool dead_after = c.policy == SLOWMO_BUF_RESET && ctx->k == c.tau - 1;
   hipError_t e = guarded(ctx, [&] {
-    return launch_local_step(a, c.base, c.grad_dtype == SLOWMO_BF16, ctx->buffers_zero, dead_after,
+    return launch_local_step(a, c.base, c.grad_dtype == SLOWMO_BF16, ctx->buffers_zero, !a.keep,
                              ctx->tune, stream);
   });
   if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
@@ -1405,9 +1405,8 @@ slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, f
   if (st != SLOWMO_OK) return st;
   if (two_kernels) {
     // same kernels as the separate calls
-    const bool dead_after = c.policy == SLOWMO_BUF_RESET && ctx->k == c.tau - 1;
     const hipError_t e = guarded(ctx, [&] {
-      return launch_local_step(a, c.base, bf16, ctx->buffers_zero, dead_after, ctx->tune, stream);
+      return launch_local_step(a, c.base, bf16, ctx->buffers_zero, !a.keep, ctx->tune, stream);
     });
     if (e != hipSuccess) return fail_hip(ctx, e, "local-step kernel launch");
     swept(ctx);

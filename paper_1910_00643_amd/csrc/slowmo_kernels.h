@@ -16,6 +16,7 @@ struct LocalArgs {
   int32_t ntiles;
   float *h;                    // device: h arena, m * d_pad
   float *v;                    // device: v arena (Adam) or nullptr
+  int32_t keep;                // 0: the gossip kernels do not store h and v (dead after this step)
   float lr;
   float wd;
   // SGD with Nesterov momentum
