@@ -122,7 +122,9 @@ def algorithmic_bytes(kernel, w, rounds, dispatches):
         first = a[2] == "true"
         r, wr = local(first, False)
         calls = (rounds if reset else 1) if first else rounds * w.tau - (rounds if reset else 1)
-        return r * md * calls, wr * md * calls, calls
+        # the last step before a reset does not store the buffers
+        unstored = rounds if reset and (not first or w.tau == 1) else 0
+        return r * md * calls, wr * md * calls - 4 * nbuf * md * unstored, calls
     if name == "k_mix_step":
         calls = rounds * w.tau
         return 4 * md * calls, 4 * md * calls, calls
