@@ -135,7 +135,7 @@ struct LaunchTuning {
   int32_t kept_mix;     // the same for the gossip step fused with the local step (mix_keeps)
   int32_t kept_outer;   // 1: the outer step reads them as such
   int32_t write_through;  // 1: the local step writes through the L2 (sc1 stores)
-  int32_t noavg_through;  // the same for the outer step without the average
+  int32_t noavg_through;  // the same for the outer step without the average by itself
   int32_t local_lds;    // bytes of (unused) dynamic LDS per workgroup of the local step: caps the
                         // wavefronts per CU
   int32_t noavg_lds;    // the same for the outer step without the average

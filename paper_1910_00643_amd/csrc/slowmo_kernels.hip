@@ -2246,13 +2246,16 @@ hipError_t launch_local_noavg_t(const LocalArgs &a, const OuterNoAvgArgs &o, con
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), t.noavg_lds, s, a.tiles, a.slots,
                        a.gtab, a.ntiles, g.chunk, g.run, a.h, a.v, o.x0, o.u, sp, ap, p);
   };
-  if (t.local_nt) {
-    t.noavg_through ? launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, true>)
-                    : launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, false>);
-  } else if (t.outer_nt) {
-    launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, true, true>);
+  const NoAvgAccess by = noavg_access(t.local_nt, t.outer_nt, t.write_through);
+  if (by.local_nt) {
+    by.through ? launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, true>)
+               : launch(k_local_noavg<BASE, BF16, FIRST, LAST, true, true, false>);
+  } else if (by.outer_nt) {
+    by.through ? launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, true, true>)
+               : launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, true, false>);
   } else {
-    launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, false, false>);
+    by.through ? launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, false, true>)
+               : launch(k_local_noavg<BASE, BF16, FIRST, LAST, false, false, false>);
   }
   return hipGetLastError();
 }

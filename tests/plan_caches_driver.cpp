@@ -83,6 +83,16 @@ int main() {
   }
   // sweeps: the other way than the one before, and backward after a paced walk
   for (int32_t was : {0, 1}) check(next_sweep(was, false) == 1 - was && next_sweep(was, true) == 1, "sweep", was);
+  // the fused last step without the average: written through where the local step is, whatever the loads
+  for (bool local : {false, true}) {
+    for (bool outer : {false, true}) {
+      for (bool through : {false, true}) {
+        const NoAvgAccess by = noavg_access(local, outer, through);
+        check(by.local_nt == local && by.outer_nt == (local || outer), "streaming", local + 2 * outer);
+        check(by.through == through, "written through only where asked", local + 2 * outer);
+      }
+    }
+  }
   // big tiles: none below 160, never more than the workspace has room for
   for (int64_t n = 0; n < 4000; n += 37) {
     const std::vector<int64_t> list = {n * 20000 + 11, 65536 * (n % 90), 5};

@@ -30,7 +30,11 @@ def _free_gpu_memory():
     (5, LONGER, "sgd_nesterov", "bf16", "maintain", 1, STREAM), (3, SHORT, "adam", "f32", "maintain", 2, PLAIN),
     (4, LONGER, "sgd_nesterov", "f32", "reset", 3, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_OUTER_NT": "1"}),
     (2, LONGER, "adam", "bf16", "maintain", 2, {"SLOWMO_KEPT": "1", "SLOWMO_WRITE_THROUGH": "1", **STREAM}),
-    (2, LONGER, "sgd_nesterov", "f32", "reset", 2, {"SLOWMO_KEPT": "1", "SLOWMO_WRITE_THROUGH": "1", **STREAM})])
+    (2, LONGER, "sgd_nesterov", "f32", "reset", 2, {"SLOWMO_KEPT": "1", "SLOWMO_WRITE_THROUGH": "1", **STREAM}),
+    (3, LONGER, "adam", "f32", "maintain", 1, {"SLOWMO_WRITE_THROUGH": "1", **PLAIN}),
+    (4, LONGER, "sgd_nesterov", "bf16", "reset", 1,
+     {"SLOWMO_LOCAL_NT": "0", "SLOWMO_OUTER_NT": "1", "SLOWMO_WRITE_THROUGH": "1"}),
+    (3, LONGER, "adam", "bf16", "reset", 2, {"SLOWMO_WRITE_THROUGH": "0", **STREAM})])
 def test_fused_step_without_the_average(layout, m, shapes, base, grad_dtype, policy, tau, knobs):
     w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=m, policy=policy), tau=tau, rounds=2,
                             shapes=shapes, exact_average=False,
