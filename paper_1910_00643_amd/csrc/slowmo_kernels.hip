@@ -1006,12 +1006,28 @@ __device__ __forceinline__ bool mix_src_in_register(int32_t flags) {
   return (flags & (kMixSrcFromS | kMixSrcFromFirst)) || mix_src_saved(flags);
 }
 
+// The byte of a kernel's arguments at which the one of type T lies, each at a multiple of its alignment.
+template <typename T, typename K>
+struct ArgPlace;
+template <typename T, typename... A>
+struct ArgPlace<T, void (*)(A...)> {
+  static constexpr size_t find() {
+    size_t at = 0, found = ~size_t{0};
+    ((at = (at + alignof(A) - 1) / alignof(A) * alignof(A), found = std::is_same_v<A, T> ? at : found,
+      at += sizeof(A)),
+     ...);
+    return found;
+  }
+};
+
 // The entries a workgroup takes.  They lie in the kernel's arguments (a MixInline behind the first
-// kMixHead bytes, which are the same in all gossip kernels) or, from more than kMixInline workers on, in a table; constant memory in both cases, so
-// that an entry is a scalar load.  Blocks of one launch are dealt group after group (blockIdx.y).
+// kMixHead bytes, which are the same in all gossip kernels: check_mix_place) or, from more than
+// kMixInline workers on, in a table; constant memory in both cases, so that an entry is a scalar
+// load.  Blocks of one launch are dealt group after group (blockIdx.y).
 // An upload of the entries in front of every launch was 2-4 us of copy and 13-18 us of gaps on
 // the stream, and a wait of the host for the one four calls before.
-typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+// (the arguments' entries lie at multiples of 8 bytes only, which a scalar load does not mind)
+typedef uint32_t U4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef const __attribute__((address_space(4))) U4 MixSendC;
 typedef const __attribute__((address_space(4))) uint32_t WordC;
 struct MixRange {
@@ -2009,12 +2025,18 @@ dim3 mix_blocks(const MixArgs &a, const Grid &g) {
   return dim3(g.blocks, static_cast<unsigned>(a.n_groups > 0 ? a.n_groups : 1));
 }
 
+template <typename K>
+constexpr void check_mix_place(K) {
+  static_assert(ArgPlace<MixInline, K>::find() == kMixHead, "the kernel reads its entries behind kMixHead bytes");
+}
+
 }  // namespace
 
 hipError_t launch_mix_step(const MixArgs &a, const LaunchTuning &t, hipStream_t s) {
   if (a.ntiles <= 0 || (a.len <= 0 && a.n_groups <= 0)) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
+    check_mix_place(kernel);
     hipLaunchKernelGGL(kernel, mix_blocks(a, g), dim3(kOuterBlock), 0, s, a.tiles, a.tensors,
                        a.xtab_t, a.ntiles, g.chunk, g.run, a.m, mix_inline(a), mix_place(a));
   };
@@ -2035,6 +2057,7 @@ hipError_t launch_local_mix_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
   auto launch = [&](auto kernel) {
+    check_mix_place(kernel);
     hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(kOuterBlock), 0, s, x.tiles, x.tensors,
                        x.xtab_t, x.ntiles, g.chunk, g.run, x.m, mix_inline(x), mix_place(x), l.gtab,
                        l.h, l.v, d_pad, n_tensors, l.keep, sp, ap);
@@ -2077,6 +2100,7 @@ hipError_t launch_mix_paced_t(const LocalArgs &l, const MixArgs &x, int64_t d_pa
                               const PacedArgs &p, hipStream_t s) {
   const SgdP sp{l.lr, l.mu, l.wd};
   const AdamP ap{l.lr, l.wd, l.b1, l.b2, l.omb1, l.omb2, l.rc1, l.rc2, l.eps};
+  check_mix_place(&k_local_mix_paced<BASE, BF16, FIRST>);
   hipLaunchKernelGGL((k_local_mix_paced<BASE, BF16, FIRST>), dim3(kXcd * p.members),
                      dim3(kPacedBlock), 0, s, p.tiles, x.tensors, x.xtab_t, p.ntiles,
                      (p.ntiles + kXcd - 1) / kXcd, p.members, x.m, mix_inline(x), mix_place(x), p.spins,
@@ -2120,6 +2144,7 @@ hipError_t launch_team_mix_t(const LocalArgs *l, const MixArgs &x, int64_t d_pad
   const SgdP sp{a.lr, a.mu, a.wd};
   const AdamP ap{a.lr, a.wd, a.b1, a.b2, a.omb1, a.omb2, a.rc1, a.rc2, a.eps};
   auto launch = [&](auto kernel, int R) {
+    check_mix_place(kernel);
     hipLaunchKernelGGL(kernel, mix_blocks(x, g), dim3(64 * team_waves(x.team, R)), team_lds(x.team),
                        s, x.tiles, x.tensors, x.xtab_t, x.ntiles, g.chunk, g.run, x.m, mix_inline(x),
                        mix_place(x), a.gtab, a.h, a.v, d_pad, n_tensors, a.keep, sp, ap);
@@ -2217,6 +2242,8 @@ hipError_t launch_debias(const DebiasArgs &a, const LaunchTuning &t, hipStream_t
   if (a.ntiles <= 0) return hipSuccess;
   const Grid g = make_grid(a.ntiles, t);
   auto launch = [&](auto kernel) {
+    static_assert(ArgPlace<DebiasWeights, decltype(kernel)>::find() == kDebiasHead,
+                  "the kernel reads its weights behind kDebiasHead bytes");
     hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kLocalBlock), 0, s,
                        a.tiles, a.slots, a.ztab, a.w, a.n_tensors, a.ntiles, g.chunk, g.run,
                        a.inl ? *a.inl : DebiasWeights{});
