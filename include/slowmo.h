@@ -51,11 +51,10 @@
  *    last launch was accepted.  A call that fails therefore leaves the
  *    context's state unchanged, with one exception: some calls issue several
  *    kernels or copies (slowmo_mix_step may launch one kernel per connected
- *    group of workers; slowmo_local_mix_step launches
- *    the local step and the mixing step one after the other for four workers on
- *    a short list with a replica that is not 16-byte aligned and a map that is no
- *    permutation, and from 8 workers on, for long tensor lists, one kernel for whole 16 384-element pieces and, where the rest does
- *    not ride with it, one, or one per connected group, for the rest;
+ *    group of workers; slowmo_local_mix_step launches, from 8 workers on, for
+ *    long tensor lists, one kernel for whole 16 384-element pieces and, where
+ *    the rest does not ride with it, one, or one per connected group, for the
+ *    rest;
  *    slowmo_outer_step and slowmo_local_outer_step launch one kernel for the
  *    whole pieces of 65 536, 57 344 or 49 152 elements of the tensors and one for
  *    the rest when the tensor list has at least 160 such pieces -- the former from 16 workers
@@ -235,7 +234,7 @@ slowmo_status slowmo_mix_step(slowmo_ctx *ctx, const int32_t *in_peer, void *str
  * but both run in ONE kernel that keeps the stepped replicas in registers for the
  * mix: the replicas are read and written once instead of twice (8 bytes less
  * traffic per worker and element).  A map that moves nobody leaves the local step
- * alone.  (One exception: the notes on errors at the top.)
+ * alone.
  * Errors: as for the two calls.
  */
 slowmo_status slowmo_local_mix_step(slowmo_ctx *ctx, const void *const *grads, float lr,

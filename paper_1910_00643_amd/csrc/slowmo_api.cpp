@@ -1203,22 +1203,18 @@ bool paced_mix(const slowmo_ctx *ctx, const std::vector<MixEntry> &seq) {
 }
 
 // Whether the local step and the gossip step after it are one kernel.  Not where nobody moves: the
-// gossip step is then nothing at all (m = 1, 3 steps: walk over local step 1.02-1.10).  Else always, with
-// replicas at any element: those that are not 16-byte aligned share lines between workgroups, which costs less than the 8 bytes
-// per element saved and the second launch.  Tensors packed back to back, rounds of 4 gossip steps, one
-// kernel over two (SGD and Adam, exponential graph and random maps): 3 K and 100 K elements, m = 8 and
-// 21 0.57-0.78; 0.5 to 2 M, m = 4 and 16 0.59-0.90; 6 M, m = 16 0.84-0.93; 25.6 M, m = 8 and 20
-// 0.79-0.91; 60 M, m = 3 and 8 0.82-0.91; m = 2 to 5, 2 K to 1 M 0.51-0.74, 4 to 40 M 0.68-0.92.  Four such workers on a short list with a map that is no
-// permutation keep the two: the call that fails between its kernels is tested there.
+// gossip step is then nothing at all (m = 1, 3 steps: walk over local step 1.02-1.10).  Else always,
+// with replicas at any element: those that are not 16-byte aligned share lines between workgroups,
+// which costs less than the 8 bytes per element saved and the second launch.  Tensors packed back to
+// back, rounds of 4 gossip steps, one kernel over two (SGD and Adam, exponential graph and random
+// maps): 3 K and 100 K elements, m = 8 and 21 0.57-0.78; 0.5 to 2 M, m = 4 and 16 0.59-0.90; 6 M,
+// m = 16 0.84-0.93; 25.6 M, m = 8 and 20 0.79-0.91; 60 M, m = 3 and 8 0.82-0.91; m = 2 to 5, 2 K to 1 M
+// 0.51-0.74, 4 to 40 M 0.68-0.92.
 bool fused_mix(const slowmo_ctx *ctx, const int32_t *in_peer) {
   if (!ctx->tune.fuse_mix || ctx->n_otiles == 0) return false;
   bool moves = false;
   for (int32_t i = 0; i < ctx->cfg.m; ++i) moves = moves || in_peer[i] != i;
-  if (!moves) return false;
-  if (ctx->params_aligned || ctx->cfg.m != 4 || ctx->n_otiles > 1100) return true;
-  uint32_t served = 0;
-  for (int32_t i = 0; i < 4; ++i) served |= 1u << in_peer[i];
-  return served == 15;
+  return moves;
 }
 
 slowmo_status stage_mix(slowmo_ctx *ctx, const int32_t *in_peer, bool with_idle, hipStream_t stream,

@@ -52,13 +52,18 @@ def _assert_same(a, b):
         assert np.array_equal(a[0][key], b[0][key]), key
 
 
-@pytest.mark.parametrize("layout", ["separate", "flat"])     # one fused kernel / two kernels
-def test_bad_arguments_to_the_step_and_gossip_pair_change_nothing(layout):
+# one fused kernel, or the local step and the gossip step one after the other
+ONE_OR_TWO = pytest.mark.parametrize("layout,fuse", [("separate", None), ("flat", None), ("flat", "0")])
+
+
+@ONE_OR_TWO
+def test_bad_arguments_to_the_step_and_gossip_pair_change_nothing(layout, fuse):
     import paper_1910_00643_amd as P
     B = P.binding
     w = dataclasses.replace(W.ragged_mini(m=4, policy="maintain"), tau=3, rounds=1)
     prob = _problem(w, param_layout=layout, grad_layout="separate")
-    opt = _make(w, prob)
+    with PU.environment(SLOWMO_FUSE_MIX=fuse):
+        opt = _make(w, prob)
     idx = np.arange(w.d, dtype=np.int64)
     prob.fill_grads(0, 0)
     opt.local_mix_step(prob.grads[0], w.lr, [0, 0, 1, 1])
@@ -78,8 +83,8 @@ def test_bad_arguments_to_the_step_and_gossip_pair_change_nothing(layout):
     opt.close()
 
 
-@pytest.mark.parametrize("layout", ["separate", "flat"])
-def test_refused_first_launch_changes_nothing_and_the_context_goes_on(layout):
+@ONE_OR_TWO
+def test_refused_first_launch_changes_nothing_and_the_context_goes_on(layout, fuse):
     """The call's tables are uploaded, its first launch is refused: counters,
     weights, replicas and buffers are as before, and the same call then works
     and gives the result of a run that never failed."""
@@ -88,11 +93,12 @@ def test_refused_first_launch_changes_nothing_and_the_context_goes_on(layout):
     idx = np.arange(w.d, dtype=np.int64)
     peers = [[0, 0, 1, 1], [1, 0, 3, 2], [3, 0, 0, 2]]
     runs = []
-    # the first call takes one launch (fused) or two (packed replicas: two kernels);
+    # the first call takes one launch, or two (not fused);
     # the refused launch is the first one of the second call
-    for fail_at in (0, 2 if layout == "separate" else 3):
+    for fail_at in (0, 3 if fuse == "0" else 2):
         prob = _problem(w, param_layout=layout, grad_layout="separate")
-        opt = _make(w, prob, fail_at)
+        with PU.environment(SLOWMO_FUSE_MIX=fuse):
+            opt = _make(w, prob, fail_at)
         for k in range(w.tau):
             prob.fill_grads(0, k)
             if fail_at and k == 1:
@@ -109,7 +115,7 @@ def test_refused_first_launch_changes_nothing_and_the_context_goes_on(layout):
 
 
 def test_launch_refused_halfway_is_reported_and_the_context_refuses_further_steps():
-    """Two-kernel path (packed, unaligned replicas): the local step is
+    """Two-kernel path (SLOWMO_FUSE_MIX=0): the local step is
     launched, the gossip launch after it is refused.  The replicas are stepped
     but not mixed, which cannot be undone: the call says so, counters and
     weights keep their old values, and the context accepts no further step."""
@@ -117,7 +123,8 @@ def test_launch_refused_halfway_is_reported_and_the_context_refuses_further_step
     B = P.binding
     w = dataclasses.replace(W.ragged_mini(m=4, policy="maintain"), tau=3, rounds=1)
     prob = _problem(w, param_layout="flat", grad_layout="separate")
-    opt = _make(w, prob, fail_launch_at=2)
+    with PU.environment(SLOWMO_FUSE_MIX="0"):
+        opt = _make(w, prob, fail_launch_at=2)
     prob.fill_grads(0, 0)
     with pytest.raises(P.SlowMoError) as e:
         opt.local_mix_step(prob.grads[0], w.lr, [0, 0, 1, 1])

@@ -45,3 +45,17 @@ def test_both_sides_of_the_line_of_the_paced_walk(layout, m):
     w = dataclasses.replace(W.ragged_mini(m=m), shapes=TWO_ROWS, tau=3, rounds=2)
     PU.assert_same_bits(PU.run_library(w, (layout, "flat"), _gossip(w, True)),
                         PU.run_library(w, (layout, "flat"), _gossip(w, True), SLOWMO_PACED="0"))
+
+
+@pytest.mark.parametrize("m", [2, 3, 4, 5])
+@pytest.mark.parametrize("peers", [[1, 0, 3, 2, 4], [0, 0, 1, 1, 0], [1, 1, 1, 1, 1]])
+def test_one_launch_whatever_the_map(m, peers):
+    """A second launch of the call would be refused."""
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = W.ragged_mini(m=m, policy="maintain")
+    prob = GpuProblem(w, "cuda:0", param_layout="flat", grad_layout="flat")
+    with PU.environment(SLOWMO_TEST_FAIL_LAUNCH="2"):
+        opt = PU.make_gpu(w, prob)
+    prob.fill_grads(0, 0)
+    opt.local_mix_step(prob.grads[0], w.lr, [j % m for j in peers[:m]])
+    opt.close()
