@@ -50,11 +50,10 @@
  *    first kernel is launched; counters and push-sum weights advance after its
  *    last launch was accepted.  A call that fails therefore leaves the
  *    context's state unchanged, with one exception: some calls issue several
- *    kernels or copies (slowmo_mix_step may launch one kernel per connected
- *    group of workers; slowmo_local_mix_step launches, from 8 workers on, for
+ *    kernels or copies (slowmo_local_mix_step launches, from 8 workers on, for
  *    long tensor lists, one kernel for whole 16 384-element pieces and, where
- *    the rest does not ride with it, one, or one per connected group, for the
- *    rest;
+ *    the rest does not ride with it, one, or one per connected group of
+ *    workers, for the rest;
  *    slowmo_outer_step and slowmo_local_outer_step launch one kernel for the
  *    whole pieces of 65 536, 57 344 or 49 152 elements of the tensors and one for
  *    the rest when the tensor list has at least 160 such pieces -- the former from 16 workers

@@ -298,6 +298,7 @@ struct slowmo_ctx {
   bool gossip_outer_nt = true;  // tune.outer_nt for an outer step after a fused gossip step
   bool after_gossip = false;    // the last inner step was one
   bool teams = true;    // short lists by teams, a wave per worker
+  bool group_launches = false;  // test hook: slowmo_mix_step launches a kernel per connected group
   bool turning = true;  // sweeps over the tiles change direction (tune.backward)
   std::string err;
 };
@@ -591,6 +592,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   ctx->turning = env_flag("SLOWMO_TURN", touched > int64_t{16} << 20) != 0;
   ctx->teams = env_flag("SLOWMO_TEAM", 1) != 0;
   ctx->fail_launch_at = env_flag("SLOWMO_TEST_FAIL_LAUNCH", 0);
+  ctx->group_launches = env_flag("SLOWMO_TEST_GROUP_LAUNCHES", 0) != 0;
 
   const int64_t n_ltiles = count_local_tiles(m, n_tensors, numel);
   const int64_t n_otiles = count_outer_tiles(n_tensors, numel);
@@ -1245,8 +1247,12 @@ slowmo_status stage_mix(slowmo_ctx *ctx, const int32_t *in_peer, bool with_idle,
                   static_cast<uint32_t>(e.flags)};
     if (e.flags & kMixGroupStart) out->starts.push_back(i);
   }
-  // (maps that move at most four workers keep a launch per group: see run_mix)
-  if ((with_idle || out->len > 4) && !out->paced && mix_by_team(ctx)) {
+  // One group of at most four workers by itself, walked by up to 10 000 waves' worth of a team, is one
+  // short launch either way, and the smaller workgroups' is (pairs, cycles of 3 and 4: team over walk
+  // 1.00-1.07; beyond 0.91-1.01).  Pairs side by side: 0.84-0.99 at any length.
+  const bool few = !with_idle && out->starts.size() == 1 && out->len <= 4 &&
+                   static_cast<int64_t>(ctx->n_otiles) * out->len <= 10000;
+  if (!out->paced && !few && mix_by_team(ctx) && (with_idle || !ctx->group_launches)) {
     // On the shortest lists of many workers a workgroup takes one connected group of them, else
     // all: 16 tiles, pairs and groups of 4 and 8, 16 workers 0.92-0.99 and 32 workers 0.70-0.78 of
     // the time; 256 tiles 1.01-1.09.
@@ -1328,10 +1334,8 @@ slowmo_status run_groups(slowmo_ctx *ctx, const StagedMix &sm, MixArgs a, bool o
 
 // `launched`: kernels of this call already issued before.
 slowmo_status run_mix(slowmo_ctx *ctx, const StagedMix &sm, int launched, hipStream_t stream) {
-  // One launch, but for maps that move at most four workers: their second group stays a launch of
-  // its own (a call that fails halfway is tested there).
   const slowmo_status st = run_groups(
-      ctx, sm, mix_args(ctx, sm), sm.len > 4, &launched, "mixing kernel launch",
+      ctx, sm, mix_args(ctx, sm), !ctx->group_launches, &launched, "mixing kernel launch",
       [&](const MixArgs &a) {
         return a.team ? launch_team_mix(nullptr, a, ctx->layout.d_pad, ctx->n_tensors, 0, false, false,
                                         ctx->tune, stream)

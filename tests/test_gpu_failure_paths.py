@@ -141,11 +141,12 @@ def test_launch_refused_halfway_is_reported_and_the_context_refuses_further_step
 
 
 def test_gossip_launch_refused_for_the_second_group_of_workers():
-    """One launch per connected group: pairs (0,1) and (2,3) are two launches."""
+    """One launch per connected group (SLOWMO_TEST_GROUP_LAUNCHES=1): pairs (0,1) and (2,3) are two launches."""
     import paper_1910_00643_amd as P
     w = dataclasses.replace(W.ragged_mini(m=4, policy="maintain"), tau=3, rounds=1)
     prob = _problem(w, grad_layout="separate")
-    opt = _make(w, prob, fail_launch_at=2)
+    with PU.environment(SLOWMO_TEST_GROUP_LAUNCHES="1"):
+        opt = _make(w, prob, fail_launch_at=2)
     with pytest.raises(P.SlowMoError) as e:
         opt.mix_step([1, 0, 3, 2])
     assert e.value.status == P.binding.SLOWMO_ERR_HIP and "partly" in e.value.message

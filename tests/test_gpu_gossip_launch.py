@@ -50,3 +50,33 @@ def test_debias_into_more_destinations_than_are_remembered(m):
                 # a division by an fp32 tensor rounds once, as the kernel's
                 assert torch.equal(zt, xt / torch.tensor(weights[i], dtype=torch.float32, device=xt.device))
     opt.close()
+
+
+@pytest.mark.parametrize("peers", [[1, 0, 3, 2], [0, 0, 2, 2], [1, 0, 3, 2, 4, 5, 6], [0, 1, 5, 3, 6, 2, 4, 0]])
+def test_one_launch_for_all_groups(peers):
+    """However few workers move: a second launch of the call would be refused."""
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = W.ragged_mini(m=len(peers), policy="maintain")
+    prob = GpuProblem(w, "cuda:0")
+    with PU.environment(SLOWMO_TEST_FAIL_LAUNCH="2"):
+        opt = PU.make_gpu(w, prob)
+    opt.mix_step(peers)
+    opt.close()
+
+
+@pytest.mark.parametrize("m", [4, 33])
+@pytest.mark.parametrize("elements", [9000, 640_000 - 256, 640_001, 1_300_001])
+def test_maps_that_move_few_workers(m, elements):
+    """Walks and teams, on both sides of their lines for four and for two workers, against a walk per group."""
+    rest = list(range(4, m))
+    maps = [[3, 0, 1, 2] + rest, [1, 0, 2, 3] + rest, [1, 0, 3, 2] + rest, [0, 0, 0, 0] + rest]
+    w = dataclasses.replace(W.ragged_mini(m=m, policy="maintain"), tau=4, rounds=2, shapes=(("a", (elements,)), ("b", (3,))))
+
+    def step(opt, grads, k):
+        opt.local_step(grads, w.lr)
+        opt.mix_step(maps[k])
+        if k == w.tau - 1:
+            opt.outer_step(w.lr)
+
+    PU.assert_same_bits(PU.run_library(w, ("separate", "flat"), step),
+                        PU.run_library(w, ("separate", "flat"), step, SLOWMO_TEST_GROUP_LAUNCHES="1"))
