@@ -77,13 +77,15 @@ def outer_bytes_per_element(w) -> int:
 
 def fused_bytes_per_element(w) -> int:
     """Last local step + outer step in one kernel: per worker x, h (and v), g
-    read and x written; x0, u read and written; the buffers written once per
-    worker unless the policy discards them."""
+    read and x written; x0, u read and written (every worker's own without the
+    exact average); the buffers written once per worker unless the policy
+    discards them."""
     g = 2 if w.grad_dtype == "bf16" else 4
     nbuf = 2 if w.base == "adam" else 1
     first = w.policy == "reset" and w.tau == 1
-    reads = w.m * (4 + (0 if first else 4 * nbuf) + g) + 8
-    writes = 4 * w.m + 8 + (0 if w.policy == "reset" else 4 * nbuf * w.m)
+    outer = 8 * (1 if w.exact_average else w.m)
+    reads = w.m * (4 + (0 if first else 4 * nbuf) + g) + outer
+    writes = 4 * w.m + outer + (0 if w.policy == "reset" else 4 * nbuf * w.m)
     return reads + writes
 
 
@@ -119,7 +121,7 @@ def big_elements(w, fused: bool) -> int:
 
 
 def fusable(w) -> bool:
-    return w.exact_average and w.mix == "none"
+    return w.mix == "none"
 
 
 def round_bytes(w, fused: bool = False, fused_mix: bool = False) -> int:
@@ -355,16 +357,20 @@ def measure(w, steps, warmup, ring, unfused=False, kernel_rounds=None, debias=Fa
         "fused_last_outer": fused_bytes_per_element(w) * w.d,
         "debias": 8 * w.m * w.d,
     }
+    mixing = "k_local_mix_step / k_local_mix_paced / k_team_mix"
     names = {"local": "k_local_step (steady state)", "local_first": "k_local_step (buffers read as zero)",
              "local_last": "k_local_step (buffers not stored)",
-             "local_mix": "k_local_mix_step / k_local_mix_paced (steady state; all launches of one step)",
-             "local_mix_first": "k_local_mix_step / k_local_mix_paced (buffers read as zero)",
-             "local_mix_last": "k_local_mix_step / k_local_mix_paced (buffers not stored)",
-             "mix": "k_mix_step (all launches of one step)",
+             # (the team kernels: on short lists)
+             "local_mix": mixing + " (steady state; all launches of one step)",
+             "local_mix_first": mixing + " (buffers read as zero)",
+             "local_mix_last": mixing + " (buffers not stored)",
+             "mix": "k_mix_step / k_team_mix",
              "outer": "k_outer_noavg" if not w.exact_average else
                       "k_outer_big + k_outer_step (whole big tiles + rest)"
-                      if big_elements(w, False) else "k_outer_step",
-             "fused_last_outer": "k_local_outer_big + k_local_outer_step (whole big tiles + rest)" if big_elements(w, True) else "k_local_outer_step",
+                      if big_elements(w, False) else "k_outer_step / k_team_outer",
+             "fused_last_outer": "k_local_noavg" if not w.exact_average else
+                                 "k_local_outer_big + k_local_outer_step (whole big tiles + rest)"
+                                 if big_elements(w, True) else "k_local_outer_step / k_team_outer",
              "debias": "k_debias"}
     kernels = {}
     for kind, ms in kern_ms.items():

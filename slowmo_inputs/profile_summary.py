@@ -86,13 +86,18 @@ def family(kernel):
     fam = {"k_local_step": "local", "k_local_outer_step": "local_outer", "k_outer_step": "outer",
            "k_local_outer_big": "local_outer", "k_outer_big": "outer",
            "k_mix_step": "mix", "k_local_mix_step": "local_mix", "k_local_mix_paced": "local_mix",
-           "k_outer_noavg": "outer_noavg",
+           "k_outer_noavg": "outer_noavg", "k_local_noavg": "local_outer",
            "k_debias": "debias", "k_calib_copy": "copy"}.get(name)
+    # the team kernels: base 0 and 1 after a local step, 2 and 3 by themselves
+    if name == "k_team_mix":
+        fam = "mix" if int(a[0]) >= 2 else "local_mix"
+    elif name == "k_team_outer":
+        fam = "outer" if int(a[0]) >= 2 else "local_outer"
     steady = True
     if name == "k_local_step":
         steady = a[2] == "false" and a[3] == "false"
-    elif name in ("k_local_mix_step", "k_local_mix_paced", "k_local_outer_step",
-                  "k_local_outer_big"):
+    elif name in ("k_local_mix_step", "k_local_mix_paced", "k_team_mix", "k_local_outer_step",
+                  "k_local_outer_big", "k_team_outer", "k_local_noavg"):
         steady = a[2] == "false"
     return fam, steady
 
@@ -118,16 +123,25 @@ def algorithmic_bytes(kernel, w, rounds, dispatches):
     if name == "k_local_step":
         r, wr = local(a[2] == "true", a[3] == "true")
         return r * md * calls, wr * md * calls, calls
-    if name in ("k_local_mix_step", "k_local_mix_paced"):
+    if name in ("k_local_mix_step", "k_local_mix_paced") or (name == "k_team_mix" and int(a[0]) < 2):
         first = a[2] == "true"
         r, wr = local(first, False)
         calls = (rounds if reset else 1) if first else rounds * w.tau - (rounds if reset else 1)
         # the last step before a reset does not store the buffers
         unstored = rounds if reset and (not first or w.tau == 1) else 0
         return r * md * calls, wr * md * calls - 4 * nbuf * md * unstored, calls
-    if name == "k_mix_step":
+    if name in ("k_mix_step", "k_team_mix"):
         calls = rounds * w.tau
         return 4 * md * calls, 4 * md * calls, calls
+    if name == "k_local_noavg":
+        r, wr = local(a[2] == "true", a[3] == "true")
+        return (r + 8) * md * calls, (wr + 8) * md * calls, calls
+    if name == "k_team_outer":
+        if int(a[0]) >= 2:
+            b = bench.outer_bytes_per_element(w)
+            return b // 2 * d * calls, b // 2 * d * calls, calls
+        r, wr = local(a[2] == "true", reset)
+        return (w.m * r + 8) * d * calls, (w.m * wr + 8) * d * calls, calls
     # the outer step and the fused last step run as two kernels when big tiles
     # are in use: the whole big tiles, and the rest
     if name in ("k_local_outer_step", "k_local_outer_big"):

@@ -1,12 +1,15 @@
 """The benchmark counts the bytes of big tiles by the library's own rules: both are asked for the
-same lists."""
+same lists; and it runs, and counts, one kernel where the library has one."""
+import dataclasses
 import os
 import random
 import subprocess
 import types
 
+import pytest
+
 import bench
-from slowmo_inputs import shapes
+from slowmo_inputs import shapes, workloads as W
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1910_00643_amd", "csrc")
@@ -36,3 +39,15 @@ def test_rules_agree(tmp_path):
         for m in (7, 8, 15, 16, 32):
             w = types.SimpleNamespace(numel=[1 << 24], policy=policy, m=m, exact_average=True)
             assert f"{bench.big_elements(w, True) > 0:d} {bench.big_elements(w, False) > 0:d}" == next(rules)
+
+
+@pytest.mark.parametrize("average", [True, False])
+@pytest.mark.parametrize("policy", ["reset", "maintain"])
+@pytest.mark.parametrize("base,grad_dtype", [("sgd_nesterov", "f32"), ("adam", "bf16")])
+@pytest.mark.parametrize("tau", [1, 3])
+def test_fused_last_step_without_the_average(base, grad_dtype, policy, tau, average):
+    """Every replica read and written once less than in the two kernels, with the average and without."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=5, policy=policy), tau=tau,
+                            exact_average=average)
+    assert bench.fusable(w)
+    assert bench.round_bytes(w) - bench.round_bytes(w, fused=True) == 8 * w.m * w.d
