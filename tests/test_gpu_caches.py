@@ -53,16 +53,18 @@ def _gossip(w):
     return step
 
 
+# the walks from worker to worker, and teams where the library takes them on lists of this length
+@pytest.mark.parametrize("team", ["0", None])
 @pytest.mark.parametrize("layout", ["arena", "flat"])
 @pytest.mark.parametrize("base,grad_dtype,policy,calls,average", [
     ("sgd_nesterov", "f32", "reset", _fused, True), ("sgd_nesterov", "bf16", "maintain", _separate, True),
     ("adam", "bf16", "maintain", _fused, True), ("adam", "f32", "average", _separate, True),
     ("sgd_nesterov", "f32", "maintain", _separate, False), ("adam", "bf16", "reset", _gossip, True)])
-def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layout):
+def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layout, team):
     w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, policy=policy, m=3), tau=3,
                             exact_average=average,
                             shapes=tuple((f"t{n}", (n,)) for n in LENGTHS))
-    want = PU.run_library(w, (layout, "padded"), calls(w), **STREAMING)
+    want = PU.run_library(w, (layout, "padded"), calls(w), SLOWMO_TEAM="0", **STREAMING)
     for other in ({"SLOWMO_LOCAL_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_OUTER_NT": "0"}, {"SLOWMO_LOCAL_NT": "0", "SLOWMO_WRITE_THROUGH": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1000"},
@@ -70,7 +72,7 @@ def test_accesses_and_directions(base, grad_dtype, policy, calls, average, layou
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "3", "SLOWMO_BIG_TILES": "1"},
                   {"SLOWMO_WRITE_THROUGH": "1", "SLOWMO_KEPT": "1", "SLOWMO_BIG_TILES": "1"}):
         PU.assert_same_bits(want, PU.run_library(w, (layout, "padded"), calls(w),
-                                                 **{**STREAMING, "SLOWMO_TURN": "1", **other}))
+                                                 **{**STREAMING, "SLOWMO_TURN": "1", "SLOWMO_TEAM": team, **other}))
 
 
 def test_debias_of_a_list_that_stays_in_the_caches():

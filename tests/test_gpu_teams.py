@@ -61,6 +61,23 @@ def test_gossip_by_teams(m, shapes, base, grad_dtype, policy, fused):
                             PU.run_library(w, layouts, _gossip(w, fused), SLOWMO_TEAM="0"))
 
 
+# the accesses that the library would take on lists past the caches, and those on lists inside them
+ACCESSES = pytest.mark.parametrize("nt", ["0", "1"])
+
+
+@ACCESSES
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("m,base,grad_dtype", [(5, "adam", "bf16"), (17, "sgd_nesterov", "f32"),
+                                               (32, "adam", "f32")])
+def test_gossip_by_teams_streaming_or_not(m, base, grad_dtype, fused, nt):
+    """One and two workers per wave; nothing kept, which a team would not take."""
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=m, policy="maintain"),
+                            shapes=LONGER, tau=5, rounds=2)
+    PU.assert_same_bits(
+        PU.run_library(w, ("separate", "flat"), _gossip(w, fused), SLOWMO_LOCAL_NT=nt, SLOWMO_KEPT="0"),
+        PU.run_library(w, ("separate", "flat"), _gossip(w, fused), SLOWMO_TEAM="0"))
+
+
 def _outer(w, fused):
     def step(opt, grads, k):
         if fused and k == w.tau - 1:
@@ -86,6 +103,19 @@ def test_outer_step_by_teams(m, base, grad_dtype, policy, tau, fused):
     for layouts in (("separate", "separate"), ("flat", "flat")):
         PU.assert_same_bits(PU.run_library(w, layouts, _outer(w, fused)),
                             PU.run_library(w, layouts, _outer(w, fused), SLOWMO_TEAM="0"))
+
+
+@ACCESSES
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("m,base,grad_dtype,policy", [
+    (5, "adam", "bf16", "maintain"), (17, "sgd_nesterov", "f32", "average"), (32, "adam", "f32", "average"),
+    (32, "sgd_nesterov", "bf16", "reset")])
+def test_outer_step_by_teams_streaming_or_not(m, base, grad_dtype, policy, fused, nt):
+    w = dataclasses.replace(W.ragged_mini(base=base, grad_dtype=grad_dtype, m=m, policy=policy),
+                            shapes=LONGER, tau=2, rounds=2)
+    PU.assert_same_bits(
+        PU.run_library(w, ("separate", "flat"), _outer(w, fused), SLOWMO_OUTER_NT=nt, SLOWMO_KEPT="0"),
+        PU.run_library(w, ("separate", "flat"), _outer(w, fused), SLOWMO_TEAM="0"))
 
 
 @pytest.mark.parametrize("tiles", [768, 769, 1024, 1025])
