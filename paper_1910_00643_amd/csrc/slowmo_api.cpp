@@ -782,7 +782,7 @@ slowmo_status slowmo_create(slowmo_ctx **out, const slowmo_config *cfg, int32_t 
   }
   // paced tiles
   const bool pays = ctx->tune.paced >= 2 ||
-                    paced_pays(count_paced_pieces(m, n_tensors, numel, false), cus, touched, ctx->params_aligned);
+                    paced_pays(m, count_paced_pieces(m, n_tensors, numel, false), cus, touched, ctx->params_aligned);
   if (ctx->tune.paced != 0 && pays && ctx->tune.nontemporal && ctx->tune.fuse_mix &&
       count_paced_pieces(m, n_tensors, numel, ctx->tune.paced >= 2) > 0) {
     ctx->paced.members = cus / 8;

@@ -185,10 +185,13 @@ int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, b
 // 1.01-1.03, 2.6 0.99-1.01, 3.0 0.93-1.00, 5.1 0.92-0.99.  On tensors packed back to back single waves
 // lose more: SGD, fp32 1.2 GB 1.02-1.04, 1.6 1.00-1.02, 1.9 0.98-1.00, 2.3 0.94-1.00, 3.8 0.89-0.99;
 // bf16 1.3 GB 1.00-1.05, 1.6 1.00-1.01, 1.9 0.96-1.00; Adam 1.6 GB 1.00-1.03, 2.1 0.98-1.00, 5.1
-// 0.89-0.98.  An aligned list of less than two rows is paced in any case (1.00-1.10 times single
-// waves): what its launches leave behind when one of them fails is tested there.
-bool paced_pays(int64_t pieces, int64_t row, int64_t read_bytes, bool aligned) {
-  return (aligned && pieces < 2 * row) || read_bytes >= (aligned ? kPacedFromBytes : kPacedPackedFromBytes);
+// 0.89-0.98.  Aligned lists of less than two rows go by the workers instead: 300 to 511 pieces, both base
+// optimizers and gradient types, maps mixed, cycles and random, m = 8 1.00-1.21, 12 1.03-1.16, 14
+// 0.98-1.07, 16 0.98-1.10, 18 0.97-1.05, 20 0.97-1.04, 24 0.95-1.04, 32 0.91-1.01 (SGD, fp32, 511 pieces:
+// m = 8 1066 us paced, 917 in single waves; m = 32 4180 and 4429).
+bool paced_pays(int32_t m, int64_t pieces, int64_t row, int64_t read_bytes, bool aligned) {
+  if (aligned && pieces < 2 * row) return m >= kPacedShortFromWorkers;
+  return read_bytes >= (aligned ? kPacedFromBytes : kPacedPackedFromBytes);
 }
 
 // The CUs without a piece in the last row have its whole time for the left-over tiles, one

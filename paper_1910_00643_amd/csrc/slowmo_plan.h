@@ -59,11 +59,9 @@ constexpr int32_t kPacedBlock = 512;
 constexpr int32_t kPacedVpt = 8;
 constexpr int32_t kPacedTile = 4 * kPacedBlock * kPacedVpt;
 constexpr int32_t kPacedFromWorkers = 8;
-// Pieces a list must have: a full row and some to go with its second launch (300 pieces
-// 0.83-0.95 of the time in single waves, 8 to 32 workers).  128 pieces gain nothing
-// (0.98-1.05); single rows of 192 to 256 would (0.82-1.00, with SLOWMO_PACED=2) and are
-// not taken so far.
+// Pieces a list must have: a full row and some to go with its second launch.
 constexpr int32_t kPacedMinTiles = 300;
+constexpr int32_t kPacedShortFromWorkers = 17;         // aligned lists of less than two rows: see paced_pays
 constexpr int64_t kPacedFromBytes = 2200000000;        // bytes that a step reads, from which pacing pays,
 constexpr int64_t kPacedPackedFromBytes = 1750000000;  // ... on replicas that are not 16-byte aligned
 constexpr int32_t kPacedSaved = 2;      // saved values of the gossip walk (kMixSaved in single waves)
@@ -240,9 +238,9 @@ int32_t choose_big_vpt(int32_t n_tensors, const int64_t *numel, int32_t cus);
 bool last_takes_big(int policy, bool asked);
 bool outer_takes_big(int32_t m, int policy, bool asked);
 int64_t count_pieces(int32_t n_tensors, const int64_t *numel, int64_t piece);
-// Whether a list of `pieces` paced tiles, of whose workers a step reads `read_bytes`, is paced on a chip of
-// `row` CUs.
-bool paced_pays(int64_t pieces, int64_t row, int64_t read_bytes, bool aligned);
+// Whether a list of `pieces` paced tiles, of whose m workers a step reads `read_bytes`, is paced on a chip
+// of `row` CUs.
+bool paced_pays(int32_t m, int64_t pieces, int64_t row, int64_t read_bytes, bool aligned);
 // Whole kPacedTile pieces of a list that paced walks may take: 0 when the list or the
 // worker count is too small (with `forced`, only when no tensor has such a piece).
 int64_t count_paced_pieces(int32_t m, int32_t n_tensors, const int64_t *numel, bool forced);

@@ -130,6 +130,23 @@ static void paced_rule() {
         "forced: all whole pieces", 0);
 }
 
+// Whether a list is paced: by the bytes that a step reads, short aligned lists by the workers.
+static void paying_rule() {
+  const int64_t row = 256, none = 0, lots = int64_t{1} << 40;
+  for (int32_t m : {8, 16, 17, 32}) {
+    for (int64_t bytes : {none, lots}) {
+      check(paced_pays(m, 300, row, bytes, true) == (m > 16) && paced_pays(m, 511, row, bytes, true) == (m > 16),
+            "less than two rows, aligned", m);
+      check(paced_pays(m, 512, row, bytes, true) == (bytes == lots), "two rows", m);
+      check(paced_pays(m, 300, row, bytes, false) == (bytes == lots), "packed back to back", m);
+    }
+    check(!paced_pays(m, 512, row, kPacedFromBytes - 1, true) && paced_pays(m, 512, row, kPacedFromBytes, true),
+          "the line of aligned lists", m);
+    check(!paced_pays(m, 300, row, kPacedPackedFromBytes - 1, false) &&
+              paced_pays(m, 300, row, kPacedPackedFromBytes, false), "the line of packed lists", m);
+  }
+}
+
 // Left-over tiles that ride: up to 6 per wave of the CUs without a piece in the last row, and 1200.
 static void riding_rule() {
   check(!rest_rides(512, 1, 256) && !rest_rides(505, 1, 256), "a full row: no CU to spare", 0);
@@ -142,6 +159,7 @@ static void riding_rule() {
 
 int main() {
   paced_rule();
+  paying_rule();
   riding_rule();
   std::mt19937 rng(7);
   int reads = 0, workers = 0;

@@ -203,7 +203,7 @@ def test_outer_step_on_big_tiles_is_two_launches(fused):
     _assert_same(results[0], results[1])
 
 
-@pytest.mark.parametrize("m,group,launches", [(8, 8, 2), (16, 4, 5)])
+@pytest.mark.parametrize("m,group,launches", [(17, 17, 2), (32, 8, 5)])
 def test_paced_gossip_step_and_the_launches_for_the_rest(m, group, launches):
     """300 pieces of 16 384 elements and 61 shorter tensors: the paced kernel, then the rest
     (more than a quarter of the list) once per connected group.  The first launch refused:

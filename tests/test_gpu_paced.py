@@ -25,10 +25,12 @@ def _free_gpu_memory():
 
 # below a tile, exactly one, one and a few, two and an odd rest, a tile that is not the first
 SMALL = (("a", (TILE - 1,)), ("b", (TILE,)), ("c", (7,)), ("d", (TILE + 5,)), ("e", (2 * TILE + 4099,)))
-# what the library paces by itself: 300 pieces (256 of them paced), the rest with the short
-# tensors more than a quarter of the list; 513 pieces (512 paced), cut inside the last tensor
+# what the library paces by itself, from the worker counts below on: 300 pieces (256 of them paced), the
+# rest with the short tensors more than a quarter of the list; 513 pieces (512 paced), cut inside the last
+# tensor; 1100 (1024 paced)
 ONE_ROW = (("a", (300 * TILE + 3,)),) + tuple((f"s{j}", (TILE - 1,)) for j in range(61))
 TWO_ROWS = (("a", (200 * TILE + 1,)), ("b", (5,)), ("c", (150 * TILE,)), ("d", (163 * TILE + TILE - 1,)))
+FOUR_ROWS = (("a", (1100 * TILE + 77,)),)
 # more than one tile per CU: full rows, in which the workgroups pace each other, and a part of one
 ROWS = (("a", (300 * TILE + 3,)), ("b", (301 * TILE,)))
 
@@ -77,23 +79,47 @@ def _groups(*sizes):
     return [int(a + (i - 1) % n) for a, n in zip(starts, sizes) for i in range(n)]
 
 
-@pytest.mark.parametrize("shapes,m,base,grad_dtype,policy", [
-    (ONE_ROW, 8, "adam", "bf16", "maintain"),
-    (ONE_ROW, 16, "sgd_nesterov", "f32", "reset"),
-    (TWO_ROWS, 9, "adam", "f32", "reset"),
-    (TWO_ROWS, 16, "sgd_nesterov", "bf16", "maintain"),
+@pytest.mark.parametrize("shapes,m,base,grad_dtype,policy,paced", [
+    (ONE_ROW, 8, "adam", "bf16", "maintain", "2"),
+    (ONE_ROW, 16, "sgd_nesterov", "f32", "reset", "2"),
+    (TWO_ROWS, 9, "adam", "f32", "reset", "2"),
+    (TWO_ROWS, 16, "sgd_nesterov", "bf16", "maintain", "2"),
+    (ONE_ROW, 17, "adam", "bf16", "maintain", None),
+    (ONE_ROW, 32, "sgd_nesterov", "f32", "reset", None),
+    (TWO_ROWS, 17, "adam", "f32", "reset", None),
+    (TWO_ROWS, 27, "sgd_nesterov", "bf16", "maintain", None),
+    (FOUR_ROWS, 8, "adam", "f32", "maintain", None),
 ])
-def test_gossip_steps_that_the_library_paces_by_itself(shapes, m, base, grad_dtype, policy):
+def test_gossip_steps_that_the_library_paces_by_itself(shapes, m, base, grad_dtype, policy, paced):
     """No variable set: whole rows of paced tiles, the pieces beyond them with the rest, and
     in one context maps that are paced (one cycle, a star, large groups) next to maps that
-    are not (pairs)."""
+    are not (pairs).  Below the lines of the rule: all pieces paced, whatever the map."""
     maps = [_groups(m), _groups(*[2] * (m // 2) + [1] * (m % 2)), [0] * m,
             _groups(*[4] * (m // 4) + [1] * (m % 4)),
             [int(v) for v in np.random.default_rng(m).integers(0, m, size=m)]]
     w = _workload(shapes, m, base, grad_dtype, policy, tau=5)
     step = _gossip(w, maps)
-    PU.assert_same_bits(PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED=None),
+    PU.assert_same_bits(PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED=paced),
                         PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED="0"))
+
+
+@pytest.mark.parametrize("shapes,m,base,grad_dtype,launches", [
+    (ONE_ROW, 16, "adam", "bf16", 1), (ONE_ROW, 17, "adam", "bf16", 2), (ONE_ROW, 32, "sgd_nesterov", "f32", 2),
+    (TWO_ROWS, 16, "adam", "f32", 1), (TWO_ROWS, 17, "adam", "f32", 2), (TWO_ROWS, 26, "sgd_nesterov", "bf16", 1),
+    (TWO_ROWS, 27, "sgd_nesterov", "bf16", 2), (FOUR_ROWS, 7, "adam", "f32", 1), (FOUR_ROWS, 8, "adam", "f32", 2)])
+def test_what_the_library_paces_by_itself(shapes, m, base, grad_dtype, launches):
+    """The rest of a paced list is a second launch here, which is made to fail."""
+    import contextlib
+    import paper_1910_00643_amd as P
+    from slowmo_inputs.gpu_problem import GpuProblem
+    w = _workload(shapes, m, base, grad_dtype, "maintain", tau=2)
+    prob = GpuProblem(w, "cuda:0", param_layout="arena", grad_layout="flat")
+    with PU.environment(SLOWMO_TEST_FAIL_LAUNCH="2"):
+        opt = PU.make_gpu(w, prob)
+    prob.fill_grads(0, 0)
+    with pytest.raises(P.SlowMoError) if launches == 2 else contextlib.nullcontext():
+        opt.local_mix_step(prob.grads[0], w.lr, _groups(m))
+    opt.close()
 
 
 def test_workgroups_that_stop_waiting_for_each_other():

@@ -28,6 +28,7 @@ LAST_CU = (("a", (504 * TILE,)), ("b", (63 * 256,)), ("c", (62 * 256 + 77,))) + 
 
 @pytest.mark.parametrize("shapes,m,base,grad_dtype,policy,rest", [
     (PART, 8, "sgd_nesterov", "f32", "reset", None), (PART, 9, "adam", "bf16", "maintain", None),
+    (PART, 17, "sgd_nesterov", "f32", "reset", None), (LAST_CU, 18, "adam", "bf16", "maintain", None),
     (LAST_CU, 8, "adam", "f32", "maintain", None), (LAST_CU, 8, "sgd_nesterov", "bf16", "reset", "0"),
     # forced: no piece at all for some XCDs; full rows, so every workgroup takes some
     (SMALL, 8, "adam", "f32", "reset", "1"), (TWO_ROWS, 8, "sgd_nesterov", "bf16", "maintain", "1"),
@@ -35,27 +36,29 @@ LAST_CU = (("a", (504 * TILE,)), ("b", (63 * 256,)), ("c", (62 * 256 + 77,))) + 
 def test_rest_of_a_paced_launch(shapes, m, base, grad_dtype, policy, rest):
     w = _workload(shapes, m, base, grad_dtype, policy, tau=3)
     step = _gossip(w, [_groups(m), [0] * m, [int(v) for v in np.random.default_rng(m).integers(0, m, size=m)]])
-    paced = None if shapes in (PART, LAST_CU) else "2"
+    # (by the library's own rule from 17 workers on)
+    paced = None if m >= 17 else "2"
     PU.assert_same_bits(
         PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED=paced, SLOWMO_PACED_REST=rest),
         PU.run_library(w, ("arena", "flat"), step, SLOWMO_PACED="0"))
 
 
+@pytest.mark.parametrize("m", [17, 32])
 @pytest.mark.parametrize("shapes", [PART, LAST_CU])
 @pytest.mark.parametrize("rest,launches", [(None, 1), ("1", 1), ("0", 2)])
-def test_riding_tiles_take_no_launch(shapes, rest, launches):
+def test_riding_tiles_take_no_launch(shapes, rest, launches, m):
     """By the library's rule the step is one launch; a second one, made to fail, comes only where
     the tiles are launched by themselves."""
     import paper_1910_00643_amd as P
     from slowmo_inputs.gpu_problem import GpuProblem
-    w = _workload(shapes, 8, "sgd_nesterov", "f32", "reset", tau=3)
+    w = _workload(shapes, m, "sgd_nesterov", "f32", "reset", tau=3)
     prob = GpuProblem(w, "cuda:0", param_layout="arena", grad_layout="flat")
     with PU.environment(SLOWMO_PACED_REST=rest, SLOWMO_TEST_FAIL_LAUNCH="2"):
         opt = PU.make_gpu(w, prob)
     prob.fill_grads(0, 0)
     if launches == 1:
-        opt.local_mix_step(prob.grads[0], w.lr, _groups(8))
+        opt.local_mix_step(prob.grads[0], w.lr, _groups(m))
     else:
         with pytest.raises(P.SlowMoError):
-            opt.local_mix_step(prob.grads[0], w.lr, _groups(8))
+            opt.local_mix_step(prob.grads[0], w.lr, _groups(m))
     opt.close()
