@@ -247,7 +247,11 @@ def summarize(directory, bench_args, out_md, title, extra_note=""):
                    f"{gbps:.0f} | {gbps / 8000:.3f} | {tr} |")
         fam, steady = family(k)
         if steady and k in fetch and k in write:
-            fam_traffic[fam] += (fr + wr) / calls
+            per_call = (ar + aw) / calls
+            if fam == "local_mix":      # one instance runs the steady steps and the last one, whose
+                # buffers are not stored: the ratio of both together, at the steady step's bytes
+                per_call = bench.local_bytes_per_update(w, False) * w.m * w.d
+            fam_traffic[fam] += (fr + wr) / (ar + aw) * per_call
             if fam not in fam_biggest or ar + aw > fam_biggest[fam][1]:
                 fam_biggest[fam] = (k, ar + aw)
     km = {k: v for k, v in j.get("kernels", {}).items()}
@@ -298,8 +302,9 @@ if __name__ == "__main__":
                 "three minutes; it was the eighth profiler process of that session, the seven "
                 "before it (same command line apart from the variant flag) and the kernel-trace "
                 "pass of this very command had each finished in about four seconds, and every "
-                "other variant was profiled later without incident.  Whether counter collection "
+                "other variant was profiled later without incident, and the rounds of that time ended "
+                "with `k_outer_noavg` by itself.  Whether counter collection "
                 "or a kernel under counter collection stalled cannot be told from the log, so "
-                "the pass has not been repeated; `k_outer_noavg` moves 24 bytes per worker and "
-                "element by construction (3 streams read, 3 written, one workgroup per tile).")
+                "the pass has not been repeated; `k_local_noavg` moves x, h, v, x0 and u in and out "
+                "and the gradient in, once each, by construction (one wave per tile of a worker).")
     print(summarize(d, rest, os.path.join(ROOT, "profiles", nm + ".md"), title, note))
